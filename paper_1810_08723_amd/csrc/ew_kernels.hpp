@@ -22,19 +22,28 @@ namespace ocn {
 // kernel arguments (plain data, passed by value)
 // ---------------------------------------------------------------------------------------
 
+// Arguments of the kernel for rows of any length and alignment.
 struct RowsArgs {
   char *out;
   const char *a, *b;
+  int64_t numel;
+  int64_t nvec;      // vectors in total
+  uint32_t flags;    // kRows* bits; operands in the other byte order in bits 8..10
+  uint32_t block;    // lanes per workgroup
+  uint32_t shift;    // flat form: elements by which the first vector starts before the output
+  uint32_t inner;    // elements per row
+  FastDiv rdiv;      // flat form: elements per row; row form: vectors per row
+  int32_t nouter;
   int64_t so[kMaxDims - 1], sa[kMaxDims - 1], sb[kMaxDims - 1];  // outer strides, fastest outer first
   FastDiv odiv[kMaxDims - 1];                                    // outer sizes, same order
-  int32_t nouter;
-  FastDiv vpr_div;   // vectors per row
-  int64_t inner;     // elements per row
-  int64_t nvec;      // vectors in total
-  int32_t a_bcast, b_bcast;
-  int32_t nt_store;  // stream the output past the caches
-  int32_t nt_a, nt_b; // read that input with streaming (non-temporal) loads
-  int32_t swap;       // operands stored in the other byte order: bit 0 a, bit 1 b, bit 2 out
+};
+enum : uint32_t {
+  kRowsFlat = 1,        // the output is one contiguous run: vectors are aligned pieces of it and may cross rows
+  kRowsALinear = 2, kRowsBLinear = 4,   // flat form: that input is contiguous along with the output
+  kRowsABcast = 8, kRowsBBcast = 16,    // that input is broadcast along the rows
+  kRowsNtA = 32, kRowsNtB = 64,         // read that input with streaming (non-temporal) loads
+  kRowsNtStore = 128,                   // stream the output past the caches
+  kRowsSwapShift = 8
 };
 
 constexpr int kMaxTilePasses = 16;  // a tile holds at most 4096 elements = 16 passes of 256 lanes
@@ -228,6 +237,95 @@ template <class S, int V> OCN_DEV void store_pack(char *p, const Pack<S, V> &src
   }
 }
 
+// The same accesses for addresses that are only multiples of the scalar size.  gfx950 loads and
+// stores up to 16 bytes per lane at any such address; a wavefront's access then touches one
+// cache line more than an aligned one (a flat copy with the inputs off by one element: 61.8
+// against 60.2 us for 48 M floats).  Copied through packed types, so that the compiler knows.
+template <int AL> struct Unaligned;
+#define OCN_UNALIGNED(AL)                                                   \
+  template <> struct Unaligned<AL> {                                        \
+    typedef uint32_t W4 __attribute__((ext_vector_type(4), aligned(AL)));   \
+    typedef uint32_t W2 __attribute__((ext_vector_type(2), aligned(AL)));   \
+    typedef uint32_t W1 __attribute__((aligned(AL)));                       \
+    typedef uint16_t H1 __attribute__((aligned(AL)));                       \
+  };
+OCN_UNALIGNED(1)
+OCN_UNALIGNED(2)
+OCN_UNALIGNED(4)
+OCN_UNALIGNED(8)
+#undef OCN_UNALIGNED
+template <class S, int V, int AL> OCN_DEV void load_pack_any(const char *p, Pack<S, V> &dst, bool nt = false) {
+  using X = Unaligned<AL>;
+  constexpr int B = sizeof(S) * V;
+  if constexpr (B >= 16) {
+    typename X::W4 w[B / 16];
+    if (B == 16 && nt) {
+      OCN_KEEP_BRANCH();
+      w[0] = __builtin_nontemporal_load(reinterpret_cast<const typename X::W4 *>(p));
+      OCN_KEEP_BRANCH();
+    } else {
+#pragma unroll
+      for (int i = 0; i < B / 16; ++i) w[i] = reinterpret_cast<const typename X::W4 *>(p)[i];
+    }
+    __builtin_memcpy(&dst, w, B);
+  } else if constexpr (B == 8) {
+    const typename X::W2 w = *reinterpret_cast<const typename X::W2 *>(p);
+    __builtin_memcpy(&dst, &w, B);
+  } else if constexpr (B == 4) {
+    const uint32_t w = *reinterpret_cast<const typename X::W1 *>(p);
+    __builtin_memcpy(&dst, &w, B);
+  } else if constexpr (B == 2) {
+    const uint16_t w = *reinterpret_cast<const typename X::H1 *>(p);
+    __builtin_memcpy(&dst, &w, B);
+  } else {
+    __builtin_memcpy(&dst, p, B);
+  }
+}
+template <class S, int V, int AL> OCN_DEV void store_pack_any(char *p, const Pack<S, V> &src, bool nt = false) {
+  using X = Unaligned<AL>;
+  constexpr int B = sizeof(S) * V;
+  if constexpr (B >= 16) {
+    typename X::W4 w[B / 16];
+    __builtin_memcpy(w, &src, B);
+#pragma unroll
+    for (int i = 0; i < B / 16; ++i) {
+      if (nt) {
+        OCN_KEEP_BRANCH();
+        __builtin_nontemporal_store(w[i], reinterpret_cast<typename X::W4 *>(p) + i);
+        OCN_KEEP_BRANCH();
+      } else {
+        reinterpret_cast<typename X::W4 *>(p)[i] = w[i];
+      }
+    }
+  } else if constexpr (B == 8) {
+    typename X::W2 w;
+    __builtin_memcpy(&w, &src, B);
+    if (nt) {
+      OCN_KEEP_BRANCH();
+      __builtin_nontemporal_store(w, reinterpret_cast<typename X::W2 *>(p));
+      OCN_KEEP_BRANCH();
+    } else {
+      *reinterpret_cast<typename X::W2 *>(p) = w;
+    }
+  } else if constexpr (B == 4) {
+    uint32_t w;
+    __builtin_memcpy(&w, &src, B);
+    if (nt) {
+      OCN_KEEP_BRANCH();
+      __builtin_nontemporal_store(w, reinterpret_cast<typename X::W1 *>(p));
+      OCN_KEEP_BRANCH();
+    } else {
+      *reinterpret_cast<typename X::W1 *>(p) = w;
+    }
+  } else if constexpr (B == 2) {
+    uint16_t w;
+    __builtin_memcpy(&w, &src, B);
+    *reinterpret_cast<typename X::H1 *>(p) = w;
+  } else {
+    __builtin_memcpy(p, &src, B);
+  }
+}
+
 // ---------------------------------------------------------------------------------------
 // one element: load-convert, operate, convert-store
 // ---------------------------------------------------------------------------------------
@@ -276,103 +374,6 @@ template <int OP, int SA, int SB, int SO, int NIN> struct Sig {
 // ---------------------------------------------------------------------------------------
 // rows kernel
 // ---------------------------------------------------------------------------------------
-
-template <class G> OCN_DEV void rows_general(const RowsArgs &p) {
-  constexpr int V = G::VR, U = G::UR;
-  using SAt = typename G::SAt;
-  using SBt = typename G::SBt;
-  using SOt = typename G::SOt;
-  constexpr bool BIN = G::NIN2;
-
-  const int64_t g0 = (int64_t)blockIdx.x * (kBlock * U) + threadIdx.x;
-  Pack<SAt, V> va[U];
-  Pack<SBt, V> vb[U];
-  int64_t oo[U];
-  int nvalid[U];
-
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int64_t g = g0 + (int64_t)u * kBlock;
-    nvalid[u] = 0;
-    oo[u] = 0;
-    if (g < p.nvec) {
-      int64_t col, off_o = 0, off_a = 0, off_b = 0;
-      if (p.nouter == 0) {
-        col = g;
-      } else {
-        uint32_t row = fastdiv((uint32_t)g, p.vpr_div);
-        col = (uint32_t)g - row * p.vpr_div.d;
-#pragma unroll
-        for (int k = 0; k < kMaxDims - 1; ++k) {
-          if (k < p.nouter) {
-            uint32_t q = (k == p.nouter - 1) ? 0u : fastdiv(row, p.odiv[k]);
-            uint32_t i = row - q * p.odiv[k].d;
-            row = q;
-            off_o += (int64_t)i * p.so[k];
-            off_a += (int64_t)i * p.sa[k];
-            if constexpr (BIN) off_b += (int64_t)i * p.sb[k];
-          }
-        }
-      }
-      const int64_t e0 = col * V;
-      const int64_t left = p.inner - e0;
-      const int n = left >= V ? V : (int)left;
-      nvalid[u] = n;
-      oo[u] = off_o + e0 * (int64_t)sizeof(SOt);
-      const char *pa = p.a + off_a + (p.a_bcast ? 0 : e0 * (int64_t)sizeof(SAt));
-      const char *pb = nullptr;
-      if constexpr (BIN) pb = p.b + off_b + (p.b_bcast ? 0 : e0 * (int64_t)sizeof(SBt));
-      if (n == V) {
-        if (p.a_bcast) {
-          SAt s = *reinterpret_cast<const SAt *>(pa);
-#pragma unroll
-          for (int i = 0; i < V; ++i) va[u].v[i] = s;
-        } else {
-          load_pack<SAt, V>(pa, va[u], p.nt_a != 0);
-        }
-        if constexpr (BIN) {
-          if (p.b_bcast) {
-            SBt s = *reinterpret_cast<const SBt *>(pb);
-#pragma unroll
-            for (int i = 0; i < V; ++i) vb[u].v[i] = s;
-          } else {
-            load_pack<SBt, V>(pb, vb[u], p.nt_b != 0);
-          }
-        }
-      } else {
-#pragma unroll
-        for (int i = 0; i < V; ++i) {
-          if (i < n) {
-            va[u].v[i] = reinterpret_cast<const SAt *>(pa)[p.a_bcast ? 0 : i];
-            if constexpr (BIN) vb[u].v[i] = reinterpret_cast<const SBt *>(pb)[p.b_bcast ? 0 : i];
-          }
-        }
-      }
-    }
-  }
-
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int n = nvalid[u];
-    if (n == 0) continue;
-    Pack<SOt, V> r;
-    if (p.swap) G::order_inputs(p.swap, va[u], vb[u]);
-#pragma unroll
-    for (int i = 0; i < V; ++i) {
-      if constexpr (BIN) r.v[i] = G::eval(va[u].v[i], vb[u].v[i]);
-      else r.v[i] = G::eval(va[u].v[i], SBt{});
-    }
-    if (p.swap) G::order_output(p.swap, r);
-    char *po = p.out + oo[u];
-    if (n == V) {
-      store_pack<SOt, V>(po, r, p.nt_store != 0);
-    } else {
-#pragma unroll
-      for (int i = 0; i < V; ++i)
-        if (i < n) reinterpret_cast<SOt *>(po)[i] = r.v[i];
-    }
-  }
-}
 
 // The common shapes - at most one outer dim, rows of whole vectors, fewer than 2^31 vectors -
 // get a kernel of their own.  With one vector per lane a wavefront lives for one memory round
@@ -459,8 +460,181 @@ template <class G> __global__ __launch_bounds__(kSlimBlock) void ew_rows_slim_ke
   }
 }
 
-template <class G> __global__ __launch_bounds__(kBlock) void ew_rows_kernel(const RowsArgs p) {
-  rows_general<G>(p);
+// Rows of any length and alignment, any number of outer dims.  Bound by HBM like the kernel
+// above; what it has to avoid is element-sized accesses where rows do not start on vector
+// boundaries (an odd row length).  Two forms:
+//   flat  The output is one contiguous run, which is cut into aligned vectors regardless of where
+//         rows end, so that stores are whole lines.  An input that runs along with it is read
+//         in the same aligned vectors; any other input (broadcast along some dim, rows in
+//         another order) is read at its own, possibly unaligned, address, and element by
+//         element by the few lanes whose vector crosses from one row into the next.
+//   rows  Vectors start where rows start; a row's last, partial vector goes element by element.
+// int32 [8000, 6001] times a float row of 6001: 126 us as single elements, 61.4 us here (6.25 TB/s;
+// starting vectors where rows start took 67 us).  64-lane workgroups as above.
+// byte offsets of a row in the three operands
+template <class P> OCN_HDF void rows_outer(const P &p, uint32_t row, int64_t (&off)[3]) {
+  off[0] = off[1] = off[2] = 0;
+  const int nouter = p.nouter;
+  for (int k = 0; k < nouter; ++k) {
+    const uint32_t d = p.odiv[k].d;
+    const uint32_t q = k + 1 < nouter ? fastdiv(row, FastDiv{d, p.odiv[k].m, p.odiv[k].s}) : 0u;
+    const int64_t i = (int64_t)(row - q * d);
+    row = q;
+    off[0] += i * p.so[k];
+    off[1] += i * p.sa[k];
+    off[2] += i * p.sb[k];
+  }
+}
+
+// where vector number g lies
+struct RowsPlace {
+  int64_t first;    // flat form: its first element (may lie before the output)
+  int64_t off[3];   // byte offsets of its row in out / a / b
+  uint32_t row, col;
+  int lo, hi;       // the elements of the vector that exist: lo .. hi - 1
+  bool inrow;       // all of them lie in one row
+};
+template <int V, class P> OCN_HDF RowsPlace rows_place(const P &p, int64_t g) {
+  RowsPlace r;
+  r.first = 0;
+  r.row = r.col = 0;
+  r.lo = 0;
+  r.inrow = true;
+  r.off[0] = r.off[1] = r.off[2] = 0;
+  const uint32_t flags = p.flags, inner = p.inner;
+  const FastDiv rdiv{p.rdiv.d, p.rdiv.m, p.rdiv.s};
+  if (flags & kRowsFlat) {
+    const int64_t numel = p.numel;
+    r.first = g * V - (int64_t)p.shift;
+    r.lo = r.first < 0 ? (int)-r.first : 0;
+    r.hi = numel - r.first < V ? (int)(numel - r.first) : V;
+    if (p.nouter) {
+      const uint32_t e = (uint32_t)(r.first + r.lo);
+      r.row = fastdiv(e, rdiv);
+      r.col = e - r.row * rdiv.d;
+      r.inrow = r.col + (uint32_t)(r.hi - r.lo) <= inner;
+      rows_outer(p, r.row, r.off);
+    }
+  } else {
+    r.row = fastdiv((uint32_t)g, rdiv);
+    r.col = ((uint32_t)g - r.row * rdiv.d) * (uint32_t)V;
+    r.hi = inner - r.col < (uint32_t)V ? (int)(inner - r.col) : V;
+    rows_outer(p, r.row, r.off);
+  }
+  return r;
+}
+// byte offset of element i of vector r in operand x (0 out, 1 a, 2 b; es its element size, lin:
+// it runs along with a contiguous output, bc: it is broadcast along the rows); r.row, r.col and
+// r.off are those of element i
+template <class R> OCN_HDF int64_t rows_offset(const R &r, int x, int i, int es, bool lin, bool bc) {
+  return lin ? (r.first + i) * es : r.off[x] + (bc ? 0 : (int64_t)r.col * es);
+}
+// on to the next element (past the last row nothing is read)
+template <class P> OCN_HDF void rows_next(const P &p, RowsPlace &r) {
+  if (++r.col == p.inner && p.nouter) {
+    r.col = 0;
+    rows_outer(p, ++r.row, r.off);
+  }
+}
+
+template <class G> __global__ __launch_bounds__(kBlock) void ew_rows_kernel(const RowsArgs by_value) {
+  constexpr int V = G::VR, U = G::UR;
+  using SAt = typename G::SAt;
+  using SBt = typename G::SBt;
+  using SOt = typename G::SOt;
+  constexpr int ALA = scalar_bytes(G::SA_DT), ALB = scalar_bytes(G::SB_DT), ALO = scalar_bytes(G::SO_DT);
+  constexpr int ESA = (int)sizeof(SAt), ESB = (int)sizeof(SBt), ESO = (int)sizeof(SOt);
+  constexpr bool BIN = G::NIN2;
+  (void)by_value;  // read through the kernarg segment: the outer dims are indexed at run time
+  using KArgs = const __attribute__((address_space(4))) RowsArgs;
+  KArgs &p = *(KArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  OCN_ARGS_NOW("s"(p.out), "s"(p.a), "s"(p.b), "s"(p.numel), "s"(p.nvec), "s"(p.flags), "s"(p.block), "s"(p.shift),
+               "s"(p.inner), "s"(p.rdiv.d), "s"(p.rdiv.m), "s"(p.rdiv.s), "s"(p.nouter));
+  const uint32_t flags = p.flags, block = p.block;
+  const bool flat = (flags & kRowsFlat) != 0;
+  const bool alin = (flags & kRowsALinear) != 0, blin = (flags & kRowsBLinear) != 0;
+  const bool abc = (flags & kRowsABcast) != 0, bbc = (flags & kRowsBBcast) != 0;
+
+  const int64_t g0 = (int64_t)blockIdx.x * (int64_t)(block * U) + threadIdx.x;
+  Pack<SAt, V> va[U];
+  Pack<SBt, V> vb[U];
+  char *po[U];
+  int lo[U], hi[U];
+  bool inrow[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t g = g0 + (int64_t)u * block;
+    lo[u] = hi[u] = 0;
+    inrow[u] = true;
+    if (g < p.nvec) {
+      RowsPlace r = rows_place<V>(p, g);
+      lo[u] = r.lo;
+      hi[u] = r.hi;
+      inrow[u] = r.inrow;
+      po[u] = p.out + rows_offset(r, 0, 0, ESO, flat, false);
+      const bool whole = r.hi - r.lo == V;
+      const bool va_ok = whole && (alin || r.inrow), vb_ok = !BIN || (whole && (blin || r.inrow));
+      if (va_ok) {
+        const char *pa = p.a + rows_offset(r, 1, 0, ESA, alin, abc);
+        if (abc && !alin) va[u].v[0] = *reinterpret_cast<const SAt *>(pa);
+        else load_pack_any<SAt, V, ALA>(pa, va[u], (flags & kRowsNtA) != 0);
+      }
+      if constexpr (BIN) {
+        if (vb_ok) {
+          const char *pb = p.b + rows_offset(r, 2, 0, ESB, blin, bbc);
+          if (bbc && !blin) vb[u].v[0] = *reinterpret_cast<const SBt *>(pb);
+          else load_pack_any<SBt, V, ALB>(pb, vb[u], (flags & kRowsNtB) != 0);
+        }
+      }
+      // element by element: a vector that is not whole, or an input whose rows it crosses
+      if (!va_ok || !vb_ok) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+          if (i >= r.lo && i < r.hi) {
+            if (!va_ok) va[u].v[i] = *reinterpret_cast<const SAt *>(p.a + rows_offset(r, 1, i, ESA, alin, abc));
+            if constexpr (BIN) {
+              if (!vb_ok) vb[u].v[i] = *reinterpret_cast<const SBt *>(p.b + rows_offset(r, 2, i, ESB, blin, bbc));
+            }
+            rows_next(p, r);
+          }
+        }
+      }
+    }
+  }
+  const int swap = (int)(flags >> kRowsSwapShift);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int n = hi[u] - lo[u];
+    if (n > 0) {
+      if (n == V && inrow[u]) {   // an input broadcast along the row: its one element, spread out
+        if (abc && !alin) {
+#pragma unroll
+          for (int i = 1; i < V; ++i) va[u].v[i] = va[u].v[0];
+        }
+        if constexpr (BIN) {
+          if (bbc && !blin) {
+#pragma unroll
+            for (int i = 1; i < V; ++i) vb[u].v[i] = vb[u].v[0];
+          }
+        }
+      }
+      Pack<SOt, V> r;
+      if (swap) G::order_inputs(swap, va[u], vb[u]);
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        if constexpr (BIN) r.v[i] = G::eval(va[u].v[i], vb[u].v[i]);
+        else r.v[i] = G::eval(va[u].v[i], SBt{});
+      }
+      if (swap) G::order_output(swap, r);
+      if (n == V) {
+        store_pack_any<SOt, V, ALO>(po[u], r, (flags & kRowsNtStore) != 0);
+      } else {
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+          if (i >= lo[u] && i < hi[u]) reinterpret_cast<SOt *>(po[u])[i] = r.v[i];
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------

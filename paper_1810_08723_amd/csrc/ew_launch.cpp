@@ -2,6 +2,7 @@
 #include "ew_launch.hpp"
 
 #include <algorithm>
+#include <cstdint>
 #include <cstring>
 
 namespace ocn {
@@ -9,13 +10,16 @@ namespace ocn {
 EwLauncher g_binary_launchers[B_COUNT][DT_COUNT][DT_COUNT][DT_COUNT];
 EwLauncher g_unary_launchers[U_COUNT][DT_COUNT][DT_COUNT];
 
-RowsArgs make_rows_args(const EwPlan &p) {
+RowsArgs make_rows_args(const EwPlan &p, int64_t *grid) {
   RowsArgs r;
   std::memset(&r, 0, sizeof r);
   r.out = p.out.ptr;
   r.a = p.a.ptr;
   r.b = p.b.ptr;
+  r.numel = p.numel;
   const int inner = p.ndim - 1;
+  const int64_t n0 = p.size[inner];
+  const int es_o = dt_size(p.out.dtype), es_a = dt_size(p.a.dtype), es_b = dt_size(p.b.dtype);
   r.nouter = inner;
   for (int k = 0; k < inner; ++k) {  // fastest outer dim first
     const int d = inner - 1 - k;
@@ -24,16 +28,42 @@ RowsArgs make_rows_args(const EwPlan &p) {
     r.sb[k] = p.b.stride[d];
     r.odiv[k] = make_fastdiv((uint32_t)p.size[d]);
   }
-  r.inner = p.size[inner];
-  const int64_t vpr = (r.inner + p.vec - 1) / p.vec;
-  r.vpr_div = make_fastdiv((uint32_t)(inner > 0 ? vpr : 1));
-  r.nvec = vpr * (p.numel / r.inner);
-  r.a_bcast = p.a_inner_bcast;
-  r.b_bcast = p.b_inner_bcast;
-  r.nt_store = p.nt_store;
-  r.swap = p.swap;
-  r.nt_a = p.nt_a;
-  r.nt_b = p.nt_b;
+  r.inner = (uint32_t)std::min<int64_t>(n0, INT32_MAX);   // (longer than that only without outer dims: unused)
+  // is the operand one contiguous run in the order of the dims?
+  auto linear = [&](const Operand &x, int es) {
+    int64_t expect = es;
+    for (int d = inner; d >= 0; --d) {
+      if (x.stride[d] != expect) return false;
+      expect *= p.size[d];
+    }
+    return true;
+  };
+  r.flags = (p.a_inner_bcast ? kRowsABcast : 0u) | (p.b_inner_bcast ? kRowsBBcast : 0u) | (p.nt_store ? kRowsNtStore : 0u) |
+            ((uint32_t)p.swap << kRowsSwapShift);
+  // flat form: element numbers are split into row and column in 32 bits
+  if (linear(p.out, es_o) && (inner == 0 || p.numel + 2 * p.vec < ((int64_t)1 << 31))) {
+    r.flags |= kRowsFlat;
+    // (not where the one vector more that a shift may take would be one workgroup too many)
+    if ((intptr_t)p.out.ptr % es_o == 0 && p.numel / p.vec + 2 < max_launch_blocks() * kBlock * p.unroll)
+      r.shift = (uint32_t)(((intptr_t)p.out.ptr / es_o) % p.vec);
+    r.nvec = (p.numel + r.shift + p.vec - 1) / p.vec;
+    r.rdiv = make_fastdiv(r.inner);
+    // (the streaming hint only where the vectors of the input are aligned like the output's)
+    auto aligned = [&](const Operand &x, int es) { return ((intptr_t)x.ptr - (int64_t)r.shift * es) % ((int64_t)p.vec * es) == 0; };
+    if (linear(p.a, es_a)) r.flags |= kRowsALinear | (p.nt_a && aligned(p.a, es_a) ? kRowsNtA : 0u);
+    if (p.nin == 2 && linear(p.b, es_b)) r.flags |= kRowsBLinear | (p.nt_b && aligned(p.b, es_b) ? kRowsNtB : 0u);
+  } else {
+    const int64_t vpr = (n0 + p.vec - 1) / p.vec;
+    r.rdiv = make_fastdiv((uint32_t)(inner > 0 ? vpr : 1));
+    r.nvec = vpr * (p.numel / n0);
+  }
+  // one-wavefront workgroups, four times fewer of four wavefronts where a launch cannot have as many
+  r.block = kSlimBlock;
+  *grid = (r.nvec + (int64_t)r.block * p.unroll - 1) / ((int64_t)r.block * p.unroll);
+  if (*grid > max_launch_blocks()) {
+    r.block = kBlock;
+    *grid = (r.nvec + (int64_t)r.block * p.unroll - 1) / ((int64_t)r.block * p.unroll);
+  }
   return r;
 }
 
@@ -41,7 +71,7 @@ bool make_rows_slim_args(const EwPlan &p, int block, RowsSlimArgs *args, int64_t
   const int inner = p.ndim - 1;
   if (inner < 0 || inner > 1) return false;
   const int64_t n0 = p.size[inner];
-  if (n0 % p.vec != 0) return false;
+  if (!p.rows_aligned || n0 % p.vec != 0) return false;
   const int64_t vpr = n0 / p.vec;
   const int64_t nvec = vpr * (inner == 1 ? p.size[0] : 1);
   const int64_t g = (nvec + (int64_t)block * p.unroll - 1) / ((int64_t)block * p.unroll);

@@ -13,7 +13,8 @@ using EwLauncher = hipError_t (*)(const EwPlan &, hipStream_t);
 extern EwLauncher g_binary_launchers[B_COUNT][DT_COUNT][DT_COUNT][DT_COUNT];
 extern EwLauncher g_unary_launchers[U_COUNT][DT_COUNT][DT_COUNT];
 
-RowsArgs make_rows_args(const EwPlan &p);
+// arguments and grid of the kernel for rows of any length and alignment
+RowsArgs make_rows_args(const EwPlan &p, int64_t *grid);
 // arguments of the kernel for the common row shapes; false if the plan is not one of them
 bool make_rows_slim_args(const EwPlan &p, int block, RowsSlimArgs *args, int64_t *grid);
 TiledArgs make_tiled_args(const EwPlan &p, int es_a);
@@ -32,8 +33,8 @@ hipError_t launch_ew(const EwPlan &p, hipStream_t stream) {
     if (make_rows_slim_args(p, kSlimBlock, &slim, &slim_grid)) {
       hipLaunchKernelGGL((ew_rows_slim_kernel<G>), dim3((unsigned)slim_grid), dim3(kSlimBlock), 0, stream, slim);
     } else {
-      const RowsArgs args = make_rows_args(p);
-      hipLaunchKernelGGL((ew_rows_kernel<G>), dim3((unsigned)p.grid), dim3(kBlock), 0, stream, args);
+      const RowsArgs args = make_rows_args(p, &slim_grid);
+      hipLaunchKernelGGL((ew_rows_kernel<G>), dim3((unsigned)slim_grid), dim3(args.block), 0, stream, args);
     }
   } else if (p.fast_tiled) {
     const FastTiledArgs args = make_fast_tiled_args(p, (int)sizeof(typename G::SAt));

@@ -422,7 +422,7 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
   bool rows = p.specialised && p.out.stride[inner] == es_o && inner_ok(p.a.stride[inner], es_a) &&
               (nin == 1 || inner_ok(p.b.stride[inner], es_b));
   if (rows) {
-    // every row start of every non-broadcast operand must be aligned to its vector
+    // does every row of every non-broadcast operand start on a boundary of its vector?
     auto aligned = [&](const Operand &x, int es) {
       if (x.stride[inner] == 0) return true;
       const int64_t vb = (int64_t)V * es;
@@ -431,16 +431,17 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
         if (x.stride[d] % vb != 0) return false;
       return true;
     };
-    rows = aligned(p.out, es_o) && aligned(p.a, es_a) && (nin == 1 || aligned(p.b, es_b));
+    p.rows_aligned = aligned(p.out, es_o) && aligned(p.a, es_a) && (nin == 1 || aligned(p.b, es_b));
     // 32-bit vector and row indices (a flat 1-D tensor needs no division and may be larger)
     const int64_t vpr = (p.size[inner] + V - 1) / V;
     const int64_t nrows = numel / p.size[inner];
     if (n > 1 && (vpr * nrows >= ((int64_t)1 << 31))) rows = false;
-    // more workgroups than one launch may have: the generic kernel, which loops, takes it
+    // more workgroups than one launch may have: the generic kernel, which loops, takes it (rows
+    // that are not aligned go to the tiled kernel below, which has its own numbering)
     if ((vpr * nrows + (int64_t)kBlock * rows_stream_unroll(V, es_min) - 1) /
             ((int64_t)kBlock * rows_stream_unroll(V, es_min)) > max_launch_blocks()) {
       rows = false;
-      p.specialised = false;
+      if (p.rows_aligned) p.specialised = false;
     }
     if (rows) {
       p.kernel = OCN_KERNEL_EW_ROWS;

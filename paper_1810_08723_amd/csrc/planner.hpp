@@ -59,6 +59,7 @@ struct EwPlan {
   int vec = 1;                  // elements per lane access
   int unroll = 1;               // vectors per lane
   bool a_inner_bcast = false, b_inner_bcast = false;
+  bool rows_aligned = false;    // every row of every operand starts on a vector boundary
   // tiled kernel
   int tile_log2[kMaxDims] = {0};
   int tile_bits = 0;            // log2 of the elements of one tile
