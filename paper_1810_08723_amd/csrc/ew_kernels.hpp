@@ -1,12 +1,14 @@
 // Elementwise kernels of the tensor engine for gfx950 (wave64, 256-lane workgroups).
 //
-// Three kernels cover every canonical plan the host planner can produce:
+// These kernels cover every canonical plan the host planner can produce:
 //   ew_rows_kernel    every operand is contiguous (or broadcast) along the innermost canonical
 //                     dimension: 128-bit lane accesses, several vectors in flight per lane.
 //   ew_tiled_kernel   operands disagree on their fastest axis: a power-of-two tile spanning
 //                     those axes is staged through LDS so that every operand is read and
 //                     written along its own fastest axis.  Without staging it is the plain
 //                     strided kernel for specialised dtypes.
+//   ew_tiled_fast_kernel, ew_tiled_any_kernel  the same tiles for the plans that are whole, aligned
+//                     vectors throughout, and for clipped tiles and any alignment.
 //   ew_interp_kernel  any dtype combination, conversions chosen by runtime switches.
 // The operations follow sections 3.2 and 3.2.1 of the paper (elementwise arithmetic with
 // implicit type casting fused into the kernel: no intermediate tensors).
@@ -45,6 +47,10 @@ enum : uint32_t {
   kRowsNtStore = 128,                   // stream the output past the caches
   kRowsSwapShift = 8
 };
+
+// Launches of at most this many tiles fetch all their arguments first (warm_arguments); in larger
+// ones the extra scalar loads of every wavefront cost more than the few first misses.
+constexpr int64_t kWarmTiles = 2048;
 
 constexpr int kMaxTilePasses = 16;  // a tile holds at most 4096 elements = 16 passes of 256 lanes
 
@@ -103,6 +109,7 @@ struct FastOrder {
 struct FastTiledArgs {
   char *out;
   const char *a, *b;
+  int32_t warm;                             // few workgroups: touch all argument lines first
   int32_t ntd;                              // entries of the tile-number decomposition, fastest first
   int32_t stage_a, stage_b;
   int32_t nt_store;                         // stream the output past the caches
@@ -120,6 +127,50 @@ struct FastTiledArgs {
   uint32_t st_el[2][16];                    // ... from the element number inside a vector
   uint32_t rd_hi[2][kMaxTilePasses];        // compute-phase reads: from the pass number
   uint32_t rd_ch[2][16];                    // ... from the 16-byte chunk inside a vector
+};
+
+// Arguments of the tiled kernel for clipped tiles and operands that are aligned to their elements
+// only: the tables of the form above, plus what it takes to tell which elements of a clipped tile
+// exist.  A tile's limits, and the coordinates contributed by a pass number, are packed as 16 bits
+// per tiled dim, in the enumeration order of the operand they are compared for.
+constexpr int kAnyDims = 4;                 // most tiled dims
+constexpr int kAnyMaxBlock = 1024;
+struct AnyOrder {
+  int32_t niter;                            // passes of the workgroup's lanes
+  int32_t vecw;                             // log2 of the vector length along the first dim
+  uint32_t nvec;                            // vectors of the tile
+  uint32_t shift[kAnyDims], mask[kAnyDims], up[kAnyDims];  // lane number -> coordinate, as FastOrder
+  uint32_t slot_shift[kAnyDims];
+  uint32_t stride[3][kAnyDims];             // byte strides for out / a / b
+  uint32_t lim_shift[kAnyDims];             // where that dim's limit sits in the packed limits
+  uint32_t hi_off[3][kMaxTilePasses];       // byte offsets contributed by the pass number
+  uint64_t hi_c[kMaxTilePasses];            // packed coordinates contributed by the pass number
+};
+struct AnyTiledArgs {
+  char *out;
+  const char *a, *b;
+  int32_t warm;                             // few workgroups: touch all argument lines first
+  uint32_t block;                           // lanes per workgroup: 256, 512 or 1024
+  int32_t nord;                             // tiled dims
+  int32_t ntd;                              // entries of the tile-number decomposition, fastest first
+  int32_t stage_a, stage_b;
+  int32_t nt_store, swap;                   // as FastTiledArgs
+  uint32_t sa0, sb0;                        // byte strides of the inputs along the output's fastest dim
+  uint32_t stage_stride[2];                 // byte stride of a staged input along its own fastest dim
+  const char *end[2];                       // ends of the inputs: one past the highest byte
+  uint32_t lds_base[2], es_log2[2];
+  uint64_t inner;                           // the limits of a tile that is not the last along any dim
+  uint64_t whole;                           // the limits of an unclipped tile: its extents
+  FastDiv ntdiv[kMaxDims];
+  int64_t step[3][kMaxDims];                // bytes from one tile to the next along that dim
+  uint32_t dim_shift[kMaxDims];             // where the dim's limit sits in the packed limits (64: not a tiled dim)
+  uint32_t last[kMaxDims];                  // the limit of the dim's last tile
+  TileSwizzle swz[2];
+  AnyOrder ord[3];
+  uint32_t st_hi[2][kMaxTilePasses];        // LDS byte addresses, as FastTiledArgs
+  uint32_t st_el[2][16];
+  uint32_t rd_hi[2][kMaxTilePasses];
+  uint32_t rd_el[2][16];                    // compute-phase reads: from the element number inside a vector
 };
 
 struct InterpArgs {
@@ -712,6 +763,19 @@ OCN_HDF uint32_t swizzle(uint32_t slot, const TileSwizzle &z) { return swizzle(s
 
 extern __shared__ uint4 ocn_lds_raw[];
 
+// Touches every 64-byte line of a kernel's arguments at once.  They arrive over the scalar cache,
+// one line per miss and a miss per table, and a wavefront of a tiled kernel reads from a dozen
+// tables one after the other: left to themselves those round trips were a third of the time
+// of a small launch (17 000 floats added: 6.4 -> 5.2 us).
+using KTable = const __attribute__((address_space(4))) uint32_t;
+template <class Args> OCN_DEV void warm_arguments() {
+  KTable *k = (KTable *)__builtin_amdgcn_kernarg_segment_ptr();
+  uint32_t any = 0;
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(Args) / 64); ++i) any |= k[i * 16];
+  asm volatile("" ::"s"(any));
+}
+
 // The kernel reads its argument struct through the constant address space (the kernarg
 // segment itself): indexing the per-pass tables with a runtime pass number then becomes a
 // scalar load instead of forcing a private copy of the whole struct.
@@ -981,6 +1045,7 @@ template <class G> __global__ __launch_bounds__(kBlock) void ew_tiled_fast_kerne
   (void)by_value;  // read through the kernarg segment instead (it is the only argument)
   KFastArgs &p = *(KFastArgs *)__builtin_amdgcn_kernarg_segment_ptr();
   char *lds = reinterpret_cast<char *>(ocn_lds_raw);
+  if (p.warm) warm_arguments<FastTiledArgs>();
 
   // tile origin (uniform over the workgroup).  Workgroups go to the eight XCDs in turn, each
   // with an L2 of its own: tiles that share input lines (consecutive tile numbers, in groups
@@ -1113,6 +1178,251 @@ template <class G> __global__ __launch_bounds__(kBlock) void ew_tiled_fast_kerne
       if (p.swap) G::order_output(p.swap, r);
       store_pack<SOt, VC>(out + p.ord[0].hi_off[0][jj] + off[0], r, p.nt_store != 0);
     }
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// tiled kernel, any size and alignment
+// ---------------------------------------------------------------------------------------
+//
+// The all-vector form above for tiles that are clipped by the end of the tensor and operands
+// whose rows start anywhere: unaligned 16-byte accesses, and per vector a comparison of its
+// coordinates with the tile's limits, which costs a scalar subtraction and a vector compare per
+// tiled dim where the tile is clipped and nothing where it is not.  Inputs that are not
+// staged may be contiguous, broadcast or strided along the output's fastest dim.
+
+using KAnyArgs = const __attribute__((address_space(4))) AnyTiledArgs;
+using KAnyOrder = const __attribute__((address_space(4))) AnyOrder;
+
+// lane part of a vector's position: coordinates, byte offsets, LDS slot
+struct AnyLane {
+  uint32_t c[kAnyDims];
+  uint32_t off[3];
+  uint32_t slot;
+};
+template <class O> OCN_HDF AnyLane any_lane(const O &o, int nord, uint32_t tid) {
+  AnyLane r;
+  r.off[0] = r.off[1] = r.off[2] = r.slot = 0;
+#pragma unroll
+  for (int k = 0; k < kAnyDims; ++k) {
+    r.c[k] = 0;
+    if (k < nord) {
+      r.c[k] = ((tid >> o.shift[k]) & o.mask[k]) << o.up[k];
+#pragma unroll
+      for (int x = 0; x < 3; ++x) r.off[x] += r.c[k] * o.stride[x][k];
+      r.slot += r.c[k] << o.slot_shift[k];
+    }
+  }
+  return r;
+}
+// how many elements of the lane's vector in this pass lie inside a tile with these limits
+template <class O> OCN_HDF int any_inside(const O &o, int nord, const AnyLane &l, uint64_t lim, uint64_t hi_c, int v) {
+  int n = v;
+#pragma unroll
+  for (int k = 0; k < kAnyDims; ++k) {
+    if (k < nord) {
+      const int left = (int)((uint32_t)(lim >> o.lim_shift[k]) & 0xffffu) - (int)((uint32_t)(hi_c >> (16 * k)) & 0xffffu) -
+                       (int)l.c[k];
+      if (k == 0) n = left < n ? left : n;
+      else if (left <= 0) n = 0;
+    }
+  }
+  return n < 0 ? 0 : n;
+}
+// tile number -> offsets of its origin and its limits (packed in the output's order)
+template <class P> OCN_HDF uint64_t any_tile(const P &p, uint32_t t, int64_t (&base)[3]) {
+  uint64_t lim = p.inner;
+  base[0] = base[1] = base[2] = 0;
+  const int ntd = p.ntd;
+  for (int j = 0; j < ntd; ++j) {
+    const uint32_t dv = p.ntdiv[j].d;
+    const uint32_t q = j + 1 < ntd ? fastdiv(t, FastDiv{dv, p.ntdiv[j].m, p.ntdiv[j].s}) : 0u;
+    const uint32_t tc = t - q * dv;
+    t = q;
+    for (int x = 0; x < 3; ++x) base[x] += (int64_t)tc * p.step[x][j];
+    const uint32_t sh = p.dim_shift[j];
+    if (sh < 64 && tc + 1 == dv) lim = (lim & ~((uint64_t)0xffffu << sh)) | ((uint64_t)p.last[j] << sh);
+  }
+  return lim;
+}
+
+// Where a lane loads the whole vector at `src` from: at src, or - a vector at the end of a clipped
+// tile, of which only the first elements exist - as far before it as the operand's last byte
+// demands; `back` is the distance in elements.  The elements in between belong to the operand's
+// storage and are dropped.  (Loading just the elements that exist takes a branch with loads on
+// both sides, and the compiler waits for one side before it issues the other.)
+OCN_HDF const char *any_address(const char *src, const char *last, int es_log2, int &back) {
+  const bool over = src > last;
+  back = over ? (int)((src - last) >> es_log2) : 0;
+  return over ? last : src;
+}
+// element i of the vector is element i + back of what was loaded
+template <class S, int V> OCN_DEV void any_shift(Pack<S, V> &v, int back) {
+  while (back > 0) {
+#pragma unroll
+    for (int i = 0; i + 1 < V; ++i) v.v[i] = v.v[i + 1];
+    --back;
+  }
+}
+// n of V elements from global memory, s0 bytes apart
+template <class S, int V, int AL> OCN_DEV void any_load(const char *src, const char *last, uint32_t s0, int n, Pack<S, V> &v, int &back) {
+  back = 0;
+  if (n > 0) {
+    if (s0 == (uint32_t)sizeof(S)) {
+      constexpr int L = sizeof(S) == 16 ? 4 : sizeof(S) == 8 ? 3 : sizeof(S) == 4 ? 2 : sizeof(S) == 2 ? 1 : 0;
+      load_pack_any<S, V, AL>(any_address(src, last, L, back), v);
+    } else {
+#pragma unroll
+      for (int i = 0; i < V; ++i)   // (past the last element that exists: that one again)
+        v.v[i] = *reinterpret_cast<const S *>(src + (uint32_t)(i < n ? i : n - 1) * s0);
+    }
+  }
+}
+// one vector of a staged input into LDS
+template <class S, int V> OCN_DEV void any_park(char *lds, uint32_t addr, const Pack<S, V> &v, int n, KTable *el) {
+#pragma unroll
+  for (int i = 0; i < V; ++i)
+    if (i < n) *reinterpret_cast<S *>(lds + (addr ^ el[i])) = v.v[i];
+}
+template <class S, int V> OCN_DEV void any_staged(const char *lds, uint32_t addr, KTable *el, Pack<S, V> &v) {
+  constexpr int EP = (16 / (int)sizeof(S)) < V ? (16 / (int)sizeof(S)) : V;  // elements per LDS access
+#pragma unroll
+  for (int c = 0; c < V; c += EP)
+    *reinterpret_cast<Pack<S, EP> *>(&v.v[c]) = *reinterpret_cast<const Pack<S, EP> *>(lds + (addr ^ el[c]));
+}
+
+// One vector per lane, operand and pass, and enough lanes (256 to 1024, the planner's choice) that
+// a tile takes one or two passes: two or four vectors per lane held over the same loop needed 92
+// to 151 vector registers instead of 58 and ran 10 to 25 % slower.  float 6000 x 5000 plus a
+// transpose: 86.7 us in the general form, 74.8 here; 500 x 381 x 250: 243 -> 133; complex products
+// of five-dimensional views [15, 31, 63, 61, 7]: 163 -> 98, [12, 6, 11, 3, 19]: 16.2 -> 7.7.
+template <class G> __global__ __launch_bounds__(kAnyMaxBlock) void ew_tiled_any_kernel(const AnyTiledArgs by_value) {
+  using SAt = typename G::SAt;
+  using SBt = typename G::SBt;
+  using SOt = typename G::SOt;
+  constexpr bool BIN = G::NIN2;
+  constexpr int VA = 16 / (int)sizeof(SAt) > 1 ? 16 / (int)sizeof(SAt) : 1;
+  constexpr int VB = 16 / (int)sizeof(SBt) > 1 ? 16 / (int)sizeof(SBt) : 1;
+  constexpr int V = G::V;
+  constexpr int ALA = scalar_bytes(G::SA_DT), ALB = scalar_bytes(G::SB_DT), ALO = scalar_bytes(G::SO_DT);
+  (void)by_value;  // read through the kernarg segment instead (it is the only argument)
+  KAnyArgs &p = *(KAnyArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  char *lds = reinterpret_cast<char *>(ocn_lds_raw);
+  if (p.warm) warm_arguments<AnyTiledArgs>();
+  const uint32_t tid = threadIdx.x, block = p.block;
+  const int nord = p.nord;
+  const bool stage_a = p.stage_a, stage_b = BIN && p.stage_b;
+  int64_t base[3];
+  const uint64_t lim = any_tile(p, blockIdx.x, base);
+  const bool full = lim == p.whole;
+  char *out = p.out + base[0];
+  const char *pa = p.a + base[1];
+  const char *pb = BIN ? p.b + base[2] : nullptr;
+
+  // How many elements of the lane's vector in this pass exist.  (A pass never reaches niter; the
+  // comparison is there for what the compiler makes of the loads around it: without it the
+  // complex products of [15, 31, 63, 61, 7] took 106 us instead of 97.)
+  auto inside = [&](KAnyOrder &o, const AnyLane &l, int pass, int v) -> int {
+    if (pass >= o.niter || tid + (uint32_t)pass * block >= o.nvec) return 0;
+    return full ? v : any_inside(o, nord, l, lim, o.hi_c[pass], v);
+  };
+
+  // inputs read in place: the first pass is on its way while the staged ones are fetched
+  KAnyOrder &oo = p.ord[0];
+  const AnyLane lo = any_lane(oo, nord, tid);
+  Pack<SAt, V> av;
+  Pack<SBt, V> bv;
+  int n, back_a, back_b;
+  auto fetch = [&](int j) {
+    n = inside(oo, lo, j, V);
+    if (!stage_a)
+      any_load<SAt, V, ALA>(pa + oo.hi_off[1][j] + lo.off[1], p.end[0] - V * (int)sizeof(SAt), p.sa0, n, av, back_a);
+    if constexpr (BIN) {
+      if (!stage_b)
+        any_load<SBt, V, ALB>(pb + oo.hi_off[2][j] + lo.off[2], p.end[1] - V * (int)sizeof(SBt), p.sb0, n, bv, back_b);
+    }
+  };
+  fetch(0);
+
+  if (stage_a || stage_b) {
+    AnyLane la, lb;
+    uint32_t wa = 0, wb = 0;  // lane part of the swizzled LDS byte address
+    int na = 0, nb = 0;
+    if (stage_a) {
+      la = any_lane(p.ord[1], nord, tid);
+      wa = (swizzle(la.slot, p.swz[0].src, p.swz[0].mask, p.swz[0].dst) << p.es_log2[0]) | p.lds_base[0];
+      na = p.ord[1].niter;
+    }
+    if (stage_b) {
+      lb = any_lane(p.ord[2], nord, tid);
+      wb = (swizzle(lb.slot, p.swz[1].src, p.swz[1].mask, p.swz[1].dst) << p.es_log2[1]) | p.lds_base[1];
+      nb = p.ord[2].niter;
+    }
+    const int nmax = na > nb ? na : nb;
+    for (int j = 0; j < nmax; ++j) {
+      Pack<SAt, VA> va;
+      Pack<SBt, VB> vb;
+      int ca = 0, cb = 0, da, db;
+      // (both loads are issued before either vector is parked)
+      if (j < na) {
+        ca = inside(p.ord[1], la, j, VA);
+        any_load<SAt, VA, ALA>(pa + p.ord[1].hi_off[1][j] + la.off[1], p.end[0] - VA * (int)sizeof(SAt), p.stage_stride[0], ca, va, da);
+      }
+      if constexpr (BIN) {
+        if (j < nb) {
+          cb = inside(p.ord[2], lb, j, VB);
+          any_load<SBt, VB, ALB>(pb + p.ord[2].hi_off[2][j] + lb.off[2], p.end[1] - VB * (int)sizeof(SBt), p.stage_stride[1], cb, vb, db);
+        }
+      }
+      if (j < na) {
+        if (!full) any_shift<SAt, VA>(va, da);
+        any_park<SAt, VA>(lds, wa ^ p.st_hi[0][j], va, ca, p.st_el[0]);
+      }
+      if constexpr (BIN) {
+        if (j < nb) {
+          if (!full) any_shift<SBt, VB>(vb, db);
+          any_park<SBt, VB>(lds, wb ^ p.st_hi[1][j], vb, cb, p.st_el[1]);
+        }
+      }
+    }
+    __syncthreads();
+  }
+
+  // compute phase, in the output's order
+  const uint32_t slot = tid * (uint32_t)V;
+  uint32_t ra = 0, rb = 0;
+  if (stage_a) ra = (swizzle(slot, p.swz[0].src, p.swz[0].mask, p.swz[0].dst) << p.es_log2[0]) | p.lds_base[0];
+  if (stage_b) rb = (swizzle(slot, p.swz[1].src, p.swz[1].mask, p.swz[1].dst) << p.es_log2[1]) | p.lds_base[1];
+  const int niter = oo.niter;
+  for (int j = 0;;) {
+    if (n > 0) {
+      if (stage_a) any_staged<SAt, V>(lds, ra ^ p.rd_hi[0][j], p.rd_el[0], av);
+      else if (!full) any_shift<SAt, V>(av, back_a);
+      if constexpr (BIN) {
+        if (stage_b) any_staged<SBt, V>(lds, rb ^ p.rd_hi[1][j], p.rd_el[1], bv);
+        else if (!full) any_shift<SBt, V>(bv, back_b);
+      }
+    }
+    if (n > 0) {
+      Pack<SOt, V> r;
+      if (p.swap) G::order_inputs(p.swap, av, bv);
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        if constexpr (BIN) r.v[i] = G::eval(av.v[i], bv.v[i]);
+        else r.v[i] = G::eval(av.v[i], SBt{});
+      }
+      if (p.swap) G::order_output(p.swap, r);
+      char *po = out + oo.hi_off[0][j] + lo.off[0];
+      if (n == V) {
+        store_pack_any<SOt, V, ALO>(po, r, p.nt_store != 0);
+      } else {
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+          if (i < n) reinterpret_cast<SOt *>(po)[i] = r.v[i];
+      }
+    }
+    if (++j >= niter) break;  // uniform
+    fetch(j);
   }
 }
 

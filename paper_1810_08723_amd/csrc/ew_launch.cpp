@@ -183,6 +183,7 @@ FastTiledArgs make_fast_tiled_args(const EwPlan &p, int es_a) {
   const TiledArgs t = make_tiled_args(p, es_a);
   FastTiledArgs f;
   std::memset(&f, 0, sizeof f);
+  f.warm = p.total_tiles <= kWarmTiles;
   f.out = t.out;
   f.a = t.a;
   f.b = t.b;
@@ -275,6 +276,108 @@ FastTiledArgs make_fast_tiled_args(const EwPlan &p, int es_a) {
       f.rd_hi[y][j] = swizzle(((uint32_t)j * kBlock) << p.vecw_o, z) << sh;
     const int epc = std::min(std::max(1, 16 / es[y]), 1 << p.vecw_o);
     for (int c = 0; c * epc < (1 << p.vecw_o) && c < 16; ++c) f.rd_ch[y][c] = swizzle((uint32_t)(c * epc), z) << sh;
+  }
+  return f;
+}
+
+AnyTiledArgs make_any_tiled_args(const EwPlan &p, int es_a) {
+  const TiledArgs t = make_tiled_args(p, es_a);
+  AnyTiledArgs f;
+  std::memset(&f, 0, sizeof f);
+  f.out = t.out;
+  f.a = t.a;
+  f.b = t.b;
+  auto end_of = [&](const Operand &x) {
+    const char *e = x.ptr + dt_size(x.dtype);
+    for (int d = 0; d < p.ndim; ++d)
+      if (x.stride[d] > 0) e += (p.size[d] - 1) * x.stride[d];
+    return e;
+  };
+  f.end[0] = end_of(p.a);
+  if (p.nin == 2) f.end[1] = end_of(p.b);
+  f.warm = p.total_tiles <= kWarmTiles;
+  f.block = (uint32_t)p.block;
+  f.nord = p.nord;
+  f.stage_a = t.stage_a;
+  f.stage_b = t.stage_b;
+  f.nt_store = t.nt_store;
+  f.swap = t.swap;
+  f.sa0 = (uint32_t)p.a.stride[p.ord_o[0]];
+  f.sb0 = (uint32_t)p.b.stride[p.ord_o[0]];
+  f.stage_stride[0] = (uint32_t)p.a.stride[p.ord_a[0]];
+  f.stage_stride[1] = (uint32_t)p.b.stride[p.ord_b[0]];
+  // packed limits: 16 bits per tiled dim, in the output's order
+  int pos[kMaxDims];
+  for (int d = 0; d < kMaxDims; ++d) pos[d] = -1;
+  for (int k = 0; k < p.nord; ++k) {
+    const int d = p.ord_o[k];
+    pos[d] = k;
+    f.inner |= (uint64_t)std::min<int64_t>((int64_t)1 << p.tile_log2[d], p.size[d]) << (16 * k);
+    f.whole |= (uint64_t)1 << p.tile_log2[d] << (16 * k);
+  }
+  for (int d = p.ndim - 1; d >= 0; --d) {
+    if (p.ntiles[d] <= 1) continue;
+    const int j = f.ntd++;
+    f.ntdiv[j] = make_fastdiv((uint32_t)p.ntiles[d]);
+    f.step[0][j] = t.so[d] * ((int64_t)1 << t.tl[d]);
+    f.step[1][j] = t.sa[d] * ((int64_t)1 << t.tl[d]);
+    f.step[2][j] = t.sb[d] * ((int64_t)1 << t.tl[d]);
+    f.dim_shift[j] = pos[d] >= 0 ? (uint32_t)(16 * pos[d]) : 64u;
+    f.last[j] = (uint32_t)(p.size[d] - ((p.ntiles[d] - 1) << p.tile_log2[d]));
+  }
+  const int es[2] = {es_a, p.nin == 2 ? dt_size(p.b.dtype) : 1};
+  const int64_t tile_elems = (int64_t)1 << p.tile_bits;
+  const int64_t bytes_a = p.stage_a ? tile_elems * es[0] : 0, bytes_b = p.stage_b ? tile_elems * es[1] : 0;
+  // the larger staging area first, so that each base can be OR-ed into XOR-built addresses
+  if (bytes_a >= bytes_b) { f.lds_base[0] = 0; f.lds_base[1] = (uint32_t)bytes_a; }
+  else { f.lds_base[1] = 0; f.lds_base[0] = (uint32_t)bytes_b; }
+  for (int y = 0; y < 2; ++y) {
+    f.swz[y] = t.swz[y];
+    while ((1 << f.es_log2[y]) < es[y]) ++f.es_log2[y];
+  }
+  uint32_t hi_slot[3][kMaxTilePasses];
+  const uint32_t lane_bits = f.block == 1024 ? 10 : f.block == 512 ? 9 : 8;
+  for (int x = 0; x < 3; ++x) {
+    const TileOrder &o = t.ord[x];
+    AnyOrder &g = f.ord[x];
+    g.vecw = o.vecw;
+    g.nvec = (uint32_t)(tile_elems >> o.vecw);
+    g.niter = (int32_t)((g.nvec + f.block - 1) / f.block);
+    uint32_t shift = 0, upper[kAnyDims], above[kAnyDims];   // bits of each dim's index held by the pass number
+    for (int k = 0; k < o.nord; ++k) {
+      const uint32_t vw = k == 0 ? (uint32_t)o.vecw : 0u, w = (uint32_t)o.width[k] - vw;
+      const uint32_t wl = shift < lane_bits ? std::min(w, lane_bits - shift) : 0u;   // bits held by the lane number
+      g.shift[k] = std::min(shift, 31u);
+      g.mask[k] = (1u << wl) - 1u;
+      g.up[k] = vw;
+      g.slot_shift[k] = (uint32_t)o.lds_shift[k];
+      g.lim_shift[k] = (uint32_t)(16 * pos[o.dim[k]]);
+      for (int y = 0; y < 3; ++y) g.stride[y][k] = (uint32_t)o.stride[y][k];
+      upper[k] = w - wl;
+      above[k] = vw + wl;
+      shift += w;
+    }
+    for (int j = 0; j < g.niter; ++j) {
+      const LanePos hi = lane_pos(o, (uint32_t)j * f.block);
+      for (int y = 0; y < 3; ++y) g.hi_off[y][j] = (uint32_t)hi.off[y];
+      hi_slot[x][j] = hi.slot;
+      uint32_t rest = (uint32_t)j;
+      for (int k = 0; k < o.nord; ++k) {
+        const uint32_t c = (rest & ((1u << upper[k]) - 1u)) << above[k];
+        rest >>= upper[k];
+        g.hi_c[j] |= (uint64_t)c << (16 * k);
+      }
+    }
+  }
+  for (int y = 0; y < 2; ++y) {
+    if (!(y == 0 ? p.stage_a : p.stage_b)) continue;
+    const TileOrder &o = t.ord[y + 1];
+    const TileSwizzle &z = t.swz[y];
+    const uint32_t sh = f.es_log2[y];
+    for (int j = 0; j < f.ord[y + 1].niter; ++j) f.st_hi[y][j] = swizzle(hi_slot[y + 1][j], z) << sh;
+    for (int i = 0; i < (1 << o.vecw) && i < 16; ++i) f.st_el[y][i] = swizzle((uint32_t)i << o.lds_shift[0], z) << sh;
+    for (int j = 0; j < f.ord[0].niter; ++j) f.rd_hi[y][j] = swizzle(((uint32_t)j * f.block) << p.vecw_o, z) << sh;
+    for (int i = 0; i < (1 << p.vecw_o) && i < 16; ++i) f.rd_el[y][i] = swizzle((uint32_t)i, z) << sh;
   }
   return f;
 }

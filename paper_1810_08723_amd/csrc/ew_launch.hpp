@@ -19,6 +19,7 @@ RowsArgs make_rows_args(const EwPlan &p, int64_t *grid);
 bool make_rows_slim_args(const EwPlan &p, int block, RowsSlimArgs *args, int64_t *grid);
 TiledArgs make_tiled_args(const EwPlan &p, int es_a);
 FastTiledArgs make_fast_tiled_args(const EwPlan &p, int es_a);
+AnyTiledArgs make_any_tiled_args(const EwPlan &p, int es_a);
 InterpArgs make_interp_args(const EwPlan &p);
 hipError_t launch_interp(const EwPlan &p, hipStream_t stream);
 hipError_t launch_interleave(const EwPlan &p, hipStream_t stream);
@@ -36,6 +37,9 @@ hipError_t launch_ew(const EwPlan &p, hipStream_t stream) {
       const RowsArgs args = make_rows_args(p, &slim_grid);
       hipLaunchKernelGGL((ew_rows_kernel<G>), dim3((unsigned)slim_grid), dim3(args.block), 0, stream, args);
     }
+  } else if (p.kernel == kKernelTiledAny) {
+    const AnyTiledArgs args = make_any_tiled_args(p, (int)sizeof(typename G::SAt));
+    hipLaunchKernelGGL((ew_tiled_any_kernel<G>), dim3((unsigned)p.grid), dim3(args.block), (size_t)p.lds_bytes, stream, args);
   } else if (p.fast_tiled) {
     const FastTiledArgs args = make_fast_tiled_args(p, (int)sizeof(typename G::SAt));
     hipLaunchKernelGGL((ew_tiled_fast_kernel<G>), dim3((unsigned)p.grid), dim3(kBlock), (size_t)p.lds_bytes, stream, args);

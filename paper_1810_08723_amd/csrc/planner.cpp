@@ -229,7 +229,10 @@ void tile_order(const EwPlan &p, const int64_t *stride, int8_t *ord) {
 // than large ones on MI355X once every run is a full cache line.
 constexpr int64_t kMaxLdsBytes = 32 * 1024;
 
-void choose_tiles(EwPlan &p, bool general_form) {
+// kTilesVector: for the all-vector form; kTilesAny: for tiles of any size and alignment;
+// kTilesGeneral: for the general form
+enum TileRule { kTilesVector, kTilesAny, kTilesGeneral };
+void choose_tiles(EwPlan &p, TileRule rule, int fa, int fb) {
   // Operands that want coalescing along their own fastest axis: the output and every staged
   // input.  Tile bits are handed out one at a time, each to the fastest unsaturated dimension
   // of one operand.  First every staged input is grown to a contiguous run of a full 128-byte
@@ -249,7 +252,7 @@ void choose_tiles(EwPlan &p, bool general_form) {
   int vbits = 0;
   while ((1 << vbits) < vmax) ++vbits;
   int preferred = std::min(budget, 8 + vbits);
-  if (general_form) {  // larger tiles, within 16 KiB of LDS
+  if (rule != kTilesVector) {  // larger tiles, within 16 KiB of LDS
     preferred = budget;
     while (preferred > 8 && ((int64_t)staged_bytes << preferred) > 16 * 1024) --preferred;
   }
@@ -289,7 +292,18 @@ void choose_tiles(EwPlan &p, bool general_form) {
     }
     return run;
   };
-  const int64_t target[3] = {p.nt_store ? 128 : 64, 128, 128};
+  // Tiles of any size move whole vectors along the output's and every staged input's fastest dim:
+  // an extent below the vector's length is rounded up to it (its vectors are then never whole).
+  if (rule == kTilesAny) {
+    auto at_least = [&](int d, int bits) {
+      while (d >= 0 && p.tile_log2[d] < bits) { ++p.tile_log2[d]; ++used; }
+    };
+    auto log2i = [](int v) { int l = 0; while ((1 << l) < v) ++l; return l; };
+    at_least(p.ndim - 1, log2i(rows_vec(es[0], es_max)));
+    if (p.stage_a) at_least(fa, log2i(16 / es[1]));
+    if (p.stage_b) at_least(fb, log2i(16 / es[2]));
+  }
+  const int64_t target[3] = {rule == kTilesAny && p.nt_store && !(p.stage_a && p.stage_b) ? 512 : p.nt_store ? 128 : 64, 128, 128};
   bool progress = true;
   while (used < budget && progress) {
     progress = false;
@@ -514,8 +528,8 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
   // axis is shorter than 32 bytes: coalescing along such an axis gains less than the general
   // form's staging costs (measured on channel-last to channel-first copies with 3 channels).
   bool stage_a0 = p.stage_a, stage_b0 = p.stage_b;
-  for (int attempt = 0; attempt < 2; ++attempt) {
-    if (attempt == 1) {
+  for (int rule = kTilesVector; rule <= kTilesGeneral; ++rule) {
+    if (rule == kTilesAny) {
       if (stage_a0 && p.size[fa] * es_a < 32) stage_a0 = false;
       if (stage_b0 && p.size[fb] * es_b < 32) stage_b0 = false;
     }
@@ -523,7 +537,7 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
     p.stage_b = stage_b0;
     for (int d = 0; d < kMaxDims; ++d) p.tile_log2[d] = 0;
     p.fast_tiled = false;
-    choose_tiles(p, attempt == 1);
+    choose_tiles(p, (TileRule)rule, fa, fb);
     tile_order(p, p.out.stride, p.ord_o);
     tile_order(p, p.a.stride, p.ord_a);
     tile_order(p, p.b.stride, p.ord_b);
@@ -537,6 +551,7 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
     // ---- vector widths of the three enumeration orders -----------------------------------
     // aligned: base pointer and every stride except the one along `skip` are multiples of vb
     auto aligned = [&](const Operand &x, int64_t vb, int skip) {
+      if (rule == kTilesAny) return true;   // that form takes any alignment
       if ((intptr_t)x.ptr % vb != 0) return false;
       for (int d = 0; d < n; ++d)
         if (d != skip && x.stride[d] % vb != 0) return false;
@@ -560,6 +575,7 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
         const int v = 16 / es;
         if (v <= 1) return 0;
         const int f = ord[0];
+        if (rule == kTilesAny) return log2i(v);   // (strided: its elements are fetched one by one)
         if (x.stride[f] != es || p.tile_log2[f] < log2i(v) || !aligned(x, 16, f)) return 0;
         return log2i(v);
       };
@@ -583,7 +599,7 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
     // order moves whole vectors over at least one full pass, inputs that are not staged are
     // contiguous along the output's fastest dim, and inside a tile every stride is non-negative
     // with offsets that fit 31 bits.
-    if (p.kernel == OCN_KERNEL_EW_TILED && p.vecw_o > 0) {
+    if (rule != kTilesAny && p.kernel == OCN_KERNEL_EW_TILED && p.vecw_o > 0) {
       bool ok = true;
       const int d0 = p.ord_o[0];
       if (p.stage_a ? p.vecw_a == 0 : p.a.stride[d0] != es_a) ok = false;
@@ -637,7 +653,47 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
       }
       break;
     }
-  }  // attempts
+    if (rule == kTilesAny) {
+      // Tiles of any size and alignment: up to four tiled dims, the output contiguous along its
+      // fastest one, non-negative strides and offsets below 2^31 bytes inside a tile.
+      bool ok = p.nord > 0 && p.nord <= 4 && p.out.stride[p.ord_o[0]] == es_o && p.vecw_o == log2i(VT) && p.tile_bits <= 12 &&
+                (!p.stage_a || p.tile_log2[p.ord_a[0]] >= p.vecw_a) && (!p.stage_b || p.tile_log2[p.ord_b[0]] >= p.vecw_b) && p.total_tiles <= max_launch_blocks();
+      int64_t span_o = 0, span_a = 0, span_b = 0;
+      for (int d = 0; d < n && ok; ++d) {
+        const int64_t ext = (int64_t)1 << p.tile_log2[d];
+        if (ext > 1 && (p.a.stride[d] < 0 || p.b.stride[d] < 0)) ok = false;
+        span_o += ext * p.out.stride[d];
+        span_a += ext * iabs64(p.a.stride[d]);
+        span_b += ext * iabs64(p.b.stride[d]);
+      }
+      const int64_t lim = ((int64_t)1 << 31) - 64;
+      // An input that is read in vectors has to be as long as one: a vector that runs past its end
+      // is loaded from further back.
+      auto long_enough = [&](const Operand &x, int es, bool staged, const int8_t *ord, int vecw) {
+        if (x.stride[staged ? ord[0] : p.ord_o[0]] != es) return true;
+        int64_t bytes = es;
+        for (int d = 0; d < n; ++d) bytes += (p.size[d] - 1) * iabs64(x.stride[d]);
+        return bytes >= (int64_t)es << vecw;
+      };
+      ok = ok && long_enough(p.a, es_a, p.stage_a, p.ord_a, p.stage_a ? p.vecw_a : p.vecw_o) &&
+           (nin == 1 || long_enough(p.b, es_b, p.stage_b, p.ord_b, p.stage_b ? p.vecw_b : p.vecw_o));
+      if (ok && span_o < lim && span_a < lim && span_b < lim) {
+        p.kernel = kKernelTiledAny;
+        // Lanes per workgroup.  With one vector per lane, operand and pass a workgroup of 512 lanes
+        // has a tile of 4096 floats in flight at once and two of them share a CU's wavefront slots
+        // evenly (float 6000 x 5000 plus a transpose: 74.8 us, 79.6 with 256 lanes, 85.3 with 1024),
+        // but more lanes than the output has vectors only wait for the others.  Few tiles leave
+        // most of the chip idle anyway: there every lane is worth having (45 000 complex products: 7.7
+        // us with 1024, 10.3 with 256).
+        const int nvec_o = 1 << (p.tile_bits - p.vecw_o);
+        const int nvec = std::max(nvec_o, std::max(p.stage_a ? 1 << (p.tile_bits - p.vecw_a) : 0, p.stage_b ? 1 << (p.tile_bits - p.vecw_b) : 0));
+        const bool few = p.total_tiles <= kNumCUs;
+        p.block = kBlock;
+        while (p.block < (few ? 1024 : 512) && p.block < (few ? nvec : nvec_o)) p.block *= 2;
+        break;
+      }
+    }
+  }  // rules
   p.vec = 1 << p.vecw_o;
   if (p.total_tiles >= ((int64_t)1 << 31)) {  // tile coordinates are 32-bit: use the 64-bit generic kernel
     p.specialised = false;
@@ -1326,7 +1382,7 @@ void plan_second_pass(const RedPlan &first, char *workspace, RedPlan *second) {
 
 void fill_info(const EwPlan &p, ocn_plan_info *info) {
   std::memset(info, 0, sizeof *info);
-  info->kernel = p.kernel;
+  info->kernel = p.kernel != kKernelTiledAny ? p.kernel : p.stage_a || p.stage_b ? OCN_KERNEL_EW_TILED : OCN_KERNEL_EW_GENERIC;
   info->compute_dtype = p.T;
   info->ndim = p.ndim;
   for (int d = 0; d < p.ndim; ++d) {

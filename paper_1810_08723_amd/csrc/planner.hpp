@@ -45,6 +45,10 @@ struct Operand {
   int32_t dtype;
 };
 
+// EwPlan::kernel of the tiled form for tiles of any size and alignment (ew_tiled_any_kernel); plan
+// inspection reports it as OCN_KERNEL_EW_TILED, or OCN_KERNEL_EW_GENERIC when nothing is staged.
+constexpr int kKernelTiledAny = 100;
+
 struct EwPlan {
   int kernel = OCN_KERNEL_NONE;
   int op = 0;
@@ -70,6 +74,7 @@ struct EwPlan {
   int64_t ntiles[kMaxDims] = {0};
   int64_t total_tiles = 0;
   bool specialised = false;     // a dtype-specialised kernel exists for this signature
+  int block = kBlock;           // lanes per workgroup of the tiled form for any size and alignment
   bool fast_tiled = false;      // tiled kernel: the unclipped all-vector form applies
   bool nt_store = false;        // the output is too large to stay cached: stream it past the caches
   bool nt_a = false, nt_b = false;  // rows kernel: that input is read with streaming loads
