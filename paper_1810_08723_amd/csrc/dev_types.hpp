@@ -31,6 +31,38 @@ struct cf64 { double re, im; };
 // wait for one another - each a round trip during which the wavefront has nothing in flight.
 #define OCN_ARGS_NOW(...) asm volatile("" ::__VA_ARGS__)
 
+// ---- memory accesses at addresses that are multiples of AL bytes only -------------------
+#if defined(__HIPCC__)
+template <int AL> struct Unaligned;
+#define OCN_UNALIGNED(AL)                                                   \
+  template <> struct Unaligned<AL> {                                        \
+    typedef uint32_t W4 __attribute__((ext_vector_type(4), aligned(AL)));   \
+    typedef uint32_t W2 __attribute__((ext_vector_type(2), aligned(AL)));   \
+    typedef uint32_t W1 __attribute__((aligned(AL)));                       \
+    typedef uint16_t H1 __attribute__((aligned(AL)));                       \
+  };
+OCN_UNALIGNED(1)
+OCN_UNALIGNED(2)
+OCN_UNALIGNED(4)
+OCN_UNALIGNED(8)
+#undef OCN_UNALIGNED
+#endif
+
+#if defined(__HIPCC__)
+// Touches every 64-byte line of a kernel's arguments at once.  They arrive over the scalar cache,
+// one line per miss and a miss per table, and a wavefront of a tiled kernel reads from a dozen
+// tables one after the other: left to themselves those round trips were a third of the time
+// of a small launch (17 000 floats added: 6.4 -> 5.2 us).
+using KTable = const __attribute__((address_space(4))) uint32_t;
+template <class Args> OCN_DEV void warm_arguments() {
+  KTable *k = (KTable *)__builtin_amdgcn_kernarg_segment_ptr();
+  uint32_t any = 0;
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(Args) / 64); ++i) any |= k[i * 16];
+  asm volatile("" ::"s"(any));
+}
+#endif
+
 // ---- storage representations ----------------------------------------------------------
 struct alignas(4) chalf_s { _Float16 re, im; };
 struct alignas(8) cfloat_s { float re, im; };

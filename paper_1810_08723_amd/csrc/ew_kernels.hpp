@@ -292,19 +292,6 @@ template <class S, int V> OCN_DEV void store_pack(char *p, const Pack<S, V> &src
 // stores up to 16 bytes per lane at any such address; a wavefront's access then touches one
 // cache line more than an aligned one (a flat copy with the inputs off by one element: 61.8
 // against 60.2 us for 48 M floats).  Copied through packed types, so that the compiler knows.
-template <int AL> struct Unaligned;
-#define OCN_UNALIGNED(AL)                                                   \
-  template <> struct Unaligned<AL> {                                        \
-    typedef uint32_t W4 __attribute__((ext_vector_type(4), aligned(AL)));   \
-    typedef uint32_t W2 __attribute__((ext_vector_type(2), aligned(AL)));   \
-    typedef uint32_t W1 __attribute__((aligned(AL)));                       \
-    typedef uint16_t H1 __attribute__((aligned(AL)));                       \
-  };
-OCN_UNALIGNED(1)
-OCN_UNALIGNED(2)
-OCN_UNALIGNED(4)
-OCN_UNALIGNED(8)
-#undef OCN_UNALIGNED
 template <class S, int V, int AL> OCN_DEV void load_pack_any(const char *p, Pack<S, V> &dst, bool nt = false) {
   using X = Unaligned<AL>;
   constexpr int B = sizeof(S) * V;
@@ -762,19 +749,6 @@ OCN_HDF uint32_t swizzle(uint32_t slot, uint32_t src, uint32_t mask, uint32_t ds
 OCN_HDF uint32_t swizzle(uint32_t slot, const TileSwizzle &z) { return swizzle(slot, z.src, z.mask, z.dst); }
 
 extern __shared__ uint4 ocn_lds_raw[];
-
-// Touches every 64-byte line of a kernel's arguments at once.  They arrive over the scalar cache,
-// one line per miss and a miss per table, and a wavefront of a tiled kernel reads from a dozen
-// tables one after the other: left to themselves those round trips were a third of the time
-// of a small launch (17 000 floats added: 6.4 -> 5.2 us).
-using KTable = const __attribute__((address_space(4))) uint32_t;
-template <class Args> OCN_DEV void warm_arguments() {
-  KTable *k = (KTable *)__builtin_amdgcn_kernarg_segment_ptr();
-  uint32_t any = 0;
-#pragma unroll
-  for (int i = 0; i < (int)(sizeof(Args) / 64); ++i) any |= k[i * 16];
-  asm volatile("" ::"s"(any));
-}
 
 // The kernel reads its argument struct through the constant address space (the kernarg
 // segment itself): indexing the per-pass tables with a runtime pass number then becomes a

@@ -17,34 +17,30 @@ namespace ocn {
 #if defined(__HIPCC__)
 
 // input byte offsets (a and b) of reduced index q over the reduced dims from `first` upward
-OCN_DEV void reduced_offset2(const RedArgs &p, uint32_t q, int first, int64_t &oa, int64_t &ob) {
+OCN_DEV void reduced_offset2(KRedArgs &p, uint32_t q, int first, int64_t &oa, int64_t &ob) {
   oa = 0;
   ob = 0;
-#pragma unroll
-  for (int k = 0; k < kMaxDims; ++k) {
-    if (k >= first && k < p.nred) {
-      const uint32_t qq = (k == p.nred - 1) ? 0u : rfastdiv(q, p.rdiv[k]);
-      const uint32_t i = q - qq * p.rdiv[k].d;
-      q = qq;
-      oa += (int64_t)i * p.rsa[k];
-      ob += (int64_t)i * p.rsb[k];
-    }
+  const int nred = p.nred;
+  for (int k = first; k < nred; ++k) {
+    const uint32_t qq = (k == nred - 1) ? 0u : rfastdiv(q, args_div(p.rdiv[k]));
+    const uint32_t i = q - qq * p.rdiv[k].d;
+    q = qq;
+    oa += (int64_t)i * p.rsa[k];
+    ob += (int64_t)i * p.rsb[k];
   }
 }
 
 // byte offsets of output number `o` in a, b and out
-OCN_DEV void kept_offsets2(const RedArgs &p, uint32_t o, int64_t &off_a, int64_t &off_b, int64_t &off_o) {
+OCN_DEV void kept_offsets2(KRedArgs &p, uint32_t o, int64_t &off_a, int64_t &off_b, int64_t &off_o) {
   off_a = off_b = off_o = 0;
-#pragma unroll
-  for (int k = 0; k < kMaxDims; ++k) {
-    if (k < p.nkept) {
-      const uint32_t q = (k == p.nkept - 1) ? 0u : rfastdiv(o, p.kdiv[k]);
-      const uint32_t i = o - q * p.kdiv[k].d;
-      o = q;
-      off_a += (int64_t)i * p.ksa[k];
-      off_b += (int64_t)i * p.ksb[k];
-      off_o += (int64_t)i * p.kso[k];
-    }
+  const int nkept = p.nkept;
+  for (int k = 0; k < nkept; ++k) {
+    const uint32_t q = (k == nkept - 1) ? 0u : rfastdiv(o, args_div(p.kdiv[k]));
+    const uint32_t i = o - q * p.kdiv[k].d;
+    o = q;
+    off_a += (int64_t)i * p.ksa[k];
+    off_b += (int64_t)i * p.ksb[k];
+    off_o += (int64_t)i * p.kso[k];
   }
 }
 
@@ -55,8 +51,7 @@ template <class S, int V, bool NT = false> OCN_DEV void fused_load(const char *s
 #pragma unroll
     for (int i = 0; i < V; ++i) dst.v[i] = s;
   } else {
-    if constexpr (NT) load_vec<S, V, true>(src, dst);
-    else load_pack<S, V>(src, dst);
+    load_vec<S, V, NT && sizeof(S) * V >= 16>(src, dst);
   }
 }
 
@@ -74,7 +69,7 @@ template <class G, int OP> struct FusedFold {
 // ---------------------------------------------------------------------------------------
 
 template <class G, int OP, int V>
-OCN_DEV typename FusedFold<G, OP>::A fred_rows_accumulate(const RedArgs &p, const char *pa, const char *pb,
+OCN_DEV typename FusedFold<G, OP>::A fred_rows_accumulate(KRedArgs &p, const char *pa, const char *pb,
                                                           int64_t t0, int64_t t1, int lane, int lanes) {
   using F = FusedFold<G, OP>;
   using A = typename F::A;
@@ -96,7 +91,7 @@ OCN_DEV typename FusedFold<G, OP>::A fred_rows_accumulate(const RedArgs &p, cons
   auto address = [&](int64_t tt, int64_t &e0, const char *&qa, const char *&qb) {
     int64_t oa = 0, ob = 0, iv = tt;
     if (!single) {
-      const uint32_t q = rfastdiv((uint32_t)tt, p.vpr_div);
+      const uint32_t q = rfastdiv((uint32_t)tt, args_div(p.vpr_div));
       iv = (uint32_t)tt - q * p.vpr_div.d;
       reduced_offset2(p, q, 1, oa, ob);
     }
@@ -142,7 +137,10 @@ OCN_DEV typename FusedFold<G, OP>::A fred_rows_accumulate(const RedArgs &p, cons
   return r;
 }
 
-template <class G, int OP> __global__ __launch_bounds__(kBlock) void fred_rows_kernel(const RedArgs p) {
+template <class G, int OP> __global__ __launch_bounds__(kBlock) void fred_rows_kernel(const RedArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if (p.warm) warm_arguments<RedArgs>();
   using F = FusedFold<G, OP>;
   using R = typename F::R;
   using A = typename F::A;
@@ -263,6 +261,12 @@ template <class G, int OP> __global__ __launch_bounds__(kBlock) OCN_ROWS_OCC voi
     const uint32_t lanes = per_block ? kBlock : kWave;
     if (p.nt_load) acc = fred_lean_fold<G, OP, true>(pa, pb, t0, t1, lane, lanes);
     else acc = fred_lean_fold<G, OP, false>(pa, pb, t0, t1, lane, lanes);
+    // the elements behind the last whole vector: one lane of the last split
+    if (p.tail && lane == 0 && sp + 1 == p.split) {
+      const typename G::SAt *qa = reinterpret_cast<const typename G::SAt *>(pa + (uint64_t)p.nvec * 16u);
+      const typename G::SBt *qb = reinterpret_cast<const typename G::SBt *>(pb + (uint64_t)p.nvec * 16u);
+      for (uint32_t i = 0; i < p.tail; ++i) acc = F::add(acc, qa[i], qb[i]);
+    }
   }
   acc = group_fold<R>(acc, kWave);
   if (per_block) {
@@ -282,7 +286,7 @@ template <class G, int OP> __global__ __launch_bounds__(kBlock) OCN_ROWS_OCC voi
 // Rows of at most one vector per lane of their group, a single reduced dim, no split: the same
 // groups, loads and fold order as fred_rows_kernel without its loops and 64-bit bookkeeping.
 template <class G, int OP, int V>
-OCN_DEV typename FusedFold<G, OP>::A fred_short_row(const RedArgs &p, const char *pa, const char *pb, uint32_t lane) {
+OCN_DEV typename FusedFold<G, OP>::A fred_short_row(KRedArgs &p, const char *pa, const char *pb, uint32_t lane) {
   using F = FusedFold<G, OP>;
   using A = typename F::A;
   using SAt = typename G::SAt;
@@ -311,7 +315,10 @@ OCN_DEV typename FusedFold<G, OP>::A fred_short_row(const RedArgs &p, const char
   return acc;
 }
 
-template <class G, int OP> __global__ __launch_bounds__(kBlock) void fred_rows_short_kernel(const RedArgs p) {
+template <class G, int OP> __global__ __launch_bounds__(kBlock) void fred_rows_short_kernel(const RedArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if (p.warm) warm_arguments<RedArgs>();
   using F = FusedFold<G, OP>;
   using R = typename F::R;
   using A = typename F::A;
@@ -338,7 +345,7 @@ template <class G, int OP> __global__ __launch_bounds__(kBlock) void fred_rows_s
 // NT: both inputs are read with streaming loads (one 16-byte piece per lane each).  SINGLE:
 // one reduced dim, so that row r lies r strides further on (no index decomposition).
 template <class G, int OP, int V, bool NT, bool SINGLE>
-OCN_DEV void fred_cols_body(const RedArgs &p, typename FusedFold<G, OP>::A *lds) {
+OCN_DEV void fred_cols_body(KRedArgs &p, typename FusedFold<G, OP>::A *lds) {
   using F = FusedFold<G, OP>;
   using R = typename F::R;
   using A = typename F::A;
@@ -354,31 +361,35 @@ OCN_DEV void fred_cols_body(const RedArgs &p, typename FusedFold<G, OP>::A *lds)
   const uint32_t per_split = (uint32_t)(p.colblocks_div.d * (uint32_t)(p.nout / p.nc));
   const uint32_t s = b / per_split;
   b -= s * per_split;
-  const uint32_t other = rfastdiv(b, p.colblocks_div);
+  const uint32_t other = rfastdiv(b, args_div(p.colblocks_div));
   const uint32_t cb = b - other * p.colblocks_div.d;
   // p.cpw lanes (a power of two) cover one row of columns; with fewer than 64 of them a
   // wavefront takes 64 / cpw rows at a time
   const int cpw_log2 = __ffs(p.cpw) - 1;
   const int lc = lane & (p.cpw - 1), lr = lane >> cpw_log2;
   const int RPW = kWave >> cpw_log2;
-  const int64_t col0 = ((int64_t)cb * p.cpw + lc) * V;
+  int64_t col0 = ((int64_t)cb * p.cpw + lc) * V;
   const int64_t left = p.nc - col0;
-  const int ncol = left >= V ? V : (left > 0 ? (int)left : 0);
+  int ncol = left >= V ? V : (left > 0 ? (int)left : 0);
+  int skip = 0;   // columns of the last lane's vector that are its neighbour's (as in red_cols_kernel)
+  if (ncol > 0 && ncol < V && p.nc >= V) {
+    skip = V - ncol;
+    col0 -= skip;
+    ncol = V;
+  }
 
   int64_t off_a = abc ? 0 : col0 * (int64_t)sizeof(SAt), off_b = bbc ? 0 : col0 * (int64_t)sizeof(SBt);
   int64_t off_o = col0 * p.kso[0];
   {
     uint32_t o = other;
-#pragma unroll
-    for (int k = 1; k < kMaxDims; ++k) {
-      if (k < p.nkept) {
-        const uint32_t q = (k == p.nkept - 1) ? 0u : rfastdiv(o, p.kdiv[k]);
-        const uint32_t i = o - q * p.kdiv[k].d;
-        o = q;
-        off_a += (int64_t)i * p.ksa[k];
-        off_b += (int64_t)i * p.ksb[k];
-        off_o += (int64_t)i * p.kso[k];
-      }
+    const int nkept = p.nkept;
+    for (int k = 1; k < nkept; ++k) {
+      const uint32_t q = (k == nkept - 1) ? 0u : rfastdiv(o, args_div(p.kdiv[k]));
+      const uint32_t i = o - q * p.kdiv[k].d;
+      o = q;
+      off_a += (int64_t)i * p.ksa[k];
+      off_b += (int64_t)i * p.ksb[k];
+      off_o += (int64_t)i * p.kso[k];
     }
   }
   A acc[V];
@@ -447,7 +458,7 @@ OCN_DEV void fred_cols_body(const RedArgs &p, typename FusedFold<G, OP>::A *lds)
 #pragma unroll
     for (int c = 0; c < CH; ++c) lds[((size_t)wave * CH + c) * kWave + lane] = acc[i0 + c];
     __syncthreads();
-    if (wave < CH && lr == 0 && i0 + wave < ncol) {
+    if (wave < CH && lr == 0 && i0 + wave < ncol && i0 + wave >= skip) {
       const int c = wave, i = i0 + wave;
       A v = lds[(size_t)c * kWave + lane];
       for (int w = 1; w < NW; ++w) v = R::combine(v, lds[((size_t)w * CH + c) * kWave + lane]);
@@ -462,7 +473,10 @@ OCN_DEV void fred_cols_body(const RedArgs &p, typename FusedFold<G, OP>::A *lds)
   }
 }
 
-template <class G, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) void fred_cols_kernel(const RedArgs p) {
+template <class G, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) void fred_cols_kernel(const RedArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if (p.warm) warm_arguments<RedArgs>();
   using A = typename FusedFold<G, OP>::A;
   extern __shared__ __align__(16) unsigned char fred_cols_lds_raw[];
   A *lds = reinterpret_cast<A *>(fred_cols_lds_raw);
@@ -480,7 +494,10 @@ template <class G, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) v
 // generic: any layout, one output per lane
 // ---------------------------------------------------------------------------------------
 
-template <class G, int OP> __global__ __launch_bounds__(kBlock) void fred_generic_kernel(const RedArgs p) {
+template <class G, int OP> __global__ __launch_bounds__(kBlock) void fred_generic_kernel(const RedArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if (p.warm) warm_arguments<RedArgs>();
   using F = FusedFold<G, OP>;
   using A = typename F::A;
   using SAt = typename G::SAt;
@@ -488,30 +505,24 @@ template <class G, int OP> __global__ __launch_bounds__(kBlock) void fred_generi
   // the grid is capped (a launch cannot have 2^32 lanes): more outputs than lanes loop
   for (int64_t o = (int64_t)blockIdx.x * kBlock + threadIdx.x; o < p.nout; o += (int64_t)gridDim.x * kBlock) {
   int64_t off_a = 0, off_b = 0, off_o = 0, t = o;
-#pragma unroll
-  for (int k = 0; k < kMaxDims; ++k) {
-    if (k < p.nkept) {
-      const int64_t n = p.ksize[k];
-      const int64_t q = t / n;
-      const int64_t i = t - q * n;
-      t = q;
-      off_a += i * p.ksa[k];
-      off_b += i * p.ksb[k];
-      off_o += i * p.kso[k];
-    }
+  for (int k = 0; k < p.nkept; ++k) {
+    const int64_t n = p.ksize[k];
+    const int64_t q = t / n;
+    const int64_t i = t - q * n;
+    t = q;
+    off_a += i * p.ksa[k];
+    off_b += i * p.ksb[k];
+    off_o += i * p.kso[k];
   }
   A acc = F::R::identity();
   for (int64_t r = 0; r < p.nredtot; ++r) {
     int64_t oa = 0, ob = 0, q = r;
-#pragma unroll
-    for (int k = 0; k < kMaxDims; ++k) {
-      if (k < p.nred) {
-        const int64_t n = p.rsize[k];
-        const int64_t qq = q / n;
-        oa += (q - qq * n) * p.rsa[k];
-        ob += (q - qq * n) * p.rsb[k];
-        q = qq;
-      }
+    for (int k = 0; k < p.nred; ++k) {
+      const int64_t n = p.rsize[k];
+      const int64_t qq = q / n;
+      oa += (q - qq * n) * p.rsa[k];
+      ob += (q - qq * n) * p.rsb[k];
+      q = qq;
     }
     acc = F::add(acc, *reinterpret_cast<const SAt *>(p.a + off_a + oa), *reinterpret_cast<const SBt *>(p.b + off_b + ob));
   }

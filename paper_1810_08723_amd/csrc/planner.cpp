@@ -772,6 +772,40 @@ constexpr int64_t kTargetWaves = OCN_RED_TARGET_WAVES;  // enough wavefronts to 
 // general kernel's element loads want the sixteen (full sum of a stride-2 view: 96 against 104 us).
 constexpr int64_t kLeanSplitWaves = 256 * 8;
 
+// Launch shape of the column kernels (plain and fused): lanes per row of columns, wavefronts per
+// workgroup, and workgroups that share a column block through the workspace.
+//   cpw    A whole wavefront per row, or as few lanes as the columns need, and fewer where more than
+//          30 % of the lanes would have no column (they then take several rows at a time; 777
+//          columns: 64 lanes, 76 % of them busy, ran 36 us against 41 with 32).
+//   nw     As many wavefronts per workgroup as leave each lane 16 rows, up to about 4096 in all: they
+//          combine through LDS, where more workgroups would combine through memory and a second
+//          launch (float sums over the middle of [48, 1000, 777]: 36.6 us with sixteen and no
+//          split, 38 to 40 with four and two to five splits).
+//   split  Only where that leaves half of the chip idle and the wavefronts with long runs of rows, and
+//          rounded down, so that the workgroups go out in one round ([16384, 4099]: 55 us with 15
+//          splits, 255 workgroups of sixteen wavefronts, 69 with 16).
+struct ColsShape { int cpw, nw; int64_t split; };
+ColsShape choose_cols_shape(int64_t col_lanes, int64_t others, int64_t rows, int64_t nout, int acc_es) {
+  ColsShape r;
+  r.cpw = kWave;
+  while (r.cpw > 1 && r.cpw / 2 >= col_lanes) r.cpw /= 2;
+  while (r.cpw > 16 && col_lanes * 10 < (col_lanes + r.cpw - 1) / r.cpw * r.cpw * 7) r.cpw /= 2;
+  const int64_t rpw = kWave / r.cpw;
+  const int64_t blocks0 = (col_lanes + r.cpw - 1) / r.cpw * others;
+  r.nw = 4;
+  while (r.nw < 16 && blocks0 * r.nw * 2 <= kTargetWaves && rows >= r.nw * 2 * 16 * rpw) r.nw *= 2;
+  r.split = 1;
+  if ((blocks0 * r.nw < kTargetWaves / 4 || blocks0 * 2 <= kNumCUs) && rows >= r.nw * rpw * 48) {
+    const int64_t want = std::max<int64_t>(1, kTargetWaves / (blocks0 * r.nw));
+    r.split = std::min(want, rows / (r.nw * rpw * 8));
+    // eight rows per lane, but sixteen where the partial results would outgrow what a call without
+    // a workspace has
+    const int64_t fits = (int64_t)OCN_REDUCE_SCRATCH_BYTES / (nout * acc_es);
+    r.split = std::max<int64_t>(1, std::min(r.split, std::max(fits, std::min(want, rows / (r.nw * rpw * 16)))));
+  }
+  return r;
+}
+
 void choose_reduce_launch(RedPlan &p) {
   const int es = dt_size(p.a_dtype);
   const int acc_es = dt_size(p.acc_dtype);
@@ -797,6 +831,7 @@ void choose_reduce_launch(RedPlan &p) {
   for (int d = 0; d < p.nred; ++d) idx32 = idx32 && p.rsize[d] < ((int64_t)1 << 31);
   // a flat contiguous full reduction may be longer than 2^31 elements
   const bool flat_full = p.nkept == 0 && p.nred == 1;
+  bool aligned = true;   // every vector starts on a vector boundary
 
   const bool rows_contig = p.nred >= 1 && r_fast == es && (k_fast_dim < 0 || k_fast > r_fast);
   const bool cols_ok = k_fast_dim >= 0 && k_fast == es && p.kstride_a[k_fast_dim] == es &&
@@ -807,8 +842,11 @@ void choose_reduce_launch(RedPlan &p) {
     // With the reduced axis the input's fastest, lanes load whole vectors; any other layout
     // goes element by element with the innermost reduced stride.
     p.kernel = OCN_KERNEL_RED_ROWS;
-    p.vec = rows_contig && all_aligned((int64_t)vfull * es, -1, p.nred - 1) ? vfull : 1;
+    // Rows that do not start on vector boundaries are read in whole vectors all the same (at
+    // unaligned addresses) as soon as they hold two.
     const int64_t n0 = p.rsize[p.nred - 1];
+    aligned = all_aligned((int64_t)vfull * es, -1, p.nred - 1);
+    p.vec = rows_contig && (aligned || n0 >= 2 * vfull) ? vfull : 1;
     const int64_t vpr = (n0 + p.vec - 1) / p.vec;         // vectors per innermost run
     const int64_t nvec = vpr * (p.nredtot / n0);          // vectors per output
     int64_t cover = 1;                                    // lanes one output can keep busy
@@ -828,9 +866,9 @@ void choose_reduce_launch(RedPlan &p) {
     const int64_t groups_per_block = kBlock / p.group;
     const int64_t waves = (p.nout * p.group + kWave - 1) / kWave;
     p.split = 1;
-    // the common 2-D shape: one reduced dim of whole vectors, at most one kept dim, a wavefront or
+    // the common 2-D shape: one reduced dim read in vectors, at most one kept dim, a wavefront or
     // a workgroup per output (or per split of it), everything below 2^31
-    const bool lean_shape = p.nred == 1 && p.nkept <= 1 && p.vec > 1 && es < 16 && n0 % p.vec == 0 &&
+    const bool lean_shape = p.nred == 1 && p.nkept <= 1 && p.vec > 1 && es < 16 &&
                             p.group >= kWave && nvec < ((int64_t)1 << 31);
     if (p.group >= kWave && waves < kTargetWaves) {
       // split long reductions so the device fills; keep >= 16 vectors per lane per split
@@ -848,27 +886,15 @@ void choose_reduce_launch(RedPlan &p) {
     // ---- cols: a kept axis is the input's fastest; lanes own output columns -------------
     // (requires that axis to be the last canonical kept dim, i.e. also the output's fastest)
     p.kernel = OCN_KERNEL_RED_COLS;
-    p.vec = all_aligned((int64_t)vfull * es, p.nkept - 1, -1) ? vfull : 1;
     const int64_t nc = p.ksize[p.nkept - 1];
-    // few columns: a wavefront covers 64 / cpw rows at a time
-    const int64_t col_lanes = (nc + p.vec - 1) / p.vec;
-    p.cpw = kWave;
-    while (p.cpw > 1 && p.cpw / 2 >= col_lanes) p.cpw /= 2;
-    const int rpw = kWave / p.cpw;
-    const int64_t colblocks = (nc + (int64_t)p.cpw * p.vec - 1) / ((int64_t)p.cpw * p.vec);
-    const int64_t others = p.nout / nc;
-    const int64_t blocks0 = colblocks * others;
-    // Rows are dealt to the wavefronts of a workgroup, which combine through LDS, and to
-    // `split` workgroups, which combine through the workspace.  Sixteen wavefronts per
-    // workgroup keep the partial results (and the second pass) four times smaller.
-    int nw = 4;
-    p.split = 1;
-    if (blocks0 * nw < kTargetWaves) {
-      if (p.nredtot >= 16 * 64 * rpw && blocks0 * 16 * 2 <= kTargetWaves) nw = 16;
-      const int64_t want = (kTargetWaves + blocks0 * nw - 1) / (blocks0 * nw);
-      const int64_t most = std::max<int64_t>(1, p.nredtot / ((int64_t)nw * rpw * 16));  // >= 16 rows per lane
-      p.split = std::max<int64_t>(1, std::min(want, most));
-    }
+    aligned = all_aligned((int64_t)vfull * es, p.nkept - 1, -1);
+    p.vec = aligned || nc >= vfull ? vfull : 1;
+    const int64_t col_lanes = (nc + p.vec - 1) / p.vec, others = p.nout / nc;
+    const ColsShape shape = choose_cols_shape(col_lanes, others, p.nredtot, p.nout, acc_es);
+    p.cpw = shape.cpw;
+    p.split = shape.split;
+    const int nw = shape.nw;
+    const int64_t blocks0 = (col_lanes + p.cpw - 1) / p.cpw * others;
     p.block = nw * kWave;
     p.chunk = (p.nredtot + p.split - 1) / p.split;
     p.split = (p.nredtot + p.chunk - 1) / p.chunk;
@@ -894,7 +920,7 @@ void choose_reduce_launch(RedPlan &p) {
   p.workspace_bytes = p.split > 1 ? (size_t)(p.nout * p.split * acc_es) : 0;
   // an input that cannot stay in the caches anyway is read with streaming loads (whole
   // 16-byte vectors only: neighbouring lanes then cover whole lines)
-  p.nt_load = p.vec > 1 && p.kernel != OCN_KERNEL_RED_GENERIC && p.nout * p.nredtot * es >= kStreamBytes;
+  p.nt_load = p.vec > 1 && aligned && p.kernel != OCN_KERNEL_RED_GENERIC && p.nout * p.nredtot * es >= kStreamBytes;
 }
 
 }  // namespace
@@ -1046,8 +1072,9 @@ void choose_fused_launch(RedPlan &p) {
     p.kernel = OCN_KERNEL_RED_ROWS;
     p.a_fast_bcast = p.rstride_a[p.nred - 1] == 0;
     p.b_fast_bcast = p.rstride_b[p.nred - 1] == 0;
-    p.vec = all_aligned(-1, p.nred - 1, p.a_fast_bcast, p.b_fast_bcast) ? vfull : 1;
     const int64_t n0 = p.rsize[p.nred - 1];
+    // (unaligned rows in whole vectors too once they hold two, as in the plain reduction)
+    p.vec = n0 >= 2 * vfull || all_aligned(-1, p.nred - 1, p.a_fast_bcast, p.b_fast_bcast) ? vfull : 1;
     const int64_t vpr = (n0 + p.vec - 1) / p.vec;
     const int64_t nvec = vpr * (p.nredtot / n0);
     int64_t cover = 1;                                    // lanes one output can keep busy
@@ -1066,14 +1093,11 @@ void choose_fused_launch(RedPlan &p) {
     p.short_rows = p.group <= kWave && nvec <= p.group && p.nred == 1 && p.split == 1 &&
                    p.nout * p.group < ((int64_t)1 << 32) && n0 < ((int64_t)1 << 31);
     // The common 2-D shape takes the lean form of the kernel: one reduced dim along which both
-    // inputs are contiguous and made of whole, aligned 16-byte vectors, at most one kept dim,
-    // at least a wavefront per output, everything below 2^31.  Its vectors are 16 bytes of
+    // inputs are contiguous, at most one kept dim, at least a wavefront's vectors per output, everything below 2^31.  Its vectors are 16 bytes of
     // each input whatever the intermediate type is.
     const int lv = es_a == es_b && es_a <= 16 ? 16 / es_a : 0;   // elements per vector
     if (!p.short_rows && lv >= 1 && p.nred == 1 && p.nkept <= 1 && !p.a_fast_bcast && !p.b_fast_bcast &&
-        n0 % lv == 0 && n0 / lv >= kWave && n0 / lv < ((int64_t)1 << 31) && p.nout < ((int64_t)1 << 31) &&
-        (intptr_t)p.a_ptr % 16 == 0 && (intptr_t)p.b_ptr % 16 == 0 &&
-        (p.nkept == 0 || (p.kstride_a[0] % 16 == 0 && p.kstride_b[0] % 16 == 0))) {
+        n0 / lv >= kWave && n0 / lv < ((int64_t)1 << 31) && p.nout < ((int64_t)1 << 31)) {
       const int64_t nv = n0 / lv;
       const int group = nv * 32 <= 16 * 1024 ? kWave : kBlock;    // as above: rows of up to 16 KiB take a wavefront
       const int64_t lwaves = (p.nout * group + kWave - 1) / kWave;
@@ -1095,7 +1119,9 @@ void choose_fused_launch(RedPlan &p) {
         // inputs far larger than the caches are streamed; one that is broadcast along the kept
         // dim is re-read by every output and stays cacheable, and then so does the other (one flag)
         const bool a_rows = p.nkept == 0 || p.kstride_a[0] != 0, b_rows = p.nkept == 0 || p.kstride_b[0] != 0;
-        p.nt_load = a_rows && b_rows && p.nout * n0 * es_a >= kStreamBytes;
+        const bool aligned = (intptr_t)p.a_ptr % 16 == 0 && (intptr_t)p.b_ptr % 16 == 0 &&
+                             (p.nkept == 0 || (p.kstride_a[0] % 16 == 0 && p.kstride_b[0] % 16 == 0));
+        p.nt_load = a_rows && b_rows && aligned && p.nout * n0 * es_a >= kStreamBytes;
       }
     }
   } else if (k_fast_dim >= 0 && k_fast_dim == p.nkept - 1 && p.nred >= 1 && idx32 &&
@@ -1103,27 +1129,20 @@ void choose_fused_launch(RedPlan &p) {
     p.kernel = OCN_KERNEL_RED_COLS;
     p.a_fast_bcast = p.kstride_a[k_fast_dim] == 0;
     p.b_fast_bcast = p.kstride_b[k_fast_dim] == 0;
-    p.vec = all_aligned(p.nkept - 1, -1, p.a_fast_bcast, p.b_fast_bcast) ? vfull : 1;
     const int64_t nc = p.ksize[p.nkept - 1];
-    // few columns: a wavefront covers 64 / cpw rows at a time
-    const int64_t col_lanes = (nc + p.vec - 1) / p.vec;
-    p.cpw = kWave;
-    while (p.cpw > 1 && p.cpw / 2 >= col_lanes) p.cpw /= 2;
-    const int rpw = kWave / p.cpw;
-    const int64_t colblocks = (nc + (int64_t)p.cpw * p.vec - 1) / ((int64_t)p.cpw * p.vec);
-    const int64_t blocks0 = colblocks * (p.nout / nc);
-    int nw = 4;   // as in the plain column reduction: sixteen wavefronts keep the partial results small
-    if (blocks0 * nw < kTargetWaves) {
-      if (p.nredtot >= 16 * 64 * rpw && blocks0 * 16 * 2 <= kTargetWaves) nw = 16;
-      const int64_t want = (kTargetWaves + blocks0 * nw - 1) / (blocks0 * nw);
-      const int64_t most = std::max<int64_t>(1, p.nredtot / ((int64_t)nw * rpw * 16));
-      p.split = std::max<int64_t>(1, std::min(want, most));
-    }
+    const bool aligned = all_aligned(p.nkept - 1, -1, p.a_fast_bcast, p.b_fast_bcast);
+    p.vec = aligned || nc >= vfull ? vfull : 1;
+    const int64_t col_lanes = (nc + p.vec - 1) / p.vec, others = p.nout / nc;
+    const ColsShape shape = choose_cols_shape(col_lanes, others, p.nredtot, p.nout, acc_es);
+    p.cpw = shape.cpw;
+    p.split = shape.split;
+    const int nw = shape.nw;
+    const int64_t blocks0 = (col_lanes + p.cpw - 1) / p.cpw * others;
     p.block = nw * kWave;
     // inputs far larger than the caches, each read as one 16-byte piece per lane and broadcast
     // along no dim: streaming loads
     {
-      bool plain = p.vec > 1 && (int64_t)p.vec * es_a == 16 && (int64_t)p.vec * es_b == 16;
+      bool plain = aligned && p.vec > 1 && (int64_t)p.vec * es_a == 16 && (int64_t)p.vec * es_b == 16;
       for (int d = 0; d < p.nkept; ++d) plain = plain && p.kstride_a[d] != 0 && p.kstride_b[d] != 0;
       for (int d = 0; d < p.nred; ++d) plain = plain && p.rstride_a[d] != 0 && p.rstride_b[d] != 0;
       p.nt_load = plain && p.nout * p.nredtot * es_a >= kStreamBytes;

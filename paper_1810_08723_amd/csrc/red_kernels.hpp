@@ -29,6 +29,7 @@ struct RedArgs {
   const char *a;
   char *out;                        // final output (used when split == 1)
   char *partial;                    // workspace (used when split > 1)
+  int32_t warm;                     // few workgroups: touch all argument lines first
   int32_t nkept, nred, out_dtype, vec, group;
   int64_t ksa[kMaxDims], kso[kMaxDims];    // kept dims: input / output byte strides, fastest first
   FastDiv kdiv[kMaxDims];                  // kept sizes, same order
@@ -69,7 +70,8 @@ struct RedLeanArgs {
   int64_t ksa, kso;        // byte strides of the kept dim in the input and the output
   int64_t ksb;             // ... in the second input
   uint32_t nout, split;    // outputs; partial results per output
-  uint32_t nvec, chunk;    // vectors per output; vectors per split
+  uint32_t nvec, chunk;    // whole vectors per output; vectors per split
+  uint32_t tail;           // elements of an output behind its last whole vector
   int32_t out_dtype, group, nt_load;
   int32_t swap_a, swap_o;  // the input / the output is stored in the other byte order
 };
@@ -77,6 +79,12 @@ struct RedLeanArgs {
 #if defined(__HIPCC__)
 
 OCN_DEV uint32_t rfastdiv(uint32_t n, const FastDiv &f) { return (__umulhi(n, f.m) + n) >> f.s; }
+
+// The general kernels read their arguments where they lie, in the constant address space, and loop
+// over the dims there are.  Passed by value and unrolled over eight dims, the arguments of all of
+// them were fetched ahead into scalar registers and spilled (160 to 200 of them).
+using KRedArgs = const __attribute__((address_space(4))) RedArgs;
+OCN_DEV FastDiv args_div(const __attribute__((address_space(4))) FastDiv &f) { return FastDiv{f.d, f.m, f.s}; }
 
 // ---------------------------------------------------------------------------------------
 // accumulators
@@ -220,32 +228,28 @@ template <class A> __device__ __noinline__ void store_result(char *p, int dt, A 
 }
 
 // byte offsets of output number `o` (linear over the kept dims) in the input and the output
-OCN_DEV void kept_offsets(const RedArgs &p, uint32_t o, int64_t &off_a, int64_t &off_o) {
+OCN_DEV void kept_offsets(KRedArgs &p, uint32_t o, int64_t &off_a, int64_t &off_o) {
   off_a = 0;
   off_o = 0;
-#pragma unroll
-  for (int k = 0; k < kMaxDims; ++k) {
-    if (k < p.nkept) {
-      const uint32_t q = (k == p.nkept - 1) ? 0u : rfastdiv(o, p.kdiv[k]);
-      const uint32_t i = o - q * p.kdiv[k].d;
-      o = q;
-      off_a += (int64_t)i * p.ksa[k];
-      off_o += (int64_t)i * p.kso[k];
-    }
+  const int nkept = p.nkept;
+  for (int k = 0; k < nkept; ++k) {
+    const uint32_t q = (k == nkept - 1) ? 0u : rfastdiv(o, args_div(p.kdiv[k]));
+    const uint32_t i = o - q * p.kdiv[k].d;
+    o = q;
+    off_a += (int64_t)i * p.ksa[k];
+    off_o += (int64_t)i * p.kso[k];
   }
 }
 
 // input byte offset of reduced index q over the reduced dims from `first` upward
-OCN_DEV int64_t reduced_offset(const RedArgs &p, uint32_t q, int first) {
+OCN_DEV int64_t reduced_offset(KRedArgs &p, uint32_t q, int first) {
   int64_t off = 0;
-#pragma unroll
-  for (int k = 0; k < kMaxDims; ++k) {
-    if (k >= first && k < p.nred) {
-      const uint32_t qq = (k == p.nred - 1) ? 0u : rfastdiv(q, p.rdiv[k]);
-      const uint32_t i = q - qq * p.rdiv[k].d;
-      q = qq;
-      off += (int64_t)i * p.rsa[k];
-    }
+  const int nred = p.nred;
+  for (int k = first; k < nred; ++k) {
+    const uint32_t qq = (k == nred - 1) ? 0u : rfastdiv(q, args_div(p.rdiv[k]));
+    const uint32_t i = q - qq * p.rdiv[k].d;
+    q = qq;
+    off += (int64_t)i * p.rsa[k];
   }
   return off;
 }
@@ -370,14 +374,19 @@ template <int S> OCN_DEV storage_t<S> load_one(bool swapped, const char *src) {
   return v;
 }
 
+// (four-byte elements are scalars except for complex halves)
+template <class St> constexpr int vec_scalar() { return std::is_same<St, chalf_s>::value ? 2 : 4; }
+// at any address that is a multiple of the scalar size (of four bytes for wider scalars)
 template <class St, int V, bool NT = false, class Pk> OCN_DEV void load_vec(const char *src, Pk &pk) {
   if constexpr (sizeof(St) * V >= 16) {
-    using Q = uint32_t __attribute__((ext_vector_type(4)));
+    using Q = typename Unaligned<(sizeof(St) < 4 ? (int)alignof(St) < 2 ? 1 : 2 : sizeof(St) == 4 ? (int)vec_scalar<St>() : 4)>::W4;
+    Q w[sizeof(St) * V / 16];
 #pragma unroll
     for (int i = 0; i < (int)(sizeof(St) * V / 16); ++i) {
-      if constexpr (NT) reinterpret_cast<Q *>(&pk)[i] = __builtin_nontemporal_load(reinterpret_cast<const Q *>(src) + i);
-      else reinterpret_cast<Q *>(&pk)[i] = reinterpret_cast<const Q *>(src)[i];
+      if constexpr (NT) w[i] = __builtin_nontemporal_load(reinterpret_cast<const Q *>(src) + i);
+      else w[i] = reinterpret_cast<const Q *>(src)[i];
     }
+    __builtin_memcpy(&pk, w, sizeof(St) * V);
   } else {
 #pragma unroll
     for (int i = 0; i < V; ++i) pk.v[i] = reinterpret_cast<const St *>(src)[i];
@@ -389,7 +398,7 @@ template <class St, int V, bool NT = false, class Pk> OCN_DEV void load_vec(cons
 // ragged remainder - the last few vectors, and the partial vector at the end of a run whose
 // length is not a multiple of V - goes through a checked loop.
 template <int S, int OP, int V, bool SINGLE, bool NT>
-OCN_DEV typename Reducer<S, OP>::A rows_accumulate_impl(const RedArgs &p, const char *base, int64_t t0,
+OCN_DEV typename Reducer<S, OP>::A rows_accumulate_impl(KRedArgs &p, const char *base, int64_t t0,
                                                         int64_t t1, int lane, int lanes) {
   using R = Reducer<S, OP>;
   using St = storage_t<S>;
@@ -399,7 +408,7 @@ OCN_DEV typename Reducer<S, OP>::A rows_accumulate_impl(const RedArgs &p, const 
   auto address = [&](int64_t tt, int64_t &e0) -> const char * {
     int64_t off = 0, iv = tt;
     if constexpr (!SINGLE) {
-      const uint32_t q = rfastdiv((uint32_t)tt, p.vpr_div);
+      const uint32_t q = rfastdiv((uint32_t)tt, args_div(p.vpr_div));
       iv = (uint32_t)tt - q * p.vpr_div.d;
       off = reduced_offset(p, q, 1);
     }
@@ -486,7 +495,7 @@ OCN_DEV typename Reducer<S, OP>::A rows_accumulate_impl(const RedArgs &p, const 
 // length is not a multiple of V - goes through a checked loop.  A single reduced dimension
 // (the common case) needs no index decomposition at all.
 template <int S, int OP, int V>
-OCN_DEV typename Reducer<S, OP>::A rows_accumulate(const RedArgs &p, const char *base, int64_t t0, int64_t t1,
+OCN_DEV typename Reducer<S, OP>::A rows_accumulate(KRedArgs &p, const char *base, int64_t t0, int64_t t1,
                                                    int lane, int lanes) {
   if (p.nred == 1) {
     if (V > 1 && p.nt_load) return rows_accumulate_impl<S, OP, V, true, (V > 1)>(p, base, t0, t1, lane, lanes);
@@ -500,7 +509,10 @@ OCN_DEV typename Reducer<S, OP>::A rows_accumulate(const RedArgs &p, const char 
 #ifndef OCN_ROWS_OCC
 #define OCN_ROWS_OCC __attribute__((amdgpu_waves_per_eu(8, 8)))
 #endif
-template <int S, int OP> __global__ __launch_bounds__(kBlock) OCN_ROWS_OCC void red_rows_kernel(const RedArgs p) {
+template <int S, int OP> __global__ __launch_bounds__(kBlock) OCN_ROWS_OCC void red_rows_kernel(const RedArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if (p.warm) warm_arguments<RedArgs>();
   using R = Reducer<S, OP>;
   using A = typename R::A;
   constexpr int VF = 16 / (int)sizeof(storage_t<S>) > 0 ? 16 / (int)sizeof(storage_t<S>) : 1;
@@ -613,7 +625,7 @@ template <int S, int OP> __global__ __launch_bounds__(kBlock) OCN_ROWS_OCC void 
   if constexpr (sizeof(storage_t<S>) < 16) {
     RedLeanArgs p = q;
     OCN_ARGS_NOW("s"(p.a), "s"(p.out), "s"(p.partial), "s"(p.ksa), "s"(p.kso), "s"(p.nout), "s"(p.split), "s"(p.nvec),
-                 "s"(p.chunk), "s"(p.out_dtype), "s"(p.group), "s"(p.nt_load), "s"(p.swap_a), "s"(p.swap_o));
+                 "s"(p.chunk), "s"(p.tail), "s"(p.out_dtype), "s"(p.group), "s"(p.nt_load), "s"(p.swap_a), "s"(p.swap_o));
     __shared__ A lds[kBlock / kWave];
     const uint32_t tid = threadIdx.x, lane_in_wave = tid & (kWave - 1), wave = tid / kWave;
     const bool per_block = p.group == kBlock;
@@ -641,6 +653,12 @@ template <int S, int OP> __global__ __launch_bounds__(kBlock) OCN_ROWS_OCC void 
         if (p.nt_load) acc = lean_fold<S, OP, true, false>(base, t0, t1, lane, lanes);
         else acc = lean_fold<S, OP, false, false>(base, t0, t1, lane, lanes);
       }
+      // the elements behind the last whole vector: one lane of the last split
+      if (p.tail && lane == 0 && sp + 1 == p.split) {
+        const char *src = base + (uint64_t)p.nvec * 16u;
+        for (uint32_t i = 0; i < p.tail; ++i)
+          acc = R::combine(acc, R::lift(from_storage<S>(load_one<S>(p.swap_a != 0, src + i * (uint32_t)sizeof(storage_t<S>)))));
+      }
     }
     acc = group_fold<R>(acc, kWave);
     if (per_block) {
@@ -662,7 +680,7 @@ template <int S, int OP> __global__ __launch_bounds__(kBlock) OCN_ROWS_OCC void 
 // same groups, loads and fold order as red_rows_kernel without its loops and its 64-bit
 // bookkeeping (short rows are bound by instruction issue, not by memory).
 template <int S, int OP, int V, bool NT>
-OCN_DEV typename Reducer<S, OP>::A short_row_fold(const RedArgs &p, const char *base, uint32_t lane) {
+OCN_DEV typename Reducer<S, OP>::A short_row_fold(KRedArgs &p, const char *base, uint32_t lane) {
   using St = storage_t<S>;
   using F = VecFold<S, OP, V>;
   using Pk = typename F::Pk;
@@ -686,7 +704,10 @@ OCN_DEV typename Reducer<S, OP>::A short_row_fold(const RedArgs &p, const char *
   return one.result();
 }
 
-template <int S, int OP> __global__ __launch_bounds__(kBlock) void red_rows_short_kernel(const RedArgs p) {
+template <int S, int OP> __global__ __launch_bounds__(kBlock) void red_rows_short_kernel(const RedArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if (p.warm) warm_arguments<RedArgs>();
   using R = Reducer<S, OP>;
   using A = typename R::A;
   constexpr int VF = 16 / (int)sizeof(storage_t<S>) > 0 ? 16 / (int)sizeof(storage_t<S>) : 1;
@@ -752,7 +773,7 @@ template <class A> OCN_HD constexpr size_t cols_lds_bytes(int block, int vec) {
 
 // SINGLE: one reduced dim, so that row r lies r strides further on (no index decomposition)
 template <int S, int OP, int V, bool NT, bool SINGLE>
-OCN_DEV void cols_body(const RedArgs &p, typename Reducer<S, OP>::A *lds) {
+OCN_DEV void cols_body(KRedArgs &p, typename Reducer<S, OP>::A *lds) {
   using R = Reducer<S, OP>;
   using A = typename R::A;
   using St = storage_t<S>;
@@ -770,30 +791,36 @@ OCN_DEV void cols_body(const RedArgs &p, typename Reducer<S, OP>::A *lds) {
   const uint32_t per_split = (uint32_t)(p.colblocks_div.d * (uint32_t)(p.nout / p.nc));
   const uint32_t s = b / per_split;
   b -= s * per_split;
-  const uint32_t other = rfastdiv(b, p.colblocks_div);
+  const uint32_t other = rfastdiv(b, args_div(p.colblocks_div));
   const uint32_t cb = b - other * p.colblocks_div.d;
   // p.cpw lanes (a power of two) cover one row of columns; with fewer than 64 of them a
   // wavefront takes 64 / cpw rows at a time
   const int cpw_log2 = __ffs(p.cpw) - 1;
   const int lc = lane & (p.cpw - 1), lr = lane >> cpw_log2;
   const int RPW = kWave >> cpw_log2;
-  const int64_t col0 = ((int64_t)cb * p.cpw + lc) * V;
+  int64_t col0 = ((int64_t)cb * p.cpw + lc) * V;
   const int64_t left = p.nc - col0;
-  const int ncol = left >= V ? V : (left > 0 ? (int)left : 0);
+  int ncol = left >= V ? V : (left > 0 ? (int)left : 0);
+  // The lane with the last few columns takes a whole vector that ends with the last column: the
+  // first `skip` of its columns are its neighbour's and are dropped at the end.
+  int skip = 0;
+  if (ncol > 0 && ncol < V && p.nc >= V) {
+    skip = V - ncol;
+    col0 -= skip;
+    ncol = V;
+  }
 
   // offsets of the other kept dims (kept dim 0 is the column dim)
   int64_t off_a = col0 * (int64_t)sizeof(St), off_o = col0 * p.kso[0];
   {
     uint32_t o = other;
-#pragma unroll
-    for (int k = 1; k < kMaxDims; ++k) {
-      if (k < p.nkept) {
-        const uint32_t q = (k == p.nkept - 1) ? 0u : rfastdiv(o, p.kdiv[k]);
-        const uint32_t i = o - q * p.kdiv[k].d;
-        o = q;
-        off_a += (int64_t)i * p.ksa[k];
-        off_o += (int64_t)i * p.kso[k];
-      }
+    const int nkept = p.nkept;
+    for (int k = 1; k < nkept; ++k) {
+      const uint32_t q = (k == nkept - 1) ? 0u : rfastdiv(o, args_div(p.kdiv[k]));
+      const uint32_t i = o - q * p.kdiv[k].d;
+      o = q;
+      off_a += (int64_t)i * p.ksa[k];
+      off_o += (int64_t)i * p.kso[k];
     }
   }
 
@@ -891,7 +918,7 @@ OCN_DEV void cols_body(const RedArgs &p, typename Reducer<S, OP>::A *lds) {
     };
     if (p.swap_a) rows(std::true_type{});
     else rows(std::false_type{});
-  } else if (ncol > 0) {  // the ragged last column block
+  } else if (ncol > 0) {  // fewer columns than a vector holds
     for (; r < r1; r += RS) {
       const char *src = p.a + off_a + row_offset(r);
 #pragma unroll
@@ -918,7 +945,7 @@ OCN_DEV void cols_body(const RedArgs &p, typename Reducer<S, OP>::A *lds) {
 #pragma unroll
     for (int c = 0; c < CH; ++c) lds[((size_t)wave * CH + c) * kWave + lane] = acc[i0 + c];
     __syncthreads();
-    if (wave < CH && lr == 0 && i0 + wave < ncol) {
+    if (wave < CH && lr == 0 && i0 + wave < ncol && i0 + wave >= skip) {
       const int c = wave, i = i0 + wave;
       A v = lds[(size_t)c * kWave + lane];
       for (int w = 1; w < NW; ++w) v = R::combine(v, lds[((size_t)w * CH + c) * kWave + lane]);
@@ -933,7 +960,10 @@ OCN_DEV void cols_body(const RedArgs &p, typename Reducer<S, OP>::A *lds) {
   }
 }
 
-template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) void red_cols_kernel(const RedArgs p) {
+template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) void red_cols_kernel(const RedArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if (p.warm) warm_arguments<RedArgs>();
   using A = typename Reducer<S, OP>::A;
   constexpr int VF = 16 / (int)sizeof(storage_t<S>) > 0 ? 16 / (int)sizeof(storage_t<S>) : 1;
   extern __shared__ __align__(16) unsigned char red_cols_lds_raw[];
@@ -952,7 +982,10 @@ template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) voi
 // generic
 // ---------------------------------------------------------------------------------------
 
-template <int S, int OP> __global__ __launch_bounds__(kBlock) void red_generic_kernel(const RedArgs p) {
+template <int S, int OP> __global__ __launch_bounds__(kBlock) void red_generic_kernel(const RedArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if (p.warm) warm_arguments<RedArgs>();
   using R = Reducer<S, OP>;
   using A = typename R::A;
   using St = storage_t<S>;
@@ -960,28 +993,22 @@ template <int S, int OP> __global__ __launch_bounds__(kBlock) void red_generic_k
   for (int64_t o = (int64_t)blockIdx.x * kBlock + threadIdx.x; o < p.nout; o += (int64_t)gridDim.x * kBlock) {
   // 64-bit decomposition over the kept dims (fastest first)
   int64_t off_a = 0, off_o = 0, t = o;
-#pragma unroll
-  for (int k = 0; k < kMaxDims; ++k) {
-    if (k < p.nkept) {
-      const int64_t n = p.ksize[k];
-      const int64_t q = t / n;
-      const int64_t i = t - q * n;
-      t = q;
-      off_a += i * p.ksa[k];
-      off_o += i * p.kso[k];
-    }
+  for (int k = 0; k < p.nkept; ++k) {
+    const int64_t n = p.ksize[k];
+    const int64_t q = t / n;
+    const int64_t i = t - q * n;
+    t = q;
+    off_a += i * p.ksa[k];
+    off_o += i * p.kso[k];
   }
   A acc = R::identity();
   for (int64_t r = 0; r < p.nredtot; ++r) {
     int64_t off = 0, q = r;
-#pragma unroll
-    for (int k = 0; k < kMaxDims; ++k) {
-      if (k < p.nred) {
-        const int64_t n = p.rsize[k];
-        const int64_t qq = q / n;
-        off += (q - qq * n) * p.rsa[k];
-        q = qq;
-      }
+    for (int k = 0; k < p.nred; ++k) {
+      const int64_t n = p.rsize[k];
+      const int64_t qq = q / n;
+      off += (q - qq * n) * p.rsa[k];
+      q = qq;
     }
     acc = R::combine(acc, R::lift(from_storage<S>(load_one<S>(p.swap_a != 0, p.a + off_a + off))));
   }

@@ -14,6 +14,7 @@ RedArgs make_red_args(const RedPlan &p, char *partial) {
   r.a = p.a_ptr;
   r.out = p.out_ptr;
   r.partial = partial;
+  r.warm = p.grid <= 1024;
   r.nkept = p.nkept;
   r.nred = p.nred;
   r.out_dtype = p.out_dtype;
@@ -71,6 +72,7 @@ RedLeanArgs make_red_lean_args(const RedPlan &p, char *partial) {
   r.nout = (uint32_t)p.nout;
   r.split = (uint32_t)p.split;
   r.nvec = (uint32_t)(p.nredtot / p.vec);
+  r.tail = (uint32_t)(p.nredtot % p.vec);
   r.chunk = (uint32_t)p.chunk;
   r.out_dtype = p.out_dtype;
   r.group = p.group;
