@@ -243,7 +243,7 @@ int ocn_index_offsets(const ocn_tensor *index, int64_t dim_size, int64_t stride_
  * index.  Writes the offsets sum_d i_d * target_strides[d] of the selected positions, in
  * row-major order of the mask's dimensions, to offsets[0 .. min(count, capacity)) and the
  * number selected to *count (DEVICE int64).  workspace: DEVICE scratch of
- * ocn_mask_offsets_workspace_bytes(mask) bytes, 8-byte aligned.  Three kernel launches.
+ * ocn_mask_offsets_workspace_bytes(mask) bytes, 8-byte aligned.  One to three kernel launches.
  */
 size_t ocn_mask_offsets_workspace_bytes(const ocn_tensor *mask);
 int ocn_mask_offsets(const ocn_tensor *mask, const int64_t *target_strides, void *offsets,

@@ -5,10 +5,11 @@
 //
 //   ocn_index_offsets  one lane per index: wrap, range check, multiply by the stride; invalid
 //                      indices are counted (one integer atomic per wavefront that saw any)
-//   ocn_mask_offsets   stream compaction in the mask's row-major order, three launches and no
+//   ocn_mask_offsets   stream compaction in the mask's row-major order, one to three launches and no
 //                      waiting between workgroups: per-workgroup counts, an exclusive scan of
 //                      the counts by one workgroup (through LDS, coalesced both ways), then every workgroup writes the offsets of
-//                      its selected elements behind its prefix (staged in LDS so that the
+//                      its selected elements behind its prefix (smaller masks: behind the sum of the counts,
+//                      or of the mask itself, before it) (staged in LDS so that the
 //                      stores are coalesced).  Lanes own 16 consecutive mask bytes (one 128-bit
 //                      load when the mask is contiguous).
 //   ocn_gather/scatter one lane per copied item (an element, or 16 bytes where the rows' fastest
@@ -118,6 +119,40 @@ __global__ __launch_bounds__(kBlock) void index_offsets_flat_kernel(const IndexA
   }
 }
 
+// Few indices, both tensors contiguous: one workgroup of 1024 lanes binds them all and writes the
+// number of invalid ones itself, where several would add to a counter that another launch has to
+// clear first (launch and gap of that one: 2.5 us of a call's host time, 1.3 us on the device).
+constexpr int64_t kIndexOneBlock = 16384;
+__global__ __launch_bounds__(1024) void index_offsets_small_kernel(const IndexArgs p) {
+  constexpr int U = 4;
+  __shared__ int32_t waves[1024 / kWave];
+  int32_t nbad = 0;
+  for (int64_t e0 = threadIdx.x; e0 < p.n; e0 += 1024 * U) {
+    int64_t v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (e0 + u * 1024 < p.n) v[u] = reinterpret_cast<const int64_t *>(p.idx)[e0 + u * 1024];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (e0 + u * 1024 < p.n) {
+        const int64_t i = v[u] < 0 ? v[u] + p.dim_size : v[u];
+        const bool bad = i < 0 || i >= p.dim_size;
+        reinterpret_cast<int64_t *>(p.off)[e0 + u * 1024] = bad ? 0 : i * p.stride;
+        nbad += bad ? 1 : 0;
+      }
+    }
+  }
+#pragma unroll
+  for (int d = kWave / 2; d >= 1; d >>= 1) nbad += __shfl_xor(nbad, d, kWave);
+  if ((threadIdx.x & (kWave - 1)) == 0) waves[threadIdx.x / kWave] = nbad;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t all = 0;
+    for (int w = 0; w < 1024 / kWave; ++w) all += waves[w];
+    *p.invalid = (unsigned long long)all;
+  }
+}
+
 // ---------------------------------------------------------------------------------------
 // boolean masks
 // ---------------------------------------------------------------------------------------
@@ -129,8 +164,9 @@ struct MaskArgs {
   int64_t sm[kMaxDims], st[kMaxDims]; // mask / target byte strides
   uint32_t n;                         // mask elements (< 2^31)
   int32_t contig;                     // the mask is one contiguous, 16-byte aligned run
-  int64_t *block_counts;              // [nblocks]; after the scan: exclusive prefixes
+  uint32_t *block_counts;             // [nblocks]; after the scan: exclusive prefixes
   uint32_t nblocks;
+  int32_t before;                     // how a workgroup of the write kernel finds its place: kBefore*
   int64_t *offsets;
   int64_t capacity;
   int64_t *count;
@@ -197,13 +233,19 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *l
   return before + inc - v;
 }
 
+// bytes that are not zero: bit 7 of each byte of ((w & 0x7f..) + 0x7f..) | w
+__device__ __forceinline__ uint32_t nonzero_bytes(const uint4 &v) {
+  auto word = [](uint32_t w) { return (uint32_t)__popc((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u); };
+  return word(v.x) + word(v.y) + word(v.z) + word(v.w);
+}
+
 __global__ __launch_bounds__(kBlock) void mask_count_kernel(const MaskArgs p) {
   __shared__ uint32_t lds[kBlock / kWave];
   const uint32_t e0 = (blockIdx.x * kBlock + threadIdx.x) * kMaskPerLane;
   const uint32_t c = (uint32_t)__popc(mask_flags(p, e0));
   uint32_t sum;
   (void)block_exclusive_scan(c, lds, sum);
-  if (threadIdx.x == 0) p.block_counts[blockIdx.x] = (int64_t)sum;
+  if (threadIdx.x == 0) p.block_counts[blockIdx.x] = sum;
 }
 
 // The same counts for a contiguous mask: a wavefront per chunk of kMaskChunk bytes, every lane
@@ -231,21 +273,18 @@ __global__ __launch_bounds__(kBlock) void mask_count_contig_kernel(const MaskArg
       v[k] = make_uint4(w[0], w[1], w[2], w[3]);
     }
   }
-  // bytes that are not zero: bit 7 of each byte of ((w & 0x7f..) + 0x7f..) | w
-  auto nonzero_bytes = [](uint32_t w) { return (uint32_t)__popc((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u); };
 #pragma unroll
-  for (int k = 0; k < kPieces; ++k)
-    c += nonzero_bytes(v[k].x) + nonzero_bytes(v[k].y) + nonzero_bytes(v[k].z) + nonzero_bytes(v[k].w);
+  for (int k = 0; k < kPieces; ++k) c += nonzero_bytes(v[k]);
 #pragma unroll
   for (int d = kWave / 2; d >= 1; d >>= 1) c += (uint32_t)__shfl_xor((int)c, d, kWave);
-  if (lane == 0) p.block_counts[chunk] = (int64_t)c;
+  if (lane == 0) p.block_counts[chunk] = c;
 }
 
 // one workgroup: block_counts[i] := sum of block_counts[0 .. i), *count := total.  Rounds of
 // 1024 x 16 counts: read coalesced into LDS, each lane adds up 16 consecutive ones, the lane
 // sums are scanned with wavefront shuffles, and the prefixes go back through LDS so that the
 // stores are coalesced too.  Counts are at most kMaskChunk and a round's total stays below
-// 2^26, so LDS holds 32-bit values; the carry between rounds is 64-bit.
+// 2^26; a mask has fewer than 2^31 elements, so every prefix fits 32 bits.
 __global__ __launch_bounds__(kScanBlock) void mask_scan_kernel(const MaskArgs p) {
   constexpr int kPer = 16, kRound = kScanBlock * kPer, kWaves = kScanBlock / kWave;
   __shared__ uint32_t tile[kRound + kRound / kPer];   // one pad word per lane segment: no bank conflicts
@@ -257,7 +296,7 @@ __global__ __launch_bounds__(kScanBlock) void mask_scan_kernel(const MaskArgs p)
     for (int k = 0; k < kPer; ++k) {
       const int64_t i = base + k * kScanBlock + t;
       const int j = k * kScanBlock + t;
-      tile[j + j / kPer] = i < (int64_t)p.nblocks ? (uint32_t)p.block_counts[i] : 0u;
+      tile[j + j / kPer] = i < (int64_t)p.nblocks ? p.block_counts[i] : 0u;
     }
     __syncthreads();
     uint32_t own[kPer], s = 0;
@@ -291,7 +330,7 @@ __global__ __launch_bounds__(kScanBlock) void mask_scan_kernel(const MaskArgs p)
     for (int k = 0; k < kPer; ++k) {
       const int64_t i = base + k * kScanBlock + t;
       const int j = k * kScanBlock + t;
-      if (i < (int64_t)p.nblocks) p.block_counts[i] = carry + (int64_t)tile[j + j / kPer];
+      if (i < (int64_t)p.nblocks) p.block_counts[i] = (uint32_t)carry + tile[j + j / kPer];
     }
     carry += (int64_t)total;
     __syncthreads();   // the next round overwrites tile and wave_sum
@@ -299,15 +338,40 @@ __global__ __launch_bounds__(kScanBlock) void mask_scan_kernel(const MaskArgs p)
   if (t == 0) *p.count = carry;
 }
 
+// A workgroup of the write kernel takes a chunk and needs the number of elements that are selected
+// before it:
+//   kBeforeCount  adds up the mask itself up to there: no other launch at all (contiguous masks of at
+//                 most kMaskDirect elements: the last workgroup reads 60 KiB, a few round trips,
+//                 against the 2.5 us and more that each further launch costs);
+//   kBeforeSum    adds up the chunk counts up to there, which saves the scan launch; the counts are read
+//                 once per workgroup, so
+//   kBeforeScan   reads its prefix where they are more than kMaskSumChunks (8.4 million elements; at 30
+//                 million the sums cost 9 us, the scan 6.3).
+enum { kBeforeCount = 0, kBeforeSum = 1, kBeforeScan = 2 };
+constexpr uint32_t kMaskDirect = 65536, kMaskSumChunks = 2048;
+
 __global__ __launch_bounds__(kBlock) void mask_write_kernel(const MaskArgs p) {
-  __shared__ uint32_t lds[kBlock / kWave];
+  __shared__ uint32_t lds[kBlock / kWave], lds_before[kBlock / kWave];
   // the positions (inside this workgroup's chunk) of its selected elements, in order: 8 KiB,
   // where the offsets themselves would take 32 KiB and leave room for five workgroups per CU
   __shared__ uint16_t staged[kMaskChunk];
   static_assert(kMaskChunk <= 65536, "positions inside a chunk are staged as 16-bit values");
-  const uint32_t chunk0 = blockIdx.x * (uint32_t)kMaskChunk;
-  const uint32_t e0 = chunk0 + threadIdx.x * kMaskPerLane;
-  const uint32_t flags = mask_flags(p, e0);
+  const uint32_t chunk = blockIdx.x, chunk0 = chunk * (uint32_t)kMaskChunk;
+  const uint32_t flags = mask_flags(p, chunk0 + threadIdx.x * kMaskPerLane);
+  if (p.before != kBeforeScan) {
+    uint32_t c = 0;
+    if (p.before == kBeforeCount) {
+#pragma unroll 4
+      for (uint32_t e = threadIdx.x * 16u; e < chunk0; e += kBlock * 16u)
+        c += nonzero_bytes(*reinterpret_cast<const uint4 *>(p.mask + e));
+    } else {
+#pragma unroll 4
+      for (uint32_t i = threadIdx.x; i < chunk; i += kBlock) c += p.block_counts[i];
+    }
+#pragma unroll
+    for (int d = kWave / 2; d >= 1; d >>= 1) c += (uint32_t)__shfl_xor((int)c, d, kWave);
+    if ((threadIdx.x & (kWave - 1)) == 0) lds_before[threadIdx.x / kWave] = c;   // read behind the next barrier
+  }
   uint32_t sum;
   uint32_t slot = block_exclusive_scan((uint32_t)__popc(flags), lds, sum);
   uint32_t f = flags;
@@ -317,8 +381,15 @@ __global__ __launch_bounds__(kBlock) void mask_write_kernel(const MaskArgs p) {
     staged[slot++] = (uint16_t)(threadIdx.x * kMaskPerLane + (uint32_t)k);
   }
   __syncthreads();
+  int64_t base = 0;
+  if (p.before == kBeforeScan) {
+    base = p.block_counts[chunk];
+  } else {
+#pragma unroll
+    for (int w = 0; w < kBlock / kWave; ++w) base += lds_before[w];
+    if (chunk + 1 == p.nblocks && threadIdx.x == 0) *p.count = base + sum;
+  }
   // coalesced stores behind this workgroup's prefix; a position becomes its offset on the way out
-  const int64_t base = p.block_counts[blockIdx.x];
   for (uint32_t i = threadIdx.x; i < sum; i += kBlock)
     if (base + i < p.capacity) {
       int64_t om, ot;
@@ -487,6 +558,77 @@ template <int ES, bool SCATTER> __global__ __launch_bounds__(kBlock) void gather
   }
 }
 
+// Rows that are one contiguous run on both sides, of any length and alignment, in pieces of P
+// bytes: 16, or the largest power of two that fits into a shorter row.  The last piece of a row
+// ends with the row and may overlap the one before it (the same bytes are written twice).  Lanes
+// are numbered through all pieces of all rows, so none idles for padding, and take U pieces each,
+// a workgroup apart, so that a lane has several of the dependent loads (offset, then row) in
+// flight.  65536 rows of 1200 bytes gathered: 44.4 us with 75 pieces of a row in 128 lanes and one
+// piece per lane, 27 us here.
+struct RowPieceArgs {
+  const char *src;
+  char *dst;
+  const int64_t *offsets;
+  int64_t lo, hi, row_stride;
+  uint32_t total;                     // pieces: rows x items (below 2^31)
+  uint32_t bytes;                     // of a row
+  FastDiv items_div;                  // pieces per row
+  int32_t nt_rows, swap_sc;           // as GatherArgs
+};
+template <int P, bool SCATTER, int U> __global__ __launch_bounds__(kBlock) void row_pieces_kernel(const RowPieceArgs p) {
+  using QU = uint32_t __attribute__((ext_vector_type(4), aligned(1)));
+  struct __attribute__((packed, aligned(1))) Any { unsigned char b[P]; };
+  const uint32_t t0 = blockIdx.x * (uint32_t)(kBlock * U) + threadIdx.x;
+  int64_t off[U], at[U];
+  Bytes<P> v[U];
+  bool ok[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t t = t0 + (uint32_t)(u * kBlock);
+    ok[u] = t < p.total;
+    const uint32_t row = fdiv(ok[u] ? t : 0u, p.items_div);
+    const uint32_t b = ((ok[u] ? t : 0u) - row * p.items_div.d) * (uint32_t)P;
+    at[u] = b + (uint32_t)P <= p.bytes ? b : p.bytes - (uint32_t)P;
+    off[u] = p.offsets[row];
+    ok[u] = ok[u] && off[u] >= p.lo && off[u] <= p.hi;
+    off[u] += at[u];
+    at[u] += (int64_t)row * p.row_stride;
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (ok[u]) {
+      const char *src = p.src + (SCATTER ? at[u] : off[u]);
+      if constexpr (P == 16) {
+        const QU q = *reinterpret_cast<const QU *>(src);
+        __builtin_memcpy(&v[u], &q, 16);
+      } else {
+        const Any a = *reinterpret_cast<const Any *>(src);
+        __builtin_memcpy(&v[u], &a, P);
+      }
+    }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (ok[u]) {
+      reorder(v[u], p.swap_sc);
+      char *dst = p.dst + (SCATTER ? off[u] : at[u]);
+      if constexpr (P == 16) {
+        QU q;
+        __builtin_memcpy(&q, &v[u], 16);
+        if (!SCATTER && p.nt_rows) {
+          asm volatile("");
+          __builtin_nontemporal_store(q, reinterpret_cast<QU *>(dst));
+          asm volatile("");
+        } else {
+          *reinterpret_cast<QU *>(dst) = q;
+        }
+      } else {
+        Any a;
+        __builtin_memcpy(&a, &v[u], P);
+        *reinterpret_cast<Any *>(dst) = a;
+      }
+    }
+}
+
 int done(hipError_t e) {
   if (e == hipSuccess) return OCN_OK;
   record_hip_error((int)e);
@@ -580,14 +722,20 @@ int ocn_index_offsets(const ocn_tensor *index, int64_t dim_size, int64_t stride_
   const int64_t grid = std::min<int64_t>((a.n + kBlock - 1) / kBlock, max_launch_blocks());   // the kernel loops beyond that
   if (a.n > 0 && (!index->base || !offsets->base)) return OCN_ERR_NULLPTR;
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(fill_u64_kernel, dim3(1), dim3(1), 0, s, a.invalid, 0ull);
-  // both tensors contiguous in row-major order and 16-byte aligned: the flat kernel
-  bool flat = ((uintptr_t)a.idx % 16) == 0 && ((uintptr_t)a.off % 16) == 0;
+  // both tensors contiguous in row-major order: one workgroup for few indices, else, if they are
+  // 16-byte aligned too, the flat kernel
+  bool contiguous = true;
   int64_t expect = 8;
-  for (int d = index->ndim - 1; d >= 0 && flat; --d) {
-    if (a.size[d] != 1 && (a.si[d] != expect || a.so[d] != expect)) flat = false;
+  for (int d = index->ndim - 1; d >= 0 && contiguous; --d) {
+    if (a.size[d] != 1 && (a.si[d] != expect || a.so[d] != expect)) contiguous = false;
     expect *= a.size[d];
   }
+  if (contiguous && a.n > 0 && a.n <= kIndexOneBlock) {
+    hipLaunchKernelGGL(index_offsets_small_kernel, dim3(1), dim3(1024), 0, s, a);
+    return done(hipGetLastError());
+  }
+  const bool flat = contiguous && ((uintptr_t)a.idx % 16) == 0 && ((uintptr_t)a.off % 16) == 0;
+  hipLaunchKernelGGL(fill_u64_kernel, dim3(1), dim3(1), 0, s, a.invalid, 0ull);
   if (a.n > 0 && flat) {
     const int64_t npair = (a.n + 1) / 2;
     const int64_t fgrid = std::min<int64_t>((npair + kBlock - 1) / kBlock, max_launch_blocks());
@@ -619,17 +767,20 @@ int ocn_mask_offsets(const ocn_tensor *mask, const int64_t *target_strides, void
   if (!mask->base) return OCN_ERR_NULLPTR;
   if (!workspace || workspace_bytes < ocn_mask_offsets_workspace_bytes(mask)) return OCN_ERR_WORKSPACE;
   if ((uintptr_t)workspace % 8) return OCN_ERR_ALIGN;
-  m.block_counts = (int64_t *)workspace;
+  m.block_counts = (uint32_t *)workspace;
   m.offsets = (int64_t *)offsets;
   m.capacity = capacity;
   m.count = (int64_t *)count;
   m.nt_store = std::min<int64_t>(capacity, m.n) * 8 >= ((int64_t)32 << 20);  // too large to stay cached
-  if (m.contig)
-    hipLaunchKernelGGL(mask_count_contig_kernel, dim3((m.nblocks + kBlock / kWave - 1) / (kBlock / kWave)), dim3(kBlock),
-                       0, s, m);
-  else
-    hipLaunchKernelGGL(mask_count_kernel, dim3(m.nblocks), dim3(kBlock), 0, s, m);
-  hipLaunchKernelGGL(mask_scan_kernel, dim3(1), dim3(kScanBlock), 0, s, m);
+  m.before = m.contig && m.n <= kMaskDirect ? kBeforeCount : m.nblocks <= kMaskSumChunks ? kBeforeSum : kBeforeScan;
+  if (m.before != kBeforeCount) {
+    if (m.contig)
+      hipLaunchKernelGGL(mask_count_contig_kernel, dim3((m.nblocks + kBlock / kWave - 1) / (kBlock / kWave)), dim3(kBlock),
+                         0, s, m);
+    else
+      hipLaunchKernelGGL(mask_count_kernel, dim3(m.nblocks), dim3(kBlock), 0, s, m);
+  }
+  if (m.before == kBeforeScan) hipLaunchKernelGGL(mask_scan_kernel, dim3(1), dim3(kScanBlock), 0, s, m);
   hipLaunchKernelGGL(mask_write_kernel, dim3(m.nblocks), dim3(kBlock), 0, s, m);
   return done(hipGetLastError());
 }
@@ -743,6 +894,47 @@ static int run_gather(bool scatter, const ocn_tensor *inner, const void *offsets
 #undef OCN_LAUNCH4
     }
     return done(hipGetLastError());
+  }
+  // rows that are one contiguous run on both sides
+  if (inner_elems == 1 || (m == 1 && d[0].si == es && d[0].sr == es && inner_elems * es < ((int64_t)1 << 31))) {
+    const int64_t bytes = inner_elems * es;
+    int piece = 16;
+    while (piece > bytes) piece /= 2;
+    const int64_t items = (bytes + piece - 1) / piece;
+    const bool many = n * items >= kNumCUs * kBlock * 4;       // enough for four pieces per lane
+    const int64_t per_block = (int64_t)kBlock * (many ? 4 : 1);
+    const int64_t rows_max = std::min<int64_t>((((int64_t)1 << 31) - 8 * kBlock) / items, max_blocks * per_block / items);
+    if (rows_max >= 1) {
+      RowPieceArgs r;
+      r.lo = lo;
+      r.hi = hi;
+      r.row_stride = g.row_stride;
+      r.bytes = (uint32_t)bytes;
+      r.items_div = make_fastdiv((uint32_t)items);
+      r.nt_rows = !scatter && n * bytes >= ((int64_t)32 << 20);
+      r.swap_sc = g.swap_sc;
+      for (int64_t j0 = 0; j0 < n; j0 += rows_max) {
+        const int64_t rows_now = std::min<int64_t>(rows_max, n - j0);
+        r.src = g.src + (scatter ? j0 * g.row_stride : 0);
+        r.dst = g.dst + (scatter ? 0 : j0 * g.row_stride);
+        r.offsets = g.offsets + j0;
+        r.total = (uint32_t)(rows_now * items);
+        const unsigned launch_grid = (unsigned)(((int64_t)r.total + per_block - 1) / per_block);
+#define OCN_LAUNCH_ROWS(P, S, U) hipLaunchKernelGGL((row_pieces_kernel<P, S, U>), dim3(launch_grid), dim3(kBlock), 0, s, r)
+#define OCN_LAUNCH_PIECE(P)                                                        \
+  case P:                                                                          \
+    if (scatter) { if (many) OCN_LAUNCH_ROWS(P, true, 4); else OCN_LAUNCH_ROWS(P, true, 1); }     \
+    else { if (many) OCN_LAUNCH_ROWS(P, false, 4); else OCN_LAUNCH_ROWS(P, false, 1); }           \
+    break;
+        switch (piece) {
+          OCN_LAUNCH_PIECE(1) OCN_LAUNCH_PIECE(2) OCN_LAUNCH_PIECE(4) OCN_LAUNCH_PIECE(8) OCN_LAUNCH_PIECE(16)
+          default: break;
+        }
+#undef OCN_LAUNCH_PIECE
+#undef OCN_LAUNCH_ROWS
+      }
+      return done(hipGetLastError());
+    }
   }
   // A launch may not exceed 2^32 lanes: longer lists of offsets go out in several launches,
   // each over a contiguous run of rows (the kernels are independent of one another).
