@@ -183,6 +183,8 @@ struct InterpArgs {
   int32_t swap;               // operands stored in the other byte order: bit 0 a, bit 1 b, bit 2 out
   int32_t vec;                // 4: a lane takes four consecutive elements of the innermost dim (sizes, strides and
                               // numel then count groups of four); 1: one element
+  int32_t nt_store;           // stream the output past the caches
+  int32_t back[3];            // vec == 4: bytes (out / a / b) by which a row's last group is moved back to end with the row
   int32_t inner_a, inner_b;   // vec == 4: the input is contiguous along the innermost dim (else broadcast there)
   FastDiv div[kMaxDims];
 };

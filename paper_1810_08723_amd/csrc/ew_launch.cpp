@@ -404,29 +404,32 @@ InterpArgs make_interp_args(const EwPlan &p) {
   a.numel = p.numel;
   a.swap = p.swap;
   a.vec = 1;
-  // Four elements per lane where the innermost dim allows it: a multiple of four long,
-  // contiguous in the output, contiguous or broadcast in the inputs, and every group of four
-  // aligned as one access (at most 16 bytes).  The elementary functions stay at one.
+  // Four elements per lane where the innermost dim allows it: contiguous in the output, contiguous
+  // or broadcast in the inputs, and at least four long.  Alignment does not matter (one access of at
+  // most 16 bytes per 16 bytes at any multiple of the scalar size).  Where the length is not a
+  // multiple of four, a row's last group ends with the row and repeats elements of the one before
+  // it - not in place, where those may have been overwritten by then.  The elementary functions
+  // stay at one.
   const bool elementary = p.nin == 1 && ((p.op >= U_SIN && p.op <= U_LOG) || (p.op >= U_ASIN && p.op <= U_TANH));
   if (p.ndim >= 1 && !elementary) {
     const int last = p.ndim - 1;
-    auto fits = [&](const Operand &x, bool may_broadcast) {
-      const int64_t es = dt_size(x.dtype), al = std::min<int64_t>(16, 4 * es);
-      if (x.stride[last] == 0) return may_broadcast;
-      if (x.stride[last] != es || (intptr_t)x.ptr % al) return false;
-      for (int d = 0; d < last; ++d)
-        if (x.stride[d] % al) return false;
-      return true;
-    };
-    if (p.size[last] % 4 == 0 && fits(p.out, false) && fits(p.a, true) && (p.nin == 1 || fits(p.b, true))) {
+    const int64_t n0 = p.size[last], es_o = dt_size(p.out.dtype);
+    auto fits = [&](const Operand &x) { return x.stride[last] == 0 || x.stride[last] == dt_size(x.dtype); };
+    const bool in_place = p.a.ptr == p.out.ptr || (p.nin == 2 && p.b.ptr == p.out.ptr);
+    if (p.out.stride[last] == es_o && fits(p.a) && (p.nin == 1 || fits(p.b)) && n0 >= 4 && (n0 % 4 == 0 || !in_place)) {
+      const int64_t groups = (n0 + 3) / 4, over = groups * 4 - n0;
       a.vec = 4;
       a.inner_a = p.a.stride[last] != 0;
       a.inner_b = p.nin == 2 && p.b.stride[last] != 0;
-      a.size[last] /= 4;
+      a.back[0] = (int32_t)(over * p.out.stride[last]);
+      a.back[1] = (int32_t)(over * p.a.stride[last]);
+      a.back[2] = p.nin == 2 ? (int32_t)(over * p.b.stride[last]) : 0;
+      a.nt_store = p.nt_store && es_o == 4;   // one 16-byte piece per lane
+      a.size[last] = groups;
       a.so[last] *= 4;
       a.sa[last] *= 4;
       a.sb[last] *= 4;
-      a.numel /= 4;
+      a.numel = a.numel / n0 * groups;
     }
   }
   a.idx32 = a.numel < ((int64_t)1 << 31);
