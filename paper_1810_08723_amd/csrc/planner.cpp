@@ -321,6 +321,30 @@ void choose_tiles(EwPlan &p, TileRule rule, int fa, int fb) {
 
 }  // namespace
 
+namespace {
+// Is this copy or cast one between planes and pixels that the pixel kernels take?  C channels side
+// by side on one side (pixels dense: C elements apart) and planes on the other, contiguous along the
+// pixels; at least one vector of pixels; the types the kernels exist for; native byte order, or a
+// plain copy within the other one.
+int pixel_layout(const EwPlan &p, int es_o, int es_a) {
+  const int n = p.ndim, sa = p.a.dtype, so = p.out.dtype;
+  if (n < 2) return 0;
+  auto sample = [](int dt) { return dt == DT_U8 || dt == DT_U16 || dt == DT_I16 || dt == DT_F16 || dt == DT_F32; };
+  if (sa == so ? es_o > 8 || !(p.swap == 0 || p.swap == 5) : !sample(sa) || !sample(so) || p.swap != 0) return 0;
+  const int64_t v = 16 / es_o;
+  auto fits = [&](int64_t m, int64_t c) {
+    const int64_t mvec = (m + v - 1) / v, total = mvec * (p.numel / (m * c));
+    return c >= 2 && c <= 4 && m >= v && m < ((int64_t)1 << 31) && total < ((int64_t)1 << 31) &&
+           (total + kBlock - 1) / kBlock <= max_launch_blocks();
+  };
+  const int64_t c1 = p.size[n - 2], c2 = p.size[n - 1];
+  if (p.out.stride[n - 1] == es_o && p.a.stride[n - 2] == es_a && p.a.stride[n - 1] == c1 * es_a && fits(c2, c1)) return kKernelToPlanes;
+  if (p.out.stride[n - 1] == es_o && p.out.stride[n - 2] == c2 * es_o && p.a.stride[n - 2] == es_a && p.a.stride[n - 1] != es_a && fits(c1, c2))
+    return kKernelToPixels;
+  return 0;
+}
+}  // namespace
+
 int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
                      const ocn_tensor *out, uint32_t flags, EwPlan *plan) {
   EwPlan p;
@@ -516,6 +540,21 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
     return OCN_OK;
   }
 
+  // A copy or cast between planes and interleaved pixels of two to four channels takes the pixel
+  // kernels where the all-vector tiled form does not apply (uint8 pixels [32, 480, 640, 3] to float
+  // planes: 32.6 us in tiles of any alignment, 21.8 there; uint8 planes to float pixels 65.7 and 21.8).
+  const int pixels = nin == 1 && op == U_IDENT ? pixel_layout(p, es_o, es_a) : 0;
+  const bool pixels_ok = pixels != 0;
+  auto plan_pixels = [&](EwPlan &q) {
+    q.kernel = pixels;
+    q.vec = 16 / es_o;
+    q.stage_a = q.stage_b = false;
+    q.lds_bytes = pixels == kKernelToPixels ? (int64_t)kBlock * 16 * q.size[n - 1] : 0;
+    for (int d = 0; d < kMaxDims; ++d) q.tile_log2[d] = 0;
+    const int64_t m = q.size[pixels == kKernelToPlanes ? n - 1 : n - 2], c = q.size[pixels == kKernelToPlanes ? n - 2 : n - 1];
+    q.grid = ((m + q.vec - 1) / q.vec * (numel / (m * c)) + kBlock - 1) / kBlock;
+  };
+
   // tiled / generic: stage an input through LDS when its fastest axis is not the output's
   const int fo = inner;  // the output's fastest dim after sorting
   const int fa = fastest_dim(n, [&](int d) { return p.a.stride[d]; });
@@ -529,6 +568,11 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
   // form's staging costs (measured on channel-last to channel-first copies with 3 channels).
   bool stage_a0 = p.stage_a, stage_b0 = p.stage_b;
   for (int rule = kTilesVector; rule <= kTilesGeneral; ++rule) {
+    if (rule == kTilesAny && pixels_ok) {
+      *plan = p;
+      plan_pixels(*plan);
+      return OCN_OK;
+    }
     if (rule == kTilesAny) {
       if (stage_a0 && p.size[fa] * es_a < 32) stage_a0 = false;
       if (stage_b0 && p.size[fb] * es_b < 32) stage_b0 = false;
@@ -1401,7 +1445,8 @@ void plan_second_pass(const RedPlan &first, char *workspace, RedPlan *second) {
 
 void fill_info(const EwPlan &p, ocn_plan_info *info) {
   std::memset(info, 0, sizeof *info);
-  info->kernel = p.kernel != kKernelTiledAny ? p.kernel : p.stage_a || p.stage_b ? OCN_KERNEL_EW_TILED : OCN_KERNEL_EW_GENERIC;
+  info->kernel = p.kernel == kKernelTiledAny ? (p.stage_a || p.stage_b ? OCN_KERNEL_EW_TILED : OCN_KERNEL_EW_GENERIC)
+                 : p.kernel == kKernelToPlanes || p.kernel == kKernelToPixels ? OCN_KERNEL_EW_GENERIC : p.kernel;
   info->compute_dtype = p.T;
   info->ndim = p.ndim;
   for (int d = 0; d < p.ndim; ++d) {

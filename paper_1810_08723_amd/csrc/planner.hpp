@@ -48,6 +48,8 @@ struct Operand {
 // EwPlan::kernel of the tiled form for tiles of any size and alignment (ew_tiled_any_kernel); plan
 // inspection reports it as OCN_KERNEL_EW_TILED, or OCN_KERNEL_EW_GENERIC when nothing is staged.
 constexpr int kKernelTiledAny = 100;
+// Copies and casts between planes and interleaved pixels (reported as OCN_KERNEL_EW_GENERIC).
+constexpr int kKernelToPlanes = 101, kKernelToPixels = 102;
 
 struct EwPlan {
   int kernel = OCN_KERNEL_NONE;
