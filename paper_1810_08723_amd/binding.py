@@ -7,6 +7,7 @@ missing the import fails loudly: there is no fallback path.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from dataclasses import dataclass, field
 from typing import Any, Optional, Sequence, Tuple
@@ -131,7 +132,7 @@ def lib() -> C.CDLL:
     return _lib
 
 
-@dataclass
+@dataclass(init=False)
 class Tensor:
     """A view on device storage: the descriptor the C ABI takes, plus a keep-alive reference."""
     base: int                      # device address of the storage start
@@ -143,6 +144,18 @@ class Tensor:
     keepalive: Any = field(default=None, repr=False, compare=False)
     byteswapped: bool = False      # the storage holds every scalar in the other byte order
 
+    # The C struct is built at the first call that takes the tensor and dropped when a field is
+    # assigned (the library never writes to it).  _ref: the struct by reference, as the calls take it.
+    _ref = None
+
+    def __init__(self, base, dtype, sizes, strides, offset=0, device=0, keepalive=None, byteswapped=False):
+        self.__dict__.update(base=base, dtype=dtype, sizes=sizes, strides=strides, offset=offset, device=device,
+                             keepalive=keepalive, byteswapped=byteswapped)
+
+    def __setattr__(self, name, value):
+        self.__dict__[name] = value
+        self.__dict__.pop("_ref", None)
+
     @staticmethod
     def on_storage(storage, dtype: str, sizes: Sequence[int], strides: Sequence[int],
                    offset: int = 0, byteswapped: bool = False) -> "Tensor":
@@ -150,12 +163,7 @@ class Tensor:
         dev = storage.device.index if storage.device.index is not None else 0
         return Tensor(storage.data_ptr(), dtype, tuple(sizes), tuple(strides), offset, dev, storage, byteswapped)
 
-    def desc(self) -> OcnTensor:
-        # the C struct is rebuilt only when a field has changed (the library never writes to it)
-        key = (self.base, self.dtype, self.sizes, self.strides, self.offset, self.device, self.byteswapped)
-        cached = self.__dict__.get("_desc_cache")
-        if cached is not None and cached[0] == key:
-            return cached[1]
+    def _make_ref(self):
         t = OcnTensor()
         t.base = self.base
         t.offset = self.offset
@@ -166,15 +174,47 @@ class Tensor:
             t.stride[d] = self.strides[d]
         t.device = self.device
         t.byteswapped = 1 if self.byteswapped else 0
-        self.__dict__["_desc_cache"] = (key, t)
-        return t
+        ref = C.byref(t)
+        # kept only where the sizes and strides cannot change behind the tensor's back
+        if type(self.sizes) is tuple and type(self.strides) is tuple:
+            self.__dict__["_ref"] = ref
+        return ref
+
+    def desc(self) -> OcnTensor:
+        return (self._ref or self._make_ref())._obj
+
+
+# The current stream's handle.  torch builds a Stream object around it at every call (1.5 us of a 7 us
+# call); the handle itself is one call into torch's runtime away once the first call has
+# initialised it (forgotten in a forked child, where torch has its say again).
+_raw_stream = None
+
+
+def _current_stream() -> int:
+    global _raw_stream
+    import torch
+    handle = int(torch.cuda.current_stream().cuda_stream)
+    get_device, get_stream = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if get_device is not None and get_stream is not None and torch.cuda.is_initialized():
+        _raw_stream = (get_stream, get_device)
+    return handle
+
+
+def _forget_stream() -> None:
+    global _raw_stream
+    _raw_stream = None
+
+
+os.register_at_fork(after_in_child=_forget_stream)
 
 
 def _stream(stream) -> int:
     if stream is not None:
         return int(stream)
-    import torch
-    return int(torch.cuda.current_stream().cuda_stream)
+    raw = _raw_stream
+    if raw is None:
+        return _current_stream()
+    return raw[0](raw[1]())
 
 
 def _check(rc: int) -> None:
@@ -195,21 +235,46 @@ def _scratch(nbytes: int, device: int, stream):
     return ws
 
 
+@functools.lru_cache(maxsize=256, typed=True)
+def _axes_array(*axes):
+    return (C.c_int32 * max(len(axes), 1))(*axes)     # (read only: the library takes it as const)
+
+
 def _axes(axes: Sequence[int]):
-    return (C.c_int32 * max(len(axes), 1))(*axes), len(axes)
+    return _axes_array(*axes), len(axes)
+
+
+def _function(name: str):
+    """The library's function, looked up at its first call."""
+    def first(*args):
+        f = getattr(lib(), name)
+        globals()["_" + name] = f
+        return f(*args)
+    return first
+
+
+for _name in ("ocn_unary", "ocn_binary", "ocn_cast_copy", "ocn_reduce", "ocn_binary_reduce", "ocn_reduce_scratch",
+              "ocn_index_offsets", "ocn_mask_offsets", "ocn_gather", "ocn_scatter"):
+    globals()["_" + _name] = _function(_name)
 
 
 def unary(op: str, a: Tensor, out: Tensor, flags: int = 0, stream=None) -> None:
-    _check(lib().ocn_unary(UNARY_CODE[op], C.byref(a.desc()), C.byref(out.desc()), flags, _stream(stream)))
+    rc = _ocn_unary(UNARY_CODE[op], a._ref or a._make_ref(), out._ref or out._make_ref(), flags, _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def binary(op: str, a: Tensor, b: Tensor, out: Tensor, flags: int = 0, stream=None) -> None:
-    _check(lib().ocn_binary(BINARY_CODE[op], C.byref(a.desc()), C.byref(b.desc()),
-                            C.byref(out.desc()), flags, _stream(stream)))
+    rc = _ocn_binary(BINARY_CODE[op], a._ref or a._make_ref(), b._ref or b._make_ref(), out._ref or out._make_ref(),
+                     flags, _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def cast_copy(src: Tensor, dst: Tensor, stream=None) -> None:
-    _check(lib().ocn_cast_copy(C.byref(src.desc()), C.byref(dst.desc()), _stream(stream)))
+    rc = _ocn_cast_copy(src._ref or src._make_ref(), dst._ref or dst._make_ref(), _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def reduce_workspace_bytes(op: str, a: Tensor, axes: Sequence[int], out: Tensor) -> int:
@@ -230,8 +295,10 @@ def reduce(op: str, a: Tensor, axes: Sequence[int], out: Tensor, workspace=None,
             workspace = _scratch(need, a.device, stream)
     if workspace is not None:
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel()
-    _check(lib().ocn_reduce(REDUCE_CODE[op], C.byref(a.desc()), ax, n, C.byref(out.desc()),
-                            ws_ptr, ws_bytes, _stream(stream)))
+    rc = _ocn_reduce(REDUCE_CODE[op], a._ref or a._make_ref(), ax, n, out._ref or out._make_ref(), ws_ptr, ws_bytes,
+                     _stream(stream))
+    if rc:
+        _check(rc)
 
 
 REDUCE_SCRATCH_BYTES = 1 << 20
@@ -241,8 +308,9 @@ def reduce_scratch(op: str, a: Tensor, axes: Sequence[int], out: Tensor, stream=
     """ocn_reduce without a workspace: partial results go to the library's fixed device array
     (at most REDUCE_SCRATCH_BYTES); nothing is allocated, here or in the library."""
     ax, n = _axes(axes)
-    _check(lib().ocn_reduce_scratch(REDUCE_CODE[op], C.byref(a.desc()), ax, n, C.byref(out.desc()),
-                                    _stream(stream)))
+    rc = _ocn_reduce_scratch(REDUCE_CODE[op], a._ref or a._make_ref(), ax, n, out._ref or out._make_ref(), _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def binary_reduce_workspace_bytes(ew_op: str, red_op: str, a: Tensor, b: Tensor, axes: Sequence[int],
@@ -264,38 +332,49 @@ def binary_reduce(ew_op: str, red_op: str, a: Tensor, b: Tensor, axes: Sequence[
             workspace = _scratch(need, a.device, stream)
     if workspace is not None:
         ws_ptr, ws_bytes = workspace.data_ptr(), workspace.numel()
-    _check(lib().ocn_binary_reduce(BINARY_CODE[ew_op], REDUCE_CODE[red_op], C.byref(a.desc()), C.byref(b.desc()),
-                                   ax, n, C.byref(out.desc()), DTYPE_CODE[mid_dtype], ws_ptr, ws_bytes,
-                                   _stream(stream)))
+    rc = _ocn_binary_reduce(BINARY_CODE[ew_op], REDUCE_CODE[red_op], a._ref or a._make_ref(), b._ref or b._make_ref(),
+                            ax, n, out._ref or out._make_ref(), DTYPE_CODE[mid_dtype], ws_ptr, ws_bytes, _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def index_offsets(index: Tensor, dim_size: int, stride_bytes: int, offsets: Tensor, invalid_count, stream=None) -> None:
     """`invalid_count`: a 1-element int64 torch tensor on the device (overwritten)."""
-    _check(lib().ocn_index_offsets(C.byref(index.desc()), dim_size, stride_bytes, C.byref(offsets.desc()),
-                                   invalid_count.data_ptr(), _stream(stream)))
+    rc = _ocn_index_offsets(index._ref or index._make_ref(), dim_size, stride_bytes, offsets._ref or offsets._make_ref(),
+                            invalid_count.data_ptr(), _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def mask_offsets(mask: Tensor, target_strides: Sequence[int], offsets, count, workspace=None, stream=None) -> None:
     """`offsets`: int64 torch tensor on the device (its length is the capacity); `count`: 1-element
     int64 torch tensor; `workspace`: uint8 torch tensor or None to allocate one through torch."""
-    need = int(lib().ocn_mask_offsets_workspace_bytes(C.byref(mask.desc())))
     if workspace is None:
+        need = int(lib().ocn_mask_offsets_workspace_bytes(C.byref(mask.desc())))
         workspace = _scratch(max(need, 8), mask.device, stream)
     ts = (C.c_int64 * max(len(target_strides), 1))(*target_strides)
-    _check(lib().ocn_mask_offsets(C.byref(mask.desc()), ts, offsets.data_ptr() if offsets.numel() else None,
-                                  offsets.numel(), count.data_ptr(), workspace.data_ptr(), workspace.numel(),
-                                  _stream(stream)))
+    n = offsets.numel()
+    rc = _ocn_mask_offsets(mask._ref or mask._make_ref(), ts, offsets.data_ptr() if n else None, n, count.data_ptr(),
+                           workspace.data_ptr(), workspace.numel(), _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def gather(a_inner: Tensor, offsets, lo: int, hi: int, out: Tensor, stream=None) -> None:
     """`offsets`: int64 torch tensor on the device, one entry per row of `out`."""
-    _check(lib().ocn_gather(C.byref(a_inner.desc()), offsets.data_ptr() if offsets.numel() else None,
-                            offsets.numel(), lo, hi, C.byref(out.desc()), _stream(stream)))
+    n = offsets.numel()
+    rc = _ocn_gather(a_inner._ref or a_inner._make_ref(), offsets.data_ptr() if n else None, n, lo, hi,
+                     out._ref or out._make_ref(), _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def scatter(src: Tensor, offsets, lo: int, hi: int, out_inner: Tensor, stream=None) -> None:
-    _check(lib().ocn_scatter(C.byref(src.desc()), offsets.data_ptr() if offsets.numel() else None,
-                             offsets.numel(), lo, hi, C.byref(out_inner.desc()), _stream(stream)))
+    n = offsets.numel()
+    rc = _ocn_scatter(src._ref or src._make_ref(), offsets.data_ptr() if n else None, n, lo, hi,
+                      out_inner._ref or out_inner._make_ref(), _stream(stream))
+    if rc:
+        _check(rc)
 
 
 def domain_check(op: str, a: Tensor, flag=None, workspace=None, stream=None):
