@@ -41,7 +41,7 @@ template <int S, int OP> hipError_t launch_red(const RedPlan &p, char *partial, 
         f.split = (uint32_t)p.nredtot;
         f.out_dtype = p.out_dtype;
         f.swap_o = p.swap_o ? 1 : 0;
-        hipLaunchKernelGGL((red_fold_kernel<S, OP>), dim3((unsigned)p.grid), dim3(kWave), 0, stream, f);
+        hipLaunchKernelGGL((red_fold_kernel<S, OP>), dim3((unsigned)p.grid), dim3(kFoldWaves * kWave), 0, stream, f);
         break;
       }
       {
