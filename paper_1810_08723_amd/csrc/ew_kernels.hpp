@@ -429,9 +429,10 @@ struct RowsSlimArgs {
   int64_t so, sa, sb;   // byte strides of the outer dim (zero and unused without one)
   uint32_t nvec;        // vectors in total
   FastDiv vpr_div;      // vectors per row
-  uint32_t flags;       // kSlim* bits; operands in the other byte order in bits 8..10
+  uint32_t flags;       // kSlim* bits; operands in the other byte order in bits 8..10; from bit 16: elements behind
+                        // the last whole vector (without an outer dim only)
 };
-enum : uint32_t { kSlimABcast = 1, kSlimBBcast = 2, kSlimNtA = 4, kSlimNtB = 8, kSlimNtStore = 16, kSlimSwapShift = 8 };
+enum : uint32_t { kSlimABcast = 1, kSlimBBcast = 2, kSlimNtA = 4, kSlimNtB = 8, kSlimNtStore = 16, kSlimSwapShift = 8, kSlimTailShift = 16 };
 #ifndef OCN_SLIM_BLOCK
 #define OCN_SLIM_BLOCK 64
 #endif
@@ -473,7 +474,7 @@ template <class G> __global__ __launch_bounds__(kSlimBlock) void ew_rows_slim_ke
       }
     }
   }
-  const int swap = (int)(flags >> kSlimSwapShift);
+  const int swap = (int)(flags >> kSlimSwapShift) & 7;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     if (g0 + (uint32_t)u * kSlimBlock < p.nvec) {
@@ -496,6 +497,28 @@ template <class G> __global__ __launch_bounds__(kSlimBlock) void ew_rows_slim_ke
       }
       if (swap) G::order_output(swap, r);
       store_pack<SOt, V>(p.out + oo[u], r, (flags & kSlimNtStore) != 0);
+    }
+  }
+  // The elements behind the last whole vector of a one-dimensional tensor, by the lane that the next
+  // vector would be (a > b over 30 000 001 floats: 28.6 us in the kernel for rows of any length, which
+  // holds four vectors per lane here, 25.5 with the tail in this one).
+  if constexpr (U > 1) {
+    const uint32_t tail = flags >> kSlimTailShift;
+    const uint32_t ahead = p.nvec - g0;
+    if (tail != 0 && ahead % kSlimBlock == 0 && ahead / kSlimBlock < (uint32_t)U) {
+      const int64_t e0 = (int64_t)p.nvec * V;
+      for (uint32_t i = 0; i < tail; ++i) {
+        Pack<SAt, 1> x;
+        Pack<SBt, 1> y;
+        Pack<SOt, 1> r;
+        x.v[0] = reinterpret_cast<const SAt *>(p.a)[flags & kSlimABcast ? 0 : e0 + i];
+        if constexpr (BIN) y.v[0] = reinterpret_cast<const SBt *>(p.b)[flags & kSlimBBcast ? 0 : e0 + i];
+        if (swap) G::order_inputs(swap, x, y);
+        if constexpr (BIN) r.v[0] = G::eval(x.v[0], y.v[0]);
+        else r.v[0] = G::eval(x.v[0], SBt{});
+        if (swap) G::order_output(swap, r);
+        reinterpret_cast<SOt *>(p.out)[e0 + i] = r.v[0];
+      }
     }
   }
 }

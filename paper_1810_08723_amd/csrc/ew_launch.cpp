@@ -71,10 +71,14 @@ bool make_rows_slim_args(const EwPlan &p, int block, RowsSlimArgs *args, int64_t
   const int inner = p.ndim - 1;
   if (inner < 0 || inner > 1) return false;
   const int64_t n0 = p.size[inner];
-  if (!p.rows_aligned || n0 % p.vec != 0) return false;
+  // whole vectors; a one-dimensional tensor may end with part of one where a lane takes several (with
+  // one vector per lane the kernel for rows of any length is as fast)
+  const int64_t tail = n0 % p.vec;
+  if (!p.rows_aligned || (tail != 0 && (inner == 1 || p.unroll == 1))) return false;
   const int64_t vpr = n0 / p.vec;
   const int64_t nvec = vpr * (inner == 1 ? p.size[0] : 1);
-  const int64_t g = (nvec + (int64_t)block * p.unroll - 1) / ((int64_t)block * p.unroll);
+  const int64_t lanes = nvec + (tail != 0 ? 1 : 0);
+  const int64_t g = (lanes + (int64_t)block * p.unroll - 1) / ((int64_t)block * p.unroll);
   // 32-bit vector numbers (including those of the lanes past the end), one launch
   if (nvec >= ((int64_t)1 << 31) || g * block * p.unroll >= ((int64_t)1 << 32) || g > max_launch_blocks() || g < 1)
     return false;
@@ -89,9 +93,10 @@ bool make_rows_slim_args(const EwPlan &p, int block, RowsSlimArgs *args, int64_t
     r.sb = p.b.stride[0];
   }
   r.nvec = (uint32_t)nvec;
-  r.vpr_div = make_fastdiv((uint32_t)vpr);   // without an outer dim: row 0 for every vector
+  // without an outer dim: row 0 for every vector
+  r.vpr_div = make_fastdiv((uint32_t)std::max<int64_t>(vpr, 1));
   r.flags = (p.a_inner_bcast ? kSlimABcast : 0u) | (p.b_inner_bcast ? kSlimBBcast : 0u) | (p.nt_a ? kSlimNtA : 0u) |
-            (p.nt_b ? kSlimNtB : 0u) | (p.nt_store ? kSlimNtStore : 0u) | ((uint32_t)p.swap << kSlimSwapShift);
+            (p.nt_b ? kSlimNtB : 0u) | (p.nt_store ? kSlimNtStore : 0u) | ((uint32_t)p.swap << kSlimSwapShift) | ((uint32_t)tail << kSlimTailShift);
   *args = r;
   *grid = g;
   return true;
