@@ -259,8 +259,8 @@ int ocn_mask_offsets(const ocn_tensor *mask, const int64_t *target_strides, void
  * old contents (pass the smallest and largest offset that stays inside the storage).
  * ocn_scatter: the reverse copy, src[j, i...] into the indexed tensor; offsets that repeat
  * leave one of the written values, which one is not defined.
- * A lane moves one item (an element, or 16 bytes where the rows' fastest dimension is
- * contiguous and 16-byte aligned on both sides); rows of up to 256 items share a workgroup.
+ * A lane moves one item: an element, or 16 bytes where the rows' fastest dimension is
+ * contiguous (rows without any gaps: at any alignment); rows of up to 256 items share a workgroup.
  * A copy of 2^32 lanes or more goes out in several launches.
  */
 int ocn_gather(const ocn_tensor *a_inner, const void *offsets, int64_t n, int64_t lo, int64_t hi,
@@ -338,7 +338,7 @@ typedef enum {
   OCN_KERNEL_EW_ROWS,      /* vectorised rows: every operand contiguous (or broadcast)
                               along the innermost canonical dimension                      */
   OCN_KERNEL_EW_TILED,     /* LDS-staged tiles: operands disagree on their fastest axis     */
-  OCN_KERNEL_EW_GENERIC,   /* one element per lane, arbitrary strides                       */
+  OCN_KERNEL_EW_GENERIC,   /* one or four elements per lane, any strides; planes <-> pixels  */
   OCN_KERNEL_RED_ROWS,     /* reduced axis is the input's fastest                           */
   OCN_KERNEL_RED_COLS,     /* a kept axis is the input's fastest                            */
   OCN_KERNEL_RED_GENERIC,  /* one output per lane, arbitrary strides                        */

@@ -504,8 +504,10 @@ template <class G> __global__ __launch_bounds__(kSlimBlock) void ew_rows_slim_ke
   // holds four vectors per lane here, 25.5 with the tail in this one).
   if constexpr (U > 1) {
     const uint32_t tail = flags >> kSlimTailShift;
+    if (tail == 0) return;          // (a scalar branch: nothing else is left to do for all other launches)
+    OCN_KEEP_BRANCH();
     const uint32_t ahead = p.nvec - g0;
-    if (tail != 0 && ahead % kSlimBlock == 0 && ahead / kSlimBlock < (uint32_t)U) {
+    if (ahead % kSlimBlock == 0 && ahead / kSlimBlock < (uint32_t)U) {
       const int64_t e0 = (int64_t)p.nvec * V;
       for (uint32_t i = 0; i < tail; ++i) {
         Pack<SAt, 1> x;

@@ -13,7 +13,8 @@
 //                      stores are coalesced).  Lanes own 16 consecutive mask bytes (one 128-bit
 //                      load when the mask is contiguous).
 //   ocn_gather/scatter one lane per copied item (an element, or 16 bytes where the rows' fastest
-//                      dimension is contiguous and aligned), rows of `inner` elements per offset;
+//                      dimension is contiguous and aligned), rows of `inner` elements per offset
+//                      (gapless rows in 16-byte pieces of any alignment: row_pieces_kernel);
 //                      short rows share a workgroup, long ones take several.  Offsets outside the stated range are skipped, never followed.
 #include <hip/hip_runtime.h>
 
