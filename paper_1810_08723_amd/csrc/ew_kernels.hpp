@@ -33,7 +33,8 @@ struct RowsArgs {
   uint32_t flags;    // kRows* bits; operands in the other byte order in bits 8..10
   uint32_t block;    // lanes per workgroup
   uint32_t shift;    // flat form: elements by which the first vector starts before the output
-  uint32_t inner;    // elements per row
+  uint32_t inner;    // flat form: elements per row (row form: 0, no vector crosses into the next row)
+  uint32_t last;     // row form: elements of a row's last vector
   FastDiv rdiv;      // flat form: elements per row; row form: vectors per row
   int32_t nouter;
   int64_t so[kMaxDims - 1], sa[kMaxDims - 1], sb[kMaxDims - 1];  // outer strides, fastest outer first
@@ -551,22 +552,22 @@ template <class P> OCN_HDF void rows_outer(const P &p, uint32_t row, int64_t (&o
   }
 }
 
-// where vector number g lies
+// where vector number g lies (es_*: element sizes)
 struct RowsPlace {
   int64_t first;    // flat form: its first element (may lie before the output)
-  int64_t off[3];   // byte offsets of its row in out / a / b
-  uint32_t row, col;
+  int64_t off[3];   // byte offsets of its row in out / a / b (row form: of its first element)
+  uint32_t row, col; // (row form: col counts from the vector's first element; a row may be longer than 2^32)
   int lo, hi;       // the elements of the vector that exist: lo .. hi - 1
   bool inrow;       // all of them lie in one row
 };
-template <int V, class P> OCN_HDF RowsPlace rows_place(const P &p, int64_t g) {
+template <int V, class P> OCN_HDF RowsPlace rows_place(const P &p, int64_t g, int es_o, int es_a, int es_b) {
   RowsPlace r;
   r.first = 0;
   r.row = r.col = 0;
   r.lo = 0;
   r.inrow = true;
   r.off[0] = r.off[1] = r.off[2] = 0;
-  const uint32_t flags = p.flags, inner = p.inner;
+  const uint32_t flags = p.flags;
   const FastDiv rdiv{p.rdiv.d, p.rdiv.m, p.rdiv.s};
   if (flags & kRowsFlat) {
     const int64_t numel = p.numel;
@@ -577,14 +578,18 @@ template <int V, class P> OCN_HDF RowsPlace rows_place(const P &p, int64_t g) {
       const uint32_t e = (uint32_t)(r.first + r.lo);
       r.row = fastdiv(e, rdiv);
       r.col = e - r.row * rdiv.d;
-      r.inrow = r.col + (uint32_t)(r.hi - r.lo) <= inner;
+      r.inrow = r.col + (uint32_t)(r.hi - r.lo) <= p.inner;
       rows_outer(p, r.row, r.off);
     }
   } else {
     r.row = fastdiv((uint32_t)g, rdiv);
-    r.col = ((uint32_t)g - r.row * rdiv.d) * (uint32_t)V;
-    r.hi = inner - r.col < (uint32_t)V ? (int)(inner - r.col) : V;
+    const uint32_t c = (uint32_t)g - r.row * rdiv.d;
+    r.hi = c + 1 == rdiv.d ? (int)p.last : V;
     rows_outer(p, r.row, r.off);
+    const int64_t e0 = (int64_t)c * V;
+    r.off[0] += e0 * es_o;
+    if (!(flags & kRowsABcast)) r.off[1] += e0 * es_a;
+    if (!(flags & kRowsBBcast)) r.off[2] += e0 * es_b;
   }
   return r;
 }
@@ -614,7 +619,7 @@ template <class G> __global__ __launch_bounds__(kBlock) void ew_rows_kernel(cons
   using KArgs = const __attribute__((address_space(4))) RowsArgs;
   KArgs &p = *(KArgs *)__builtin_amdgcn_kernarg_segment_ptr();
   OCN_ARGS_NOW("s"(p.out), "s"(p.a), "s"(p.b), "s"(p.numel), "s"(p.nvec), "s"(p.flags), "s"(p.block), "s"(p.shift),
-               "s"(p.inner), "s"(p.rdiv.d), "s"(p.rdiv.m), "s"(p.rdiv.s), "s"(p.nouter));
+               "s"(p.inner), "s"(p.last), "s"(p.rdiv.d), "s"(p.rdiv.m), "s"(p.rdiv.s), "s"(p.nouter));
   const uint32_t flags = p.flags, block = p.block;
   const bool flat = (flags & kRowsFlat) != 0;
   const bool alin = (flags & kRowsALinear) != 0, blin = (flags & kRowsBLinear) != 0;
@@ -632,7 +637,7 @@ template <class G> __global__ __launch_bounds__(kBlock) void ew_rows_kernel(cons
     lo[u] = hi[u] = 0;
     inrow[u] = true;
     if (g < p.nvec) {
-      RowsPlace r = rows_place<V>(p, g);
+      RowsPlace r = rows_place<V>(p, g, ESO, ESA, ESB);
       lo[u] = r.lo;
       hi[u] = r.hi;
       inrow[u] = r.inrow;

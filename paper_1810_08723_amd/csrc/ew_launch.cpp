@@ -28,7 +28,6 @@ RowsArgs make_rows_args(const EwPlan &p, int64_t *grid) {
     r.sb[k] = p.b.stride[d];
     r.odiv[k] = make_fastdiv((uint32_t)p.size[d]);
   }
-  r.inner = (uint32_t)std::min<int64_t>(n0, INT32_MAX);   // (longer than that only without outer dims: unused)
   // is the operand one contiguous run in the order of the dims?
   auto linear = [&](const Operand &x, int es) {
     int64_t expect = es;
@@ -47,6 +46,7 @@ RowsArgs make_rows_args(const EwPlan &p, int64_t *grid) {
     if ((intptr_t)p.out.ptr % es_o == 0 && p.numel / p.vec + 2 < max_launch_blocks() * kBlock * p.unroll)
       r.shift = (uint32_t)(((intptr_t)p.out.ptr / es_o) % p.vec);
     r.nvec = (p.numel + r.shift + p.vec - 1) / p.vec;
+    r.inner = (uint32_t)n0;   // (below 2^31 with outer dims, unused without)
     r.rdiv = make_fastdiv(r.inner);
     // (the streaming hint only where the vectors of the input are aligned like the output's)
     auto aligned = [&](const Operand &x, int es) { return ((intptr_t)x.ptr - (int64_t)r.shift * es) % ((int64_t)p.vec * es) == 0; };
@@ -54,6 +54,7 @@ RowsArgs make_rows_args(const EwPlan &p, int64_t *grid) {
     if (p.nin == 2 && linear(p.b, es_b)) r.flags |= kRowsBLinear | (p.nt_b && aligned(p.b, es_b) ? kRowsNtB : 0u);
   } else {
     const int64_t vpr = (n0 + p.vec - 1) / p.vec;
+    r.last = (uint32_t)(n0 - (vpr - 1) * p.vec);
     r.rdiv = make_fastdiv((uint32_t)(inner > 0 ? vpr : 1));
     r.nvec = vpr * (p.numel / n0);
   }

@@ -7,7 +7,10 @@
 //   * every output element is written exactly once and nothing else is,
 //   * every element read belongs to that output position,
 //   * a vector moved in one piece is contiguous in that operand and inside its range.
+// Rows of more than 2^31 elements (under outer dims) are replayed around columns 2^31 and 2^32 and
+// at their ends only.
 // Exit code 0 when every case passes.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -84,7 +87,7 @@ template <int V> static int replay(const EwPlan &p, const RowsArgs &q, int64_t g
 #define FAIL(msg) do { std::printf("case %d: %s (vector %ld element %d)\n", case_no, msg, (long)g, i); return 1; } while (0)
   for (int64_t g = 0; g < grid * q.block * p.unroll; ++g) {
     if (g >= q.nvec) continue;   // the kernel's own condition
-    RowsPlace r = rows_place<V>(q, g);
+    RowsPlace r = rows_place<V>(q, g, es[0], es[1], es[2]);
     const RowsPlace start = r;
     const bool whole = r.hi - r.lo == V;
     if (!whole) ++g_partial;
@@ -135,7 +138,89 @@ static int check_case(int nin, int op, int da, int db, int dout, int ndim, const
   }
 }
 
+// A row's vectors around columns 0, 2^31 and 2^32 and at its end: they hold the row's elements in
+// order, each once, none behind the row.  (No memory stands behind the addresses.)
+template <int V> static int replay_long(const EwPlan &p, const RowsArgs &q, int case_no) {
+  const int es[3] = {dt_size(p.out.dtype), dt_size(p.a.dtype), dt_size(p.b.dtype)};
+  const int64_t n0 = p.size[p.ndim - 1], vpr = (n0 + V - 1) / V, nrows = p.numel / n0;
+  const bool bc[3] = {false, (q.flags & kRowsABcast) != 0, (q.flags & kRowsBBcast) != 0};
+  if (q.flags & kRowsFlat || q.nvec != vpr * nrows) { std::printf("long %d: not the row form\n", case_no); return 1; }
+  for (int64_t row = 0; row < nrows; ++row) {
+    int64_t want[3] = {0, 0, 0}, rem = row;
+    for (int d = p.ndim - 2; d >= 0; --d) {
+      want[0] += rem % p.size[d] * p.out.stride[d];
+      want[1] += rem % p.size[d] * p.a.stride[d];
+      want[2] += rem % p.size[d] * p.b.stride[d];
+      rem /= p.size[d];
+    }
+    for (const int64_t around : {(int64_t)0, (int64_t)1 << 31, (int64_t)1 << 32, n0})
+      for (int64_t c = std::max<int64_t>(0, around / V - 3); c < std::min(vpr, around / V + 3); ++c) {
+        RowsPlace r = rows_place<V>(q, row * vpr + c, es[0], es[1], es[2]);
+        const int n = (int)std::min<int64_t>(V, n0 - c * V);
+        if (r.lo != 0 || r.hi != n || !r.inrow) {
+          std::printf("long %d: row %ld vector %ld holds %d..%d, not 0..%d\n", case_no, (long)row, (long)c, r.lo, r.hi, n);
+          return 1;
+        }
+        const int64_t first = rows_offset(r, 0, 0, es[0], false, false);
+        for (int i = 0; i < n; ++i) {
+          for (int x = 0; x <= p.nin; ++x) {
+            const int64_t off = x == 0 ? first + (int64_t)i * es[0] : rows_offset(r, x, i, es[x], false, bc[x]);
+            if (off != want[x] + (bc[x] ? 0 : (c * V + i) * es[x])) {
+              std::printf("long %d: row %ld column %ld operand %d\n", case_no, (long)row, (long)(c * V + i), x);
+              return 1;
+            }
+          }
+          rows_next(q, r);
+        }
+      }
+  }
+  return 0;
+}
+
+static int check_long_rows() {
+  const int64_t G = (int64_t)1 << 31;
+  // outer sizes, row length, elements between rows, b broadcast along the rows (1) or over them (2)
+  const struct { int nin, op, a, b, o; int64_t outer[2], n0, gap; int bcast; } cases[] = {
+      {2, B_ADD, DT_U8, DT_U8, DT_U8, {1, 2}, G + 5, 0, 1},    {2, B_ADD, DT_U8, DT_U8, DT_U8, {1, 2}, G + 13, 0, 2},
+      {1, U_IDENT, DT_U8, DT_U8, DT_U8, {2, 2}, G + 16, 16, 0}, {1, U_IDENT, DT_U8, DT_U8, DT_U8, {2, 3}, 2 * G + 21, 5, 0},
+      {2, B_ADD, DT_F32, DT_F32, DT_F32, {1, 3}, G + 3, 4, 1},  {2, B_GT, DT_F16, DT_F16, DT_BOOL, {1, 2}, 2 * G + 9, 1, 0},
+      {1, U_IDENT, DT_U8, DT_U8, DT_U8, {1, 2}, G - 1, 3, 0},  {2, B_ADD, DT_U8, DT_U8, DT_U8, {1, 5}, G - 15, 1, 1}};
+  int case_no = 0;
+  for (const auto &c : cases) {
+    ocn_tensor t[3];   // out, a, b
+    const int dts[3] = {c.o, c.a, c.b};
+    for (int x = 0; x < 3; ++x) {
+      std::memset(&t[x], 0, sizeof t[x]);
+      const int64_t es = dt_size(dts[x]), row = (c.n0 + c.gap) * es;
+      t[x].base = (char *)((uint64_t)(x + 1) << 44);
+      t[x].dtype = dts[x];
+      t[x].ndim = 3;
+      const int64_t size[3] = {c.outer[0], c.outer[1], c.n0}, stride[3] = {2 * row * c.outer[1], row, es};
+      for (int d = 0; d < 3; ++d) { t[x].size[d] = size[d]; t[x].stride[d] = stride[d]; }
+      if (x == 2 && c.bcast == 1) { t[x].size[2] = 1; t[x].stride[2] = 0; }
+      if (x == 2 && c.bcast == 2) t[x].size[1] = 1;
+    }
+    EwPlan p;
+    const int rc = plan_elementwise(c.nin, c.op, &t[1], c.nin == 2 ? &t[2] : nullptr, &t[0], 0, &p);
+    if (rc != OCN_OK || p.kernel != OCN_KERNEL_EW_ROWS) { std::printf("long %d: plan %d, kernel %d\n", case_no, rc, p.kernel); return 1; }
+    int64_t grid;
+    const RowsArgs q = make_rows_args(p, &grid);
+    int bad = 1;
+    switch (p.vec) {
+      case 1: bad = replay_long<1>(p, q, case_no); break;
+      case 2: bad = replay_long<2>(p, q, case_no); break;
+      case 4: bad = replay_long<4>(p, q, case_no); break;
+      case 8: bad = replay_long<8>(p, q, case_no); break;
+      case 16: bad = replay_long<16>(p, q, case_no); break;
+    }
+    if (bad) return 1;
+    ++case_no;
+  }
+  return 0;
+}
+
 int main(int argc, char **argv) {
+  if (check_long_rows()) return 1;
   const int ncases = argc > 1 ? std::atoi(argv[1]) : 1000;
   const struct { int nin, op, a, b, o; } kinds[] = {
       {2, B_ADD, DT_F32, DT_F32, DT_F32}, {2, B_MUL, DT_I32, DT_F32, DT_F32}, {2, B_MUL, DT_F16, DT_F32, DT_F32},

@@ -65,3 +65,25 @@ def test_three_outer_dims_and_long_rows():
     b = random_view(rng, "float", (1, 7, 1, 1001))
     H.check_binary("mul", a, b, View.empty("float", (5, 7, 3, 1001)))
     H.check_binary("mul", b, a, View.empty("float", (5, 8, 3, 1003)).slice(1, 0, 7, 1).slice(3, 2, 1003, 1))
+
+
+def test_rows_longer_than_two_to_the_31():
+    # uint8 rows of 2^31 + 5 elements plus one element per row: every element is written and nothing
+    # behind the output is.  Reference: the same sums on the device (wrapping, as the library's).
+    import torch
+    import paper_1810_08723_amd as ocn
+    n = (1 << 31) + 5
+    a = torch.randint(0, 256, (2, n), dtype=torch.uint8, device="cuda:0")
+    b = torch.tensor([[7], [201]], dtype=torch.uint8, device="cuda:0")
+    out = torch.full((2 * n + 64,), 0x5A, dtype=torch.uint8, device="cuda:0")
+    print("rows of", n, flush=True)
+    ocn.binary("add", ocn.Tensor(a.data_ptr(), "uint8", (2, n), (n, 1), 0, 0, a),
+               ocn.Tensor(b.data_ptr(), "uint8", (2, 1), (1, 1), 0, 0, b),
+               ocn.Tensor(out.data_ptr(), "uint8", (2, n), (n, 1), 0, 0, out))
+    torch.cuda.synchronize()
+    a.add_(b)
+    for row in range(2):
+        for lo in range(0, n, 1 << 28):
+            hi = min(n, lo + (1 << 28))
+            assert torch.equal(out[row * n + lo:row * n + hi], a[row, lo:hi]), (row, lo)
+    assert bool((out[2 * n:] == 0x5A).all())
