@@ -732,8 +732,10 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
         const int nvec_o = 1 << (p.tile_bits - p.vecw_o);
         const int nvec = std::max(nvec_o, std::max(p.stage_a ? 1 << (p.tile_bits - p.vecw_a) : 0, p.stage_b ? 1 << (p.tile_bits - p.vecw_b) : 0));
         const bool few = p.total_tiles <= kNumCUs;
+        // The bound on workgroups is one on lanes (256 in each): larger workgroups keep to it.
+        const int64_t most = max_launch_blocks() * kBlock;
         p.block = kBlock;
-        while (p.block < (few ? 1024 : 512) && p.block < (few ? nvec : nvec_o)) p.block *= 2;
+        while (p.block < (few ? 1024 : 512) && p.block < (few ? nvec : nvec_o) && p.total_tiles * p.block * 2 <= most) p.block *= 2;
         break;
       }
     }

@@ -163,7 +163,46 @@ static int replay(const EwPlan &p, const HostTensor *h, int case_no) {
   return 0;
 }
 
+// A launch stays below 2^32 lanes, and below the bound set, whatever the lanes per workgroup.
+static int check_launch_sizes() {
+  const struct { int dt; int64_t n, m; } shapes[] = {
+      {DT_F16, 10000001, 17}, {DT_F32, 140000003, 9}, {DT_F32, 8388607, 17}, {DT_U8, 16777215, 17}, {DT_F32, 1000, 17}};
+  int taken = 0;
+  for (const int64_t bound : {(int64_t)0, (int64_t)1500})
+    for (const auto &s : shapes) {
+      const int64_t es = dt_size(s.dt);
+      ocn_tensor a, o;
+      std::memset(&a, 0, sizeof a);
+      a.dtype = s.dt;
+      a.ndim = 3;
+      a.size[0] = s.n;
+      a.size[1] = a.size[2] = s.m;
+      a.stride[0] = s.m * s.m * es;
+      a.stride[1] = s.m * es;
+      a.stride[2] = es;
+      o = a;
+      a.base = (char *)((uint64_t)1 << 44);
+      o.base = (char *)((uint64_t)2 << 44);
+      std::swap(a.stride[1], a.stride[2]);
+      set_max_launch_blocks(bound);
+      EwPlan p;
+      const int rc = plan_elementwise(1, U_NEG, &a, nullptr, &o, 0, &p);
+      const int64_t most = max_launch_blocks() * kBlock;
+      set_max_launch_blocks(0);
+      if (rc != OCN_OK) { std::printf("launch sizes: plan rc=%d\n", rc); return 1; }
+      if (p.kernel != kKernelTiledAny) continue;
+      ++taken;
+      if (p.grid * p.block > most || p.grid * p.block >= (int64_t)1 << 32) {
+        std::printf("launch sizes: %ld x %ld x %ld goes out with %ld workgroups of %d lanes\n", (long)s.n, (long)s.m, (long)s.m,
+                    (long)p.grid, p.block);
+        return 1;
+      }
+    }
+  return taken >= 4 ? 0 : 1;
+}
+
 int main(int argc, char **argv) {
+  if (check_launch_sizes()) return 1;
   const int ncases = argc > 1 ? std::atoi(argv[1]) : 1000;
   const struct { int nin, op, a, b, o; } kinds[] = {
       {2, B_ADD, DT_F32, DT_F32, DT_F32}, {2, B_MUL, DT_C32, DT_C32, DT_C32}, {2, B_ABSGT, DT_C32, DT_C32, DT_BOOL},
