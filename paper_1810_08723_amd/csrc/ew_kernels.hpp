@@ -1253,14 +1253,14 @@ template <class P> OCN_HDF uint64_t any_tile(const P &p, uint32_t t, int64_t (&b
 }
 
 // Where a lane loads the whole vector at `src` from: at src, or - a vector at the end of a clipped
-// tile, of which only the first elements exist - as far before it as the operand's last byte
-// demands; `back` is the distance in elements.  The elements in between belong to the operand's
-// storage and are dropped.  (Loading just the elements that exist takes a branch with loads on
-// both sides, and the compiler waits for one side before it issues the other.)
+// tile, of which only the first elements exist - so many whole elements before it that it ends
+// with the operand's last byte or before (views of complex elements may have rows an odd number
+// of scalars apart); `back` is the distance in elements.  The elements in between belong to the
+// operand's storage and are dropped.  (Loading just the elements that exist takes a branch with
+// loads on both sides, and the compiler waits for one side before it issues the other.)
 OCN_HDF const char *any_address(const char *src, const char *last, int es_log2, int &back) {
-  const bool over = src > last;
-  back = over ? (int)((src - last) >> es_log2) : 0;
-  return over ? last : src;
+  back = src > last ? (int)((src - last + (((int64_t)1 << es_log2) - 1)) >> es_log2) : 0;
+  return src - ((int64_t)back << es_log2);
 }
 // element i of the vector is element i + back of what was loaded
 template <class S, int V> OCN_DEV void any_shift(Pack<S, V> &v, int back) {

@@ -712,12 +712,16 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
       }
       const int64_t lim = ((int64_t)1 << 31) - 64;
       // An input that is read in vectors has to be as long as one: a vector that runs past its end
-      // is loaded from further back.
+      // is loaded from further back, by whole elements.
       auto long_enough = [&](const Operand &x, int es, bool staged, const int8_t *ord, int vecw) {
         if (x.stride[staged ? ord[0] : p.ord_o[0]] != es) return true;
         int64_t bytes = es;
-        for (int d = 0; d < n; ++d) bytes += (p.size[d] - 1) * iabs64(x.stride[d]);
-        return bytes >= (int64_t)es << vecw;
+        bool whole = true;
+        for (int d = 0; d < n; ++d) {
+          bytes += (p.size[d] - 1) * iabs64(x.stride[d]);
+          whole = whole && x.stride[d] % es == 0;
+        }
+        return bytes >= ((int64_t)es << vecw) + (whole ? 0 : es - scalar_size(x.dtype));
       };
       ok = ok && long_enough(p.a, es_a, p.stage_a, p.ord_a, p.stage_a ? p.vecw_a : p.vecw_o) &&
            (nin == 1 || long_enough(p.b, es_b, p.stage_b, p.ord_b, p.stage_b ? p.vecw_b : p.vecw_o));

@@ -25,7 +25,10 @@ static int rnd_in(int lo, int hi) { return lo + (int)(rnd() % (uint32_t)(hi - lo
 
 struct HostTensor { ocn_tensor t; int64_t lo, hi; };
 
-// dims permuted over a dense buffer, perhaps stepped along one axis, inputs perhaps broadcast
+static int g_odd;
+
+// dims permuted over a dense buffer, perhaps stepped along one axis, inputs perhaps broadcast, complex
+// inputs perhaps with rows that lie an odd number of scalars apart (apart or as overlapping windows)
 static HostTensor make_view(int dt, int ndim, const int64_t *sizes, char *base, bool input) {
   HostTensor h;
   std::memset(&h, 0, sizeof h);
@@ -48,6 +51,16 @@ static HostTensor make_view(int dt, int ndim, const int64_t *sizes, char *base, 
     acc *= sizes[ax] * step;
   }
   h.hi = h.lo + acc;
+  const int sc = dt_size(dt_real_of(dt));
+  if (input && sc < es && ndim > 1 && rnd() % 3 == 0) {
+    const int slow = perm[rnd_in(0, ndim - 2)];
+    h.t.stride[slow] = rnd() % 2 ? (int64_t)sc * rnd_in(1, 9) : h.t.stride[slow] + sc;
+    h.t.offset += sc * (int)(rnd() % 2);
+    h.lo = h.t.offset;
+    h.hi = h.lo + es;
+    for (int d = 0; d < ndim; ++d) h.hi += (h.t.size[d] - 1) * h.t.stride[d];
+    ++g_odd;
+  }
   if (input)
     for (int d = 0; d < ndim; ++d)
       if (rnd() % 10 == 0) { h.t.size[d] = 1; h.t.stride[d] = 0; }
@@ -208,7 +221,8 @@ int main(int argc, char **argv) {
       {2, B_ADD, DT_F32, DT_F32, DT_F32}, {2, B_MUL, DT_C32, DT_C32, DT_C32}, {2, B_ABSGT, DT_C32, DT_C32, DT_BOOL},
       {2, B_MUL, DT_I32, DT_F64, DT_F64}, {2, B_ADD, DT_U8, DT_U8, DT_U8}, {2, B_MUL, DT_C64, DT_C64, DT_C64},
       {1, U_IDENT, DT_F64, DT_F64, DT_I16}, {1, U_IDENT, DT_U8, DT_U8, DT_F32}, {1, U_NEG, DT_F16, DT_F16, DT_F16},
-      {1, U_IDENT, DT_F32, DT_F32, DT_U8}, {2, B_LT, DT_I64, DT_I64, DT_BOOL}};
+      {1, U_IDENT, DT_F32, DT_F32, DT_U8}, {2, B_LT, DT_I64, DT_I64, DT_BOOL}, {2, B_ADD, DT_C16, DT_C16, DT_C16},
+      {2, B_MUL, DT_F32, DT_C32, DT_C32}};
   for (int c = 0; c < ncases; ++c) {
     const int ndim = rnd_in(2, 5);
     int64_t sizes[8], total = 1;
@@ -233,7 +247,7 @@ int main(int argc, char **argv) {
       return 1;
     }
   }
-  std::printf("ok: %d cases, %d in this form (tiled dims 1: %d, 2: %d, 3: %d, 4: %d); clipped tiles %d, staged a %d, b %d, element orders %d, strided reads %d, moved back %d\n",
-              ncases, g_any, g_dims[1], g_dims[2], g_dims[3], g_dims[4], g_clipped, g_staged[0], g_staged[1], g_element_orders, g_strided, g_back);
-  return g_any > 300 && g_clipped > 100 && g_staged[0] > 100 && g_staged[1] > 100 && g_element_orders > 20 && g_strided > 20 && g_back > 20 ? 0 : 1;
+  std::printf("ok: %d cases, %d in this form (tiled dims 1: %d, 2: %d, 3: %d, 4: %d); clipped tiles %d, staged a %d, b %d, element orders %d, strided reads %d, moved back %d, complex inputs with odd strides %d\n",
+              ncases, g_any, g_dims[1], g_dims[2], g_dims[3], g_dims[4], g_clipped, g_staged[0], g_staged[1], g_element_orders, g_strided, g_back, g_odd);
+  return g_any > 300 && g_clipped > 100 && g_staged[0] > 100 && g_staged[1] > 100 && g_element_orders > 20 && g_strided > 20 && g_back > 20 && g_odd > 200 ? 0 : 1;
 }

@@ -78,3 +78,18 @@ def test_vectors_at_the_end_of_an_operand():
         for dt in ("float", "half", "uint8", "cfloat"):
             a = random_view(rng, dt, (n0, n1)).permute(1, 0)
             H.check_unary("ident", a, View.empty(dt, (n1, n0)))
+
+
+@pytest.mark.parametrize("dt,sc", [("cfloat", 4), ("chalf", 2), ("cdouble", 8)])
+def test_complex_rows_an_odd_number_of_scalars_apart(dt, sc):
+    # windows one scalar apart, rows with a gap of one scalar, a base off by one: strides that are
+    # multiples of the scalar but not of the element
+    rng = rng_for(22980 + sc)
+    for rows, cols in ((2, 3), (6, 40), (5, 33), (37, 70)):
+        for apart, shift in ((1, 0), (1, 1), (3, 0), (2 * cols + 1, 1)):
+            store = random_view(rng, dt, (rows * cols * 2 + rows * 2 + 8,), specials=False)
+            a = View(store.storage, dt, (rows, cols), (apart * sc, 2 * sc), shift * sc)
+            print("odd complex strides", dt, rows, cols, apart, shift, flush=True)
+            H.check_binary("add", a, _stored(rng, dt, (rows, cols), (1, 0), 0), View.empty(dt, (rows, cols)))
+            H.check_unary("ident", a.permute(1, 0), View.empty(dt, (cols, rows)))
+            H.check_binary("absgt", _stored(rng, dt, (rows, cols), (1, 0), 1), a, View.empty("bool", (rows, cols)))
