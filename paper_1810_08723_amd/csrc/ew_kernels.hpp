@@ -198,6 +198,9 @@ OCN_HDF uint32_t fastdiv(uint32_t n, const FastDiv &f) {
   return (uint32_t)((((uint64_t)n * f.m) >> 32) + n) >> f.s;
 }
 
+// four stored bools: any byte but zero is true, written as 1
+OCN_HDF uint32_t bool_bytes(uint32_t w) { return ((((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) >> 7) & 0x01010101u; }
+
 // ---------------------------------------------------------------------------------------
 // raw vector access
 // ---------------------------------------------------------------------------------------

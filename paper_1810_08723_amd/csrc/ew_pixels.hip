@@ -37,19 +37,34 @@ struct PixelArgs {
   int64_t so[kMaxDims], sa[kMaxDims];
 };
 
-// a copy of elements of ES bytes, whatever their type
+// a copy of elements of ES bytes, whatever their type (but bool)
 template <int ES> struct CopyOf {
   struct alignas(ES) Elem { unsigned char b[ES]; };
   using In = Elem;
   using Out = Elem;
   static constexpr int AL = ES;
   OCN_DEV static Out cv(const In &x) { return x; }
+  template <int N> OCN_DEV static void loaded(unsigned char (&)[N]) {}
+};
+// a copy of bools: whatever byte stands for true, 1 is written (four at a time, as they are loaded)
+struct CopyOfBool : CopyOf<1> {
+  template <int N> OCN_DEV static void loaded(unsigned char (&b)[N]) {
+    static_assert(N % 4 == 0, "whole words");
+#pragma unroll
+    for (int i = 0; i < N; i += 4) {
+      uint32_t w;
+      __builtin_memcpy(&w, b + i, 4);
+      w = bool_bytes(w);
+      __builtin_memcpy(b + i, &w, 4);
+    }
+  }
 };
 template <int SA, int SO> struct CastOf {
   using In = storage_t<SA>;
   using Out = storage_t<SO>;
   static constexpr int AL = sizeof(In) < 8 ? (int)sizeof(In) : 8;
   OCN_DEV static Out cv(const In &x) { return to_storage<SO>(convert<SO>(from_storage<SA>(x))); }
+  template <int N> OCN_DEV static void loaded(unsigned char (&)[N]) {}
 };
 
 // N consecutive bytes at an address that is a multiple of AL
@@ -121,6 +136,7 @@ template <class F, int C> __global__ __launch_bounds__(kBlock) void to_planes_ke
   const uint32_t e = pixel_place<V>(p, g, off_o, off_a);
   union { unsigned char b[V * C * sizeof(In)]; In v[V * C]; } in;
   load_bytes<V * C * (int)sizeof(In), F::AL>(p.a + off_a + (int64_t)e * (C * (int)sizeof(In)), in.b);
+  F::loaded(in.b);
   char *out = p.out + off_o + (int64_t)e * (int)sizeof(Out);
 #pragma unroll
   for (int c = 0; c < C; ++c) {
@@ -149,8 +165,10 @@ template <class F, int C> __global__ __launch_bounds__(kBlock) void to_pixels_ke
     off_o += (int64_t)e * (16 * C / V);
     union { unsigned char b[V * sizeof(In)]; In v[V]; } in[C];
 #pragma unroll
-    for (int c = 0; c < C; ++c)
+    for (int c = 0; c < C; ++c) {
       load_bytes<V * (int)sizeof(In), F::AL>(p.a + off_a + (int64_t)c * p.plane + (int64_t)e * (int)sizeof(In), in[c].b);
+      F::loaded(in[c].b);
+    }
     Out o[V * C];
 #pragma unroll
     for (int i = 0; i < V * C; ++i) o[i] = F::cv(in[i % C].v[i / C]);
@@ -220,6 +238,7 @@ hipError_t launch_pixels(const EwPlan &p, hipStream_t stream) {
   a.nvec = (uint32_t)(rows * mvec);
   a.nt_store = p.nt_store;
   const int c = (int)p.size[dc];
+  if (p.a.dtype == DT_BOOL && p.out.dtype == DT_BOOL) return launch_form<CopyOfBool>(a, c, to_planes, stream);
   if (p.a.dtype == p.out.dtype) {
     switch (dt_size(p.out.dtype)) {
       case 1: return launch_form<CopyOf<1>>(a, c, to_planes, stream);

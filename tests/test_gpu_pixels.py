@@ -62,3 +62,17 @@ def test_many_workgroups_of_pixels():
     rng = rng_for(26700)
     _both_ways(rng, "uint8", "float", 3, 5, 211, 307, 0)
     _both_ways(rng, "float", "float", 2, 7, 128, 130, 1)
+
+
+def test_stored_bools_are_zero_or_one_afterwards():
+    # any byte but zero is true, and a copy writes it as 1, whichever kernel a size and alignment gets
+    rng = rng_for(26800)
+    for shape in ((2, 9, 11, 3), (1, 15, 15, 2), (3, 19, 23, 4), (2, 7, 6, 5)):
+        n, h, w, c = shape
+        for k in (0, 1):
+            print("bool bytes", shape, k, flush=True)
+            for flipped in (False, True):
+                a = _off_by(rng, "uint8", (n, c, h, w) if flipped else shape, k)
+                a = View(a.storage, "bool", a.sizes, a.strides, a.offset)
+                a = a.permute(0, 2, 3, 1) if flipped else a.permute(0, 3, 1, 2)
+                H.check_unary("ident", a, _off_by(None, "bool", a.sizes, k))
