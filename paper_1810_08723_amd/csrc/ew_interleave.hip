@@ -34,7 +34,8 @@ struct InterleaveArgs {
 
 using Q = uint32_t __attribute__((ext_vector_type(4)));
 
-template <int ES, int C> __global__ __launch_bounds__(kBlock) void ew_interleave_kernel(const InterleaveArgs p) {
+// BOOL: whatever byte stands for true, 1 is written
+template <int ES, int C, bool BOOL> __global__ __launch_bounds__(kBlock) void ew_interleave_kernel(const InterleaveArgs p) {
   constexpr int V = 16 / ES;
   struct alignas(ES) Elem { unsigned char b[ES]; };
   __shared__ Q parked[kBlock * C];
@@ -69,6 +70,12 @@ template <int ES, int C> __global__ __launch_bounds__(kBlock) void ew_interleave
         in[c].q = *src;
       }
     }
+    if constexpr (BOOL) {
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) in[c].q[i] = bool_bytes(in[c].q[i]);
+    }
     union { Q q[C]; Elem e[V * C]; } o;
 #pragma unroll
     for (int j = 0; j < V * C; ++j) o.e[j] = in[j % C].e[j / C];
@@ -98,10 +105,10 @@ template <int ES, int C> __global__ __launch_bounds__(kBlock) void ew_interleave
   }
 }
 
-template <int ES> hipError_t launch_es(int c, unsigned grid, hipStream_t s, const InterleaveArgs &a) {
+template <int ES, bool BOOL = false> hipError_t launch_es(int c, unsigned grid, hipStream_t s, const InterleaveArgs &a) {
   switch (c) {
 #define OCN_CASE(CC) \
-  case CC: hipLaunchKernelGGL((ew_interleave_kernel<ES, CC>), dim3(grid), dim3(kBlock), 0, s, a); break;
+  case CC: hipLaunchKernelGGL((ew_interleave_kernel<ES, CC, BOOL>), dim3(grid), dim3(kBlock), 0, s, a); break;
     OCN_CASE(2) OCN_CASE(3) OCN_CASE(4) OCN_CASE(5) OCN_CASE(6) OCN_CASE(7) OCN_CASE(8)
 #undef OCN_CASE
     default: return hipErrorInvalidValue;
@@ -135,7 +142,7 @@ hipError_t launch_interleave(const EwPlan &p, hipStream_t stream) {
   a.nt_load = p.nt_a;
   const unsigned grid = (unsigned)p.grid;
   switch (es) {
-    case 1: return launch_es<1>((int)c, grid, stream, a);
+    case 1: return p.out.dtype == DT_BOOL ? launch_es<1, true>((int)c, grid, stream, a) : launch_es<1>((int)c, grid, stream, a);
     case 2: return launch_es<2>((int)c, grid, stream, a);
     case 4: return launch_es<4>((int)c, grid, stream, a);
     case 8: return launch_es<8>((int)c, grid, stream, a);

@@ -57,3 +57,13 @@ def test_many_workgroups():
     out = View.empty("float", (5, 128, 132, 3))
     assert _plan(a, out)["kernel"] == "ew_interleave" and _plan(a, out)["grid"] > 64
     H.check_unary("ident", a, out)
+
+
+@pytest.mark.parametrize("c", (2, 3, 4, 5, 8))
+def test_bools_stored_as_other_bytes(c):
+    rng = rng_for(20300 + c)
+    planes = random_view(rng, "uint8", (3, c, 20, 24))
+    a = View(planes.storage, "bool", planes.sizes, planes.strides, planes.offset).permute(0, 2, 3, 1)
+    out = View.empty("bool", (3, 20, 24, c))
+    assert _plan(a, out)["kernel"] == "ew_interleave"
+    H.check_unary("ident", a, out)
