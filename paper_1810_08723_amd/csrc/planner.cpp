@@ -834,8 +834,11 @@ constexpr int64_t kLeanSplitWaves = 256 * 8;
 //   split  Only where that leaves half of the chip idle and the wavefronts with long runs of rows, and
 //          rounded down, so that the workgroups go out in one round ([16384, 4099]: 55 us with 15
 //          splits, 255 workgroups of sixteen wavefronts, 69 with 16).
+// bounded: the partial results never outgrow what a call without a workspace has (columns whose
+// vectors are not aligned: 8-bit ones have sixteen times the accumulators of one column per lane, and
+// int8 [5000, 32767] would take 2 MiB for eight splits).
 struct ColsShape { int cpw, nw; int64_t split; };
-ColsShape choose_cols_shape(int64_t col_lanes, int64_t others, int64_t rows, int64_t nout, int acc_es) {
+ColsShape choose_cols_shape(int64_t col_lanes, int64_t others, int64_t rows, int64_t nout, int acc_es, bool bounded) {
   ColsShape r;
   r.cpw = kWave;
   while (r.cpw > 1 && r.cpw / 2 >= col_lanes) r.cpw /= 2;
@@ -852,6 +855,11 @@ ColsShape choose_cols_shape(int64_t col_lanes, int64_t others, int64_t rows, int
     // a workspace has
     const int64_t fits = (int64_t)OCN_REDUCE_SCRATCH_BYTES / (nout * acc_es);
     r.split = std::max<int64_t>(1, std::min(r.split, std::max(fits, std::min(want, rows / (r.nw * rpw * 16)))));
+    if (bounded && r.split > fits) {
+      r.split = std::max<int64_t>(1, fits);
+      // narrower columns instead, until the workgroups go round once
+      while (r.cpw > 16 && (col_lanes + r.cpw / 2 - 1) / (r.cpw / 2) * others * r.split <= kNumCUs + kNumCUs / 16) r.cpw /= 2;
+    }
   }
   return r;
 }
@@ -940,7 +948,7 @@ void choose_reduce_launch(RedPlan &p) {
     aligned = all_aligned((int64_t)vfull * es, p.nkept - 1, -1);
     p.vec = aligned || nc >= vfull ? vfull : 1;
     const int64_t col_lanes = (nc + p.vec - 1) / p.vec, others = p.nout / nc;
-    const ColsShape shape = choose_cols_shape(col_lanes, others, p.nredtot, p.nout, acc_es);
+    const ColsShape shape = choose_cols_shape(col_lanes, others, p.nredtot, p.nout, acc_es, !aligned);
     p.cpw = shape.cpw;
     p.split = shape.split;
     const int nw = shape.nw;
@@ -1183,7 +1191,7 @@ void choose_fused_launch(RedPlan &p) {
     const bool aligned = all_aligned(p.nkept - 1, -1, p.a_fast_bcast, p.b_fast_bcast);
     p.vec = aligned || nc >= vfull ? vfull : 1;
     const int64_t col_lanes = (nc + p.vec - 1) / p.vec, others = p.nout / nc;
-    const ColsShape shape = choose_cols_shape(col_lanes, others, p.nredtot, p.nout, acc_es);
+    const ColsShape shape = choose_cols_shape(col_lanes, others, p.nredtot, p.nout, acc_es, false);
     p.cpw = shape.cpw;
     p.split = shape.split;
     const int nw = shape.nw;

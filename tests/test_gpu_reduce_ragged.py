@@ -90,3 +90,17 @@ def test_in_the_other_byte_order():
     a = random_view(rng, "float", (201, 77), specials=False).in_other_byte_order()
     for axes in ((0,), (1,)):
         _check("max", a, axes, "float")
+
+
+@pytest.mark.parametrize("shape", [(1000, 65537), (5000, 32767), (3000, 8193)])
+def test_byte_columns_within_the_library_s_own_scratch(shape):
+    # narrower column blocks instead of more splits where the partial results are bounded
+    import torch
+    import paper_1810_08723_amd as ocn
+    x = torch.randint(-128, 128, shape, dtype=torch.int8, device="cuda:0")
+    out = torch.empty(shape[1], dtype=torch.int64, device="cuda:0")
+    print("byte columns", shape, flush=True)
+    ocn.binding.reduce_scratch("sum", ocn.Tensor(x.data_ptr(), "int8", shape, (shape[1], 1), 0, 0, x), [0],
+                               ocn.Tensor(out.data_ptr(), "int64", shape[1:], (8,), 0, 0, out))
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), x.cpu().numpy().astype(np.int64).sum(axis=0))

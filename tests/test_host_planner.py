@@ -254,3 +254,14 @@ def test_reduction_layouts():
     assert p["kernel"] == "red_cols" and p["passes"] == 2
     # no contiguous axis at all
     assert plan(View.empty("float", (300, 50, 2)).select(2, 1), [0])["kernel"] == "red_rows"
+
+
+@pytest.mark.parametrize("dtype", ("int8", "uint8", "bool"))
+@pytest.mark.parametrize("shape,pitch", [((1000, 65537), 65537), ((5000, 32767), 32767), ((100000, 8193), 8193),
+                                         ((67712, 4160), 4161), ((100000, 101), 101), ((300, 131071), 131071)])
+def test_unaligned_byte_columns_need_no_more_than_the_library_s_own_scratch(dtype, shape, pitch):
+    """Columns of bytes that start anywhere are taken sixteen per lane; their partial results stay
+    within what ocn_reduce_scratch has, which takes such calls."""
+    a = ocn.Tensor(1 << 40, dtype, shape, (pitch, 1))
+    out = ocn.Tensor(1 << 41, "int64", shape[1:], (8,))
+    assert ocn.binding.reduce_workspace_bytes("sum", a, [0], out) <= ocn.binding.REDUCE_SCRATCH_BYTES
