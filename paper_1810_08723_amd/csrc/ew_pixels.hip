@@ -37,12 +37,13 @@ struct PixelArgs {
   int64_t so[kMaxDims], sa[kMaxDims];
 };
 
-// a copy of elements of ES bytes, whatever their type (but bool)
-template <int ES> struct CopyOf {
+// a copy of elements of ES bytes made of scalars of AL bytes, whatever their type (but bool);
+// AL: operands are aligned to their scalars only
+template <int ES, int AL_ = ES> struct CopyOf {
   struct alignas(ES) Elem { unsigned char b[ES]; };
   using In = Elem;
   using Out = Elem;
-  static constexpr int AL = ES;
+  static constexpr int AL = AL_, ALO = AL_;
   OCN_DEV static Out cv(const In &x) { return x; }
   template <int N> OCN_DEV static void loaded(unsigned char (&)[N]) {}
 };
@@ -62,7 +63,7 @@ struct CopyOfBool : CopyOf<1> {
 template <int SA, int SO> struct CastOf {
   using In = storage_t<SA>;
   using Out = storage_t<SO>;
-  static constexpr int AL = sizeof(In) < 8 ? (int)sizeof(In) : 8;
+  static constexpr int AL = (int)sizeof(In), ALO = (int)sizeof(Out);
   OCN_DEV static Out cv(const In &x) { return to_storage<SO>(convert<SO>(from_storage<SA>(x))); }
   template <int N> OCN_DEV static void loaded(unsigned char (&)[N]) {}
 };
@@ -143,7 +144,7 @@ template <class F, int C> __global__ __launch_bounds__(kBlock) void to_planes_ke
     Out o[V];
 #pragma unroll
     for (int i = 0; i < V; ++i) o[i] = F::cv(in.v[i * C + c]);
-    store16<sizeof(Out) < 8 ? (int)sizeof(Out) : 8>(out + (int64_t)c * p.plane, o, p.nt_store != 0);
+    store16<F::ALO>(out + (int64_t)c * p.plane, o, p.nt_store != 0);
   }
 }
 
@@ -190,7 +191,7 @@ template <class F, int C> __global__ __launch_bounds__(kBlock) void to_pixels_ke
     const int ok = __shfl(valid ? 1 : 0, (int)from, kWave);
     if (ok) {
       const Q q = parked[wave * kWave * C + piece];
-      store16<sizeof(Out) < 8 ? (int)sizeof(Out) : 8>(p.out + (int64_t)(((uint64_t)hi << 32) | lo) + (int64_t)part * 16, &q,
+      store16<F::ALO>(p.out + (int64_t)(((uint64_t)hi << 32) | lo) + (int64_t)part * 16, &q,
                                                        p.nt_store != 0);
     }
   }
@@ -243,8 +244,12 @@ hipError_t launch_pixels(const EwPlan &p, hipStream_t stream) {
     switch (dt_size(p.out.dtype)) {
       case 1: return launch_form<CopyOf<1>>(a, c, to_planes, stream);
       case 2: return launch_form<CopyOf<2>>(a, c, to_planes, stream);
-      case 4: return launch_form<CopyOf<4>>(a, c, to_planes, stream);
-      case 8: return launch_form<CopyOf<8>>(a, c, to_planes, stream);
+      case 4:
+        if (p.out.dtype == DT_C16) return launch_form<CopyOf<4, 2>>(a, c, to_planes, stream);
+        return launch_form<CopyOf<4>>(a, c, to_planes, stream);
+      case 8:
+        if (p.out.dtype == DT_C32) return launch_form<CopyOf<8, 4>>(a, c, to_planes, stream);
+        return launch_form<CopyOf<8>>(a, c, to_planes, stream);
       default: return hipErrorInvalidValue;
     }
   }

@@ -42,6 +42,19 @@ def test_plain_copies_of_other_types(dtype):
         _both_ways(rng, dtype, dtype, c, 2, 9, 11, 1)
 
 
+@pytest.mark.parametrize("dtype,sc", [("chalf", 2), ("cfloat", 4)])
+def test_complex_copies_aligned_to_their_scalars_only(dtype, sc):
+    rng = rng_for(26550 + sc)
+    for c in (2, 3, 4):
+        for shift in (sc, 3 * sc):
+            a, out = _off_by(rng, dtype, (2, 9, 11, c), 0), _off_by(None, dtype, (2, c, 9, 11), 0)
+            a = View(a.storage, dtype, a.sizes, a.strides, shift)
+            out = View(out.storage, dtype, out.sizes, out.strides, shift)
+            print("complex pixels", dtype, c, shift, flush=True)
+            H.check_unary("ident", a.permute(0, 3, 1, 2), out)
+            H.check_unary("ident", out.permute(0, 2, 3, 1), View(View.empty(dtype, (2 * 9 * 11 * c + 8,)).storage, dtype, a.sizes, a.strides, shift))
+
+
 def test_padded_rows_reversed_planes_and_byte_order():
     rng = rng_for(26600)
     big = random_view(rng, "uint8", (2, 20, 33, 3))
