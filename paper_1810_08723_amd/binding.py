@@ -235,12 +235,15 @@ def _scratch(nbytes: int, device: int, stream):
     return ws
 
 
-@functools.lru_cache(maxsize=256, typed=True)
+@functools.lru_cache(maxsize=256)
 def _axes_array(*axes):
     return (C.c_int32 * max(len(axes), 1))(*axes)     # (read only: the library takes it as const)
 
 
 def _axes(axes: Sequence[int]):
+    for ax in axes:
+        if type(ax) is not int:    # anything else with an index may change or have no hash: not kept
+            return (C.c_int32 * len(axes))(*axes), len(axes)
     return _axes_array(*axes), len(axes)
 
 

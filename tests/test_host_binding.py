@@ -45,3 +45,15 @@ def test_axes_of_another_type_stay_refused():
         ocn.plan_reduce("sum", a, [1.0], out)
     with pytest.raises(ocn.OcnError):
         ocn.plan_reduce("sum", a, [2], out)
+
+
+def test_axes_that_are_not_plain_ints_are_read_at_every_call():
+    np, torch = pytest.importorskip("numpy"), pytest.importorskip("torch")
+    a, out = ocn.Tensor(1 << 40, "float", (4, 8), (32, 4)), ocn.Tensor(1 << 41, "float", (4,), (4,))
+    assert ocn.plan_reduce("sum", a, [np.array(1)], out)["red_size"] == (8,)      # a 0-d array has an index, but no hash
+    assert ocn.plan_reduce("sum", a, [np.int64(1)], out)["red_size"] == (8,)
+    axis = torch.tensor(1)
+    assert ocn.plan_reduce("sum", a, [axis], out)["red_size"] == (8,)
+    axis.fill_(0)                                                                  # the same object, another value
+    tall = ocn.Tensor(1 << 41, "float", (8,), (4,))
+    assert ocn.plan_reduce("sum", a, [axis], tall)["red_size"] == (4,)
