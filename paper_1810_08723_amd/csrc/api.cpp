@@ -233,6 +233,7 @@ int ocn_plan_unary(int op, const ocn_tensor *a, const ocn_tensor *out, uint32_t 
   const int rc = plan_elementwise(1, op, a, nullptr, out, flags, &p);
   if (rc != OCN_OK) return rc;
   fill_info(p, info);
+  ew_launch_shape(p, &info->grid, &info->block);
   return OCN_OK;
 }
 
@@ -243,6 +244,7 @@ int ocn_plan_binary(int op, const ocn_tensor *a, const ocn_tensor *b, const ocn_
   const int rc = plan_elementwise(2, op, a, b, out, flags, &p);
   if (rc != OCN_OK) return rc;
   fill_info(p, info);
+  ew_launch_shape(p, &info->grid, &info->block);
   return OCN_OK;
 }
 

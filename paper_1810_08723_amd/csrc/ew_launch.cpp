@@ -103,6 +103,15 @@ bool make_rows_slim_args(const EwPlan &p, int block, RowsSlimArgs *args, int64_t
   return true;
 }
 
+void ew_launch_shape(const EwPlan &p, int64_t *grid, int64_t *block) {
+  *grid = p.grid;
+  *block = p.kernel == kKernelTiledAny ? p.block : kBlock;
+  if (p.kernel != OCN_KERNEL_EW_ROWS) return;
+  RowsSlimArgs slim;
+  *block = kSlimBlock;
+  if (!make_rows_slim_args(p, kSlimBlock, &slim, grid)) *block = make_rows_args(p, grid).block;
+}
+
 TiledArgs make_tiled_args(const EwPlan &p, int es_a) {
   TiledArgs t;
   std::memset(&t, 0, sizeof t);

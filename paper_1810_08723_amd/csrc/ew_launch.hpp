@@ -17,6 +17,8 @@ extern EwLauncher g_unary_launchers[U_COUNT][DT_COUNT][DT_COUNT];
 RowsArgs make_rows_args(const EwPlan &p, int64_t *grid);
 // arguments of the kernel for the common row shapes; false if the plan is not one of them
 bool make_rows_slim_args(const EwPlan &p, int block, RowsSlimArgs *args, int64_t *grid);
+// workgroups and lanes per workgroup that the plan goes out with (plan inspection)
+void ew_launch_shape(const EwPlan &p, int64_t *grid, int64_t *block);
 TiledArgs make_tiled_args(const EwPlan &p, int es_a);
 FastTiledArgs make_fast_tiled_args(const EwPlan &p, int es_a);
 AnyTiledArgs make_any_tiled_args(const EwPlan &p, int es_a);

@@ -1479,7 +1479,7 @@ void fill_info(const EwPlan &p, ocn_plan_info *info) {
   info->specialised = p.specialised;
   info->passes = p.kernel == OCN_KERNEL_NONE ? 0 : 1;
   info->grid = p.grid;
-  info->block = kBlock;
+  info->block = kBlock;   // (rows and tiles of any size: the caller puts in what they are launched with)
   info->split = 1;
   info->lds_bytes = p.lds_bytes;
   info->unclipped = p.fast_tiled ? 1 : 0;

@@ -265,3 +265,21 @@ def test_unaligned_byte_columns_need_no_more_than_the_library_s_own_scratch(dtyp
     a = ocn.Tensor(1 << 40, dtype, shape, (pitch, 1))
     out = ocn.Tensor(1 << 41, "int64", shape[1:], (8,))
     assert ocn.binding.reduce_workspace_bytes("sum", a, [0], out) <= ocn.binding.REDUCE_SCRATCH_BYTES
+
+
+def test_plan_inspection_reports_the_launch():
+    # rows: 64-lane workgroups, as many as the lanes of one vector or four need
+    def plan(shape, strides_a, strides_o, dt="float", es=4):
+        a, out = ocn.Tensor(1 << 40, dt, shape, strides_a), ocn.Tensor(1 << 41, dt, shape, strides_o)
+        return ocn.plan_unary("neg", a, out)
+    for n in (64 * 4, 1 << 20, (1 << 20) + 3):
+        p = plan((n,), (4,), (4,))
+        assert (p["kernel"], p["block"]) == ("ew_rows", 64)
+        assert (p["grid"] - 1) * 64 * p["vec"] < n <= p["grid"] * 64 * p["vec"] * 4
+    # tiles of any size: 512 lanes where many are launched, up to 1024 where few are
+    big = plan((6000, 5000), (4, 6000 * 4), (5000 * 4, 4))
+    assert (big["kernel"], big["block"], big["unclipped"]) == ("ew_tiled", 512, False)
+    few = plan((61, 50), (4, 61 * 4), (50 * 4, 4))
+    assert few["kernel"] == "ew_tiled" and few["block"] == 1024
+    # the all-vector form: 256
+    assert plan((2048, 2048), (4, 2048 * 4), (2048 * 4, 4))["block"] == 256
