@@ -21,8 +21,9 @@ template <int S, int OP> hipError_t launch_red(const RedPlan &p, char *partial, 
   switch (p.kernel) {
     case OCN_KERNEL_RED_ROWS:
       if (p.lean) {
-        hipLaunchKernelGGL((red_rows_lean_kernel<S, OP>), dim3((unsigned)p.grid), dim3(kBlock), 0, stream,
-                           make_red_lean_args(p, partial));
+        const RedLeanArgs lean = make_red_lean_args(p, partial);
+        if (lean.tail) hipLaunchKernelGGL((red_rows_lean_kernel<S, OP, true>), dim3((unsigned)p.grid), dim3(kBlock), 0, stream, lean);
+        else hipLaunchKernelGGL((red_rows_lean_kernel<S, OP, false>), dim3((unsigned)p.grid), dim3(kBlock), 0, stream, lean);
         break;
       }
       if (p.short_rows) {
