@@ -1,7 +1,8 @@
 // Generic-dtype elementwise kernel: any combination of the fifteen element types, with the
 // conversions picked by (wavefront-uniform) runtime switches.  It serves the combinations for
-// which no dtype-specialised kernel is instantiated; one element per lane; 32-bit multiply-shift
-// index arithmetic below 2^31 elements, 64-bit division above.
+// which no dtype-specialised kernel is instantiated; four elements per lane along a contiguous
+// innermost dim, else (and for the elementary functions) one; 32-bit multiply-shift index
+// arithmetic below 2^31 elements, 64-bit division above.
 #include <algorithm>
 
 #include "ew_launch.hpp"
@@ -52,7 +53,7 @@ template <class R, int N> __device__ __noinline__ void store_as(char *p, int dt,
     Pack<storage_t<D>, N> pk;                                                                    \
     _Pragma("unroll") for (int i = 0; i < N; ++i) pk.v[i] = to_storage<D>(convert<D>(r.v[i]));   \
     if (swapped) reverse_scalars<scalar_bytes(D)>(pk);                                           \
-    store_pack_any<storage_t<D>, N, scalar_bytes(D)>(p, pk, nt);                                 \
+    store_pack_any<storage_t<D>, N, scalar_bytes(D)>(p, pk, sizeof(pk) == 16 && nt);             \
   } break;
     OCN_CASE(DT_BOOL) OCN_CASE(DT_I8) OCN_CASE(DT_I16) OCN_CASE(DT_I32) OCN_CASE(DT_I64)
     OCN_CASE(DT_U8) OCN_CASE(DT_U16) OCN_CASE(DT_U32) OCN_CASE(DT_U64)
@@ -69,11 +70,18 @@ template <int T, int N> OCN_DEV void store_same(char *p, const Vals<reg_t<T>, N>
 #pragma unroll
   for (int i = 0; i < N; ++i) pk.v[i] = to_storage<T>(r.v[i]);
   if (swapped) reverse_scalars<scalar_bytes(T)>(pk);
-  store_pack_any<storage_t<T>, N, scalar_bytes(T)>(p, pk, nt);
+  store_pack_any<storage_t<T>, N, scalar_bytes(T)>(p, pk, sizeof(pk) == 16 && nt);
 }
 
+// The arguments where they lie, in the constant address space (all their lines touched at once at the
+// start): passed by value and indexed in unrolled loops they were fetched whole and spilled, 110 to
+// 140 scalar registers of each kernel.  2^25 elements of int16 + float -> double 105 us so, 85.6
+// here; half + int16 -> float 93 and 57.5; sine of 2^24 int32 to float 110 and 81; five permuted
+// dims 384 and 187.
+using KInterpArgs = const __attribute__((address_space(4))) InterpArgs;
+
 template <int T, int OP, int N>
-OCN_DEV void binary_one(const InterpArgs &p, const Vals<reg_t<T>, N> &a, const Vals<reg_t<T>, N> &b, char *po) {
+OCN_DEV void binary_one(KInterpArgs &p, const Vals<reg_t<T>, N> &a, const Vals<reg_t<T>, N> &b, char *po) {
   // logical operations always compute in bool
   if constexpr (binary_supported(OP, T) && (!is_logical(OP) || T == DT_BOOL)) {
     Vals<reg_t<binary_result_dtype(OP, T)>, N> r;
@@ -90,7 +98,7 @@ OCN_DEV void binary_one(const InterpArgs &p, const Vals<reg_t<T>, N> &a, const V
   }
 }
 
-template <int T, int OP, int N> OCN_DEV void unary_one(const InterpArgs &p, const Vals<reg_t<T>, N> &a, char *po) {
+template <int T, int OP, int N> OCN_DEV void unary_one(KInterpArgs &p, const Vals<reg_t<T>, N> &a, char *po) {
   if constexpr (unary_supported(OP, T) && (OP != U_LNOT || T == DT_BOOL)) {
     constexpr int RD = unary_result_dtype(OP, T);
     Vals<reg_t<RD>, N> r;
@@ -110,7 +118,7 @@ constexpr bool is_elementary(int op) {
 }
 
 template <int T, bool ELEMENTARY, int N>
-OCN_DEV void interp_body(const InterpArgs &p, const char *pa, const char *pb, char *po) {
+OCN_DEV void interp_body(KInterpArgs &p, const char *pa, const char *pb, char *po) {
   const Vals<reg_t<T>, N> a = load_as<T, N>(pa, p.dt_a, p.inner_a != 0, (p.swap & 1) != 0);
   if constexpr (ELEMENTARY) {
     switch (p.op) {
@@ -150,28 +158,29 @@ OCN_DEV void interp_body(const InterpArgs &p, const char *pa, const char *pb, ch
 // One kernel per compute type T: each gets the registers its own operations need (a single
 // kernel for all types needed 217 vector registers - the complex elementary functions - and ran
 // everything else at two wavefronts per SIMD: int16 + float -> double over 2^25 elements 692 us).
-template <int T, bool ELEMENTARY> __global__ __launch_bounds__(kBlock) void ew_interp_kernel(const InterpArgs p) {
+template <int T, bool ELEMENTARY> __global__ __launch_bounds__(kBlock) void ew_interp_kernel(const InterpArgs by_value) {
+  (void)by_value;  // read through the kernarg segment (it is the only argument)
+  KInterpArgs &p = *(KInterpArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  warm_arguments<InterpArgs>();
   const int64_t lin0 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   const int64_t step = (int64_t)gridDim.x * kBlock;
   for (int64_t lin_k = lin0; lin_k < p.numel; lin_k += step) {
     int64_t lin = lin_k;
     int64_t off_o = 0, off_a = 0, off_b = 0;
+    bool row_end = false;
     if (p.idx32) {
       uint32_t l = (uint32_t)lin;
 #pragma unroll
       for (int d = kMaxDims - 1; d >= 0; --d) {
         if (d < p.ndim) {
-          const uint32_t q = d == 0 ? 0u : fastdiv(l, p.div[d]);   // the slowest dim takes what is left
+          // the slowest dim takes what is left
+          const uint32_t q = d == 0 ? 0u : fastdiv(l, FastDiv{p.div[d].d, p.div[d].m, p.div[d].s});
           const uint32_t i = l - q * p.div[d].d;
           l = q;
           off_o += (int64_t)i * p.so[d];
           off_a += (int64_t)i * p.sa[d];
           off_b += (int64_t)i * p.sb[d];
-          if (d == p.ndim - 1 && i + 1 == p.div[d].d) {   // a row's last group of four ends with the row
-            off_o -= p.back[0];
-            off_a -= p.back[1];
-            off_b -= p.back[2];
-          }
+          if (d == p.ndim - 1) row_end = i + 1 == p.div[d].d;
         }
       }
     } else {
@@ -184,20 +193,21 @@ template <int T, bool ELEMENTARY> __global__ __launch_bounds__(kBlock) void ew_i
           off_o += i * p.so[d];
           off_a += i * p.sa[d];
           off_b += i * p.sb[d];
-          if (d == p.ndim - 1 && i + 1 == p.size[d]) {
-            off_o -= p.back[0];
-            off_a -= p.back[1];
-            off_b -= p.back[2];
-          }
+          if (d == p.ndim - 1) row_end = i + 1 == p.size[d];
         }
       }
+    }
+    if (row_end) {   // a row's last group of four ends with the row
+      off_o -= p.back[0];
+      off_a -= p.back[1];
+      off_b -= p.back[2];
     }
     const char *pa = p.a + off_a;
     const char *pb = p.nin == 2 ? p.b + off_b : nullptr;
     char *po = p.out + off_o;
     // Four elements per lane along a contiguous innermost dim (the index arithmetic above then
-    // runs over groups of four), at any alignment, else one.  uint8 [337098, 189] times a float row:
-    // 425 us with one element per lane, 175 with four.
+    // runs over groups of four), at any alignment, else one.  uint8 [337098, 189] times a uint16 row:
+    // 401 us with one element per lane, 83 with four.
     if (!ELEMENTARY && p.vec == 4) interp_body<T, ELEMENTARY, ELEMENTARY ? 1 : 4>(p, pa, pb, po);
     else interp_body<T, ELEMENTARY, 1>(p, pa, pb, po);
   }
