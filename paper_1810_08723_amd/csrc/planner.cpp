@@ -929,9 +929,12 @@ void choose_reduce_launch(RedPlan &p) {
     const bool lean_shape = p.nred == 1 && p.nkept <= 1 && p.vec > 1 && es < 16 &&
                             p.group >= kWave && nvec < ((int64_t)1 << 31);
     if (p.group >= kWave && waves < kTargetWaves) {
-      // split long reductions so the device fills; keep >= 16 vectors per lane per split
+      // split long reductions so the device fills; keep >= 16 vectors per lane per split, but 4, one
+      // trip of the loop, where several dims are walked and a vector takes as long to find as sixteen
+      // elements did (uint8 [2830, 102] rows 103 apart: 21.9 us with four splits of 16)
       const int64_t want = ((lean_shape ? kLeanSplitWaves : kTargetWaves) + waves - 1) / waves;
-      const int64_t most = std::max<int64_t>(1, nvec / ((int64_t)p.group * 16));
+      const int64_t per_lane = p.vec > 1 && p.nred > 1 && nvec >= (int64_t)p.group * 16 ? 4 : 16;
+      const int64_t most = std::max<int64_t>(1, nvec / ((int64_t)p.group * per_lane));
       p.split = std::max<int64_t>(1, std::min(want, most));
     }
     p.chunk = (nvec + p.split - 1) / p.split;

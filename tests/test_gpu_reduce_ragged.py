@@ -104,3 +104,37 @@ def test_byte_columns_within_the_library_s_own_scratch(shape):
                                ocn.Tensor(out.data_ptr(), "int64", shape[1:], (8,), 0, 0, out))
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy(), x.cpu().numpy().astype(np.int64).sum(axis=0))
+
+
+MORE = KINDS + [("sum", "uint8", "uint64"), ("any", "int16", "bool"), ("all", "half", "bool"), ("min", "int16", "int16"),
+                ("prod", "int32", "int64"), ("sum", "cfloat", "cfloat")]
+
+
+@pytest.mark.parametrize("kind", range(len(MORE)))
+@pytest.mark.parametrize("n", (32, 33, 47, 91, 131))
+def test_several_reduced_dims_of_ragged_rows(kind, n):
+    """Rows that end inside a vector and lie a few elements apart: every lane of a group takes whole
+    vectors over several rows, the last of a row moved back to end with it."""
+    op, din, dout = MORE[kind]
+    rng = rng_for(23700 + 10 * kind + n)
+    for shape, axes, swap in (((2400, n), (0, 1), False), ((5, 900, n), (1, 2), False), ((3, 60, 50, n), (1, 2, 3), False),
+                              ((4, 700, n), (1, 2), True), ((2, 37, n), (1, 2), False)):
+        wide = shape[:-1] + (n + 3,)
+        if din == "cfloat":
+            a = View.from_numpy((rng.integers(-9, 9, size=wide) + 1j * rng.integers(-9, 9, size=wide)).astype(np.complex64))
+        elif din in FLOATS:
+            a = View.from_numpy(rng.standard_normal(wide).astype(FLOATS[din]))
+        else:
+            a = random_view(rng, din, wide, specials=False)
+        a = a.slice(len(shape) - 1, 1, n + 1, 1)
+        if len(shape) == 4:
+            a = a.permute(0, 2, 1, 3)                 # outer dims that do not merge
+        if swap and din not in ("int8", "uint8", "bool", "cfloat"):
+            a = View(a.storage, a.dtype, a.sizes, a.strides, a.offset, True)
+            if din in FLOATS and op == "sum":
+                continue                              # (reversed normals are no sums with a bound)
+        print("several reduced dims", op, din, shape, axes, swap, flush=True)
+        kept = tuple(k for d, k in enumerate(a.sizes) if d not in axes)
+        out = View.empty(dout, kept)
+        got, want = H.run_reduce(op, a, axes, out)
+        assert _same(got, want, out, a, axes), (op, din, a.sizes, axes)
