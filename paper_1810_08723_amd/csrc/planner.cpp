@@ -826,29 +826,37 @@ constexpr int64_t kLeanSplitWaves = 256 * 8;
 // workgroup, and workgroups that share a column block through the workspace.
 //   cpw    A whole wavefront per row, or as few lanes as the columns need, and fewer where more than
 //          30 % of the lanes would have no column (they then take several rows at a time; 777
-//          columns: 64 lanes, 76 % of them busy, ran 36 us against 41 with 32).
+//          columns: 64 lanes, 76 % of them busy, ran 36 us against 41 with 32) and there are enough
+//          rows to take (two rows of 42 doubles, 98352 times: 159 us with 32 lanes, 315 with 16).
 //   nw     As many wavefronts per workgroup as leave each lane 16 rows, up to about 4096 in all: they
 //          combine through LDS, where more workgroups would combine through memory and a second
 //          launch (float sums over the middle of [48, 1000, 777]: 36.6 us with sixteen and no
 //          split, 38 to 40 with four and two to five splits).
-//   split  Only where that leaves half of the chip idle and the wavefronts with long runs of rows, and
-//          rounded down, so that the workgroups go out in one round ([16384, 4099]: 55 us with 15
+//   split  Only where that leaves half of the chip idle and the wavefronts with runs of 32 rows and more
+//          (8 columns of 38191 int16, 37 rows per lane: 23.6 us in one workgroup, 14.9 split), and rounded down, so that the workgroups go out in one round ([16384, 4099]: 55 us with 15
 //          splits, 255 workgroups of sixteen wavefronts, 69 with 16).
 // bounded: the partial results never outgrow what a call without a workspace has (columns whose
 // vectors are not aligned: 8-bit ones have sixteen times the accumulators of one column per lane, and
 // int8 [5000, 32767] would take 2 MiB for eight splits).
 struct ColsShape { int cpw, nw; int64_t split; };
+// Are columns that do not start on vector boundaries taken in whole vectors?  As soon as they fill one,
+// but with eight and more elements per vector only where the vectors of all rows keep half of a
+// workgroup's lanes busy (10 rows of 27 bytes, 13860 times: 31 us with a column per lane, 124 with two
+// lanes per row; two and four elements per vector gained at every size).
+bool unaligned_columns(int64_t nc, int64_t vec, int64_t rows) {
+  return nc >= vec && (vec < 8 || (nc + vec - 1) / vec * rows >= kBlock / 2);
+}
 ColsShape choose_cols_shape(int64_t col_lanes, int64_t others, int64_t rows, int64_t nout, int acc_es, bool bounded) {
   ColsShape r;
   r.cpw = kWave;
   while (r.cpw > 1 && r.cpw / 2 >= col_lanes) r.cpw /= 2;
-  while (r.cpw > 16 && col_lanes * 10 < (col_lanes + r.cpw - 1) / r.cpw * r.cpw * 7) r.cpw /= 2;
+  while (rows >= 8 && r.cpw > 16 && col_lanes * 10 < (col_lanes + r.cpw - 1) / r.cpw * r.cpw * 7) r.cpw /= 2;
   const int64_t rpw = kWave / r.cpw;
   const int64_t blocks0 = (col_lanes + r.cpw - 1) / r.cpw * others;
   r.nw = 4;
   while (r.nw < 16 && blocks0 * r.nw * 2 <= kTargetWaves && rows >= r.nw * 2 * 16 * rpw) r.nw *= 2;
   r.split = 1;
-  if ((blocks0 * r.nw < kTargetWaves / 4 || blocks0 * 2 <= kNumCUs) && rows >= r.nw * rpw * 48) {
+  if ((blocks0 * r.nw < kTargetWaves / 4 || blocks0 * 2 <= kNumCUs) && rows >= r.nw * rpw * 32) {
     const int64_t want = std::max<int64_t>(1, kTargetWaves / (blocks0 * r.nw));
     r.split = std::min(want, rows / (r.nw * rpw * 8));
     // eight rows per lane, but sixteen where the partial results would outgrow what a call without
@@ -949,7 +957,7 @@ void choose_reduce_launch(RedPlan &p) {
     p.kernel = OCN_KERNEL_RED_COLS;
     const int64_t nc = p.ksize[p.nkept - 1];
     aligned = all_aligned((int64_t)vfull * es, p.nkept - 1, -1);
-    p.vec = aligned || nc >= vfull ? vfull : 1;
+    p.vec = aligned || unaligned_columns(nc, vfull, p.nredtot) ? vfull : 1;
     const int64_t col_lanes = (nc + p.vec - 1) / p.vec, others = p.nout / nc;
     const ColsShape shape = choose_cols_shape(col_lanes, others, p.nredtot, p.nout, acc_es, !aligned);
     p.cpw = shape.cpw;
@@ -1192,7 +1200,7 @@ void choose_fused_launch(RedPlan &p) {
     p.b_fast_bcast = p.kstride_b[k_fast_dim] == 0;
     const int64_t nc = p.ksize[p.nkept - 1];
     const bool aligned = all_aligned(p.nkept - 1, -1, p.a_fast_bcast, p.b_fast_bcast);
-    p.vec = aligned || nc >= vfull ? vfull : 1;
+    p.vec = aligned || unaligned_columns(nc, vfull, p.nredtot) ? vfull : 1;
     const int64_t col_lanes = (nc + p.vec - 1) / p.vec, others = p.nout / nc;
     const ColsShape shape = choose_cols_shape(col_lanes, others, p.nredtot, p.nout, acc_es, false);
     p.cpw = shape.cpw;

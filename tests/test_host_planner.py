@@ -283,3 +283,22 @@ def test_plan_inspection_reports_the_launch():
     assert few["kernel"] == "ew_tiled" and few["block"] == 1024
     # the all-vector form: 256
     assert plan((2048, 2048), (4, 2048 * 4), (2048 * 4, 4))["block"] == 256
+
+
+def test_unaligned_columns_keep_the_lanes_busy():
+    def plan(shape, strides, axis, dt="int8", es=1):
+        a = ocn.Tensor(1 << 40, dt, shape, tuple(s * es for s in strides))
+        kept = tuple(n for d, n in enumerate(shape) if d != axis)
+        so, acc = [], es
+        for n in reversed(kept):
+            so.insert(0, acc)
+            acc *= n
+        return ocn.plan_reduce("max", a, [axis], ocn.Tensor(1 << 41, dt, kept, tuple(so)))
+    # a few short rows of bytes: a column per lane; enough of them: sixteen
+    assert plan((90, 154, 10, 27), (47740, 310, 31, 1), 2)["vec"] == 1
+    assert plan((100, 400, 37), (400 * 37, 37, 1), 1)["vec"] == 16
+    # two and four elements per vector: always
+    assert plan((90, 10, 27), (310, 31, 1), 1, "float", 4)["vec"] == 4
+    # few columns of many rows are split over workgroups once a lane has 32 rows
+    assert plan((38191, 8), (9, 1), 0, "int16", 2)["split"] > 1
+    assert plan((1900, 248), (249, 1), 0)["split"] == 1 and plan((2328, 248), (249, 1), 0)["split"] > 1
