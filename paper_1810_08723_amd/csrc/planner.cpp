@@ -481,6 +481,18 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
       rows = false;
       if (p.rows_aligned) p.specialised = false;
     }
+    // Unaligned rows of a few elements, which vectors cross one after the other, element by element:
+    // two or four per row and eight per vector go to the tiles once they are millions (3.9 million rows
+    // of two halves 136 us here, 32 there), and a few rows of 8- or 16-bit integers with floats, a
+    // launch's time in the generic-dtype kernel (two to three rows per vector: 8.2 us, 12.4 here), to that.
+    if (rows && n > 1 && !p.rows_aligned) {
+      const int64_t n0 = p.size[inner];
+      if (V == 8 && (n0 == 2 || n0 == 4) && numel >= (int64_t)4 << 20) rows = false;
+      if (nin == 2 && small_integer_pair(sa, sb) && n0 < V + 2 && n0 % V != 0 && numel >= 1 << 14 && numel < 1 << 19) {
+        rows = false;
+        p.specialised = false;
+      }
+    }
     if (rows) {
       p.kernel = OCN_KERNEL_EW_ROWS;
       p.vec = V;
@@ -702,6 +714,16 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
       // fastest one, non-negative strides and offsets below 2^31 bytes inside a tile.
       bool ok = p.nord > 0 && p.nord <= 4 && p.out.stride[p.ord_o[0]] == es_o && p.vecw_o == log2i(VT) && p.tile_bits <= 12 &&
                 (!p.stage_a || p.tile_log2[p.ord_a[0]] >= p.vecw_a) && (!p.stage_b || p.tile_log2[p.ord_b[0]] >= p.vecw_b) && p.total_tiles <= max_launch_blocks();
+      // Not where vectors are mostly empty or gather their elements, once that is most of the time (in
+      // smaller launches this form's fewer round trips win): an output whose fastest axis is a
+      // quarter of its vector, a power of two that the general form's tiles fit exactly (2.4 M x 4 x 2
+      // int8 plus a permuted view 147 us here, 49 there; three elements gain up to six million), and
+      // two inputs strided along a single long run (4 x 2.6 M bytes, 1 and 4 apart: 42 and 23).
+      const int64_t nfo = p.size[fo];
+      if (nfo * 4 <= VT && (nfo & (nfo - 1)) == 0 && numel >= nfo << 19) ok = false;
+      auto gathered = [&](const Operand &x, int es, bool staged) { return !staged && x.stride[fo] != es && x.stride[fo] != 0; };
+      if (nin == 2 && p.nord == 1 && VT >= 8 && numel >= (int64_t)2 << 20 && gathered(p.a, es_a, p.stage_a) && gathered(p.b, es_b, p.stage_b))
+        ok = false;
       int64_t span_o = 0, span_a = 0, span_b = 0;
       for (int d = 0; d < n && ok; ++d) {
         const int64_t ext = (int64_t)1 << p.tile_log2[d];
@@ -745,7 +767,12 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
     }
   }  // rules
   p.vec = 1 << p.vecw_o;
-  if (p.total_tiles >= ((int64_t)1 << 31)) {  // tile coordinates are 32-bit: use the 64-bit generic kernel
+  // (small tensors of 8- and 16-bit integers with floats into outputs with gaps, which only the general
+  // form takes: the generic-dtype kernel; int8 [52, 55] plus a float column 17.2 us here, 7.8 there)
+  const bool small_general = nin == 2 && small_integer_pair(sa, sb) && !p.fast_tiled && p.kernel != kKernelTiledAny &&
+                             p.out.stride[fo] != es_o && numel < 1 << 19;
+  // (tile coordinates are 32-bit: beyond them the 64-bit generic kernel)
+  if (small_general || p.total_tiles >= ((int64_t)1 << 31)) {
     p.specialised = false;
     p.kernel = OCN_KERNEL_EW_GENERIC;
     p.vec = 1;

@@ -38,6 +38,12 @@ constexpr int kNumMixedPairs = (int)(sizeof(kMixedPairs) / sizeof(kMixedPairs[0]
 constexpr int kNumMixedOps = 4;  // B_ADD, B_SUB, B_MUL, B_DIV
 static_assert(B_ADD == 0 && B_DIV == 3, "the mixed-type kernels cover the first four binary operations");
 
+// is it one of the pairs of 8- or 16-bit integers with floats?
+OCN_HD constexpr bool small_integer_pair(int sa, int sb) {
+  auto small = [](int dt) { return dt == DT_U8 || dt == DT_I8 || dt == DT_U16 || dt == DT_I16; };
+  return (small(sa) && sb == DT_F32) || (sa == DT_F32 && small(sb));
+}
+
 OCN_HD constexpr bool mixed_arith_specialised(int op, int sa, int sb, int so) {
   if (op < 0 || op >= kNumMixedOps) return false;
   for (int k = 0; k < kNumMixedPairs; ++k)

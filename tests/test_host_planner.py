@@ -302,3 +302,22 @@ def test_unaligned_columns_keep_the_lanes_busy():
     # few columns of many rows are split over workgroups once a lane has 32 rows
     assert plan((38191, 8), (9, 1), 0, "int16", 2)["split"] > 1
     assert plan((1900, 248), (249, 1), 0)["split"] == 1 and plan((2328, 248), (249, 1), 0)["split"] > 1
+
+
+def test_elementwise_routes_of_short_rows_and_empty_vectors():
+    def plan(op, da, db, do, shape, sa, sb, so):
+        t = lambda base, dt, st: ocn.Tensor(base, dt, shape, tuple(k * itemsize(dt) for k in st))
+        return ocn.plan_binary(op, t(1 << 40, da, sa), t(1 << 41, db, sb), t(1 << 42, do, so))
+    # millions of rows of two halves, 3 apart, with a permuted operand: tiles; thousands: the rows kernel
+    for rows, kernel in ((3906702, "ew_tiled"), (39067, "ew_rows")):
+        p = plan("mul", "half", "half", "half", (rows, 2), (3, 1), (2, 1), (2, 1))
+        assert p["kernel"] == ("ew_rows" if kernel == "ew_rows" else "ew_generic"), p
+    # rows that fill vectors stay in the rows kernel at any size
+    assert plan("mul", "half", "half", "half", (3906702, 9), (11, 1), (9, 1), (9, 1))["kernel"] == "ew_rows"
+    # 8-bit integers with floats: odd short rows and outputs with gaps go to the generic-dtype kernel while small
+    assert not plan("add", "int8", "float", "float", (9999, 3), (4, 1), (3, 1), (3, 1))["specialised"]
+    assert plan("add", "int8", "float", "float", (999999, 3), (4, 1), (3, 1), (3, 1))["specialised"]
+    assert not plan("add", "int8", "float", "float", (52, 55), (55, 1), (2, 0), (110, 2))["specialised"]
+    # an output axis of a quarter vector: the general form's exact tiles once there are millions of elements
+    for n, vec in ((1 << 22, 1), (1 << 14, 16)):
+        assert plan("add", "int8", "int8", "int8", (n, 2), (2, 1), (1, n), (2, 1))["vec"] == vec
