@@ -100,3 +100,44 @@ def test_rows_of_every_length(dtype, width):
             got = dst.cpu().numpy()
             assert np.array_equal(got[es:-es].reshape(table, -1), want)
             assert (got[:es] == 0x5A).all() and (got[-es:] == 0x5A).all()
+
+
+@pytest.mark.parametrize("dtype,width,n", [("float", 7, 131077), ("uint8", 5, 131079), ("uint8", 3, 140001), ("half", 33, 52433),
+                                           ("double", 3, 131083), ("float", 75, 13801), ("uint8", 4099, 1021)])
+def test_four_pieces_per_lane(dtype, width, n):
+    """Enough pieces that a lane takes four (262144 and more): rows that are no multiple of a piece, the
+    base off by one element, the other byte order, offsets out of range, a ragged last workgroup."""
+    import torch
+    import paper_1810_08723_amd as ocn
+    rng = rng_for(24900 + width)
+    es = np.dtype(NP[dtype]).itemsize
+    table = n + 11
+    row = width * es
+    raw = rng.integers(0, 256, size=(table, row), dtype=np.uint8)
+    pick = rng.permutation(table)[:n]
+    lo, hi = 2 * row, (table - 3) * row
+    skipped = (pick < 2) | (pick > table - 3)
+    offs = torch.from_numpy(pick.astype(np.int64) * row).to("cuda:0")
+    for swap in (False, True) if es > 1 else (False,):
+        turned = lambda x: x.reshape(len(x), width, es)[:, :, ::-1].reshape(len(x), row) if swap else x
+        src = torch.zeros(raw.size + es, dtype=torch.uint8, device="cuda:0")
+        src[es:] = torch.from_numpy(raw.reshape(-1)).to("cuda:0")
+        out = torch.full((n * row + 2 * es,), 0xA5, dtype=torch.uint8, device="cuda:0")
+        print("four pieces", dtype, width, n, swap, flush=True)
+        ocn.gather(ocn.Tensor(src.data_ptr(), dtype, (width,), (es,), es, 0, src), offs, lo, hi,
+                   ocn.Tensor(out.data_ptr(), dtype, (n, width), (row, es), es, 0, out, swap))
+        want = turned(raw[pick]).copy()
+        want[skipped] = 0xA5
+        got = out.cpu().numpy()
+        assert np.array_equal(got[es:-es].reshape(n, row), want)
+        assert (got[:es] == 0xA5).all() and (got[-es:] == 0xA5).all()
+        vals = rng.integers(0, 256, size=(n, row), dtype=np.uint8)
+        tv = torch.from_numpy(vals).to("cuda:0")
+        dst = torch.full((table * row + 2 * es,), 0x5A, dtype=torch.uint8, device="cuda:0")
+        ocn.scatter(ocn.Tensor(tv.data_ptr(), dtype, (n, width), (row, es), 0, 0, tv, swap), offs, lo, hi,
+                    ocn.Tensor(dst.data_ptr(), dtype, (width,), (es,), es, 0, dst))
+        want = np.full((table, row), 0x5A, dtype=np.uint8)
+        want[pick[~skipped]] = turned(vals)[~skipped]
+        got = dst.cpu().numpy()
+        assert np.array_equal(got[es:-es].reshape(table, row), want)
+        assert (got[:es] == 0x5A).all() and (got[-es:] == 0x5A).all()
