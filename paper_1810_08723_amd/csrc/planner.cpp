@@ -483,12 +483,12 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
     }
     // Unaligned rows of a few elements, which vectors cross one after the other, element by element:
     // two or four per row and eight per vector go to the tiles once they are millions (3.9 million rows
-    // of two halves 136 us here, 32 there), and a few rows of 8- or 16-bit integers with floats, a
-    // launch's time in the generic-dtype kernel (two to three rows per vector: 8.2 us, 12.4 here), to that.
+    // of two halves 136 us here, 32 there), and 8- or 16-bit integers with floats to the
+    // generic-dtype kernel (rows of five: 8.2 us, 12.4 here; pairs at any size: 4.6 million 62 and 121).
     if (rows && n > 1 && !p.rows_aligned) {
       const int64_t n0 = p.size[inner];
       if (V == 8 && (n0 == 2 || n0 == 4) && numel >= (int64_t)4 << 20) rows = false;
-      if (nin == 2 && small_integer_pair(sa, sb) && n0 < V + 2 && n0 % V != 0 && numel >= 1 << 14 && numel < 1 << 19) {
+      if (nin == 2 && small_integer_pair(sa, sb) && n0 < V + 2 && n0 % V != 0 && numel >= 1 << 14 && (n0 == 2 || numel < 1 << 19)) {
         rows = false;
         p.specialised = false;
       }
@@ -853,8 +853,9 @@ constexpr int64_t kLeanSplitWaves = 256 * 8;
 // workgroup, and workgroups that share a column block through the workspace.
 //   cpw    A whole wavefront per row, or as few lanes as the columns need, and fewer where more than
 //          30 % of the lanes would have no column (they then take several rows at a time; 777
-//          columns: 64 lanes, 76 % of them busy, ran 36 us against 41 with 32) and there are enough
-//          rows to take (two rows of 42 doubles, 98352 times: 159 us with 32 lanes, 315 with 16).
+//          columns: 64 lanes, 76 % of them busy, ran 36 us against 41 with 32) and there are rows
+//          enough to take (two rows of 42 doubles, 98352 times: 159 us with 32 lanes, 315 with 16; up
+//          to 64 rows of all shapes tried ran 5 to 15 % faster without).
 //   nw     As many wavefronts per workgroup as leave each lane 16 rows, up to about 4096 in all: they
 //          combine through LDS, where more workgroups would combine through memory and a second
 //          launch (float sums over the middle of [48, 1000, 777]: 36.6 us with sixteen and no
@@ -877,7 +878,7 @@ ColsShape choose_cols_shape(int64_t col_lanes, int64_t others, int64_t rows, int
   ColsShape r;
   r.cpw = kWave;
   while (r.cpw > 1 && r.cpw / 2 >= col_lanes) r.cpw /= 2;
-  while (rows >= 8 && r.cpw > 16 && col_lanes * 10 < (col_lanes + r.cpw - 1) / r.cpw * r.cpw * 7) r.cpw /= 2;
+  while (rows >= 64 && r.cpw > 16 && col_lanes * 10 < (col_lanes + r.cpw - 1) / r.cpw * r.cpw * 7) r.cpw /= 2;
   const int64_t rpw = kWave / r.cpw;
   const int64_t blocks0 = (col_lanes + r.cpw - 1) / r.cpw * others;
   r.nw = 4;
