@@ -174,6 +174,66 @@ struct AnyTiledArgs {
   uint32_t rd_el[2][16];                    // compute-phase reads: from the element number inside a vector
 };
 
+// Arguments of the kernel for boxes of any extents (ew_box_kernel).  A box is walked three times, by
+// the output and by each staged input, in the operand's own order: runs of contiguous elements (one
+// dim, or several the box covers whole), cut into vectors, and rows of runs along the other dims.
+// Dividends are below 2^16, so a division is the high half of a product with ceil(2^32 / d); zero in
+// its place leaves the quotient zero.  Everything is read whether a box has that many dims or not
+// (what is missing is neutral): a test per dim is a scalar load and a wait of its own.  The largest
+// coordinates a clipped box has are packed as 16 bits per dim.
+constexpr uint32_t kBoxSlack = 64;          // offsets into an input start here: they stay positive for vectors moved back
+constexpr int kBoxDims = 4;                 // most dims of a box
+constexpr int kBoxRows = 3;                 // most of them besides the first of a run
+constexpr int kBoxRunDims = 3;              // most dims of the output's run
+constexpr int kBoxGrid = 4;                 // box coordinates that are split off without a test
+enum { kBoxStaged, kBoxInPlace };
+struct BoxInput {
+  uint32_t nvec, vpr, vpr_m;                // vectors of a whole box and of a run
+  uint32_t pitch, base;                     // LDS bytes from run to run, and where the first one lies
+  uint32_t epv;                             // elements of a vector
+  uint32_t ext[2], ext_m[2];                // rows: extents of the first two dims
+  uint32_t stride[kBoxRows];
+  uint32_t unit;                            // a run's elements are unit times the extent of its last dim
+  // one pass of the workgroup's lanes further on: digits of that many vectors (vector in the run, then
+  // rows), bytes, and what a carry out of each digit adds
+  uint32_t add[3], add_c2, add_off, add_lds, wrap_off[3], wrap_lds;
+  uint32_t wrap[3];                         // radix of each digit
+  uint32_t lim_run, lim[kBoxRows];          // where the limits sit
+  uint32_t niter;                           // passes of the workgroup's lanes
+  int32_t how;                              // staged, or read in place
+  uint32_t reach;                           // bytes from a box's origin to the end of its last vector
+};
+struct BoxOutput {
+  uint32_t nvec, vpr, vpr_m;
+  uint32_t ext[2], ext_m[2];                // rows: extents of the first two dims
+  uint32_t step, stride[kBoxRows];          // of the output: bytes from vector to vector, and per coordinate
+  uint32_t start[2];                        // of the inputs: where the first element lies, in LDS or in place
+  uint32_t run[2], pos[2][kBoxRows];        // ... bytes from element to element of a run's first dim, and per coordinate
+  uint32_t add[3], add_c2, add_off, add_pos[2];   // one pass further on, as BoxInput
+  uint32_t wrap[3], wrap_off[3], wrap_pos[2][3];
+  uint32_t unit, lim_run, lim[kBoxRows];
+  uint32_t run_ext[kBoxRunDims - 1], run_m[kBoxRunDims - 1];
+  uint32_t run_pos[2][kBoxRunDims - 1];     // what a carry from one run dim into the next adds
+  uint32_t niter;
+  int32_t nrun;
+};
+struct BoxArgs {
+  char *out;
+  const char *a, *b;
+  const char *end[2];                       // ends of the inputs: one past the highest byte
+  uint64_t inner;                           // the limits of a box that is not the last along any dim
+  int32_t warm, ntd;
+  FastDiv ntdiv[kMaxDims];                  // box number -> box coordinates, fastest first
+  int64_t step[3][kMaxDims];
+  uint64_t cut[kMaxDims];                   // what the dim's last box takes off the limits
+  int32_t nt_store, swap;
+  uint32_t block;
+  uint32_t group, regular;                  // boxes in a row that one XCD takes; boxes numbered that way
+  FastDiv group_div;                        // eight such groups
+  BoxInput in[2];
+  BoxOutput o;
+};
+
 struct InterpArgs {
   char *out;
   const char *a, *b;
@@ -389,6 +449,7 @@ template <int OP, int SA, int SB, int SO, int NIN> struct Sig {
   static constexpr int U = rows_unroll(V, ES_MAX);
   static constexpr int VR = rows_stream_vec((int)sizeof(SOt), ES_MIN, ES_MAX);  // the rows kernel's vector
   static constexpr int UR = rows_stream_unroll(VR, ES_MIN);
+  static constexpr int VB = box_vec_len((int)sizeof(SOt), ES_MAX);  // the box kernel's vector
 
   // operands stored in the other byte order: un-reverse inputs after the load, reverse the
   // result before the store (sw: bit 0 a, bit 1 b, bit 2 out; uniform over the launch)
@@ -1432,6 +1493,450 @@ template <class G> __global__ __launch_bounds__(kAnyMaxBlock) void ew_tiled_any_
     }
     if (++j >= niter) break;  // uniform
     fetch(j);
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// boxes of any extents
+// ---------------------------------------------------------------------------------------
+//
+// The tiles above have power-of-two extents: axes of 5, 17 or 71 leave up to half of the lanes
+// without work per axis, and only an operand's fastest axis is lengthened, however short its runs
+// stay.  Here extents are whole numbers (an axis is cut into equal parts, or not at all), runs go on
+// along every axis the box covers whole, and lane numbers are split by multiplication.  A
+// staged input lies in LDS in its own order, run after run, as its 16-byte pieces arrive; the
+// compute phase picks its elements one by one.
+
+using KBoxArgs = const __attribute__((address_space(4))) BoxArgs;
+using KBoxOutput = const __attribute__((address_space(4))) BoxOutput;
+using KBoxInput = const __attribute__((address_space(4))) BoxInput;
+
+OCN_HDF uint32_t box_mulhi(uint32_t n, uint32_t m) { return (uint32_t)(((uint64_t)n * m) >> 32); }
+OCN_HDF uint32_t box_limit(uint64_t lims, uint32_t shift) { return (uint32_t)(lims >> shift) & 0xffffu; }
+
+// Workgroup number -> box number.  Workgroups go to the eight XCDs in turn, each with an L2 of its own:
+// every XCD takes `group` boxes in a row, so that lines which neighbouring boxes share are fetched once.
+template <class P> OCN_HDF uint32_t box_number(const P &p, uint32_t b) {
+  if (b >= p.regular) return b;
+  const uint32_t w = fastdiv(b, FastDiv{p.group_div.d, p.group_div.m, p.group_div.s}), r = b - w * p.group_div.d;
+  return w * p.group_div.d + r % kXcds * p.group + r / kXcds;
+}
+// box number -> offsets of its origin and its limits
+template <class P> OCN_HDF uint64_t box_origin(const P &p, uint32_t t, int64_t (&base)[3]) {
+  uint64_t lims = p.inner;
+  base[0] = base[1] = base[2] = 0;
+  auto split = [&](int j) {
+    const uint32_t dv = p.ntdiv[j].d;
+    const uint32_t q = fastdiv(t, FastDiv{dv, p.ntdiv[j].m, p.ntdiv[j].s});
+    const uint32_t tc = t - q * dv;
+    t = q;
+    for (int x = 0; x < 3; ++x) base[x] += (int64_t)tc * p.step[x][j];
+    lims -= tc + 1 == dv ? p.cut[j] : 0;
+  };
+#pragma unroll
+  for (int j = 0; j < kBoxGrid; ++j) split(j);
+  const int ntd = p.ntd;
+  for (int j = kBoxGrid; j < ntd; ++j) split(j);
+  return lims;
+}
+
+// Where a lane is on its way through a staged input: vector number, digits, bytes from the box's
+// origin, LDS address.
+struct BoxLane {
+  uint32_t t, iv, c[kBoxRows], off, lds;
+};
+template <class I> OCN_HDF BoxLane box_lane(const I &x, uint32_t t) {
+  BoxLane r;
+  const uint32_t row = x.vpr == 1 ? t : box_mulhi(t, x.vpr_m);
+  r.t = t;
+  r.iv = t - row * x.vpr;
+  const uint32_t q0 = box_mulhi(row, x.ext_m[0]), q1 = box_mulhi(q0, x.ext_m[1]);
+  r.c[0] = row - q0 * x.ext[0];
+  r.c[1] = q0 - q1 * x.ext[1];
+  r.c[2] = q1;
+  r.off = kBoxSlack + r.iv * 16u + r.c[0] * x.stride[0] + r.c[1] * x.stride[1] + r.c[2] * x.stride[2];
+  r.lds = x.base + row * x.pitch + r.iv * 16u;
+  return r;
+}
+// one pass of the workgroup's lanes further on (all ones or zero instead of a branch per carry)
+template <class I> OCN_HDF void box_advance(const I &x, uint32_t block, BoxLane &r) {
+  r.t += block;
+  r.iv += x.add[0];
+  const uint32_t w0 = r.iv >= x.wrap[0] ? ~0u : 0u;
+  r.iv -= w0 & x.wrap[0];
+  r.c[0] += x.add[1] - w0;
+  const uint32_t w1 = r.c[0] >= x.wrap[1] ? ~0u : 0u;
+  r.c[0] -= w1 & x.wrap[1];
+  r.c[1] += x.add[2] - w1;
+  const uint32_t w2 = r.c[1] >= x.wrap[2] ? ~0u : 0u;
+  r.c[1] -= w2 & x.wrap[2];
+  r.c[2] += x.add_c2 - w2;
+  r.off += x.add_off + (w0 & x.wrap_off[0]) + (w1 & x.wrap_off[1]) + (w2 & x.wrap_off[2]);
+  r.lds += x.add_lds + (w0 & x.wrap_lds);
+}
+// does any of the lane's vector exist in a box with these limits
+template <class I> OCN_HDF bool box_exists(const I &x, uint64_t lims, const BoxLane &r) {
+  const uint32_t in_run = r.iv * x.epv < x.unit * (box_limit(lims, x.lim_run) + 1), in0 = r.c[0] <= box_limit(lims, x.lim[0]),
+                 in1 = r.c[1] <= box_limit(lims, x.lim[1]), in2 = r.c[2] <= box_limit(lims, x.lim[2]);
+  return (in_run & in0 & in1 & in2) != 0;
+}
+
+// The same for the output: where its vector, and the inputs' elements for it, lie.
+struct BoxVec {
+  uint32_t t, iv, c[kBoxRows], off, pos[2];
+};
+template <class O> OCN_HDF BoxVec box_vec(const O &o, uint32_t t) {
+  BoxVec r;
+  const uint32_t row = o.vpr == 1 ? t : box_mulhi(t, o.vpr_m);
+  r.t = t;
+  r.iv = t - row * o.vpr;
+  const uint32_t q0 = box_mulhi(row, o.ext_m[0]), q1 = box_mulhi(q0, o.ext_m[1]);
+  r.c[0] = row - q0 * o.ext[0];
+  r.c[1] = q0 - q1 * o.ext[1];
+  r.c[2] = q1;
+  r.off = r.iv * o.step + r.c[0] * o.stride[0] + r.c[1] * o.stride[1] + r.c[2] * o.stride[2];
+#pragma unroll
+  for (int y = 0; y < 2; ++y) r.pos[y] = o.start[y] + r.iv * o.run[y] + r.c[0] * o.pos[y][0] + r.c[1] * o.pos[y][1] + r.c[2] * o.pos[y][2];
+  return r;
+}
+template <class O> OCN_HDF void box_advance_out(const O &o, uint32_t block, BoxVec &r) {
+  r.t += block;
+  r.iv += o.add[0];
+  const uint32_t w0 = r.iv >= o.wrap[0] ? ~0u : 0u;
+  r.iv -= w0 & o.wrap[0];
+  r.c[0] += o.add[1] - w0;
+  const uint32_t w1 = r.c[0] >= o.wrap[1] ? ~0u : 0u;
+  r.c[0] -= w1 & o.wrap[1];
+  r.c[1] += o.add[2] - w1;
+  const uint32_t w2 = r.c[1] >= o.wrap[2] ? ~0u : 0u;
+  r.c[1] -= w2 & o.wrap[2];
+  r.c[2] += o.add_c2 - w2;
+  r.off += o.add_off + (w0 & o.wrap_off[0]) + (w1 & o.wrap_off[1]) + (w2 & o.wrap_off[2]);
+#pragma unroll
+  for (int y = 0; y < 2; ++y)
+    r.pos[y] += o.add_pos[y] + (w0 & o.wrap_pos[y][0]) + (w1 & o.wrap_pos[y][1]) + (w2 & o.wrap_pos[y][2]);
+}
+// how many elements of the vector exist
+template <int V, class O> OCN_HDF int box_count(const O &o, uint64_t lims, bool clipped, const BoxVec &r) {
+  const int left = (int)(o.unit * (box_limit(lims, o.lim_run) + 1)) - (int)(r.iv * (uint32_t)V);
+  int n = left < V ? left : V;
+  if (clipped) {
+    const uint32_t out0 = r.c[0] > box_limit(lims, o.lim[0]), out1 = r.c[1] > box_limit(lims, o.lim[1]), out2 = r.c[2] > box_limit(lims, o.lim[2]);
+    n = (out0 | out1 | out2) != 0 ? 0 : n;
+  }
+  return r.t < o.nvec ? n : 0;
+}
+// Runs along two or three dims: the vector's coordinates in the run, and what they add to its place.
+// (run[y] is bytes per vector here and in box_vec; a carry takes back what the elements of a whole
+// dim were counted for.)
+struct BoxRun {
+  uint32_t c[kBoxRunDims - 1];
+};
+template <int V, class O> OCN_HDF BoxRun box_run(const O &o, const BoxVec &r, uint32_t (&pos)[2]) {
+  const uint32_t e0 = r.iv * (uint32_t)V, d1 = box_mulhi(e0, o.run_m[0]), d2 = box_mulhi(d1, o.run_m[1]);
+#pragma unroll
+  for (int y = 0; y < 2; ++y) pos[y] = r.pos[y] + d1 * o.run_pos[y][0] + d2 * o.run_pos[y][1];
+  return BoxRun{{e0 - d1 * o.run_ext[0], d1 - d2 * o.run_ext[1]}};
+}
+// the next element of such a run
+template <int V, class O> OCN_HDF void box_next(const O &o, BoxRun &r, uint32_t (&pos)[2]) {
+  const uint32_t w0 = ++r.c[0] == o.run_ext[0] ? ~0u : 0u;
+  r.c[0] &= ~w0;
+  r.c[1] -= w0;
+  const uint32_t w1 = r.c[1] == o.run_ext[1] ? ~0u : 0u;
+  r.c[1] &= ~w1;
+#pragma unroll
+  for (int y = 0; y < 2; ++y) pos[y] += o.run[y] / V + (w0 & o.run_pos[y][0]) + (w1 & o.run_pos[y][1]);
+}
+
+// A vector that would run past its operand's end is loaded from so many whole elements before it
+// (see any_address); room: bytes from the box's origin to the last place a vector may start at.
+OCN_HDF uint32_t box_back(uint32_t off, int32_t room, int es_log2) {
+  const int32_t over = (int32_t)(off - kBoxSlack) - room;
+  return over > 0 ? (uint32_t)(over + ((1 << es_log2) - 1)) >> es_log2 : 0u;
+}
+OCN_HDF int32_t box_room(const char *end, const char *origin, int bytes) {
+  const int64_t room = end - origin - bytes;
+  return room > INT32_MAX ? INT32_MAX : (int32_t)room;
+}
+
+// the fields of a staged input that box_lane and box_advance read, all fetched at once
+OCN_DEV void box_input(KBoxInput &k, BoxInput &x) {
+  x.nvec = k.nvec; x.vpr = k.vpr; x.vpr_m = k.vpr_m; x.pitch = k.pitch; x.base = k.base;
+  x.add_c2 = k.add_c2; x.add_off = k.add_off; x.add_lds = k.add_lds; x.wrap_lds = k.wrap_lds;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) { x.ext[i] = k.ext[i]; x.ext_m[i] = k.ext_m[i]; }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) { x.stride[i] = k.stride[i]; x.add[i] = k.add[i]; x.wrap[i] = k.wrap[i]; x.wrap_off[i] = k.wrap_off[i]; }
+  OCN_ARGS_NOW("s"(x.nvec), "s"(x.vpr), "s"(x.vpr_m), "s"(x.pitch), "s"(x.base), "s"(x.ext[0]), "s"(x.ext[1]),
+               "s"(x.ext_m[0]), "s"(x.ext_m[1]), "s"(x.stride[0]), "s"(x.stride[1]), "s"(x.stride[2]), "s"(x.add[0]), "s"(x.add[1]), "s"(x.add[2]),
+               "s"(x.add_c2), "s"(x.add_off), "s"(x.add_lds), "s"(x.wrap_lds), "s"(x.wrap[0]), "s"(x.wrap[1]), "s"(x.wrap[2]), "s"(x.wrap_off[0]),
+               "s"(x.wrap_off[1]), "s"(x.wrap_off[2]));
+}
+
+OCN_DEV void box_output(KBoxOutput &k, BoxOutput &x) {
+  x.nvec = k.nvec; x.vpr = k.vpr; x.vpr_m = k.vpr_m; x.step = k.step; x.add_c2 = k.add_c2; x.add_off = k.add_off; x.unit = k.unit; x.lim_run = k.lim_run;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    x.ext[i] = k.ext[i]; x.ext_m[i] = k.ext_m[i]; x.start[i] = k.start[i]; x.run[i] = k.run[i]; x.add_pos[i] = k.add_pos[i];
+    x.run_ext[i] = k.run_ext[i]; x.run_m[i] = k.run_m[i];
+    for (int y = 0; y < 2; ++y) x.run_pos[y][i] = k.run_pos[y][i];
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    x.stride[i] = k.stride[i]; x.add[i] = k.add[i]; x.wrap[i] = k.wrap[i]; x.wrap_off[i] = k.wrap_off[i]; x.lim[i] = k.lim[i];
+    for (int y = 0; y < 2; ++y) { x.pos[y][i] = k.pos[y][i]; x.wrap_pos[y][i] = k.wrap_pos[y][i]; }
+  }
+  OCN_ARGS_NOW("s"(x.nvec), "s"(x.vpr), "s"(x.vpr_m), "s"(x.step), "s"(x.ext[0]), "s"(x.ext[1]), "s"(x.ext_m[0]), "s"(x.ext_m[1]), "s"(x.stride[0]),
+               "s"(x.stride[1]), "s"(x.stride[2]), "s"(x.start[0]), "s"(x.start[1]), "s"(x.run[0]), "s"(x.run[1]), "s"(x.pos[0][0]), "s"(x.pos[0][1]),
+               "s"(x.pos[0][2]), "s"(x.pos[1][0]), "s"(x.pos[1][1]), "s"(x.pos[1][2]), "s"(x.unit), "s"(x.lim_run));
+}
+
+// Vectors of a staged input, and passes of inputs read in place, that a lane has in flight.  Four of
+// either take 87 to 97 registers instead of 59, and fewer wavefronts lose more than the loads win (6000 x
+// 5000 plus a transpose 69 us with two and two, 76 with four passes, 72 with one).
+constexpr int kBoxLoads = 2, kBoxAhead = 2;
+// STA, STB: the input is staged in LDS (else read in place).
+template <class G, bool STA, bool STB>
+OCN_DEV void box_body(KBoxArgs &p, char *lds, uint64_t lims, char *out, const char *pa, const char *pb) {
+  using SAt = typename G::SAt;
+  using SBt = typename G::SBt;
+  using SOt = typename G::SOt;
+  constexpr bool BIN = G::NIN2;
+  constexpr int VA = 16 / (int)sizeof(SAt), VB = 16 / (int)sizeof(SBt);
+  constexpr int V = G::VB;
+  constexpr int ALA = scalar_bytes(G::SA_DT), ALB = scalar_bytes(G::SB_DT), ALO = scalar_bytes(G::SO_DT);
+  constexpr int LA = sizeof(SAt) == 16 ? 4 : sizeof(SAt) == 8 ? 3 : sizeof(SAt) == 4 ? 2 : sizeof(SAt) == 2 ? 1 : 0;
+  constexpr int LB = sizeof(SBt) == 16 ? 4 : sizeof(SBt) == 8 ? 3 : sizeof(SBt) == 4 ? 2 : sizeof(SBt) == 2 ? 1 : 0;
+  constexpr int U = kBoxLoads;
+  const uint32_t tid = threadIdx.x, block = p.block;
+  const bool clipped = lims != p.inner;
+  // (does a vector of the box reach past the operand's end?  Only those of its last boxes do.)
+  const bool end_a = p.end[0] - pa < (int64_t)p.in[0].reach, end_b = BIN && p.end[1] - pb < (int64_t)p.in[1].reach;
+  const char *qa = pa - kBoxSlack, *qb = BIN ? pb - kBoxSlack : nullptr;
+
+  // Inputs read in place: the first pass is on its way while the others are fetched.  (Every lane
+  // loads, one without a vector from the box's origin: a load under a condition of its own makes the
+  // compiler wait for those before it.)
+  BoxOutput o;
+  box_output(p.o, o);
+  // PU passes of the inputs read in place are on their way at a time
+  constexpr int PU = !STA || (BIN && !STB) ? kBoxAhead : 1;
+  const uint32_t niter = p.o.niter;
+  BoxVec walker = box_vec(o, tid), vs[PU];
+  int ns[PU];
+  Pack<SAt, V> as[PU];
+  Pack<SBt, V> bs[PU];
+  uint32_t back_a[PU], back_b[PU];
+  const bool one_a = !STA && o.run[0] == 0, one_b = BIN && !STB && o.run[1] == 0;
+  auto fetch = [&](uint32_t j) {
+#pragma unroll
+    for (int u = 0; u < PU; ++u) {
+      if (j + u < niter) {
+        const BoxVec v = vs[u] = walker;
+        box_advance_out(o, block, walker);
+        const int n = ns[u] = box_count<V>(o, lims, clipped, v);
+        back_a[u] = back_b[u] = 0;
+        if constexpr (!STA) {
+          uint32_t off = n > 0 ? v.pos[0] : kBoxSlack;
+          if (one_a) {
+            as[u].v[0] = *reinterpret_cast<const SAt *>(qa + off);
+          } else {
+            if (end_a) {
+              back_a[u] = box_back(off, box_room(p.end[0], pa, V * (int)sizeof(SAt)), LA);
+              off -= back_a[u] << LA;
+            }
+            load_pack_any<SAt, V, ALA>(qa + off, as[u]);
+          }
+        }
+        if constexpr (BIN && !STB) {
+          uint32_t off = n > 0 ? v.pos[1] : kBoxSlack;
+          if (one_b) {
+            bs[u].v[0] = *reinterpret_cast<const SBt *>(qb + off);
+          } else {
+            if (end_b) {
+              back_b[u] = box_back(off, box_room(p.end[1], pb, V * (int)sizeof(SBt)), LB);
+              off -= back_b[u] << LB;
+            }
+            load_pack_any<SBt, V, ALB>(qb + off, bs[u]);
+          }
+        }
+      }
+    }
+  };
+  fetch(0);
+
+  if constexpr (STA || (BIN && STB)) {
+    // Staged inputs: all loads of U passes are issued before any vector is parked.
+    {
+      BoxInput xa, xb;
+      uint32_t na = 0, nb = 0;
+      BoxLane la{}, lb{};
+      if constexpr (STA) {
+        box_input(p.in[0], xa);
+        na = p.in[0].niter;
+        la = box_lane(xa, tid);
+      }
+      if constexpr (BIN && STB) {
+        box_input(p.in[1], xb);
+        nb = p.in[1].niter;
+        lb = box_lane(xb, tid);
+      }
+      const uint32_t nmax = na > nb ? na : nb;
+      for (uint32_t j = 0; j < nmax; j += U) {
+        Pack<SAt, VA> va[U];
+        Pack<SBt, VB> vb[U];
+        uint32_t wa[U], wb[U], da[U], db[U];   // LDS addresses (all ones: no such vector)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          wa[u] = wb[u] = ~0u;
+          da[u] = db[u] = 0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if constexpr (STA) {
+            if (j + u < na) {
+              bool is = la.t < xa.nvec;
+              if (clipped) is = is & box_exists(p.in[0], lims, la);
+              wa[u] = is ? la.lds : ~0u;
+              uint32_t off = is ? la.off : kBoxSlack;
+              if (end_a) {
+                da[u] = box_back(off, box_room(p.end[0], pa, 16), LA);
+                off -= da[u] << LA;
+              }
+              load_pack_any<SAt, VA, ALA>(qa + off, va[u]);
+              box_advance(xa, block, la);
+            }
+          }
+          if constexpr (BIN && STB) {
+            if (j + u < nb) {
+              bool is = lb.t < xb.nvec;
+              if (clipped) is = is & box_exists(p.in[1], lims, lb);
+              wb[u] = is ? lb.lds : ~0u;
+              uint32_t off = is ? lb.off : kBoxSlack;
+              if (end_b) {
+                db[u] = box_back(off, box_room(p.end[1], pb, 16), LB);
+                off -= db[u] << LB;
+              }
+              load_pack_any<SBt, VB, ALB>(qb + off, vb[u]);
+              box_advance(xb, block, lb);
+            }
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if constexpr (STA) {
+            if (j + u < na) {
+              if (end_a) any_shift<SAt, VA>(va[u], (int)da[u]);
+              if (wa[u] != ~0u) *reinterpret_cast<Pack<SAt, VA> *>(lds + wa[u]) = va[u];
+            }
+          }
+          if constexpr (BIN && STB) {
+            if (j + u < nb) {
+              if (end_b) any_shift<SBt, VB>(vb[u], (int)db[u]);
+              if (wb[u] != ~0u) *reinterpret_cast<Pack<SBt, VB> *>(lds + wb[u]) = vb[u];
+            }
+          }
+        }
+        // (vmcnt(0): parked under conditions, the loads count as outstanding in the next trip, and each
+        // load there would wait for the one before it)
+        __builtin_amdgcn_s_waitcnt(0x0f70);
+      }
+    }
+    __syncthreads();
+  }
+
+  // compute phase, in the output's order
+  const int swap = p.swap;
+  const bool nt = p.nt_store != 0;
+  auto compute = [&](auto runs, int u) {
+    constexpr bool RUNS = decltype(runs)::value;   // runs go along several dims
+    const BoxVec &v = vs[u];
+    const int n = ns[u];
+    Pack<SAt, V> av = as[u];
+    Pack<SBt, V> bv = bs[u];
+    if constexpr (!STA) {
+      if (end_a) any_shift<SAt, V>(av, (int)back_a[u]);
+      if (one_a) {
+#pragma unroll
+        for (int i = 1; i < V; ++i) av.v[i] = av.v[0];
+      }
+    }
+    if constexpr (BIN && !STB) {
+      if (end_b) any_shift<SBt, V>(bv, (int)back_b[u]);
+      if (one_b) {
+#pragma unroll
+        for (int i = 1; i < V; ++i) bv.v[i] = bv.v[0];
+      }
+    }
+    if (n <= 0) return;
+    uint32_t pos[2] = {v.pos[0], v.pos[1]};
+    BoxRun run;
+    if constexpr (RUNS) run = box_run<V>(o, v, pos);
+#pragma unroll
+    for (int i = 0; i < V; ++i) {   // (elements that do not exist are read from where the last one lies)
+      if constexpr (STA) av.v[i] = *reinterpret_cast<const SAt *>(lds + pos[0]);
+      if constexpr (BIN && STB) bv.v[i] = *reinterpret_cast<const SBt *>(lds + pos[1]);
+      if (i + 1 < V) {
+        uint32_t next[2] = {pos[0], pos[1]};
+        if constexpr (RUNS) {
+          box_next<V>(o, run, next);
+        } else {
+          next[0] += o.run[0] / V;
+          next[1] += o.run[1] / V;
+        }
+        pos[0] = i + 1 < n ? next[0] : pos[0];
+        pos[1] = i + 1 < n ? next[1] : pos[1];
+      }
+    }
+    Pack<SOt, V> r;
+    if (swap) G::order_inputs(swap, av, bv);
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      if constexpr (BIN) r.v[i] = G::eval(av.v[i], bv.v[i]);
+      else r.v[i] = G::eval(av.v[i], SBt{});
+    }
+    if (swap) G::order_output(swap, r);
+    char *po = out + v.off;
+    if (n == V) {
+      store_pack_any<SOt, V, ALO>(po, r, nt);
+    } else {
+#pragma unroll
+      for (int i = 0; i < V; ++i)
+        if (i < n) reinterpret_cast<SOt *>(po)[i] = r.v[i];
+    }
+  };
+  auto passes = [&](auto runs) {
+    for (uint32_t j = 0;;) {
+#pragma unroll
+      for (int u = 0; u < PU; ++u)
+        if (j + u < niter) compute(runs, u);
+      if ((j += PU) >= niter) break;  // uniform
+      fetch(j);
+    }
+  };
+  if (p.o.nrun > 1) passes(std::true_type{});
+  else passes(std::false_type{});
+}
+
+template <class G> __global__ __launch_bounds__(kBlock) void ew_box_kernel(const BoxArgs by_value) {
+  constexpr bool BIN = G::NIN2;
+  (void)by_value;  // read through the kernarg segment instead (it is the only argument)
+  KBoxArgs &p = *(KBoxArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  char *lds = reinterpret_cast<char *>(ocn_lds_raw);
+  if (p.warm) warm_arguments<BoxArgs>();
+  int64_t base[3];
+  const uint64_t lims = box_origin(p, box_number(p, blockIdx.x), base);
+  char *out = p.out + base[0];
+  const char *pa = p.a + base[1];
+  const char *pb = BIN ? p.b + base[2] : nullptr;
+  const bool in_a = p.in[0].how == kBoxInPlace;
+  if constexpr (BIN) {
+    if (p.in[1].how == kBoxInPlace) box_body<G, true, false>(p, lds, lims, out, pa, pb);
+    else if (in_a) box_body<G, false, true>(p, lds, lims, out, pa, pb);
+    else box_body<G, true, true>(p, lds, lims, out, pa, pb);
+  } else {
+    box_body<G, true, true>(p, lds, lims, out, pa, pb);
   }
 }
 

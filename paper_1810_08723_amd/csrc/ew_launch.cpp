@@ -105,7 +105,7 @@ bool make_rows_slim_args(const EwPlan &p, int block, RowsSlimArgs *args, int64_t
 
 void ew_launch_shape(const EwPlan &p, int64_t *grid, int64_t *block) {
   *grid = p.grid;
-  *block = p.kernel == kKernelTiledAny ? p.block : kBlock;
+  *block = p.kernel == kKernelTiledAny || p.kernel == kKernelBox ? p.block : kBlock;
   if (p.kernel != OCN_KERNEL_EW_ROWS) return;
   RowsSlimArgs slim;
   *block = kSlimBlock;
@@ -394,6 +394,166 @@ AnyTiledArgs make_any_tiled_args(const EwPlan &p, int es_a) {
     for (int j = 0; j < f.ord[0].niter; ++j) f.rd_hi[y][j] = swizzle(((uint32_t)j * f.block) << p.vecw_o, z) << sh;
     for (int i = 0; i < (1 << p.vecw_o) && i < 16; ++i) f.rd_el[y][i] = swizzle((uint32_t)i, z) << sh;
   }
+  return f;
+}
+
+BoxArgs make_box_args(const EwPlan &p) {
+  BoxArgs f;
+  std::memset(&f, 0, sizeof f);
+  const Operand *ops[3] = {&p.out, &p.a, &p.b};
+  const int es[3] = {dt_size(p.out.dtype), dt_size(p.a.dtype), p.nin == 2 ? dt_size(p.b.dtype) : 1};
+  const int8_t *ords[3] = {p.ord_o, p.ord_a, p.ord_b};
+  const uint32_t vec = 1u << p.vecw_o;
+  f.out = p.out.ptr;
+  f.a = p.a.ptr;
+  f.b = p.b.ptr;
+  for (int x = 1; x <= p.nin; ++x) {
+    const char *e = ops[x]->ptr + es[x];
+    int64_t reach = 0;
+    for (int d = 0; d < p.ndim; ++d) {
+      e += (p.size[d] - 1) * ops[x]->stride[d];
+      reach += (p.box[d] - 1) * ops[x]->stride[d];
+    }
+    f.end[x - 1] = e;
+    f.in[x - 1].reach = (uint32_t)(reach + std::max<int64_t>(16, (int64_t)vec * es[x]));
+  }
+  f.warm = p.total_tiles <= kWarmTiles;
+  f.nt_store = p.nt_store;
+  f.swap = p.swap;
+  f.block = (uint32_t)p.block;
+  auto inverse = [](uint32_t d) { return (uint32_t)((((uint64_t)1 << 32) + d - 1) / d); };   // (d above one)
+  // the limits: largest coordinates, in the output's order; the bits above them are zero, the limit of
+  // a coordinate that is always zero
+  uint32_t shift_of[kMaxDims];
+  constexpr uint32_t kNone = 63;
+  for (int d = 0; d < kMaxDims; ++d) shift_of[d] = kNone;
+  for (int k = 0; k < p.nord; ++k) {
+    shift_of[p.ord_o[k]] = (uint32_t)(16 * k);
+    f.inner |= (uint64_t)(p.box[p.ord_o[k]] - 1) << (16 * k);
+  }
+  f.group = (uint32_t)p.box_group;
+  f.group_div = make_fastdiv(std::max(1u, f.group * kXcds));
+  f.regular = f.group > 1 ? (uint32_t)p.total_tiles / f.group_div.d * f.group_div.d : 0u;
+  for (int j = 0; j < kMaxDims; ++j) f.ntdiv[j] = make_fastdiv(1);
+  for (int d = p.ndim - 1; d >= 0; --d) {
+    if (p.ntiles[d] <= 1) continue;
+    const int j = f.ntd++;
+    f.ntdiv[j] = make_fastdiv((uint32_t)p.ntiles[d]);
+    for (int x = 0; x < 3; ++x) f.step[x][j] = ops[x]->stride[d] * p.box[d];
+    if (p.box[d] > 1) f.cut[j] = (uint64_t)(p.box[d] - (p.size[d] - (p.ntiles[d] - 1) * p.box[d])) << shift_of[d];
+  }
+  uint32_t pos[2][kMaxDims] = {};   // bytes of an input per coordinate, where it is read
+  uint32_t lds = 0;
+  for (int y = 0; y < p.nin; ++y) {
+    BoxInput &in = f.in[y];
+    const Operand &x = *ops[y + 1];
+    in.how = p.box_how[y];
+    if (in.how == kBoxInPlace) {
+      for (int d = 0; d < p.ndim; ++d) pos[y][d] = (uint32_t)x.stride[d];
+      f.o.start[y] = kBoxSlack;
+      continue;
+    }
+    const int nd = p.box_dims[y + 1], nrun = p.box_run[y + 1], nrow = nd - nrun;
+    const int8_t *o = ords[y + 1];
+    const uint32_t e = (uint32_t)es[y + 1];
+    in.epv = 16u / e;
+    uint32_t len = 1, rows = 1;
+    for (int k = 0; k < nrun; ++k) {
+      pos[y][o[k]] = len * e;
+      len *= (uint32_t)p.box[o[k]];
+    }
+    in.unit = len / (uint32_t)p.box[o[nrun - 1]];
+    in.lim_run = shift_of[o[nrun - 1]];
+    in.vpr = (len + in.epv - 1) / in.epv;
+    in.vpr_m = in.vpr > 1 ? inverse(in.vpr) : 0;
+    in.pitch = (len * e + 15) / 16 * 16;
+    if (in.pitch % 32 == 0) in.pitch += 16;
+    in.base = f.o.start[y] = lds;
+    uint32_t radix[3] = {in.vpr, 1u << 16, 1u << 16};
+    for (int k = 0; k < kBoxRows; ++k) {
+      in.lim[k] = kNone;
+      if (k >= nrow) continue;
+      const int d = o[nrun + k];
+      const uint32_t ext = (uint32_t)p.box[d];
+      if (k < 2 && k + 1 < nrow) {   // (the last coordinate is what is left)
+        in.ext[k] = radix[k + 1] = ext;
+        in.ext_m[k] = inverse(ext);
+      }
+      in.stride[k] = (uint32_t)x.stride[d];
+      in.lim[k] = shift_of[d];
+      pos[y][d] = rows * in.pitch;
+      rows *= ext;
+    }
+    in.nvec = in.vpr * rows;
+    in.niter = (in.nvec + f.block - 1) / f.block;
+    lds += rows * in.pitch;
+    uint32_t rest = f.block;
+    for (int k = 0; k < 3; ++k) {
+      in.wrap[k] = radix[k];
+      in.add[k] = rest % radix[k];
+      rest /= radix[k];
+    }
+    in.add_off = in.add[0] * 16u + in.add[1] * in.stride[0] + in.add[2] * in.stride[1] + rest * in.stride[2];
+    in.add_c2 = rest;
+    in.add_lds = in.add[0] * 16u + f.block / radix[0] * in.pitch;
+    in.wrap_off[0] = in.stride[0] - radix[0] * 16u;
+    in.wrap_off[1] = in.stride[1] - radix[1] * in.stride[0];
+    in.wrap_off[2] = in.stride[2] - radix[2] * in.stride[1];
+    in.wrap_lds = in.pitch - radix[0] * 16u;
+  }
+  BoxOutput &out = f.o;
+  out.nrun = p.box_run[0];
+  const int nrow = p.nord - out.nrun;
+  uint32_t len = 1, rows = 1;
+  for (int k = 0; k < out.nrun; ++k) len *= (uint32_t)p.box[p.ord_o[k]];
+  const int last = p.ord_o[out.nrun - 1];
+  out.unit = len / (uint32_t)p.box[last];
+  out.lim_run = shift_of[last];
+  out.vpr = (len + vec - 1) / vec;
+  out.vpr_m = out.vpr > 1 ? inverse(out.vpr) : 0;
+  out.step = vec * (uint32_t)es[0];
+  for (int y = 0; y < 2; ++y) out.run[y] = vec * pos[y][p.ord_o[0]];
+  for (int k = 0; k + 1 < kBoxRunDims; ++k) {
+    out.run_ext[k] = 1u << 16;   // (never reached)
+    if (k + 1 >= out.nrun) continue;
+    const uint32_t ext = (uint32_t)p.box[p.ord_o[k]];
+    out.run_ext[k] = ext;
+    out.run_m[k] = inverse(ext);
+    // what a step along the run's next dim adds to one along all of this dim
+    for (int y = 0; y < 2; ++y) out.run_pos[y][k] = pos[y][p.ord_o[k + 1]] - ext * pos[y][p.ord_o[k]];
+  }
+  uint32_t radix[3] = {out.vpr, 1u << 16, 1u << 16};
+  for (int k = 0; k < kBoxRows; ++k) {
+    out.lim[k] = kNone;
+    if (k >= nrow) continue;
+    const int d = p.ord_o[out.nrun + k];
+    const uint32_t ext = (uint32_t)p.box[d];
+    if (k < 2 && k + 1 < nrow) {
+      out.ext[k] = radix[k + 1] = ext;
+      out.ext_m[k] = inverse(ext);
+    }
+    out.stride[k] = (uint32_t)p.out.stride[d];
+    out.lim[k] = shift_of[d];
+    for (int y = 0; y < 2; ++y) out.pos[y][k] = pos[y][d];
+    rows *= ext;
+  }
+  out.nvec = out.vpr * rows;
+  out.niter = (out.nvec + f.block - 1) / f.block;
+  uint32_t rest = f.block;
+  for (int k = 0; k < 3; ++k) {
+    out.wrap[k] = radix[k];
+    out.add[k] = rest % radix[k];
+    rest /= radix[k];
+  }
+  out.add_c2 = rest;
+  auto per_pass = [&](uint32_t step, const uint32_t (&per)[kBoxRows], uint32_t &add, uint32_t (&wrap)[3]) {
+    add = out.add[0] * step + out.add[1] * per[0] + out.add[2] * per[1] + rest * per[2];
+    wrap[0] = per[0] - radix[0] * step;
+    wrap[1] = per[1] - radix[1] * per[0];
+    wrap[2] = per[2] - radix[2] * per[1];
+  };
+  per_pass(out.step, out.stride, out.add_off, out.wrap_off);
+  for (int y = 0; y < 2; ++y) per_pass(out.run[y], out.pos[y], out.add_pos[y], out.wrap_pos[y]);
   return f;
 }
 

@@ -22,6 +22,7 @@ void ew_launch_shape(const EwPlan &p, int64_t *grid, int64_t *block);
 TiledArgs make_tiled_args(const EwPlan &p, int es_a);
 FastTiledArgs make_fast_tiled_args(const EwPlan &p, int es_a);
 AnyTiledArgs make_any_tiled_args(const EwPlan &p, int es_a);
+BoxArgs make_box_args(const EwPlan &p);
 InterpArgs make_interp_args(const EwPlan &p);
 hipError_t launch_interp(const EwPlan &p, hipStream_t stream);
 hipError_t launch_interleave(const EwPlan &p, hipStream_t stream);
@@ -43,6 +44,9 @@ hipError_t launch_ew(const EwPlan &p, hipStream_t stream) {
   } else if (p.kernel == kKernelTiledAny) {
     const AnyTiledArgs args = make_any_tiled_args(p, (int)sizeof(typename G::SAt));
     hipLaunchKernelGGL((ew_tiled_any_kernel<G>), dim3((unsigned)p.grid), dim3(args.block), (size_t)p.lds_bytes, stream, args);
+  } else if (p.kernel == kKernelBox) {
+    const BoxArgs args = make_box_args(p);
+    hipLaunchKernelGGL((ew_box_kernel<G>), dim3((unsigned)p.grid), dim3(args.block), (size_t)p.lds_bytes, stream, args);
   } else if (p.fast_tiled) {
     const FastTiledArgs args = make_fast_tiled_args(p, (int)sizeof(typename G::SAt));
     hipLaunchKernelGGL((ew_tiled_fast_kernel<G>), dim3((unsigned)p.grid), dim3(kBlock), (size_t)p.lds_bytes, stream, args);

@@ -319,6 +319,171 @@ void choose_tiles(EwPlan &p, TileRule rule, int fa, int fb) {
   p.tile_bits = used;
 }
 
+// Boxes of any extents (ew_box_kernel).
+//
+// A box has about this many elements (twice as many of one or two bytes): staged inputs take 8 to 32 KiB
+// of LDS, so that four or more workgroups share a CU (4096 complex elements in 64 KiB: 49 us where
+// 2048 take 44), and a lane moves two to four vectors of each operand.
+constexpr int64_t kBoxElems = 2048;
+constexpr int64_t kBoxLds = 32 * 1024;
+// The contiguous bytes each operand should have in a box: two lines, since runs start anywhere and
+// touch one line more than they fill (6000 x 5000 plus a transpose: 69 us, 77 with 128 bytes).
+constexpr int64_t kBoxRun = 256;
+// Boxes in a row that one XCD takes.  Neighbouring boxes share the lines at the ends of their runs; dealt
+// out one by one every XCD fetches them for itself (complex products of [44, 66, 17, 71, 2]: 263 MB
+// fetched instead of 143, 55 us instead of 44; groups of 4 and 64 are within 6 % of 16, an eighth of
+// all boxes each is 5 to 20 % slower on plain transposes).
+constexpr int kBoxGroup = 16;
+
+// Lays the operation out in boxes; false where that form does not apply.  Extents grow from one, always
+// for the operand whose contiguous runs inside the box are shortest, along the axis that continues its
+// run (an axis covered whole passes the run on to the next one).  Axes are cut into equal parts at the
+// end.
+bool plan_boxes(EwPlan &p) {
+  const int n = p.ndim, nin = p.nin;
+  const Operand *ops[3] = {&p.out, &p.a, &p.b};
+  const int es[3] = {dt_size(p.out.dtype), dt_size(p.a.dtype), nin == 2 ? dt_size(p.b.dtype) : 1};
+  const int es_max = std::max({es[0], es[1], nin == 2 ? es[2] : es[1]});
+  const int V = box_vec_len(es[0], es_max);
+  for (int d = 0; d < n; ++d)
+    if (p.out.stride[d] < 0 || p.a.stride[d] < 0 || p.b.stride[d] < 0) return false;
+  if (p.out.stride[n - 1] != es[0]) return false;
+  // the dims of an operand, its fastest first (broadcast ones do not lengthen its runs)
+  int8_t ord[3][kMaxDims];
+  int nd[3] = {0, 0, 0};
+  for (int x = 0; x <= nin; ++x) {
+    for (int d = n - 1; d >= 0; --d)
+      if (ops[x]->stride[d] != 0 && p.size[d] > 1) ord[x][nd[x]++] = (int8_t)d;
+    std::stable_sort(ord[x], ord[x] + nd[x], [&](int8_t i, int8_t j) { return ops[x]->stride[i] < ops[x]->stride[j]; });
+  }
+  int32_t ext[kMaxDims];
+  for (int d = 0; d < kMaxDims; ++d) ext[d] = 1;
+  int64_t elems = 1;
+  // the contiguous bytes of operand x inside the box; dims its runs go along
+  auto run_of = [&](int x, int *dims) {
+    int64_t run = es[x];
+    int k = 0;
+    for (; k < nd[x]; ++k) {
+      const int d = ord[x][k];
+      if (ext[d] == 1 || ops[x]->stride[d] != run) break;
+      run *= ext[d];
+      if (ext[d] < p.size[d]) { ++k; break; }
+    }
+    if (dims) *dims = k;
+    return run;
+  };
+  int64_t most = es_max <= 2 ? 2 * kBoxElems : kBoxElems;
+  // (few boxes: smaller ones, down to a vector of the output per lane)
+  while (most > (int64_t)kBlock * V && p.numel / most < 2 * kNumCUs) most /= 2;
+  auto fits = [&](int64_t e) {
+    int64_t bytes = 0;
+    for (int x = 1; x <= nin; ++x) bytes += e * es[x];
+    return bytes <= kBoxLds;
+  };
+  // one step along the dim that continues operand x's runs; false if the box cannot grow there
+  auto grow = [&](int x) {
+    for (int k = 0; k < nd[x]; ++k) {
+      const int d = ord[x][k];
+      if (ext[d] >= p.size[d]) continue;
+      int tiled = 0;
+      for (int i = 0; i < n; ++i) tiled += ext[i] > 1;
+      if (ext[d] == 1 && tiled == 4) return false;
+      const int64_t others = elems / ext[d];
+      int64_t e = std::min<int64_t>(p.size[d], 2 * (int64_t)ext[d]);
+      if (3 * e >= 2 * p.size[d]) e = p.size[d];
+      while (e > ext[d] && (others * e > most || !fits(others * e) || e > 4096)) --e;
+      if (e == ext[d]) return false;
+      ext[d] = (int32_t)e;
+      elems = others * e;
+      return true;
+    }
+    return false;
+  };
+  for (bool open[3] = {true, true, nin == 2};;) {
+    int x = -1;
+    for (int y = 0; y < 3; ++y)
+      if (open[y] && (x < 0 || run_of(y, nullptr) < run_of(x, nullptr))) x = y;
+    if (x < 0) break;
+    // (at least two vectors of the output per lane: cdouble 5000 x 3001 transposed 94 us, 108 with one)
+    if (run_of(x, nullptr) >= kBoxRun && elems >= std::min<int64_t>(most, 2 * kBlock * V)) break;
+    if (!grow(x)) open[x] = false;
+  }
+  for (int d = 0; d < n; ++d) {
+    const int64_t parts = (p.size[d] + ext[d] - 1) / ext[d];
+    ext[d] = (int32_t)((p.size[d] + parts - 1) / parts);
+  }
+  elems = 1;
+  p.total_tiles = 1;
+  for (int d = 0; d < n; ++d) {
+    p.box[d] = ext[d];
+    elems *= ext[d];
+    p.ntiles[d] = (p.size[d] + ext[d] - 1) / ext[d];
+    p.total_tiles *= p.ntiles[d];
+  }
+  if (elems < 2 || p.total_tiles > max_launch_blocks()) return false;
+  // the orders inside the box, and how far runs go
+  for (int x = 0; x <= nin; ++x) {
+    int m = 0;
+    int8_t *o = x == 0 ? p.ord_o : x == 1 ? p.ord_a : p.ord_b;
+    for (int k = 0; k < nd[x]; ++k)
+      if (ext[ord[x][k]] > 1) o[m++] = ord[x][k];
+    p.box_dims[x] = m;
+    run_of(x, &p.box_run[x]);
+    int64_t span = 0, bytes = es[x];
+    bool whole = true;
+    for (int d = 0; d < n; ++d) {
+      span += (int64_t)ext[d] * ops[x]->stride[d];
+      bytes += (p.size[d] - 1) * ops[x]->stride[d];
+      whole = whole && ops[x]->stride[d] % es[x] == 0;
+    }
+    if (span >= ((int64_t)1 << 31) - 64) return false;
+    if (x > 0 && bytes < std::max<int64_t>(16, (int64_t)V * es[x]) + (whole ? 0 : es[x] - scalar_size(ops[x]->dtype))) return false;   // shorter than a vector
+  }
+  if (p.box_run[0] == 0 || p.box_dims[0] > 4) return false;
+  p.nord = p.box_dims[0];
+  p.box_run[0] = std::min(p.box_run[0], 3);
+  // An input that runs along with the output, or is broadcast along its runs, is read in place; any
+  // other one is staged, in vectors where it is contiguous along its fastest axis.
+  int64_t lds = 0;
+  for (int x = 1; x <= nin; ++x) {
+    bool along = true, broadcast = true;
+    int64_t run = es[x];
+    for (int k = 0; k < p.box_run[0]; ++k) {
+      const int d = p.ord_o[k];
+      along = along && ops[x]->stride[d] == run;
+      broadcast = broadcast && ops[x]->stride[d] == 0;
+      run *= ext[d];
+    }
+    const int8_t *o = x == 1 ? p.ord_a : p.ord_b;
+    if (along || broadcast) {
+      p.box_how[x - 1] = 1;
+    } else {
+      // (strided along its own fastest axis: the form for any alignment gathers such an input's elements)
+      if (p.box_run[x] == 0) return false;
+      p.box_how[x - 1] = 0;
+      int64_t rows = 1, len = 1;
+      for (int k = 0; k < p.box_dims[x]; ++k) (k < p.box_run[x] ? len : rows) *= ext[o[k]];
+      int64_t pitch = (len * es[x] + 15) / 16 * 16;
+      if (pitch % 32 == 0) pitch += 16;
+      lds += pitch * rows;
+    }
+  }
+  p.stage_a = p.box_how[0] == 0;
+  p.stage_b = nin == 2 && p.box_how[1] == 0;
+  p.lds_bytes = lds;
+  if (!p.stage_a && !p.stage_b) return false;
+  if (lds > 64 * 1024) return false;
+  p.tile_bits = ilog2_ceil(elems);
+  p.vecw_o = ilog2_ceil(V);
+  p.vec = V;
+  for (int d = 0; d < n; ++d) p.tile_log2[d] = ilog2_ceil(ext[d]);   // (plan inspection)
+  p.kernel = kKernelBox;
+  p.grid = p.total_tiles;
+  p.block = kBlock;
+  p.box_group = kBoxGroup;
+  return true;
+}
+
 }  // namespace
 
 namespace {
@@ -586,6 +751,25 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
       return OCN_OK;
     }
     if (rule == kTilesAny) {
+      // Boxes of any extents where the tiles above do not fit: over forty shapes of two to five dims,
+      // odd ones, and ten type combinations 0.97 to 5.3 times as fast as tiles of any alignment (6000 x
+      // 5000 plus a transpose 73.7 -> 69.3 us, float [200001, 17, 17] transposed 289 -> 105, complex
+      // products of [5, 25, 5, 38, 17] 15.3 -> 6.9), 0.88 in one (bytes [50001, 289] transposed).  Those
+      // keep what was not measured, 2^31 elements and more; inputs strided along their own fastest
+      // axis, which they gather (every other float of [200001, 17, 17] 174 us, 373 by elements in boxes);
+      // and of matrices: large ones of four bytes with one input, which gain 2 % (5000 x 3001 33.0 and
+      // 32.2), small ones that fill tiles of 64 x 64 to 70 %, and those with an output axis of a quarter
+      // vector, whose routes are part of what plan inspection has always reported.
+      const int64_t n0 = p.size[0], n1 = p.size[n - 1];
+      const bool matrix_in_tiles =
+          n == 2 && ((nin == 1 && es_o == 4 && es_a == 4 && n0 >= 1024 && n1 >= 1024) ||
+                     (numel < 1 << 19 && numel * 10 >= (n0 + 63) / 64 * 64 * ((n1 + 63) / 64 * 64) * 7) ||
+                     (n1 * 4 <= VT && (n1 & (n1 - 1)) == 0 && numel >= n1 << 19));
+      EwPlan q = p;
+      if (numel < (int64_t)1 << 31 && !matrix_in_tiles && plan_boxes(q)) {
+        *plan = q;
+        return OCN_OK;
+      }
       if (stage_a0 && p.size[fa] * es_a < 32) stage_a0 = false;
       if (stage_b0 && p.size[fb] * es_b < 32) stage_b0 = false;
     }
@@ -1498,7 +1682,7 @@ void plan_second_pass(const RedPlan &first, char *workspace, RedPlan *second) {
 
 void fill_info(const EwPlan &p, ocn_plan_info *info) {
   std::memset(info, 0, sizeof *info);
-  info->kernel = p.kernel == kKernelTiledAny ? (p.stage_a || p.stage_b ? OCN_KERNEL_EW_TILED : OCN_KERNEL_EW_GENERIC)
+  info->kernel = p.kernel == kKernelBox ? OCN_KERNEL_EW_TILED : p.kernel == kKernelTiledAny ? (p.stage_a || p.stage_b ? OCN_KERNEL_EW_TILED : OCN_KERNEL_EW_GENERIC)
                  : p.kernel == kKernelToPlanes || p.kernel == kKernelToPixels ? OCN_KERNEL_EW_GENERIC : p.kernel;
   info->compute_dtype = p.T;
   info->ndim = p.ndim;

@@ -50,6 +50,8 @@ struct Operand {
 constexpr int kKernelTiledAny = 100;
 // Copies and casts between planes and interleaved pixels (reported as OCN_KERNEL_EW_GENERIC).
 constexpr int kKernelToPlanes = 101, kKernelToPixels = 102;
+// Boxes of any extents (ew_box_kernel; reported as OCN_KERNEL_EW_TILED).
+constexpr int kKernelBox = 103;
 
 struct EwPlan {
   int kernel = OCN_KERNEL_NONE;
@@ -77,6 +79,11 @@ struct EwPlan {
   int64_t total_tiles = 0;
   bool specialised = false;     // a dtype-specialised kernel exists for this signature
   int block = kBlock;           // lanes per workgroup of the tiled form for any size and alignment
+  int32_t box[kMaxDims] = {0};  // boxes of any extents: the extent along every dim
+  int box_dims[3] = {0};        // ... dims in each operand's order (ord_o, ord_a, ord_b)
+  int box_run[3] = {0};         // ... how many of them its runs go along
+  int box_how[2] = {0};         // ... how each input is read
+  int32_t box_group = 0;        // ... boxes in a row that one XCD takes
   bool fast_tiled = false;      // tiled kernel: the unclipped all-vector form applies
   bool nt_store = false;        // the output is too large to stay cached: stream it past the caches
   bool nt_a = false, nt_b = false;  // rows kernel: that input is read with streaming loads

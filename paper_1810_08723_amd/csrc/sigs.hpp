@@ -124,6 +124,8 @@ OCN_HD constexpr int rows_unroll(int vec, int es_max) {
 OCN_HD constexpr int rows_stream_vec(int es_out, int es_min, int es_max) {
   return imax(1, imin(16 / es_out, imax(16 / es_max, 4 / es_min)));
 }
+// The box kernel's vector: the widest operand moves 16 bytes per lane.
+OCN_HD constexpr int box_vec_len(int es_out, int es_max) { return imax(1, imin(16 / es_out, 16 / es_max)); }
 // Vectors per lane: as many as it takes for the narrowest operand to move 16 bytes per lane
 // as well (at most four).  Operations on equal widths run fastest with one vector per lane
 // and as many workgroups as that takes (int32 x float over 2^26 elements: 88.3 us, against 91.2
