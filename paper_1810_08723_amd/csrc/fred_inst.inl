@@ -13,7 +13,7 @@ template <class G, int OP> hipError_t launch_fred(const RedPlan &p, char *partia
   switch (p.kernel) {
     case OCN_KERNEL_RED_ROWS:
       if (p.lean) {
-        hipLaunchKernelGGL((fred_rows_lean_kernel<G, OP>), dim3((unsigned)p.grid), dim3(kBlock), 0, stream,
+        hipLaunchKernelGGL((fred_rows_lean_kernel<G, OP>), dim3((unsigned)p.grid), dim3(lean_block(p)), 0, stream,
                            make_red_lean_args(p, partial));
         break;
       }

@@ -205,31 +205,44 @@ OCN_DEV typename FusedFold<G, OP>::A fred_lean_fold(const char *pa, const char *
   using SBt = typename G::SBt;
   static_assert(sizeof(SAt) == sizeof(SBt) && sizeof(SAt) <= 16, "equal input widths of at most 16 bytes");
   constexpr int V = 16 / (int)sizeof(SAt);
-  constexpr int U = 2;
+  constexpr int U = 4;
   A acc[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) acc[u] = F::R::identity();
-  uint32_t t = t0 + lane;
-  for (; t + (U - 1) * lanes < t1; t += U * lanes) {
+  // (trips are counted for all lanes alike: with the count of each lane its own, a row of 250 vectors is
+  // three round trips of a wavefront, for the lanes with four vectors and those with three)
+  uint32_t t = t0;
+  for (; t + U * lanes <= t1; t += U * lanes) {
     Pack<SAt, V> va[U];
     Pack<SBt, V> vb[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      load_vec<SAt, V, NT>(pa + (uint64_t)(t + u * lanes) * 16u, va[u]);
-      load_vec<SBt, V, NT>(pb + (uint64_t)(t + u * lanes) * 16u, vb[u]);
+      load_vec<SAt, V, NT>(pa + (uint64_t)(t + u * lanes + lane) * 16u, va[u]);
+      load_vec<SBt, V, NT>(pb + (uint64_t)(t + u * lanes + lane) * 16u, vb[u]);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int i = 0; i < V; ++i) acc[u] = F::add(acc[u], va[u].v[i], vb[u].v[i]);
   }
-  for (; t < t1; t += lanes) {
-    Pack<SAt, V> va;
-    Pack<SBt, V> vb;
-    load_vec<SAt, V, NT>(pa + (uint64_t)t * 16u, va);
-    load_vec<SBt, V, NT>(pb + (uint64_t)t * 16u, vb);
+  if (t < t1) {   // what is left, fewer than U per lane: lanes past the end load the last vector and drop it
+    Pack<SAt, V> va[U];
+    Pack<SBt, V> vb[U];
 #pragma unroll
-    for (int i = 0; i < V; ++i) acc[0] = F::add(acc[0], va.v[i], vb.v[i]);
+    for (int u = 0; u < U; ++u) {
+      if (t + u * lanes < t1) {
+        const uint32_t tt = t + u * lanes + lane < t1 ? t + u * lanes + lane : t1 - 1;
+        load_vec<SAt, V, NT>(pa + (uint64_t)tt * 16u, va[u]);
+        load_vec<SBt, V, NT>(pb + (uint64_t)tt * 16u, vb[u]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (t + u * lanes + lane < t1) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) acc[u] = F::add(acc[u], va[u].v[i], vb[u].v[i]);
+      }
+    }
   }
   A r = acc[0];
 #pragma unroll
@@ -237,13 +250,13 @@ OCN_DEV typename FusedFold<G, OP>::A fred_lean_fold(const char *pa, const char *
   return r;
 }
 
-template <class G, int OP> __global__ __launch_bounds__(kBlock) OCN_ROWS_OCC void fred_rows_lean_kernel(const RedLeanArgs p) {
+template <class G, int OP> __global__ __launch_bounds__(kLeanWaves * kWave) OCN_ROWS_OCC void fred_rows_lean_kernel(const RedLeanArgs p) {
   using F = FusedFold<G, OP>;
   using R = typename F::R;
   using A = typename F::A;
-  __shared__ A lds[kBlock / kWave];
+  __shared__ A lds[kLeanWaves];
   const uint32_t tid = threadIdx.x, lane_in_wave = tid & (kWave - 1), wave = tid / kWave;
-  const bool per_block = p.group == kBlock;
+  const bool per_block = p.group > kWave;
   const uint32_t gidx = per_block ? blockIdx.x : blockIdx.x * (kBlock / kWave) + wave;
   const bool active = gidx < p.nout * p.split;
   const uint32_t lane = per_block ? tid : lane_in_wave;
@@ -258,7 +271,7 @@ template <class G, int OP> __global__ __launch_bounds__(kBlock) OCN_ROWS_OCC voi
     }
     const char *pa = p.a + (int64_t)o * p.ksa;
     const char *pb = p.b + (int64_t)o * p.ksb;
-    const uint32_t lanes = per_block ? kBlock : kWave;
+    const uint32_t lanes = (uint32_t)p.group;
     if (p.nt_load) acc = fred_lean_fold<G, OP, true>(pa, pb, t0, t1, lane, lanes);
     else acc = fred_lean_fold<G, OP, false>(pa, pb, t0, t1, lane, lanes);
     // the elements behind the last whole vector: one lane of the last split
@@ -275,6 +288,7 @@ template <class G, int OP> __global__ __launch_bounds__(kBlock) OCN_ROWS_OCC voi
     if (tid == 0) {
 #pragma unroll
       for (int w = 1; w < kBlock / kWave; ++w) acc = R::combine(acc, lds[w]);
+      for (int w = kBlock / kWave; w < p.group / kWave; ++w) acc = R::combine(acc, lds[w]);
     }
   }
   if (active && lane == 0) {
@@ -342,9 +356,17 @@ template <class G, int OP> __global__ __launch_bounds__(kBlock) void fred_rows_s
 // cols: a kept axis is the fastest of the inputs; lanes own output columns
 // ---------------------------------------------------------------------------------------
 
-// NT: both inputs are read with streaming loads (one 16-byte piece per lane each).  SINGLE:
-// one reduced dim, so that row r lies r strides further on (no index decomposition).
-template <class G, int OP, int V, bool NT, bool SINGLE>
+// NT: inputs that are not broadcast are read with streaming loads (one 16-byte piece per lane each).
+// BC: the input that is broadcast along the columns (1: a, 2: b, 0: neither); -1: told at run time, for
+// several reduced dims and for columns taken one per lane.  With one reduced dim, row r lies r strides
+// further on (no index decomposition).
+//
+// Bound by how many rows a wavefront has in flight.  A broadcast input lands in the first slot of its
+// vector and is spread out once all loads of the trip are issued: spread right away, in a branch on
+// a flag, every row's loads were waited for before the next row's were issued (fp32 [16384, 1000] times
+// a column 18.0 -> 14.4 us, double [31614, 512] 36.7 -> 26.7, fp32 [1712, 22] 12.4 -> 6.7; 4.5 TB/s at the
+// first).
+template <class G, int OP, int V, bool NT, int BC>
 OCN_DEV void fred_cols_body(KRedArgs &p, typename FusedFold<G, OP>::A *lds) {
   using F = FusedFold<G, OP>;
   using R = typename F::R;
@@ -398,7 +420,6 @@ OCN_DEV void fred_cols_body(KRedArgs &p, typename FusedFold<G, OP>::A *lds) {
   const int64_t r0 = (int64_t)s * p.chunk;
   int64_t r1 = r0 + p.chunk;
   if (r1 > p.nredtot) r1 = p.nredtot;
-  constexpr int U = 2;
   // each wavefront takes one contiguous run of the workgroup's rows, RPW rows at a time (as in
   // red_cols_kernel: rows dealt out in turn measured 10 % slower there)
   const int RS = RPW;
@@ -406,24 +427,53 @@ OCN_DEV void fred_cols_body(KRedArgs &p, typename FusedFold<G, OP>::A *lds) {
   const int64_t w0 = r0 + (int64_t)wave * per_wave;
   if (w0 + per_wave < r1) r1 = w0 + per_wave;
   int64_t r = w0 + lr;
-  auto row_offsets = [&](int64_t rr, int64_t &oa, int64_t &ob) {
-    if constexpr (SINGLE) {
-      oa = rr * p.rsa[0];
-      ob = rr * p.rsb[0];
-    } else {
-      reduced_offset2(p, (uint32_t)rr, 0, oa, ob);
+  if constexpr (BC >= 0) {
+    if (ncol == V) {
+      constexpr int U = V * (int)(sizeof(SAt) > sizeof(SBt) ? sizeof(SAt) : sizeof(SBt)) <= 16 ? 4 : 2;   // rows in flight (eight: the same)
+      const int64_t sa = (int64_t)RS * p.rsa[0], sb = (int64_t)RS * p.rsb[0];
+      const char *qa = p.a + off_a + r * p.rsa[0], *qb = p.b + off_b + r * p.rsb[0];
+      auto load = [&](const char *ra, const char *rb, Pack<SAt, V> &va, Pack<SBt, V> &vb) {
+        if constexpr (BC == 1) va.v[0] = *reinterpret_cast<const SAt *>(ra);
+        else load_vec<SAt, V, NT && sizeof(SAt) * V == 16>(ra, va);
+        if constexpr (BC == 2) vb.v[0] = *reinterpret_cast<const SBt *>(rb);
+        else load_vec<SBt, V, NT && sizeof(SBt) * V == 16>(rb, vb);
+      };
+      auto add = [&](const Pack<SAt, V> &va, const Pack<SBt, V> &vb) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) acc[i] = F::add(acc[i], va.v[BC == 1 ? 0 : i], vb.v[BC == 2 ? 0 : i]);
+      };
+      for (; r + (int64_t)(U - 1) * RS < r1; r += RS * U) {
+        Pack<SAt, V> va[U];
+        Pack<SBt, V> vb[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          load(qa, qb, va[u], vb[u]);
+          qa += sa;
+          qb += sb;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) add(va[u], vb[u]);
+      }
+      for (; r < r1; r += RS) {
+        Pack<SAt, V> va;
+        Pack<SBt, V> vb;
+        load(qa, qb, va, vb);
+        qa += sa;
+        qb += sb;
+        add(va, vb);
+      }
     }
-  };
-  if (ncol == V) {
+  } else if (ncol == V) {
+    constexpr int U = 2;
     for (; r + (int64_t)(U - 1) * RS < r1; r += RS * U) {
       Pack<SAt, V> va[U];
       Pack<SBt, V> vb[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         int64_t oa, ob;
-        row_offsets(r + (int64_t)u * RS, oa, ob);
-        fused_load<SAt, V, NT>(p.a + off_a + oa, abc, va[u]);
-        fused_load<SBt, V, NT>(p.b + off_b + ob, bbc, vb[u]);
+        reduced_offset2(p, (uint32_t)(r + (int64_t)u * RS), 0, oa, ob);
+        fused_load<SAt, V>(p.a + off_a + oa, abc, va[u]);
+        fused_load<SBt, V>(p.b + off_b + ob, bbc, vb[u]);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u)
@@ -431,10 +481,10 @@ OCN_DEV void fred_cols_body(KRedArgs &p, typename FusedFold<G, OP>::A *lds) {
         for (int i = 0; i < V; ++i) acc[i] = F::add(acc[i], va[u].v[i], vb[u].v[i]);
     }
   }
-  if (ncol > 0) {  // remaining rows, and the ragged last column block
+  if (ncol > 0) {  // remaining rows, and fewer columns than a vector holds
     for (; r < r1; r += RS) {
       int64_t oa, ob;
-      row_offsets(r, oa, ob);
+      reduced_offset2(p, (uint32_t)r, 0, oa, ob);
       const char *qa = p.a + off_a + oa, *qb = p.b + off_b + ob;
 #pragma unroll
       for (int i = 0; i < V; ++i)
@@ -481,12 +531,14 @@ template <class G, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) v
   extern __shared__ __align__(16) unsigned char fred_cols_lds_raw[];
   A *lds = reinterpret_cast<A *>(fred_cols_lds_raw);
   if (p.vec > 1 && p.nred == 1) {
-    if (p.nt_load) fred_cols_body<G, OP, G::V, true, true>(p, lds);
-    else fred_cols_body<G, OP, G::V, false, true>(p, lds);
+    if (p.b_bcast) fred_cols_body<G, OP, G::V, false, 2>(p, lds);
+    else if (p.a_bcast) fred_cols_body<G, OP, G::V, false, 1>(p, lds);
+    else if (p.nt_load) fred_cols_body<G, OP, G::V, true, 0>(p, lds);
+    else fred_cols_body<G, OP, G::V, false, 0>(p, lds);
   } else if (p.vec > 1) {
-    fred_cols_body<G, OP, G::V, false, false>(p, lds);
+    fred_cols_body<G, OP, G::V, false, -1>(p, lds);
   } else {
-    fred_cols_body<G, OP, 1, false, false>(p, lds);
+    fred_cols_body<G, OP, 1, false, -1>(p, lds);
   }
 }
 

@@ -1032,6 +1032,11 @@ constexpr int64_t kTargetWaves = OCN_RED_TARGET_WAVES;  // enough wavefronts to 
 // 6, 12 and 16 per CU; the count of a > b over 2^26 pairs: 81.7 against 83.2 with 16).  The
 // general kernel's element loads want the sixteen (full sum of a stride-2 view: 96 against 104 us).
 constexpr int64_t kLeanSplitWaves = 256 * 8;
+// Outputs of at most this many bytes of input that would be split (a chip hardly filled) are taken whole
+// by sixteen wavefronts each: one reads 256 KiB in about 2 us, and the second launch of a split
+// reduction costs 4 to 5.
+constexpr int64_t kOneWorkgroupBytes = 256 * 1024;
+constexpr int kLeanMaxLanes = 1024;
 
 // Launch shape of the column kernels (plain and fused): lanes per row of columns, wavefronts per
 // workgroup, and workgroups that share a column block through the workspace.
@@ -1156,10 +1161,14 @@ void choose_reduce_launch(RedPlan &p) {
       const int64_t per_lane = p.vec > 1 && p.nred > 1 && nvec >= (int64_t)p.group * 16 ? 4 : 16;
       const int64_t most = std::max<int64_t>(1, nvec / ((int64_t)p.group * per_lane));
       p.split = std::max<int64_t>(1, std::min(want, most));
+      if (p.split > 1 && lean_shape && nvec * 16 <= kOneWorkgroupBytes) {
+        p.split = 1;
+        p.group = p.block = kLeanMaxLanes;
+      }
     }
     p.chunk = (nvec + p.split - 1) / p.split;
     p.split = (nvec + p.chunk - 1) / p.chunk;
-    p.grid = (p.nout * p.split + groups_per_block - 1) / groups_per_block;
+    p.grid = p.group > kBlock ? p.nout : (p.nout * p.split + groups_per_block - 1) / groups_per_block;
     p.short_rows = p.group <= kWave && nvec <= p.group && p.nred == 1 && p.split == 1 &&
                    p.nout * p.group < ((int64_t)1 << 32) && n0 < ((int64_t)1 << 31);
     p.lean = !p.short_rows && lean_shape && p.nout * p.split < ((int64_t)1 << 31) && p.chunk < ((int64_t)1 << 31);
@@ -1380,7 +1389,7 @@ void choose_fused_launch(RedPlan &p) {
     if (!p.short_rows && lv >= 1 && p.nred == 1 && p.nkept <= 1 && !p.a_fast_bcast && !p.b_fast_bcast &&
         n0 / lv >= kWave && n0 / lv < ((int64_t)1 << 31) && p.nout < ((int64_t)1 << 31)) {
       const int64_t nv = n0 / lv;
-      const int group = nv * 32 <= 16 * 1024 ? kWave : kBlock;    // as above: rows of up to 16 KiB take a wavefront
+      int group = nv * 32 <= 16 * 1024 ? kWave : kBlock;          // as above: rows of up to 16 KiB take a wavefront
       const int64_t lwaves = (p.nout * group + kWave - 1) / kWave;
       int64_t split = 1;
       if (lwaves < kTargetWaves) {
@@ -1388,15 +1397,20 @@ void choose_fused_launch(RedPlan &p) {
         const int64_t most = std::max<int64_t>(1, nv / ((int64_t)group * 8));
         split = std::max<int64_t>(1, std::min(want, most));
       }
+      if (split > 1 && nv * 32 <= kOneWorkgroupBytes) {
+        split = 1;
+        group = kLeanMaxLanes;
+      }
       const int64_t chunk = (nv + split - 1) / split;
       split = (nv + chunk - 1) / chunk;
       if (p.nout * split < ((int64_t)1 << 31)) {
         p.lean = true;
         p.vec = lv;
         p.group = group;
+        p.block = std::max(group, kBlock);
         p.split = split;
         p.chunk = chunk;
-        p.grid = (p.nout * split + kBlock / group - 1) / (kBlock / group);
+        p.grid = group > kBlock ? p.nout : (p.nout * split + kBlock / group - 1) / (kBlock / group);
         // inputs far larger than the caches are streamed; one that is broadcast along the kept
         // dim is re-read by every output and stays cacheable, and then so does the other (one flag)
         const bool a_rows = p.nkept == 0 || p.kstride_a[0] != 0, b_rows = p.nkept == 0 || p.kstride_b[0] != 0;
@@ -1423,6 +1437,9 @@ void choose_fused_launch(RedPlan &p) {
     // inputs far larger than the caches, each read as one 16-byte piece per lane and broadcast
     // along no dim: streaming loads
     {
+      // (not where one is a column vector: the other is then a matrix that the next product reads again, and up
+      // to 256 MB it finds there what this one left; streamed, the products of [16384, 1000] with a
+      // column and then with a row take 14.4 + 13.7 us, 14.9 + 11.6 so)
       bool plain = aligned && p.vec > 1 && (int64_t)p.vec * es_a == 16 && (int64_t)p.vec * es_b == 16;
       for (int d = 0; d < p.nkept; ++d) plain = plain && p.kstride_a[d] != 0 && p.kstride_b[d] != 0;
       for (int d = 0; d < p.nred; ++d) plain = plain && p.rstride_a[d] != 0 && p.rstride_b[d] != 0;

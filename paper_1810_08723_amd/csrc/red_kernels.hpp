@@ -672,18 +672,21 @@ OCN_DEV typename Reducer<S, OP>::A lean_fold(const char *base, uint32_t t0, uint
   return acc;
 }
 
+// Wavefronts that share an output: one, four, or sixteen where a single output is short enough that
+// one workgroup takes it whole (no second launch).
+constexpr int kLeanWaves = 16;
 // (TAIL: outputs have elements behind their last whole vector.  A kernel of its own, so that whole
 // vectors do not pay for the test: int8 full sum of 2^28 41.5 us, 41.8 with it.)
-template <int S, int OP, bool TAIL> __global__ __launch_bounds__(kBlock) OCN_ROWS_OCC void red_rows_lean_kernel(const RedLeanArgs q) {
+template <int S, int OP, bool TAIL> __global__ __launch_bounds__(kLeanWaves * kWave) OCN_ROWS_OCC void red_rows_lean_kernel(const RedLeanArgs q) {
   using R = Reducer<S, OP>;
   using A = typename R::A;
   if constexpr (sizeof(storage_t<S>) < 16) {
     RedLeanArgs p = q;
     OCN_ARGS_NOW("s"(p.a), "s"(p.out), "s"(p.partial), "s"(p.ksa), "s"(p.kso), "s"(p.nout), "s"(p.split), "s"(p.nvec),
                  "s"(p.chunk), "s"(p.out_dtype), "s"(p.group), "s"(p.nt_load), "s"(p.swap_a), "s"(p.swap_o));
-    __shared__ A lds[kBlock / kWave];
+    __shared__ A lds[kLeanWaves];
     const uint32_t tid = threadIdx.x, lane_in_wave = tid & (kWave - 1), wave = tid / kWave;
-    const bool per_block = p.group == kBlock;
+    const bool per_block = p.group > kWave;
     const uint32_t gidx = per_block ? blockIdx.x : blockIdx.x * (kBlock / kWave) + wave;
     const bool active = gidx < p.nout * p.split;
     const uint32_t lane = per_block ? tid : lane_in_wave;
@@ -700,7 +703,7 @@ template <int S, int OP, bool TAIL> __global__ __launch_bounds__(kBlock) OCN_ROW
     }
     const char *base = p.a + (int64_t)o * p.ksa;
     if (active) {
-      const uint32_t lanes = per_block ? kBlock : kWave;
+      const uint32_t lanes = (uint32_t)p.group;
       if (p.swap_a) {
         if (p.nt_load) acc = lean_fold<S, OP, true, true>(base, t0, t1, lane, lanes);
         else acc = lean_fold<S, OP, false, true>(base, t0, t1, lane, lanes);
@@ -725,6 +728,7 @@ template <int S, int OP, bool TAIL> __global__ __launch_bounds__(kBlock) OCN_ROW
       if (tid == 0) {
 #pragma unroll
         for (int w = 1; w < kBlock / kWave; ++w) acc = R::combine(acc, lds[w]);
+        for (int w = kBlock / kWave; w < p.group / kWave; ++w) acc = R::combine(acc, lds[w]);
       }
     }
     if (active && lane == 0) {

@@ -15,6 +15,9 @@ extern RedLauncher g_fused_launchers[B_COUNT][DT_COUNT][R_COUNT];
 RedArgs make_red_args(const RedPlan &p, char *partial);
 RedLeanArgs make_red_lean_args(const RedPlan &p, char *partial);
 
+// lanes per workgroup of the lean rows kernels
+inline unsigned lean_block(const RedPlan &p) { return p.group > kBlock ? (unsigned)p.group : (unsigned)kBlock; }
+
 #if defined(__HIPCC__)
 template <int S, int OP> hipError_t launch_red(const RedPlan &p, char *partial, hipStream_t stream) {
   const RedArgs args = make_red_args(p, partial);
@@ -22,8 +25,8 @@ template <int S, int OP> hipError_t launch_red(const RedPlan &p, char *partial, 
     case OCN_KERNEL_RED_ROWS:
       if (p.lean) {
         const RedLeanArgs lean = make_red_lean_args(p, partial);
-        if (lean.tail) hipLaunchKernelGGL((red_rows_lean_kernel<S, OP, true>), dim3((unsigned)p.grid), dim3(kBlock), 0, stream, lean);
-        else hipLaunchKernelGGL((red_rows_lean_kernel<S, OP, false>), dim3((unsigned)p.grid), dim3(kBlock), 0, stream, lean);
+        if (lean.tail) hipLaunchKernelGGL((red_rows_lean_kernel<S, OP, true>), dim3((unsigned)p.grid), dim3(lean_block(p)), 0, stream, lean);
+        else hipLaunchKernelGGL((red_rows_lean_kernel<S, OP, false>), dim3((unsigned)p.grid), dim3(lean_block(p)), 0, stream, lean);
         break;
       }
       if (p.short_rows) {
