@@ -249,36 +249,47 @@ __global__ __launch_bounds__(kBlock) void mask_count_kernel(const MaskArgs p) {
   if (threadIdx.x == 0) p.block_counts[blockIdx.x] = sum;
 }
 
-// The same counts for a contiguous mask: a wavefront per chunk of kMaskChunk bytes, every lane
-// with four 16-byte loads in flight (the loads of a wavefront cover 1 KiB each), no LDS and no
-// barrier; four chunks per workgroup.  (One load per lane and a workgroup per chunk read a
-// 64 MB mask at 3 TB/s.)
-__global__ __launch_bounds__(kBlock) void mask_count_contig_kernel(const MaskArgs p) {
+// The same counts for a contiguous mask: a wavefront per chunk of kMaskChunk bytes, every lane with four
+// 16-byte loads in flight (the loads of a wavefront cover 1 KiB each), a workgroup per kMaskGroup chunks,
+// and its total as well.  (One load per lane and a workgroup per chunk read a 64 MB mask at 3 TB/s; four
+// chunks per wavefront 30 MB in 7.5 us.)
+constexpr int kMaskGroup = 16;
+__global__ __launch_bounds__(kMaskGroup * kWave) void mask_count_contig_kernel(const MaskArgs p) {
+  __shared__ uint32_t lds[kMaskGroup];
   const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const uint32_t chunk = blockIdx.x * (kBlock / kWave) + wave;
-  if (chunk >= p.nblocks) return;     // whole wavefronts leave together
-  const uint32_t base = chunk * (uint32_t)kMaskChunk;
+  const uint32_t chunk = blockIdx.x * (uint32_t)kMaskGroup + wave;
   uint32_t c = 0;
-  constexpr int kPieces = kMaskChunk / (kWave * 16);
-  uint4 v[kPieces];
+  if (chunk < p.nblocks) {            // (the same for all lanes of a wavefront)
+    const uint32_t base = chunk * (uint32_t)kMaskChunk;
+    constexpr int kPieces = kMaskChunk / (kWave * 16);
+    uint4 v[kPieces];
 #pragma unroll
-  for (int k = 0; k < kPieces; ++k) {
-    const uint32_t e = base + (uint32_t)k * (kWave * 16) + lane * 16u;
-    v[k] = make_uint4(0u, 0u, 0u, 0u);
-    if (e + 16u <= p.n) {
-      v[k] = *reinterpret_cast<const uint4 *>(p.mask + e);
-    } else if (e < p.n) {               // the ragged end of the mask, byte by byte
-      uint32_t w[4] = {0u, 0u, 0u, 0u};
-      for (uint32_t i = 0; e + i < p.n; ++i)
-        w[i >> 2] |= (uint32_t) * reinterpret_cast<const uint8_t *>(p.mask + e + i) << (8 * (i & 3));
-      v[k] = make_uint4(w[0], w[1], w[2], w[3]);
+    for (int k = 0; k < kPieces; ++k) {
+      const uint32_t e = base + (uint32_t)k * (kWave * 16) + lane * 16u;
+      v[k] = make_uint4(0u, 0u, 0u, 0u);
+      if (e + 16u <= p.n) {
+        v[k] = *reinterpret_cast<const uint4 *>(p.mask + e);
+      } else if (e < p.n) {               // the ragged end of the mask, byte by byte
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+        for (uint32_t i = 0; e + i < p.n; ++i)
+          w[i >> 2] |= (uint32_t) * reinterpret_cast<const uint8_t *>(p.mask + e + i) << (8 * (i & 3));
+        v[k] = make_uint4(w[0], w[1], w[2], w[3]);
+      }
     }
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) c += nonzero_bytes(v[k]);
+#pragma unroll
+    for (int d = kWave / 2; d >= 1; d >>= 1) c += (uint32_t)__shfl_xor((int)c, d, kWave);
+    if (lane == 0) p.block_counts[chunk] = c;
   }
+  if (lane == 0) lds[wave] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t total = 0;
 #pragma unroll
-  for (int k = 0; k < kPieces; ++k) c += nonzero_bytes(v[k]);
-#pragma unroll
-  for (int d = kWave / 2; d >= 1; d >>= 1) c += (uint32_t)__shfl_xor((int)c, d, kWave);
-  if (lane == 0) p.block_counts[chunk] = c;
+    for (int w = 0; w < kMaskGroup; ++w) total += lds[w];
+    p.block_counts[p.nblocks + blockIdx.x] = total;
+  }
 }
 
 // one workgroup: block_counts[i] := sum of block_counts[0 .. i), *count := total.  Rounds of
@@ -342,16 +353,22 @@ __global__ __launch_bounds__(kScanBlock) void mask_scan_kernel(const MaskArgs p)
 // A workgroup of the write kernel takes a chunk and needs the number of elements that are selected
 // before it:
 //   kBeforeCount  adds up the mask itself up to there: no other launch at all (contiguous masks of at
-//                 most kMaskDirect elements: the last workgroup reads 60 KiB, a few round trips,
-//                 against the 2.5 us and more that each further launch costs);
-//   kBeforeSum    adds up the chunk counts up to there, which saves the scan launch; the counts are read
-//                 once per workgroup, so
-//   kBeforeScan   reads its prefix where they are more than kMaskSumChunks (8.4 million elements; at 30
-//                 million the sums cost 9 us, the scan 6.3).
-enum { kBeforeCount = 0, kBeforeSum = 1, kBeforeScan = 2 };
-constexpr uint32_t kMaskDirect = 65536, kMaskSumChunks = 2048;
+//                 most kMaskDirect elements: the last workgroup reads 96 KiB in two trips of sixteen
+//                 loads, against the 2.5 us and more that each further launch costs; at 100 000 elements
+//                 the kernel takes 7.3 us, 3.4 and 5.0 in two launches, at 260 000 13.6);
+//   kBeforeGroups adds up the totals of the groups of chunks before its own and the counts inside it
+//                 (contiguous masks of up to kMaskSumGroups groups, 67 million elements: 4 KiB read
+//                 per workgroup at most, which hide behind the others' stores);
+//   kBeforeSum    adds up the chunk counts (other masks of up to kMaskSumChunks chunks);
+//   kBeforeScan   reads its prefix, for which a launch of one workgroup scans the counts (6.0 us for the
+//                 7325 chunks of 30 million elements).
+enum { kBeforeCount = 0, kBeforeSum = 1, kBeforeScan = 2, kBeforeGroups = 3 };
+constexpr uint32_t kMaskDirect = 98304, kMaskSumChunks = 2048, kMaskSumGroups = 1024;
 
-__global__ __launch_bounds__(kBlock) void mask_write_kernel(const MaskArgs p) {
+// FLAT: a contiguous mask and offsets that advance by one stride.  Bound by instructions as much as by the
+// 120 MB of offsets of 30 million elements with half of them selected: two offsets per lane and store, whole
+// lines, no index decomposition (35.1 -> 30.4 us in a trace of threshold, count and this, 5 TB/s).
+template <bool FLAT> __global__ __launch_bounds__(kBlock) void mask_write_kernel(const MaskArgs p) {
   __shared__ uint32_t lds[kBlock / kWave], lds_before[kBlock / kWave];
   // the positions (inside this workgroup's chunk) of its selected elements, in order: 8 KiB,
   // where the offsets themselves would take 32 KiB and leave room for five workgroups per CU
@@ -362,9 +379,14 @@ __global__ __launch_bounds__(kBlock) void mask_write_kernel(const MaskArgs p) {
   if (p.before != kBeforeScan) {
     uint32_t c = 0;
     if (p.before == kBeforeCount) {
-#pragma unroll 4
+#pragma unroll 16
       for (uint32_t e = threadIdx.x * 16u; e < chunk0; e += kBlock * 16u)
         c += nonzero_bytes(*reinterpret_cast<const uint4 *>(p.mask + e));
+    } else if (p.before == kBeforeGroups) {
+      const uint32_t g = chunk / kMaskGroup;
+      if (threadIdx.x < chunk % kMaskGroup) c = p.block_counts[g * kMaskGroup + threadIdx.x];
+#pragma unroll 4
+      for (uint32_t i = threadIdx.x; i < g; i += kBlock) c += p.block_counts[p.nblocks + i];
     } else {
 #pragma unroll 4
       for (uint32_t i = threadIdx.x; i < chunk; i += kBlock) c += p.block_counts[i];
@@ -391,18 +413,41 @@ __global__ __launch_bounds__(kBlock) void mask_write_kernel(const MaskArgs p) {
     if (chunk + 1 == p.nblocks && threadIdx.x == 0) *p.count = base + sum;
   }
   // coalesced stores behind this workgroup's prefix; a position becomes its offset on the way out
-  for (uint32_t i = threadIdx.x; i < sum; i += kBlock)
-    if (base + i < p.capacity) {
-      int64_t om, ot;
-      mask_decode(p, chunk0 + (uint32_t)staged[i], om, ot);
+  if constexpr (FLAT) {
+    using Two = long long __attribute__((ext_vector_type(2)));
+    const int64_t stride = p.ndim > 0 ? p.st[0] : 0, origin = (int64_t)chunk0 * stride;
+    const int64_t room = p.capacity - base;          // offsets that may be stored
+    const uint32_t end = room < 0 ? 0u : room < (int64_t)sum ? (uint32_t)room : sum;
+    int64_t *out = p.offsets + base;
+    // up to the first line, pairs in whole lines from there (a streaming store of part of a line is slow),
+    // the one behind the last pair
+    const uint32_t to_line = (uint32_t)((128u - ((uintptr_t)out & 127u)) & 127u) / 8u, head = to_line < end ? to_line : end;
+    if (threadIdx.x < head) out[threadIdx.x] = origin + (int64_t)staged[threadIdx.x] * stride;
+    if (threadIdx.x == kBlock - 1 && ((end - head) & 1u)) out[end - 1] = origin + (int64_t)staged[end - 1] * stride;
+    for (uint32_t i = head + threadIdx.x * 2u; i + 1u < end; i += kBlock * 2u) {
+      const Two t = {(long long)(origin + (int64_t)staged[i] * stride), (long long)(origin + (int64_t)staged[i + 1] * stride)};
       if (p.nt_store) {  // (the empty asm keeps the compiler from merging the two stores and dropping the hint)
         asm volatile("");
-        __builtin_nontemporal_store(ot, p.offsets + base + i);
+        __builtin_nontemporal_store(t, reinterpret_cast<Two *>(out + i));
         asm volatile("");
       } else {
-        p.offsets[base + i] = ot;
+        *reinterpret_cast<Two *>(out + i) = t;
       }
     }
+  } else {
+    for (uint32_t i = threadIdx.x; i < sum; i += kBlock)
+      if (base + i < p.capacity) {
+        int64_t om, ot;
+        mask_decode(p, chunk0 + (uint32_t)staged[i], om, ot);
+        if (p.nt_store) {
+          asm volatile("");
+          __builtin_nontemporal_store(ot, p.offsets + base + i);
+          asm volatile("");
+        } else {
+          p.offsets[base + i] = ot;
+        }
+      }
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -773,16 +818,16 @@ int ocn_mask_offsets(const ocn_tensor *mask, const int64_t *target_strides, void
   m.capacity = capacity;
   m.count = (int64_t *)count;
   m.nt_store = std::min<int64_t>(capacity, m.n) * 8 >= ((int64_t)32 << 20);  // too large to stay cached
-  m.before = m.contig && m.n <= kMaskDirect ? kBeforeCount : m.nblocks <= kMaskSumChunks ? kBeforeSum : kBeforeScan;
+  const uint32_t groups = (m.nblocks + kMaskGroup - 1) / kMaskGroup;
+  m.before = m.contig ? (m.n <= kMaskDirect ? kBeforeCount : groups <= kMaskSumGroups ? kBeforeGroups : kBeforeScan)
+                      : (m.nblocks <= kMaskSumChunks ? kBeforeSum : kBeforeScan);
   if (m.before != kBeforeCount) {
-    if (m.contig)
-      hipLaunchKernelGGL(mask_count_contig_kernel, dim3((m.nblocks + kBlock / kWave - 1) / (kBlock / kWave)), dim3(kBlock),
-                         0, s, m);
-    else
-      hipLaunchKernelGGL(mask_count_kernel, dim3(m.nblocks), dim3(kBlock), 0, s, m);
+    if (m.contig) hipLaunchKernelGGL(mask_count_contig_kernel, dim3(groups), dim3(kMaskGroup * kWave), 0, s, m);
+    else hipLaunchKernelGGL(mask_count_kernel, dim3(m.nblocks), dim3(kBlock), 0, s, m);
   }
   if (m.before == kBeforeScan) hipLaunchKernelGGL(mask_scan_kernel, dim3(1), dim3(kScanBlock), 0, s, m);
-  hipLaunchKernelGGL(mask_write_kernel, dim3(m.nblocks), dim3(kBlock), 0, s, m);
+  if (m.contig && m.ndim <= 1) hipLaunchKernelGGL(mask_write_kernel<true>, dim3(m.nblocks), dim3(kBlock), 0, s, m);
+  else hipLaunchKernelGGL(mask_write_kernel<false>, dim3(m.nblocks), dim3(kBlock), 0, s, m);
   return done(hipGetLastError());
 }
 
