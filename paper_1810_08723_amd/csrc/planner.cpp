@@ -1089,6 +1089,31 @@ ColsShape choose_cols_shape(int64_t col_lanes, int64_t others, int64_t rows, int
   return r;
 }
 
+// Lanes per row of columns where the columns are cut into equal blocks and a workgroup's 1024 lanes go on
+// through further rows (cols_flat_body); 0 where blocks of `cpw` lanes are as good.  Blocks of a power
+// of two lanes leave the last one mostly empty, and with few workgroups per CU its CU idles too: what
+// counts is the lanes of the fullest CU.  A reduction that would be split over its rows takes this form
+// if it fills three quarters of the chip evenly by itself, which saves the second launch (not in blocks
+// below 24 lanes where its rows are whole lines: [20, 4000, 800] floats 45.1 us split, 49.6 in 17 lanes).
+// Floats [64, 2000, 516] 73 -> 47 us, [128, 512, 132] 15.6 -> 9.4, [200, 1000, 280] 47 -> 37; halves [48, 1000,
+// 777] 27.7 -> 19.8.
+constexpr int kFlatLanes = 1024;
+int choose_flat_columns(int64_t col_lanes, int64_t others, int64_t rows, int cpw, int64_t split, bool aligned) {
+  const int64_t blocks = (col_lanes + cpw - 1) / cpw;
+  if (blocks < 2 || blocks * others > 4 * kNumCUs || col_lanes > 4096 || rows < 128) return 0;
+  // (at least 15 % fewer lanes than the fullest CU has; at most a quarter more than an even share)
+  int64_t best = split > 1 ? col_lanes * others * 5 / (4 * kNumCUs) + 1 : (blocks * others + kNumCUs - 1) / kNumCUs * cpw * 85 / 100;
+  int lanes = 0;
+  for (int64_t n = (col_lanes + kFlatLanes / 4 - 1) / (kFlatLanes / 4); n * 16 <= col_lanes && n * others <= 2 * kNumCUs; ++n) {
+    const int64_t l = (col_lanes + n - 1) / n, groups = (col_lanes + l - 1) / l * others, cost = (groups + kNumCUs - 1) / kNumCUs * l;
+    if (cost < best && rows >= kFlatLanes / l * 8 && (split == 1 || (groups * 4 >= 3 * kNumCUs && l >= (aligned ? 24 : 16)))) {
+      best = cost;
+      lanes = (int)l;
+    }
+  }
+  return lanes;
+}
+
 void choose_reduce_launch(RedPlan &p) {
   const int es = dt_size(p.a_dtype);
   const int acc_es = dt_size(p.acc_dtype);
@@ -1183,7 +1208,14 @@ void choose_reduce_launch(RedPlan &p) {
     const ColsShape shape = choose_cols_shape(col_lanes, others, p.nredtot, p.nout, acc_es, !aligned);
     p.cpw = shape.cpw;
     p.split = shape.split;
-    const int nw = shape.nw;
+    int nw = shape.nw;
+    const int flat = p.nred == 1 && p.vec > 1 && p.vec <= 8 ? choose_flat_columns(col_lanes, others, p.nredtot, p.cpw, p.split, aligned) : 0;
+    if (flat) {
+      p.flat_cols = true;
+      p.split = 1;
+      p.cpw = flat;
+      nw = kFlatLanes / kWave;
+    }
     const int64_t blocks0 = (col_lanes + p.cpw - 1) / p.cpw * others;
     p.block = nw * kWave;
     p.chunk = (p.nredtot + p.split - 1) / p.split;

@@ -109,6 +109,7 @@ struct RedPlan {
   int block = kBlock;           // threads per workgroup (the cols kernel may use 1024)
   bool short_rows = false;      // rows kernel: every row fits one vector per lane of its group (loop-free kernel)
   int cpw = kWave;              // cols kernel: lanes per row of columns (power of two, at most a wavefront)
+  bool flat_cols = false;       // cols kernel: cpw is any number, the workgroup's lanes go on through further rows
   bool nt_load = false;         // the input is far larger than the caches: stream it (non-temporal vector loads)
   bool lean = false;            // rows kernel: the common 2-D shape, run by the lean form of the kernel
   bool fold = false;            // second launch over [split][output] partial results: one output per lane

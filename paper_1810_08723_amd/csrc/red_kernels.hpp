@@ -47,7 +47,8 @@ struct RedArgs {
   const char *b;
   int64_t ksb[kMaxDims], rsb[kMaxDims];    // its byte strides, same order as ksa / rsa
   int32_t a_bcast, b_bcast;                // broadcast along the vectorised dim
-  int32_t cpw;                             // cols: lanes per row of columns (power of two <= 64)
+  int32_t cpw;                             // cols: lanes per row of columns (power of two <= 64; any number with cpw_m)
+  uint32_t cpw_m;                          // cols: lanes numbered through whole rows: ceil(2^32 / cpw); else zero
   int32_t nt_load;                         // vector loads carry the streaming (non-temporal) hint
   int32_t swap_a, swap_o;                  // the input / the output is stored in the other byte order
 };
@@ -1041,6 +1042,93 @@ OCN_DEV void cols_body(KRedArgs &p, typename Reducer<S, OP>::A *lds) {
   }
 }
 
+// Columns whose last block would be mostly empty, in workgroups few enough that such blocks leave their
+// CUs idle: the columns are cut into equal blocks of any number of lanes, and the workgroup's lanes
+// are numbered through whole rows of its block, so that p.cpw lanes take a row and block / p.cpw rows
+// go at a time (one reduced dim, vectors of columns, every lane folds its own rows, the rows meet in LDS).
+// Float sums over the middle of [48, 1000, 777], 195 vectors per row: four blocks of 64 lanes, the last
+// with three, made 144 of 192 workgroups do the work, 33.7 us; 240 blocks of 39 lanes 28.6 (30.3 before
+// neighbouring blocks, whose rows end inside a line, went to one XCD), 5.2 TB/s.
+template <int S, int OP, int V, bool NT, bool SW>
+OCN_DEV void cols_flat_body(KRedArgs &p, typename Reducer<S, OP>::A *lds) {
+  using R = Reducer<S, OP>;
+  using A = typename R::A;
+  using St = storage_t<S>;
+  const uint32_t tid = threadIdx.x, block = blockDim.x, lanes = (uint32_t)p.cpw;
+  // (consecutive blocks on one XCD, which workgroups go to in turn: blocks of the same rows share lines)
+  const uint32_t xcd = blockIdx.x % kXcds, per_xcd = gridDim.x / kXcds, more = gridDim.x % kXcds;
+  const uint32_t b = xcd * per_xcd + (xcd < more ? xcd : more) + blockIdx.x / kXcds;
+  const uint32_t other = rfastdiv(b, args_div(p.colblocks_div)), cb = b - other * p.colblocks_div.d;
+  const uint32_t rpt = block / lanes;                         // rows per trip
+  const uint32_t g = __umulhi(tid, p.cpw_m), l = tid - g * lanes;
+  int64_t col0 = ((int64_t)cb * lanes + l) * V;
+  const int64_t left = p.nc - col0;
+  int ncol = left >= V ? V : (left > 0 ? (int)left : 0), skip = 0;
+  if (ncol > 0 && ncol < V) {   // (as in cols_body: a whole vector that ends with the last column)
+    skip = V - ncol;
+    col0 -= skip;
+    ncol = V;
+  }
+  int64_t off_a = col0 * (int64_t)sizeof(St), off_o = col0 * p.kso[0];
+  {
+    uint32_t o = other;
+    const int nkept = p.nkept;
+    for (int k = 1; k < nkept; ++k) {
+      const uint32_t q = (k == nkept - 1) ? 0u : rfastdiv(o, args_div(p.kdiv[k]));
+      const uint32_t i = o - q * p.kdiv[k].d;
+      o = q;
+      off_a += (int64_t)i * p.ksa[k];
+      off_o += (int64_t)i * p.kso[k];
+    }
+  }
+  A acc[V];
+#pragma unroll
+  for (int i = 0; i < V; ++i) acc[i] = R::identity();
+  constexpr int U = 4;
+  struct alignas(16) Pk { St v[V]; };
+  auto add = [&](Pk &pk) {
+    order_pack<S>(SW, pk);
+#pragma unroll
+    for (int i = 0; i < V; ++i) acc[i] = R::combine(acc[i], R::lift(from_storage<S>(pk.v[i])));
+  };
+  if (ncol == V && g < rpt) {
+    const int64_t rows = p.nredtot, step = (int64_t)rpt * p.rsa[0];
+    const char *src = p.a + off_a + (int64_t)g * p.rsa[0];
+    int64_t r = g;
+    for (; r + (int64_t)(U - 1) * rpt < rows; r += (int64_t)U * rpt) {
+      Pk pk[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        load_vec<St, V, NT>(src, pk[u]);
+        src += step;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) add(pk[u]);
+    }
+    for (; r < rows; r += rpt) {
+      Pk pk;
+      load_vec<St, V, NT>(src, pk);
+      src += step;
+      add(pk);
+    }
+  }
+  // CH columns per barrier; lane c * lanes + l folds column c of column lane l over the rows of a trip
+  constexpr int CH = cols_lds_columns<A>() < V ? cols_lds_columns<A>() : V;
+  const uint32_t fc = g, fl = l;   // (the same division: lanes of a row fold one column each)
+#pragma unroll
+  for (int i0 = 0; i0 < V; i0 += CH) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) lds[(size_t)c * block + tid] = acc[i0 + c];
+    __syncthreads();
+    if (fc < (uint32_t)CH && ncol == V && i0 + (int)fc >= skip) {
+      A v = lds[(size_t)fc * block + fl];
+      for (uint32_t k = 1; k < rpt; ++k) v = R::combine(v, lds[(size_t)fc * block + k * lanes + fl]);
+      store_result<A>(p.out + off_o + (int64_t)(i0 + (int)fc) * p.kso[0], p.out_dtype, v, p.swap_o != 0);
+    }
+    if (i0 + CH < V) __syncthreads();
+  }
+}
+
 template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) void red_cols_kernel(const RedArgs by_value) {
   (void)by_value;  // read through the kernarg segment, which can be indexed at run time
   KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
@@ -1049,6 +1137,18 @@ template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) voi
   constexpr int VF = 16 / (int)sizeof(storage_t<S>) > 0 ? 16 / (int)sizeof(storage_t<S>) : 1;
   extern __shared__ __align__(16) unsigned char red_cols_lds_raw[];
   A *lds = reinterpret_cast<A *>(red_cols_lds_raw);
+  if constexpr (VF > 1 && VF <= 8) {
+    if (p.cpw_m) {
+      if (p.swap_a) {
+        if (p.nt_load) cols_flat_body<S, OP, VF, true, true>(p, lds);
+        else cols_flat_body<S, OP, VF, false, true>(p, lds);
+      } else {
+        if (p.nt_load) cols_flat_body<S, OP, VF, true, false>(p, lds);
+        else cols_flat_body<S, OP, VF, false, false>(p, lds);
+      }
+      return;
+    }
+  }
   if (p.vec > 1 && p.nred == 1) {
     if (p.nt_load) cols_body<S, OP, VF, (VF > 1), true>(p, lds);
     else cols_body<S, OP, VF, false, true>(p, lds);

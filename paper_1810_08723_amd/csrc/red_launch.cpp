@@ -53,6 +53,7 @@ RedArgs make_red_args(const RedPlan &p, char *partial) {
   } else if (p.kernel == OCN_KERNEL_RED_COLS) {
     r.nc = p.ksize[p.nkept - 1];
     r.cpw = p.cpw;
+    r.cpw_m = p.flat_cols ? (uint32_t)((((uint64_t)1 << 32) + p.cpw - 1) / p.cpw) : 0u;
     const int64_t colblocks = (r.nc + (int64_t)p.cpw * p.vec - 1) / ((int64_t)p.cpw * p.vec);
     r.colblocks_div = make_fastdiv((uint32_t)colblocks);
   }
