@@ -1129,7 +1129,8 @@ OCN_DEV void cols_flat_body(KRedArgs &p, typename Reducer<S, OP>::A *lds) {
   }
 }
 
-template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) void red_cols_kernel(const RedArgs by_value) {
+// (a kernel of its own: beside the other forms it cost those registers, 2 % of some sums)
+template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) void red_cols_flat_kernel(const RedArgs by_value) {
   (void)by_value;  // read through the kernarg segment, which can be indexed at run time
   KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
   if (p.warm) warm_arguments<RedArgs>();
@@ -1138,17 +1139,24 @@ template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) voi
   extern __shared__ __align__(16) unsigned char red_cols_lds_raw[];
   A *lds = reinterpret_cast<A *>(red_cols_lds_raw);
   if constexpr (VF > 1 && VF <= 8) {
-    if (p.cpw_m) {
-      if (p.swap_a) {
-        if (p.nt_load) cols_flat_body<S, OP, VF, true, true>(p, lds);
-        else cols_flat_body<S, OP, VF, false, true>(p, lds);
-      } else {
-        if (p.nt_load) cols_flat_body<S, OP, VF, true, false>(p, lds);
-        else cols_flat_body<S, OP, VF, false, false>(p, lds);
-      }
-      return;
+    if (p.swap_a) {
+      if (p.nt_load) cols_flat_body<S, OP, VF, true, true>(p, lds);
+      else cols_flat_body<S, OP, VF, false, true>(p, lds);
+    } else {
+      if (p.nt_load) cols_flat_body<S, OP, VF, true, false>(p, lds);
+      else cols_flat_body<S, OP, VF, false, false>(p, lds);
     }
   }
+}
+
+template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) void red_cols_kernel(const RedArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if (p.warm) warm_arguments<RedArgs>();
+  using A = typename Reducer<S, OP>::A;
+  constexpr int VF = 16 / (int)sizeof(storage_t<S>) > 0 ? 16 / (int)sizeof(storage_t<S>) : 1;
+  extern __shared__ __align__(16) unsigned char red_cols_lds_raw[];
+  A *lds = reinterpret_cast<A *>(red_cols_lds_raw);
   if (p.vec > 1 && p.nred == 1) {
     if (p.nt_load) cols_body<S, OP, VF, (VF > 1), true>(p, lds);
     else cols_body<S, OP, VF, false, true>(p, lds);
