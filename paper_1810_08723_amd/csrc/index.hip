@@ -250,14 +250,15 @@ __global__ __launch_bounds__(kBlock) void mask_count_kernel(const MaskArgs p) {
 }
 
 // The same counts for a contiguous mask: a wavefront per chunk of kMaskChunk bytes, every lane with four
-// 16-byte loads in flight (the loads of a wavefront cover 1 KiB each), a workgroup per kMaskGroup chunks,
-// and its total as well.  (One load per lane and a workgroup per chunk read a 64 MB mask at 3 TB/s; four
-// chunks per wavefront 30 MB in 7.5 us.)
+// 16-byte loads in flight (the loads of a wavefront cover 1 KiB each).  TOTALS: a workgroup per
+// kMaskGroup chunks, and its total as well; else four chunks per workgroup, which fill the chip earlier
+// (64 chunks 3.4 us, 4.3 in groups).  (One load per lane and a workgroup per chunk read a 64 MB mask at
+// 3 TB/s; four chunks per wavefront 30 MB in 7.5 us, 6.7 so.)
 constexpr int kMaskGroup = 16;
-__global__ __launch_bounds__(kMaskGroup * kWave) void mask_count_contig_kernel(const MaskArgs p) {
+template <bool TOTALS> __global__ __launch_bounds__((TOTALS ? kMaskGroup : kBlock / kWave) * kWave) void mask_count_contig_kernel(const MaskArgs p) {
   __shared__ uint32_t lds[kMaskGroup];
   const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const uint32_t chunk = blockIdx.x * (uint32_t)kMaskGroup + wave;
+  const uint32_t chunk = blockIdx.x * (uint32_t)(TOTALS ? kMaskGroup : kBlock / kWave) + wave;
   uint32_t c = 0;
   if (chunk < p.nblocks) {            // (the same for all lanes of a wavefront)
     const uint32_t base = chunk * (uint32_t)kMaskChunk;
@@ -282,13 +283,15 @@ __global__ __launch_bounds__(kMaskGroup * kWave) void mask_count_contig_kernel(c
     for (int d = kWave / 2; d >= 1; d >>= 1) c += (uint32_t)__shfl_xor((int)c, d, kWave);
     if (lane == 0) p.block_counts[chunk] = c;
   }
-  if (lane == 0) lds[wave] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t total = 0;
+  if constexpr (TOTALS) {
+    if (lane == 0) lds[wave] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t total = 0;
 #pragma unroll
-    for (int w = 0; w < kMaskGroup; ++w) total += lds[w];
-    p.block_counts[p.nblocks + blockIdx.x] = total;
+      for (int w = 0; w < kMaskGroup; ++w) total += lds[w];
+      p.block_counts[p.nblocks + blockIdx.x] = total;
+    }
   }
 }
 
@@ -353,13 +356,13 @@ __global__ __launch_bounds__(kScanBlock) void mask_scan_kernel(const MaskArgs p)
 // A workgroup of the write kernel takes a chunk and needs the number of elements that are selected
 // before it:
 //   kBeforeCount  adds up the mask itself up to there: no other launch at all (contiguous masks of at
-//                 most kMaskDirect elements: the last workgroup reads 96 KiB in two trips of sixteen
+//                 most kMaskDirect elements: the last workgroup reads 96 KiB in three trips of eight
 //                 loads, against the 2.5 us and more that each further launch costs; at 100 000 elements
 //                 the kernel takes 7.3 us, 3.4 and 5.0 in two launches, at 260 000 13.6);
 //   kBeforeGroups adds up the totals of the groups of chunks before its own and the counts inside it
 //                 (contiguous masks of up to kMaskSumGroups groups, 67 million elements: 4 KiB read
 //                 per workgroup at most, which hide behind the others' stores);
-//   kBeforeSum    adds up the chunk counts (other masks of up to kMaskSumChunks chunks);
+//   kBeforeSum    adds up the chunk counts (up to kMaskSumChunks chunks, 8.4 million elements);
 //   kBeforeScan   reads its prefix, for which a launch of one workgroup scans the counts (6.0 us for the
 //                 7325 chunks of 30 million elements).
 enum { kBeforeCount = 0, kBeforeSum = 1, kBeforeScan = 2, kBeforeGroups = 3 };
@@ -379,9 +382,16 @@ template <bool FLAT> __global__ __launch_bounds__(kBlock) void mask_write_kernel
   if (p.before != kBeforeScan) {
     uint32_t c = 0;
     if (p.before == kBeforeCount) {
-#pragma unroll 16
-      for (uint32_t e = threadIdx.x * 16u; e < chunk0; e += kBlock * 16u)
-        c += nonzero_bytes(*reinterpret_cast<const uint4 *>(p.mask + e));
+      // eight loads in flight, past the end the first one again
+      constexpr uint32_t kAhead = 8;
+      for (uint32_t j = 0; j < chunk; j += kAhead) {
+        uint4 v[kAhead];
+#pragma unroll
+        for (uint32_t k = 0; k < kAhead; ++k)
+          v[k] = *reinterpret_cast<const uint4 *>(p.mask + (j + k < chunk ? j + k : 0u) * (uint32_t)kMaskChunk + threadIdx.x * 16u);
+#pragma unroll
+        for (uint32_t k = 0; k < kAhead; ++k) c += j + k < chunk ? nonzero_bytes(v[k]) : 0u;
+      }
     } else if (p.before == kBeforeGroups) {
       const uint32_t g = chunk / kMaskGroup;
       if (threadIdx.x < chunk % kMaskGroup) c = p.block_counts[g * kMaskGroup + threadIdx.x];
@@ -819,10 +829,12 @@ int ocn_mask_offsets(const ocn_tensor *mask, const int64_t *target_strides, void
   m.count = (int64_t *)count;
   m.nt_store = std::min<int64_t>(capacity, m.n) * 8 >= ((int64_t)32 << 20);  // too large to stay cached
   const uint32_t groups = (m.nblocks + kMaskGroup - 1) / kMaskGroup;
-  m.before = m.contig ? (m.n <= kMaskDirect ? kBeforeCount : groups <= kMaskSumGroups ? kBeforeGroups : kBeforeScan)
-                      : (m.nblocks <= kMaskSumChunks ? kBeforeSum : kBeforeScan);
+  m.before = m.contig && m.n <= kMaskDirect ? kBeforeCount : m.nblocks <= kMaskSumChunks ? kBeforeSum
+             : m.contig && groups <= kMaskSumGroups ? kBeforeGroups : kBeforeScan;
   if (m.before != kBeforeCount) {
-    if (m.contig) hipLaunchKernelGGL(mask_count_contig_kernel, dim3(groups), dim3(kMaskGroup * kWave), 0, s, m);
+    if (m.before == kBeforeGroups) hipLaunchKernelGGL(mask_count_contig_kernel<true>, dim3(groups), dim3(kMaskGroup * kWave), 0, s, m);
+    else if (m.contig)
+      hipLaunchKernelGGL(mask_count_contig_kernel<false>, dim3((m.nblocks + kBlock / kWave - 1) / (kBlock / kWave)), dim3(kBlock), 0, s, m);
     else hipLaunchKernelGGL(mask_count_kernel, dim3(m.nblocks), dim3(kBlock), 0, s, m);
   }
   if (m.before == kBeforeScan) hipLaunchKernelGGL(mask_scan_kernel, dim3(1), dim3(kScanBlock), 0, s, m);

@@ -6,7 +6,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", (1, 4097, 98303, 98304, 98305, 262144, 327680, 327681, 65536 * 17 + 4096, (1 << 26) + 5))
+@pytest.mark.parametrize("n", (1, 4097, 98303, 98304, 98305, 262144, 8388608, 8388609, 327680, 327681, 65536 * 17 + 4096, (1 << 26) + 5))
 def test_positions_around_the_limits(n):
     import paper_1810_08723_amd as ocn
     gen = torch.Generator(device="cuda:0").manual_seed(n)
