@@ -1114,6 +1114,11 @@ int choose_flat_columns(int64_t col_lanes, int64_t others, int64_t rows, int cpw
   return lanes;
 }
 
+// Few rows, many times over: a lane per vector of columns (cols_lane_body).  At most this many rows where
+// a wavefront's lanes would cover several rows of columns (complex sums of [244044, 5, 15] 471 -> 38 us,
+// int32 [60000, 32, 20] 152 -> 42), at most eight where columns are wide ([8, 1000, 5000] halves 32 -> 25; with
+// 16 rows of 4096 floats 21.5 and 25.6, wavefronts that stream whole lines are faster); and enough lanes.
+constexpr int64_t kLaneRows = 32, kLaneWide = 48, kLaneColumns = 32768;
 void choose_reduce_launch(RedPlan &p) {
   const int es = dt_size(p.a_dtype);
   const int acc_es = dt_size(p.acc_dtype);
@@ -1221,6 +1226,17 @@ void choose_reduce_launch(RedPlan &p) {
     p.chunk = (p.nredtot + p.split - 1) / p.split;
     p.split = (p.nredtot + p.chunk - 1) / p.chunk;
     p.grid = blocks0 * p.split;
+    const int64_t lane_vec = nc < p.vec ? 1 : p.vec, lanes = (nc + lane_vec - 1) / lane_vec * others;
+    if (p.nred == 1 && p.vec <= 8 && (p.nredtot <= 8 || (p.nredtot <= kLaneRows && col_lanes < kLaneWide)) && lanes >= kLaneColumns &&
+        lanes < ((int64_t)1 << 31) - kBlock) {
+      p.flat_cols = false;
+      p.cpw = 0;
+      p.vec = (int)lane_vec;
+      p.split = 1;
+      p.chunk = p.nredtot;
+      p.block = kBlock;
+      p.grid = (lanes + kBlock - 1) / kBlock;
+    }
   } else {
     p.kernel = OCN_KERNEL_RED_GENERIC;
     p.vec = 1;

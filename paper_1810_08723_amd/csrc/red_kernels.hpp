@@ -1129,6 +1129,78 @@ OCN_DEV void cols_flat_body(KRedArgs &p, typename Reducer<S, OP>::A *lds) {
   }
 }
 
+// Columns of a few rows each, many times over: a lane per vector of columns takes all of its rows, four in
+// flight, and stores its results; neighbouring lanes take neighbouring vectors, then the next outputs.
+// The forms above give a wavefront 64 / cpw rows and a workgroup four wavefronts: with five rows of
+// fifteen complex columns 40 of 256 lanes had any, and 244044 workgroups a barrier each (471 us, 38 here,
+// 4.6 TB/s).
+template <int S, int OP, int V, bool NT, bool SW>
+OCN_DEV void cols_lane_body(KRedArgs &p) {
+  using R = Reducer<S, OP>;
+  using A = typename R::A;
+  using St = storage_t<S>;
+  const uint32_t t = blockIdx.x * (uint32_t)kBlock + threadIdx.x;
+  const uint32_t other = rfastdiv(t, args_div(p.colblocks_div)), l = t - other * p.colblocks_div.d;
+  if (t >= (uint32_t)p.nvec) return;
+  int64_t col0 = (int64_t)l * V;
+  int skip = 0;
+  if (V > 1 && p.nc - col0 < V) {   // (as in cols_body: a whole vector that ends with the last column)
+    skip = V - (int)(p.nc - col0);
+    col0 -= skip;
+  }
+  int64_t off_a = col0 * (int64_t)sizeof(St), off_o = col0 * p.kso[0];
+  {
+    uint32_t o = other;
+    const int nkept = p.nkept;
+    for (int k = 1; k < nkept; ++k) {
+      const uint32_t q = (k == nkept - 1) ? 0u : rfastdiv(o, args_div(p.kdiv[k]));
+      const uint32_t i = o - q * p.kdiv[k].d;
+      o = q;
+      off_a += (int64_t)i * p.ksa[k];
+      off_o += (int64_t)i * p.kso[k];
+    }
+  }
+  A acc[V];
+#pragma unroll
+  for (int i = 0; i < V; ++i) acc[i] = R::identity();
+  constexpr int U = 4;
+  struct alignas(sizeof(St) * V >= 16 ? 16 : sizeof(St) * V) Pk { St v[V]; };
+  const char *src = p.a + off_a;
+  const int64_t step = p.rsa[0];
+  const uint32_t rows = (uint32_t)p.nredtot;
+  for (uint32_t r = 0; r < rows; r += U) {   // (past the last row it is loaded again and left out)
+    Pk pk[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) load_vec<St, V, NT>(src + (int64_t)(r + u < rows ? r + u : rows - 1) * step, pk[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (r + u < rows) {
+        order_pack<S>(SW, pk[u]);
+#pragma unroll
+        for (int i = 0; i < V; ++i) acc[i] = R::combine(acc[i], R::lift(from_storage<S>(pk[u].v[i])));
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < V; ++i)
+    if (i >= skip) store_result<A>(p.out + off_o + (int64_t)i * p.kso[0], p.out_dtype, acc[i], p.swap_o != 0);
+}
+template <int S, int OP> __global__ __launch_bounds__(kBlock) void red_cols_lane_kernel(const RedArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if (p.warm) warm_arguments<RedArgs>();
+  constexpr int VF = 16 / (int)sizeof(storage_t<S>) > 0 ? 16 / (int)sizeof(storage_t<S>) : 1;
+  if constexpr (VF > 1 && VF <= 8) {
+    if (p.vec > 1) {
+      if (p.swap_a) cols_lane_body<S, OP, VF, false, true>(p);
+      else cols_lane_body<S, OP, VF, false, false>(p);
+      return;
+    }
+  }
+  if (p.swap_a) cols_lane_body<S, OP, 1, false, true>(p);
+  else cols_lane_body<S, OP, 1, false, false>(p);
+}
+
 // (a kernel of its own: beside the other forms it cost those registers, 2 % of some sums)
 template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) void red_cols_flat_kernel(const RedArgs by_value) {
   (void)by_value;  // read through the kernarg segment, which can be indexed at run time

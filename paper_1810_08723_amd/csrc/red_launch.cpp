@@ -1,6 +1,7 @@
 // Kernel-argument builder for the reduction kernels (dtype independent).
 #include "red_launch.hpp"
 
+#include <algorithm>
 #include <cstring>
 
 namespace ocn {
@@ -54,7 +55,9 @@ RedArgs make_red_args(const RedPlan &p, char *partial) {
     r.nc = p.ksize[p.nkept - 1];
     r.cpw = p.cpw;
     r.cpw_m = p.flat_cols ? (uint32_t)((((uint64_t)1 << 32) + p.cpw - 1) / p.cpw) : 0u;
-    const int64_t colblocks = (r.nc + (int64_t)p.cpw * p.vec - 1) / ((int64_t)p.cpw * p.vec);
+    // (without lanes per row, one lane per vector of columns: a "block" is one lane's)
+    const int64_t wide = (int64_t)std::max(1, p.cpw) * p.vec, colblocks = (r.nc + wide - 1) / wide;
+    if (p.cpw == 0) r.nvec = colblocks * (p.nout / r.nc);
     r.colblocks_div = make_fastdiv((uint32_t)colblocks);
   }
   return r;
