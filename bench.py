@@ -405,10 +405,10 @@ def main() -> int:
         f_gather = lambda: ocn.gather(ta, offs_d, 0, 4 * (n - 1), to)
         us_b, us_g = timed(f_bind), timed(f_gather)
         assert int(cnt_d.cpu()[0]) == count_h
-        for name, us, lb, note in (("G1", us_b, n + 8 * count_h, "mask -> offsets (count, scan, write)"),
+        for name, us, lb, note in (("G1", us_b, n + 8 * count_h, "mask -> offsets (count, write)"),
                                    ("G2", us_g, 8 * count_h + 4 * n + 4 * count_h,
                                     "gather by offsets (every line of the source is touched)")):
-            next_ops.append({"case": name, "op": note, "kernel": "index", "fused": False, "passes": 3 if name == "G1" else 1,
+            next_ops.append({"case": name, "op": note, "kernel": "index", "fused": False, "passes": 2 if name == "G1" else 1,
                              "logical_bytes": lb, "us": us, "gbs": lb / (us * 1e-6) / 1e9,
                              "frac_of_peak": lb / (us * 1e-6) / 1e9 / HBM_PEAK_GBS, "two_calls_us": None})
     device_ms = sum(p["avg_us"] for p in per_op) / 1e3
