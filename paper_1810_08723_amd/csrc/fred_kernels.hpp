@@ -205,40 +205,47 @@ OCN_DEV typename FusedFold<G, OP>::A fred_lean_fold(const char *pa, const char *
   using SBt = typename G::SBt;
   static_assert(sizeof(SAt) == sizeof(SBt) && sizeof(SAt) <= 16, "equal input widths of at most 16 bytes");
   constexpr int V = 16 / (int)sizeof(SAt);
-  constexpr int U = 4;
+  // Vectors in flight of each input.  (Four spill complex sums under the 64 registers of OCN_ROWS_OCC, complex
+  // double products of [16384, 1000] 116 us where two take 76, and lose 5 to 15 % of halves and of rows of
+  // 50000; they win 5 % of float rows of 1000.)
+  constexpr int U = 2;
+  // Trips are counted for all lanes alike: with the count of each lane its own, a row of 250 vectors is
+  // three round trips of a wavefront, for the lanes with four vectors and those with three.  (Except for moduli
+  // of complex elements, where that spills: [3000, 4096] 34 us, 30 so.)
+  constexpr bool OWN = dt_kind(G::SA_DT) == K_CPLX && G::EW == B_ABSGT;
+  constexpr int T = OWN ? 1 : U;   // vectors in flight of what is left
   A acc[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) acc[u] = F::R::identity();
-  // (trips are counted for all lanes alike: with the count of each lane its own, a row of 250 vectors is
-  // three round trips of a wavefront, for the lanes with four vectors and those with three)
-  uint32_t t = t0;
-  for (; t + U * lanes <= t1; t += U * lanes) {
+  const uint32_t ahead = OWN ? 0u : lane;
+  uint32_t t = OWN ? t0 + lane : t0;
+  for (; OWN ? t + (U - 1) * lanes < t1 : t + U * lanes <= t1; t += U * lanes) {
     Pack<SAt, V> va[U];
     Pack<SBt, V> vb[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      load_vec<SAt, V, NT>(pa + (uint64_t)(t + u * lanes + lane) * 16u, va[u]);
-      load_vec<SBt, V, NT>(pb + (uint64_t)(t + u * lanes + lane) * 16u, vb[u]);
+      load_vec<SAt, V, NT>(pa + (uint64_t)(t + u * lanes + ahead) * 16u, va[u]);
+      load_vec<SBt, V, NT>(pb + (uint64_t)(t + u * lanes + ahead) * 16u, vb[u]);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int i = 0; i < V; ++i) acc[u] = F::add(acc[u], va[u].v[i], vb[u].v[i]);
   }
-  if (t < t1) {   // what is left, fewer than U per lane: lanes past the end load the last vector and drop it
-    Pack<SAt, V> va[U];
-    Pack<SBt, V> vb[U];
+  for (; t < t1; t += T * lanes) {   // what is left, fewer than U per lane: lanes past the end load the last vector and drop it
+    Pack<SAt, V> va[T];
+    Pack<SBt, V> vb[T];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
+    for (int u = 0; u < T; ++u) {
       if (t + u * lanes < t1) {
-        const uint32_t tt = t + u * lanes + lane < t1 ? t + u * lanes + lane : t1 - 1;
+        const uint32_t tt = t + u * lanes + ahead < t1 ? t + u * lanes + ahead : t1 - 1;
         load_vec<SAt, V, NT>(pa + (uint64_t)tt * 16u, va[u]);
         load_vec<SBt, V, NT>(pb + (uint64_t)tt * 16u, vb[u]);
       }
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (t + u * lanes + lane < t1) {
+    for (int u = 0; u < T; ++u) {
+      if (t + u * lanes + ahead < t1) {
 #pragma unroll
         for (int i = 0; i < V; ++i) acc[u] = F::add(acc[u], va[u].v[i], vb[u].v[i]);
       }

@@ -40,3 +40,15 @@ def test_generic_dtype_kernels_keep_their_arguments_out_of_registers():
     complex doubles are that large by themselves."""
     kernels = [(n, k) for n, k in _spills(os.path.join(CSRC, "ew_interp.hip"), "SGPRs") if "ew_interp_kernel" in n]
     assert len(kernels) == 30 and all(k == 0 for n, k in kernels if not n.startswith("_ZN3ocn16ew_interp_kernelILi14ELb1E")), kernels
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_fused_rows_of_wide_elements_keep_their_registers(tmp_path):
+    """Too many vectors in flight spill complex sums."""
+    src = tmp_path / "fused.hip"
+    rows = [("B_ADD", "DT_C32", "DT_C32"), ("B_MUL", "DT_C32", "DT_C32"), ("B_MUL", "DT_C64", "DT_C64"), ("B_SUB", "DT_C64", "DT_C64"),
+            ("B_ABSGT", "DT_C32", "DT_BOOL"), ("B_MUL", "DT_F32", "DT_F32"), ("B_MUL", "DT_F16", "DT_F16")]
+    src.write_text("".join(f'#include "{os.path.join(CSRC, h)}"\n' for h in ("fred_kernels.hpp", "red_launch.hpp")) + "namespace ocn {\n" + "".join(
+        f"template __global__ void fred_rows_lean_kernel<Sig<{op}, {t}, {t}, {o}, 2>, R_SUM>(const RedLeanArgs);\n" for op, t, o in rows) + "}\n")
+    kernels = _spills(src, "VGPRs")
+    assert len(kernels) == len(rows) and all(k == 0 for _, k in kernels), kernels
