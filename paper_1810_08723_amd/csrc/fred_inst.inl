@@ -1,5 +1,6 @@
 // Instantiates one slice of the fused elementwise+reduce kernels and registers their
 // launchers.  Included by fred_slice_*.hip with OCN_SLICE and OCN_NSLICES defined.
+#include <type_traits>
 #include <utility>
 
 #include "fred_kernels.hpp"
@@ -27,7 +28,17 @@ template <class G, int OP> hipError_t launch_fred(const RedPlan &p, char *partia
       {
         using A = typename FusedFold<G, OP>::A;
         const size_t lds = cols_lds_bytes<A>((int)p.block, p.vec > 1 ? G::V : 1);
-        hipLaunchKernelGGL((fred_cols_kernel<G, OP>), dim3((unsigned)p.grid), dim3((unsigned)p.block), lds, stream, args);
+        const dim3 grid((unsigned)p.grid), block((unsigned)p.block);
+        auto form = [&](auto bc, auto nt) {
+          constexpr int BC = fred_cols_form<G, decltype(bc)::value>() ? decltype(bc)::value : -1;
+          hipLaunchKernelGGL((fred_cols_kernel<G, OP, BC, BC == 0 && decltype(nt)::value>), grid, block, lds, stream, args);
+        };
+        using std::integral_constant;
+        if (p.vec != G::V || p.nred != 1) form(integral_constant<int, -1>{}, std::false_type{});
+        else if (args.b_bcast) form(integral_constant<int, 2>{}, std::false_type{});
+        else if (args.a_bcast) form(integral_constant<int, 1>{}, std::false_type{});
+        else if (args.nt_load) form(integral_constant<int, 0>{}, std::true_type{});
+        else form(integral_constant<int, 0>{}, std::false_type{});
       }
       break;
     default:

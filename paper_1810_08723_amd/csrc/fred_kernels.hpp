@@ -45,13 +45,13 @@ OCN_DEV void kept_offsets2(KRedArgs &p, uint32_t o, int64_t &off_a, int64_t &off
 }
 
 // V consecutive elements of one input, or V copies of one element where it is broadcast
-template <class S, int V, bool NT = false> OCN_DEV void fused_load(const char *src, bool bcast, Pack<S, V> &dst) {
+template <class S, int V> OCN_DEV void fused_load(const char *src, bool bcast, Pack<S, V> &dst) {
   if (bcast) {
     const S s = *reinterpret_cast<const S *>(src);
 #pragma unroll
     for (int i = 0; i < V; ++i) dst.v[i] = s;
   } else {
-    load_vec<S, V, NT && sizeof(S) * V >= 16>(src, dst);
+    load_vec<S, V, false>(src, dst);
   }
 }
 
@@ -384,7 +384,7 @@ OCN_DEV void fred_cols_body(KRedArgs &p, typename FusedFold<G, OP>::A *lds) {
   const int lane = tid & (kWave - 1);
   const int wave = tid / kWave;
   const int NW = (int)blockDim.x / kWave;
-  const bool abc = p.a_bcast, bbc = p.b_bcast;
+  const bool abc = BC >= 0 ? BC == 1 : p.a_bcast != 0, bbc = BC >= 0 ? BC == 2 : p.b_bcast != 0;
 
   uint32_t b = blockIdx.x;
   const uint32_t per_split = (uint32_t)(p.colblocks_div.d * (uint32_t)(p.nout / p.nc));
@@ -436,7 +436,10 @@ OCN_DEV void fred_cols_body(KRedArgs &p, typename FusedFold<G, OP>::A *lds) {
   int64_t r = w0 + lr;
   if constexpr (BC >= 0) {
     if (ncol == V) {
-      constexpr int U = V * (int)(sizeof(SAt) > sizeof(SBt) ? sizeof(SAt) : sizeof(SBt)) <= 16 ? 4 : 2;   // rows in flight (eight: the same)
+      // Rows in flight (eight of 16 bytes: the same).  Counts take 16 columns per lane, four pieces or more
+      // per row and input that share lines; rows of two such inputs go one at a time (== over floats
+      // [3000, 4096] 35 us with two, 25 so).
+      constexpr int W = V * (int)(sizeof(SAt) > sizeof(SBt) ? sizeof(SAt) : sizeof(SBt)), U = W <= 16 ? 4 : BC == 0 ? 1 : 2;
       const int64_t sa = (int64_t)RS * p.rsa[0], sb = (int64_t)RS * p.rsb[0];
       const char *qa = p.a + off_a + r * p.rsa[0], *qb = p.b + off_b + r * p.rsb[0];
       auto load = [&](const char *ra, const char *rb, Pack<SAt, V> &va, Pack<SBt, V> &vb) {
@@ -530,23 +533,23 @@ OCN_DEV void fred_cols_body(KRedArgs &p, typename FusedFold<G, OP>::A *lds) {
   }
 }
 
-template <class G, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) void fred_cols_kernel(const RedArgs by_value) {
+// A kernel per form (BC and NT as above): in one kernel each form paid for the registers of the others, and
+// counts of comparisons spilled up to 52 (== over floats [4000, 333] 31 -> 27 us, |a| > |b| over complex floats
+// [16384, 1000] against a row 37 -> 29).  Seven are spilled still where such moduli are compared with a
+// column; the form for several dims, which spills none, takes 19.8 us for [65536, 37], 16.9 so.
+// Elements of 16 bytes gain from the forms only where one input is broadcast (complex double
+// products of [4000, 333] with a column 12.3 -> 11.3 us; of two matrices [800, 20000] 94 -> 103).
+template <class G, int BC> constexpr bool fred_cols_form() { return G::V > 1 || BC > 0; }
+template <class G, int OP, int BC, bool NT = false> __global__ __launch_bounds__(kColsMaxWaves * kWave) void fred_cols_kernel(const RedArgs by_value) {
   (void)by_value;  // read through the kernarg segment, which can be indexed at run time
   KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
   if (p.warm) warm_arguments<RedArgs>();
   using A = typename FusedFold<G, OP>::A;
   extern __shared__ __align__(16) unsigned char fred_cols_lds_raw[];
   A *lds = reinterpret_cast<A *>(fred_cols_lds_raw);
-  if (p.vec > 1 && p.nred == 1) {
-    if (p.b_bcast) fred_cols_body<G, OP, G::V, false, 2>(p, lds);
-    else if (p.a_bcast) fred_cols_body<G, OP, G::V, false, 1>(p, lds);
-    else if (p.nt_load) fred_cols_body<G, OP, G::V, true, 0>(p, lds);
-    else fred_cols_body<G, OP, G::V, false, 0>(p, lds);
-  } else if (p.vec > 1) {
-    fred_cols_body<G, OP, G::V, false, -1>(p, lds);
-  } else {
-    fred_cols_body<G, OP, 1, false, -1>(p, lds);
-  }
+  if constexpr (BC >= 0) fred_cols_body<G, OP, G::V, NT, BC>(p, lds);
+  else if (p.vec > 1) fred_cols_body<G, OP, G::V, false, -1>(p, lds);
+  else fred_cols_body<G, OP, 1, false, -1>(p, lds);
 }
 
 // ---------------------------------------------------------------------------------------

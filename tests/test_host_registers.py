@@ -43,12 +43,16 @@ def test_generic_dtype_kernels_keep_their_arguments_out_of_registers():
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
-def test_fused_rows_of_wide_elements_keep_their_registers(tmp_path):
-    """Too many vectors in flight spill complex sums."""
+def test_fused_kernels_of_wide_elements_keep_their_registers(tmp_path):
+    """Too many vectors in flight spill complex sums in the row form; several column forms in one kernel spill
+    counts of comparisons."""
     src = tmp_path / "fused.hip"
     rows = [("B_ADD", "DT_C32", "DT_C32"), ("B_MUL", "DT_C32", "DT_C32"), ("B_MUL", "DT_C64", "DT_C64"), ("B_SUB", "DT_C64", "DT_C64"),
             ("B_ABSGT", "DT_C32", "DT_BOOL"), ("B_MUL", "DT_F32", "DT_F32"), ("B_MUL", "DT_F16", "DT_F16")]
+    cols = [("B_MUL", "DT_F32", "DT_F32", 0), ("B_MUL", "DT_F32", "DT_F32", 2), ("B_MUL", "DT_C64", "DT_C64", 1), ("B_EQ", "DT_F32", "DT_BOOL", 0),
+            ("B_GT", "DT_F64", "DT_BOOL", 1), ("B_EQ", "DT_C32", "DT_BOOL", 2), ("B_ABSGT", "DT_C32", "DT_BOOL", 0)]
     src.write_text("".join(f'#include "{os.path.join(CSRC, h)}"\n' for h in ("fred_kernels.hpp", "red_launch.hpp")) + "namespace ocn {\n" + "".join(
-        f"template __global__ void fred_rows_lean_kernel<Sig<{op}, {t}, {t}, {o}, 2>, R_SUM>(const RedLeanArgs);\n" for op, t, o in rows) + "}\n")
+        f"template __global__ void fred_rows_lean_kernel<Sig<{op}, {t}, {t}, {o}, 2>, R_SUM>(const RedLeanArgs);\n" for op, t, o in rows) + "".join(
+        f"template __global__ void fred_cols_kernel<Sig<{op}, {t}, {t}, {o}, 2>, R_SUM, {bc}, false>(const RedArgs);\n" for op, t, o, bc in cols) + "}\n")
     kernels = _spills(src, "VGPRs")
-    assert len(kernels) == len(rows) and all(k == 0 for _, k in kernels), kernels
+    assert len(kernels) == len(rows) + len(cols) and all(k == 0 for _, k in kernels), kernels
