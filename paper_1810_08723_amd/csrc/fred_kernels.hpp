@@ -207,8 +207,9 @@ OCN_DEV typename FusedFold<G, OP>::A fred_lean_fold(const char *pa, const char *
   constexpr int V = 16 / (int)sizeof(SAt);
   // Vectors in flight of each input.  (Four spill complex sums under the 64 registers of OCN_ROWS_OCC, complex
   // double products of [16384, 1000] 116 us where two take 76, and lose 5 to 15 % of halves and of rows of
-  // 50000; they win 5 % of float rows of 1000.)
-  constexpr int U = 2;
+  // 50000 doubles.  Products of four-byte elements win: float [16384, 1000] 21.2 -> 19.9, [20000, 600] with a row
+  // 10.7 -> 10.0.)
+  constexpr int U = sizeof(SAt) == 4 && G::SO_DT == G::SA_DT ? 4 : 2;
   // Trips are counted for all lanes alike: with the count of each lane its own, a row of 250 vectors is
   // three round trips of a wavefront, for the lanes with four vectors and those with three.  (Except for moduli
   // of complex elements, where that spills: [3000, 4096] 34 us, 30 so.)
