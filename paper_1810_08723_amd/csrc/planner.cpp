@@ -329,6 +329,9 @@ constexpr int64_t kBoxLds = 32 * 1024;
 // The contiguous bytes each operand should have in a box: two lines, since runs start anywhere and
 // touch one line more than they fill (6000 x 5000 plus a transpose: 69 us, 77 with 128 bytes).
 constexpr int64_t kBoxRun = 256;
+// Gaps of up to this many bytes do not end what an operand touches in a row: the next piece is in the
+// same line or the one after it.
+constexpr int64_t kBoxGap = 64;
 // Boxes in a row that one XCD takes.  Neighbouring boxes share the lines at the ends of their runs; dealt
 // out one by one every XCD fetches them for itself (complex products of [44, 66, 17, 71, 2]: 263 MB
 // fetched instead of 143, 55 us instead of 44; groups of 4 and 64 are within 6 % of 16, an eighth of
@@ -336,9 +339,11 @@ constexpr int64_t kBoxRun = 256;
 constexpr int kBoxGroup = 16;
 
 // Lays the operation out in boxes; false where that form does not apply.  Extents grow from one, always
-// for the operand whose contiguous runs inside the box are shortest, along the axis that continues its
-// run (an axis covered whole passes the run on to the next one).  Axes are cut into equal parts at the
-// end.
+// for the operand that touches the fewest bytes in a row inside the box, along the axis that lengthens
+// them (an axis covered whole passes on to the next one); an operand that a wide gap cuts off is left
+// as it is, or it would take the whole box (double [1965283, 14] transposed plus a stepped column 478 us,
+// 106 in tiles; float [2, 86669, 250], one input of two elements and a gap, 571 -> 233).  Axes are cut into
+// equal parts at the end.
 bool plan_boxes(EwPlan &p) {
   const int n = p.ndim, nin = p.nin;
   const Operand *ops[3] = {&p.out, &p.a, &p.b};
@@ -380,37 +385,52 @@ bool plan_boxes(EwPlan &p) {
     for (int x = 1; x <= nin; ++x) bytes += e * es[x];
     return bytes <= kBoxLds;
   };
-  // one step along the dim that continues operand x's runs; false if the box cannot grow there
-  auto grow = [&](int x) {
+  // the bytes operand x touches in a row inside the box, gaps shorter than a line's half among them, and
+  // the dim that would lengthen them (-1: none would, or not inside this box)
+  auto reach_of = [&](int x, int *next) {
+    int64_t r = es[x];
+    *next = -1;
     for (int k = 0; k < nd[x]; ++k) {
       const int d = ord[x][k];
-      if (ext[d] >= p.size[d]) continue;
-      int tiled = 0;
-      for (int i = 0; i < n; ++i) tiled += ext[i] > 1;
-      if (ext[d] == 1 && tiled == 4) return false;
-      const int64_t others = elems / ext[d];
-      int64_t e = std::min<int64_t>(p.size[d], 2 * (int64_t)ext[d]);
-      if (3 * e >= 2 * p.size[d]) e = p.size[d];
-      while (e > ext[d] && (others * e > most || !fits(others * e) || e > 4096)) --e;
-      if (e == ext[d]) return false;
-      ext[d] = (int32_t)e;
-      elems = others * e;
-      return true;
+      if (ops[x]->stride[d] > std::max<int64_t>(r, kBoxGap)) break;
+      r += (ext[d] - 1) * ops[x]->stride[d];
+      if (ext[d] < p.size[d]) { *next = d; break; }
     }
-    return false;
+    return r;
   };
+  int tiled = 0;
+  // one step along a dim; false if the box cannot grow there
+  auto grow = [&](int d) {
+    if (d < 0 || ext[d] >= p.size[d] || (ext[d] == 1 && tiled == 4)) return false;
+    const int64_t others = elems / ext[d];
+    int64_t e = std::min<int64_t>(p.size[d], 2 * (int64_t)ext[d]);
+    if (3 * e >= 2 * p.size[d]) e = p.size[d];
+    while (e > ext[d] && (others * e > most || !fits(others * e) || e > 4096)) --e;
+    if (e == ext[d]) return false;
+    tiled += ext[d] == 1;
+    ext[d] = (int32_t)e;
+    elems = others * e;
+    return true;
+  };
+  // (at least two vectors of the output per lane: cdouble 5000 x 3001 transposed 94 us, 108 with one)
+  const int64_t enough = std::min<int64_t>(most, 2 * kBlock * V);
   for (bool open[3] = {true, true, nin == 2};;) {
-    int x = -1;
-    for (int y = 0; y < 3; ++y)
-      if (open[y] && (x < 0 || run_of(y, nullptr) < run_of(x, nullptr))) x = y;
-    if (x < 0) break;
-    // (at least two vectors of the output per lane: cdouble 5000 x 3001 transposed 94 us, 108 with one)
-    if (run_of(x, nullptr) >= kBoxRun && elems >= std::min<int64_t>(most, 2 * kBlock * V)) break;
-    if (!grow(x)) open[x] = false;
+    int x = -1, next = -1;
+    int64_t reach = 0;
+    for (int y = 0; y < 3; ++y) {
+      int d;
+      const int64_t r = open[y] ? reach_of(y, &d) : 0;
+      if (open[y] && (x < 0 || r < reach)) x = y, reach = r, next = d;
+    }
+    if (x < 0 || (reach >= kBoxRun && elems >= enough)) break;
+    if (!grow(next)) open[x] = false;
   }
+  for (int k = 0; k < nd[0] && elems < enough; ++k)
+    while (elems < enough && grow(ord[0][k])) {}
   for (int d = 0; d < n; ++d) {
     const int64_t parts = (p.size[d] + ext[d] - 1) / ext[d];
-    ext[d] = (int32_t)((p.size[d] + parts - 1) / parts);
+    int64_t e = (p.size[d] + parts - 1) / parts;
+    ext[d] = (int32_t)e;
   }
   elems = 1;
   p.total_tiles = 1;

@@ -1,0 +1,32 @@
+"""Which elementwise calls go out in boxes of any extents, and what their boxes cover (no GPU needed)."""
+import paper_1810_08723_amd as ocn
+
+BASES = (0x10000000000, 0x20000000000, 0x30000000000)  # far apart: never dereferenced
+
+
+def _tensor(dtype, es, sizes, strides, which):
+    if strides is None:
+        strides, acc = [], es
+        for n in reversed(sizes):
+            strides.insert(0, acc)
+            acc *= n
+    return ocn.Tensor(BASES[which], dtype, tuple(sizes), tuple(strides), 0, 0)
+
+
+def _unary(dtype, es, sizes, sa, so=None):
+    return ocn.plan_unary("neg", _tensor(dtype, es, sizes, sa, 1), _tensor(dtype, es, sizes, so, 0))
+
+
+def _binary(dtype, es, sizes, sa, sb, so=None):
+    broadcast = [1 if s == 0 else n for n, s in zip(sizes, sb)]
+    return ocn.plan_binary("add", _tensor(dtype, es, sizes, sa, 1), _tensor(dtype, es, broadcast, sb, 2),
+                           _tensor(dtype, es, sizes, so, 0))
+
+
+def test_an_operand_cut_off_in_memory_does_not_take_the_box():
+    # b is stepped: no extent makes its runs longer, and the output's axis has 14 elements to cover
+    p = _binary("double", 8, (196528, 14), (8, 196528 * 8), (16, 0))
+    assert p["tile_log2"][1] >= 3
+    # a has two elements together and a gap, the output long runs
+    p = _unary("double", 8, (4, 300, 500), (8, 64, 19200))
+    assert p["tile_log2"][2] >= 4
