@@ -30,3 +30,9 @@ def test_an_operand_cut_off_in_memory_does_not_take_the_box():
     # a has two elements together and a gap, the output long runs
     p = _unary("double", 8, (4, 300, 500), (8, 64, 19200))
     assert p["tile_log2"][2] >= 4
+
+
+def test_parts_of_whole_vectors():
+    # five parts of 64 bytes, not of 58: the rest of a vector is stored byte by byte
+    p = _unary("uint8", 1, (50001, 289), (1, 50001))
+    assert p["vec"] == 16 and p["lds_bytes"] == 64 * (64 + 16) and p["grid"] == (50001 + 63) // 64 * 5
