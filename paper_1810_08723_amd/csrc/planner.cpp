@@ -443,6 +443,9 @@ bool plan_boxes(EwPlan &p) {
     p.total_tiles *= p.ntiles[d];
   }
   if (elems < 2 || p.total_tiles > max_launch_blocks()) return false;
+  // (four short axes, and a long one that no box may cover too: less than a wavefront's work per workgroup;
+  // float [2, 5, 866805, 2, 3] in boxes of 60 elements 1694 us, 329 in tiles)
+  if (elems < kWave * V && p.total_tiles > 2 * kNumCUs) return false;
   // the orders inside the box, and how far runs go
   for (int x = 0; x <= nin; ++x) {
     int m = 0;

@@ -36,3 +36,10 @@ def test_parts_of_whole_vectors():
     # five parts of 64 bytes, not of 58: the rest of a vector is stored byte by byte
     p = _unary("uint8", 1, (50001, 289), (1, 50001))
     assert p["vec"] == 16 and p["lds_bytes"] == 64 * (64 + 16) and p["grid"] == (50001 + 63) // 64 * 5
+
+
+def test_no_boxes_of_a_few_elements():
+    # five axes, of which a box covers four: the short ones
+    sizes = (2, 5, 8668, 2, 3)
+    p = _binary("float", 4, sizes, (1040160, 208032, 24, 12, 4), (4, 16, 240, 8, 80))
+    assert 2 * 5 * 8668 * 2 * 3 >= p["grid"] * 64 * p["vec"]
