@@ -338,6 +338,41 @@ constexpr int64_t kBoxGap = 64;
 // all boxes each is 5 to 20 % slower on plain transposes).
 constexpr int kBoxGroup = 16;
 
+// Turns that the first wavefront takes to read an element per lane from LDS, at most: lanes whose elements lie
+// in the same bank, but not in the same place.  pos: bytes per coordinate.  (A run that several dims
+// share has no gaps between rows: int32 [8, 189, 4751] with the axis of 8 fastest, 32 turns, 20.5 us in
+// boxes and 15.1 in tiles.)
+int bank_turns(const EwPlan &p, int V, int es, const int32_t *ext, const int32_t *pos) {
+  const int width = std::max(4, es), lanes = std::min(kWave, 256 / width);   // bytes of a read; lanes served at a time
+  uint32_t c[4] = {0, 0, 0, 0};
+  int64_t run = 1, e = 0;
+  for (int k = 0; k < p.box_run[0]; ++k) run *= ext[p.ord_o[k]];
+  int32_t last[kWave];
+  uint8_t count[kWave] = {0};
+  int most = 0;
+  for (int lane = 0; lane < lanes; ++lane) {
+    int32_t at = 0;
+    for (int k = 0; k < p.nord; ++k) at += (int32_t)c[k] * pos[p.ord_o[k]];
+    at /= width;
+    const int bank = at % lanes;
+    if (count[bank] == 0 || last[bank] != at) most = std::max<int>(most, ++count[bank]);
+    last[bank] = at;
+    // the next vector: further along the run, or the first of the next row
+    int k = 0;
+    if ((e += V) < run) c[0] += (uint32_t)V;
+    else {
+      e = 0;
+      for (; k < p.box_run[0]; ++k) c[k] = 0;
+      if (k < p.nord) ++c[k];
+    }
+    for (; k + 1 < p.nord && c[k] >= (uint32_t)ext[p.ord_o[k]]; ++k) {
+      c[k + 1] += c[k] / (uint32_t)ext[p.ord_o[k]];
+      c[k] %= (uint32_t)ext[p.ord_o[k]];
+    }
+  }
+  return most;
+}
+
 // Lays the operation out in boxes; false where that form does not apply.  Extents grow from one, always
 // for the operand that touches the fewest bytes in a row inside the box, along the axis that lengthens
 // them (an axis covered whole passes on to the next one); an operand that a wide gap cuts off is left
@@ -470,6 +505,7 @@ bool plan_boxes(EwPlan &p) {
   // An input that runs along with the output, or is broadcast along its runs, is read in place; any
   // other one is staged, in vectors where it is contiguous along its fastest axis.
   int64_t lds = 0;
+  const int bytes = es[0] + es[1] + (nin == 2 ? es[2] : 0);
   for (int x = 1; x <= nin; ++x) {
     bool along = true, broadcast = true;
     int64_t run = es[x];
@@ -491,6 +527,16 @@ bool plan_boxes(EwPlan &p) {
       int64_t pitch = (len * es[x] + 15) / 16 * 16;
       if (pitch % 32 == 0) pitch += 16;
       lds += pitch * rows;
+      // (lanes that read from the same few banks, more than 16 turns and three per byte that an element
+      // moves: of 970 such calls three in five lose to tiles, of 39000 others one in twenty does)
+      int32_t pos[kMaxDims] = {0};
+      int64_t at = es[x], row = pitch;
+      for (int k = 0; k < p.box_dims[x]; ++k) {
+        int64_t &step = k < p.box_run[x] ? at : row;
+        pos[o[k]] = (int32_t)step;
+        step *= ext[o[k]];
+      }
+      if (bank_turns(p, V, es[x], ext, pos) > std::max(16, 3 * bytes)) return false;
     }
   }
   p.stage_a = p.box_how[0] == 0;

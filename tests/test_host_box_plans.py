@@ -43,3 +43,8 @@ def test_no_boxes_of_a_few_elements():
     sizes = (2, 5, 8668, 2, 3)
     p = _binary("float", 4, sizes, (1040160, 208032, 24, 12, 4), (4, 16, 240, 8, 80))
     assert 2 * 5 * 8668 * 2 * 3 >= p["grid"] * 64 * p["vec"]
+
+
+def test_lanes_do_not_read_from_the_same_banks():
+    # a run of 8 x 189 elements in LDS, read eight elements apart: tiles, whose rows are padded
+    assert _unary("int32", 4, (8, 189, 4751), (4, 152032, 32))["tile_log2"] == (3, 9)
