@@ -527,7 +527,10 @@ bool plan_boxes(EwPlan &p) {
       int64_t pitch = (len * es[x] + 15) / 16 * 16;
       if (pitch % 32 == 0) pitch += 16;
       lds += pitch * rows;
-      // (lanes that read from the same few banks, more than 16 turns and three per byte that an element
+      // (16-byte loads for four bytes or less of a row: bytes [2, 18528704] three apart, cast to 16 bits, 87 us, 31
+      // in tiles; ...
+      if ((len * es[x] + 15) / 16 * 16 * rows >= 4 * elems * es[x]) return false;
+      // ... or lanes that read from the same few banks, more than 16 turns and three per byte that an element
       // moves: of 970 such calls three in five lose to tiles, of 39000 others one in twenty does)
       int32_t pos[kMaxDims] = {0};
       int64_t at = es[x], row = pitch;
@@ -544,6 +547,10 @@ bool plan_boxes(EwPlan &p) {
   p.lds_bytes = lds;
   if (!p.stage_a && !p.stage_b) return false;
   if (lds > 64 * 1024) return false;
+  // (vectors of which an eighth or less lies in a run: bytes [4, 161832, 2, 2], pairs with a gap, 13.8 us, 10.6 in tiles)
+  int64_t run = 1;
+  for (int k = 0; k < p.box_run[0]; ++k) run *= ext[p.ord_o[k]];
+  if (run * 8 <= V) return false;
   p.tile_bits = ilog2_ceil(elems);
   p.vecw_o = ilog2_ceil(V);
   p.vec = V;

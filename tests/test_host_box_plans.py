@@ -48,3 +48,10 @@ def test_no_boxes_of_a_few_elements():
 def test_lanes_do_not_read_from_the_same_banks():
     # a run of 8 x 189 elements in LDS, read eight elements apart: tiles, whose rows are padded
     assert _unary("int32", 4, (8, 189, 4751), (4, 152032, 32))["tile_log2"] == (3, 9)
+
+
+def test_no_staging_of_two_bytes_at_a_time():
+    # six bytes from pair to pair: a vector of sixteen bytes would be loaded for each
+    assert not _unary("int16", 2, (48, 157000, 2), (6, 288, 2), (2, 96, 15072000))["stage_a"]
+    # vectors of sixteen outputs of which two lie together
+    assert not _unary("uint8", 1, (4, 161832, 2), (1, 4, 647328), (970992, 6, 1))["stage_a"]
