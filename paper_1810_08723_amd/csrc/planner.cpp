@@ -379,8 +379,8 @@ int bank_turns(const EwPlan &p, int V, int es, const int32_t *ext, const int32_t
 // as it is, or it would take the whole box (double [1965283, 14] transposed plus a stepped column 478 us,
 // 106 in tiles; float [2, 86669, 250], one input of two elements and a gap, 571 -> 233).  Axes are cut into
 // equal parts at the end, the output's fastest one into whole vectors, whose rest would be stored element by
-// element (bytes [50001, 289] transposed 20.8 us in parts of 58).
-bool plan_boxes(EwPlan &p) {
+// element (bytes [50001, 289] transposed 20.8 us in parts of 58).  tiles_stage: tiles would stage an input.
+bool plan_boxes(EwPlan &p, bool tiles_stage) {
   const int n = p.ndim, nin = p.nin;
   const Operand *ops[3] = {&p.out, &p.a, &p.b};
   const int es[3] = {dt_size(p.out.dtype), dt_size(p.a.dtype), nin == 2 ? dt_size(p.b.dtype) : 1};
@@ -505,6 +505,7 @@ bool plan_boxes(EwPlan &p) {
   // An input that runs along with the output, or is broadcast along its runs, is read in place; any
   // other one is staged, in vectors where it is contiguous along its fastest axis.
   int64_t lds = 0;
+  int staged = 0;
   const int bytes = es[0] + es[1] + (nin == 2 ? es[2] : 0);
   for (int x = 1; x <= nin; ++x) {
     bool along = true, broadcast = true;
@@ -522,6 +523,7 @@ bool plan_boxes(EwPlan &p) {
       // (strided along its own fastest axis: the form for any alignment gathers such an input's elements)
       if (p.box_run[x] == 0) return false;
       p.box_how[x - 1] = 0;
+      ++staged;
       int64_t rows = 1, len = 1;
       for (int k = 0; k < p.box_dims[x]; ++k) (k < p.box_run[x] ? len : rows) *= ext[o[k]];
       int64_t pitch = (len * es[x] + 15) / 16 * 16;
@@ -551,6 +553,9 @@ bool plan_boxes(EwPlan &p) {
   int64_t run = 1;
   for (int k = 0; k < p.box_run[0]; ++k) run *= ext[p.ord_o[k]];
   if (run * 8 <= V) return false;
+  // Few boxes that stage what tiles read in place: long vectors are few lanes (of 360 calls on two such
+  // inputs of bytes 206 lose; [9, 262] 5.0 us in tiles, 6.2 so).
+  if (!tiles_stage && p.total_tiles < 2 * kNumCUs && (V >= 16 || (V >= 8 && staged == 2))) return false;
   p.tile_bits = ilog2_ceil(elems);
   p.vecw_o = ilog2_ceil(V);
   p.vec = V;
@@ -844,7 +849,8 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
                      (numel < 1 << 19 && numel * 10 >= (n0 + 63) / 64 * 64 * ((n1 + 63) / 64 * 64) * 7) ||
                      (n1 * 4 <= VT && (n1 & (n1 - 1)) == 0 && numel >= n1 << 19));
       EwPlan q = p;
-      if (numel < (int64_t)1 << 31 && !matrix_in_tiles && plan_boxes(q)) {
+      const bool tiles_stage = (stage_a0 && p.size[fa] * es_a >= 32) || (stage_b0 && p.size[fb] * es_b >= 32);
+      if (numel < (int64_t)1 << 31 && !matrix_in_tiles && plan_boxes(q, tiles_stage)) {
         *plan = q;
         return OCN_OK;
       }

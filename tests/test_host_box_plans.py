@@ -55,3 +55,9 @@ def test_no_staging_of_two_bytes_at_a_time():
     assert not _unary("int16", 2, (48, 157000, 2), (6, 288, 2), (2, 96, 15072000))["stage_a"]
     # vectors of sixteen outputs of which two lie together
     assert not _unary("uint8", 1, (4, 161832, 2), (1, 4, 647328), (970992, 6, 1))["stage_a"]
+
+
+def test_few_boxes_of_bytes():
+    # a few thousand bytes in three orders: vectors of sixteen leave most lanes without work
+    p = _binary("uint8", 1, (9, 262), (1, 9), (1, 9))
+    assert not p["stage_a"] and not p["stage_b"]
