@@ -1,0 +1,45 @@
+"""Launch shapes of reductions: outputs that one workgroup takes whole, and columns of a few rows (no GPU
+needed)."""
+import pytest
+
+import paper_1810_08723_amd as ocn
+
+BASE_A, BASE_B, BASE_OUT = 0x10000000000, 0x20000000000, 0x30000000000  # far apart: never dereferenced
+
+
+def _plan(op, dtype, es, sizes, axis, strides=None, offset=0):
+    if strides is None:
+        strides, acc = [], es
+        for n in reversed(sizes):
+            strides.insert(0, acc)
+            acc *= n
+    kept = [n for d, n in enumerate(sizes) if d != axis]
+    out, acc = [], es
+    for n in reversed(kept):
+        out.insert(0, acc)
+        acc *= n
+    return ocn.plan_reduce(op, ocn.Tensor(BASE_A, dtype, tuple(sizes), tuple(strides), offset, 0), [axis],
+                           ocn.Tensor(BASE_OUT, dtype, tuple(kept), tuple(out), 0, 0))
+
+
+@pytest.mark.parametrize("dtype,es,offset,whole", [("half", 2, 0, 256), ("half", 2, 4, 256), ("half", 2, 2, 0), ("uint8", 1, 0, 224),
+                                                   ("uint8", 1, 1, 0), ("int8", 1, 2, 0), ("float", 4, 4, 256), ("double", 8, 8, 256)])
+def test_one_workgroup_reads_whole_words(dtype, es, offset, whole):
+    """Vectors that start inside four bytes are left to several workgroups."""
+    for kib in (160, 220, 250, 300):
+        p = _plan("max", dtype, es, (kib * 1024 // es,), 0, offset=offset)
+        assert (p["passes"], p["block"]) == ((1, 1024) if kib <= whole else (2, 256)), (kib, p)
+
+
+def test_one_workgroup_reads_whole_words_of_every_row():
+    n = 100000
+    assert _plan("max", "half", 2, (3, n), 1)["passes"] == 1
+    assert _plan("max", "half", 2, (3, n), 1, strides=(2 * n + 2, 2))["passes"] == 2
+
+
+@pytest.mark.parametrize("offset,passes", [(0, 1), (4, 1), (2, 2)])
+def test_one_workgroup_of_a_fused_product(offset, passes):
+    n = 50000
+    a, b = (ocn.Tensor(base, "half", (n,), (2,), offset, 0) for base in (BASE_A, BASE_B))
+    p = ocn.plan_binary_reduce("mul", "sum", a, b, [0], ocn.Tensor(BASE_OUT, "half", (), (), 0, 0), "half")
+    assert p["passes"] == passes and p["fused"]
