@@ -43,3 +43,13 @@ def test_one_workgroup_of_a_fused_product(offset, passes):
     a, b = (ocn.Tensor(base, "half", (n,), (2,), offset, 0) for base in (BASE_A, BASE_B))
     p = ocn.plan_binary_reduce("mul", "sum", a, b, [0], ocn.Tensor(BASE_OUT, "half", (), (), 0, 0), "half")
     assert p["passes"] == passes and p["fused"]
+
+
+@pytest.mark.parametrize("dtype,es,rows,cols,lane", [("int16", 2, 2, 335298, False), ("half", 2, 7, 600800, False), ("half", 2, 7, 900000, True),
+                                                     ("float", 4, 2, 335298, True), ("int32", 4, 8, 131072, True), ("int32", 4, 9, 131072, False),
+                                                     ("double", 8, 8, 65536, True), ("double", 8, 8, 65534, False)])
+def test_few_rows_of_wide_columns(dtype, es, rows, cols, lane):
+    """A lane per vector of columns where there are enough of them, more of the long vectors of 16 bits."""
+    lanes = -(-cols // (16 // es))
+    p = _plan("max", dtype, es, (rows, cols), 0)
+    assert p["vec"] == 16 // es and (p["grid"] == -(-lanes // 256)) == lane, p
