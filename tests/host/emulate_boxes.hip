@@ -66,13 +66,16 @@ static HostTensor make_view(int dt, int ndim, const int64_t *sizes, char *base, 
   return h;
 }
 
-static int g_boxes, g_clipped, g_how[2], g_back, g_dims[5], g_runs[4], g_broadcast, g_carry;
+static int g_boxes, g_full, g_clipped, g_how[2], g_back, g_dims[5], g_runs[4], g_broadcast, g_carry;
 
 static int replay(const EwPlan &p, const HostTensor *h, int case_no) {
   const int es[3] = {dt_size(p.out.dtype), dt_size(p.a.dtype), dt_size(p.b.dtype)};
   const BoxArgs f = make_box_args(p);
   const int nin = p.nin;
   ++g_boxes;
+  int64_t elems = 1;
+  for (int d = 0; d < p.ndim; ++d) elems *= p.box[d];
+  if (elems >= 1500 && es[0] >= 4) ++g_full;   // (boxes are halved until there are enough of them)
   ++g_dims[p.nord];
   ++g_runs[f.o.nrun];
   std::vector<uint8_t> written((h[0].hi - h[0].lo) / es[0], 0);
@@ -199,7 +202,8 @@ int main(int argc, char **argv) {
       {1, U_IDENT, DT_F32, DT_F32, DT_U8}, {2, B_LT, DT_I64, DT_I64, DT_BOOL}, {2, B_ADD, DT_C16, DT_C16, DT_C16},
       {2, B_MUL, DT_F32, DT_C32, DT_C32}, {2, B_ADD, DT_F16, DT_F16, DT_F16}};
   for (int c = 0; c < ncases; ++c) {
-    const int ndim = rnd_in(2, 6);
+    const bool large = c % 80 == 79;   // boxes of full size
+    const int ndim = rnd_in(2, large ? 4 : 6);
     int64_t sizes[8], total = 1;
     for (int i = 0; i < ndim; ++i) {
       const int kind = rnd_in(0, 3);
@@ -207,6 +211,7 @@ int main(int argc, char **argv) {
       if (total * sizes[i] > 100000) sizes[i] = 2;
       total *= sizes[i];
     }
+    if (large) sizes[rnd_in(0, ndim - 1)] *= (1200000 + total - 1) / total;
     const auto &k = kinds[rnd() % (sizeof kinds / sizeof kinds[0])];
     const HostTensor h[3] = {make_view(k.o, ndim, sizes, (char *)0x300000000ull, false), make_view(k.a, ndim, sizes, (char *)0x100000000ull, true),
                              make_view(k.b, ndim, sizes, (char *)0x200000000ull, true)};
@@ -222,8 +227,8 @@ int main(int argc, char **argv) {
       return 1;
     }
   }
-  std::printf("ok: %d cases, %d in boxes (dims 1: %d, 2: %d, 3: %d, 4: %d; runs along 1: %d, 2: %d, 3: %d); clipped %d, staged %d, in place %d, broadcast %d, moved back %d, carries %d, complex inputs with odd strides %d\n",
+  std::printf("ok: %d cases, %d in boxes (dims 1: %d, 2: %d, 3: %d, 4: %d; runs along 1: %d, 2: %d, 3: %d); clipped %d, staged %d, in place %d, broadcast %d, moved back %d, carries %d, complex inputs with odd strides %d, of full size %d\n",
               ncases, g_boxes, g_dims[1], g_dims[2], g_dims[3], g_dims[4], g_runs[1], g_runs[2], g_runs[3], g_clipped, g_how[0], g_how[1],
-              g_broadcast, g_back, g_carry, g_odd);
-  return g_boxes > 300 && g_dims[3] && g_dims[4] && g_runs[1] && g_runs[2] && g_runs[3] && g_clipped > 100 && g_how[0] > 100 && g_how[1] > 100 && g_broadcast > 20 && g_back > 20 && g_carry > 100 ? 0 : 1;
+              g_broadcast, g_back, g_carry, g_odd, g_full);
+  return g_boxes > 300 && g_full * 1000 >= ncases && g_dims[3] && g_dims[4] && g_runs[1] && g_runs[2] && g_runs[3] && g_clipped > 100 && g_how[0] > 100 && g_how[1] > 100 && g_broadcast > 20 && g_back > 20 && g_carry > 100 ? 0 : 1;
 }

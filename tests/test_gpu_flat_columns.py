@@ -9,7 +9,20 @@ from workloads.views import View
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(48, 1000, 777), (100, 500, 260), (3, 40, 300, 260), (64, 129, 516), (100, 131, 400), (30, 128, 1001)]
+# (the last five take the form for the types in FLAT; the others for some types, and the forms beside it)
+SHAPES = [(100, 500, 260), (3, 40, 300, 260), (64, 129, 516), (100, 131, 400), (30, 128, 1001),
+          (48, 1000, 777), (3, 257, 777), (2, 200, 1300), (5, 200, 1040), (3, 515, 1040)]
+VECTOR = {"int32": 4, "int64": 2, "int16": 8, "float": 4, "double": 2, "half": 8, "cfloat": 2}
+FLAT = {(48, 1000, 777): (2, 4, 8), (3, 257, 777): (2, 4, 8), (2, 200, 1300): (2, 4, 8), (5, 200, 1040): (2, 4), (3, 515, 1040): (8,)}
+
+
+def _in_equal_blocks(op, a, axis, out, vec):
+    """Are the columns cut into blocks of another number of lanes than a power of two?"""
+    import paper_1810_08723_amd as ocn
+    p = ocn.plan_reduce(op, ocn.Tensor(0x1000000000, a.dtype, a.sizes, a.strides, a.offset, 0, byteswapped=getattr(a, "byteswapped", False)), [axis],
+                        ocn.Tensor(0x2000000000, out.dtype, out.sizes, out.strides, out.offset, 0))
+    lanes, others = -(-a.sizes[-1] // vec), int(np.prod(out.sizes[:-1]))
+    return p["kernel"] == "red_cols" and p["vec"] == vec and p["split"] == 1 and all(p["grid"] != -(-lanes // c) * others for c in (1, 2, 4, 8, 16, 32, 64))
 
 
 @pytest.mark.parametrize("shape", SHAPES)
@@ -26,6 +39,7 @@ def test_equal_column_blocks(shape, dtype):
         kept = [n for d, n in enumerate(a.sizes) if d != axis]
         for op in ("sum", "max") if dtype != "cfloat" else ("sum",):
             out = View.empty(("int64" if exact else dtype) if op == "sum" else dtype, kept)
+            assert VECTOR[dtype] not in FLAT.get(shape, ()) or _in_equal_blocks(op, a, axis, out, VECTOR[dtype]), (op, dtype, a.sizes)
             print("flat columns", op, dtype, a.sizes, a.strides, flush=True)
             got, want = H.run_reduce(op, a, (axis,), out)
             if exact or op == "max":
