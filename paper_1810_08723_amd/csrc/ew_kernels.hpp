@@ -182,8 +182,7 @@ struct AnyTiledArgs {
 // (what is missing is neutral): a test per dim is a scalar load and a wait of its own.  The largest
 // coordinates a clipped box has are packed as 16 bits per dim.
 constexpr uint32_t kBoxSlack = 64;          // offsets into an input start here: they stay positive for vectors moved back
-constexpr int kBoxDims = 4;                 // most dims of a box
-constexpr int kBoxRows = 3;                 // most of them besides the first of a run
+constexpr int kBoxRows = 3;                 // most dims of a box (four) besides the first of a run
 constexpr int kBoxRunDims = 3;              // most dims of the output's run
 constexpr int kBoxGrid = 4;                 // box coordinates that are split off without a test
 enum { kBoxStaged, kBoxInPlace };

@@ -1349,7 +1349,7 @@ void choose_reduce_launch(RedPlan &p) {
   p.workspace_bytes = p.split > 1 ? (size_t)(p.nout * p.split * acc_es) : 0;
   // an input that cannot stay in the caches anyway is read with streaming loads (whole
   // 16-byte vectors only: neighbouring lanes then cover whole lines)
-  p.nt_load = p.vec > 1 && aligned && p.kernel != OCN_KERNEL_RED_GENERIC && p.nout * p.nredtot * es >= kStreamBytes;
+  p.nt_load = p.vec > 1 && aligned && p.cpw != 0 && p.kernel != OCN_KERNEL_RED_GENERIC && p.nout * p.nredtot * es >= kStreamBytes;
 }
 
 }  // namespace

@@ -105,10 +105,11 @@ struct RedPlan {
   int a_dtype = 0, out_dtype = 0;
   int64_t nout = 0, nredtot = 0;
   int vec = 1;
-  int group = kBlock;           // lanes cooperating on one output (rows kernel): a power of two up to 64, or 256
+  int group = kBlock;           // lanes cooperating on one output (rows kernel): a power of two up to 64, or 256, or 1024
   int block = kBlock;           // threads per workgroup (the cols kernel may use 1024)
   bool short_rows = false;      // rows kernel: every row fits one vector per lane of its group (loop-free kernel)
-  int cpw = kWave;              // cols kernel: lanes per row of columns (power of two, at most a wavefront)
+  int cpw = kWave;              // cols kernel: lanes per row of columns, a power of two up to a wavefront; 0: every
+                                // vector of columns has a lane of its own, for all of its rows
   bool flat_cols = false;       // cols kernel: cpw is any number, the workgroup's lanes go on through further rows
   bool nt_load = false;         // the input is far larger than the caches: stream it (non-temporal vector loads)
   bool lean = false;            // rows kernel: the common 2-D shape, run by the lean form of the kernel

@@ -1134,7 +1134,7 @@ OCN_DEV void cols_flat_body(KRedArgs &p, typename Reducer<S, OP>::A *lds) {
 // The forms above give a wavefront 64 / cpw rows and a workgroup four wavefronts: with five rows of
 // fifteen complex columns 40 of 256 lanes had any, and 244044 workgroups a barrier each (471 us, 38 here,
 // 4.6 TB/s).
-template <int S, int OP, int V, bool NT, bool SW>
+template <int S, int OP, int V, bool SW>
 OCN_DEV void cols_lane_body(KRedArgs &p) {
   using R = Reducer<S, OP>;
   using A = typename R::A;
@@ -1171,7 +1171,7 @@ OCN_DEV void cols_lane_body(KRedArgs &p) {
   for (uint32_t r = 0; r < rows; r += U) {   // (past the last row it is loaded again and left out)
     Pk pk[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) load_vec<St, V, NT>(src + (int64_t)(r + u < rows ? r + u : rows - 1) * step, pk[u]);
+    for (int u = 0; u < U; ++u) load_vec<St, V, false>(src + (int64_t)(r + u < rows ? r + u : rows - 1) * step, pk[u]);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (r + u < rows) {
@@ -1192,13 +1192,13 @@ template <int S, int OP> __global__ __launch_bounds__(kBlock) void red_cols_lane
   constexpr int VF = 16 / (int)sizeof(storage_t<S>) > 0 ? 16 / (int)sizeof(storage_t<S>) : 1;
   if constexpr (VF > 1 && VF <= 8) {
     if (p.vec > 1) {
-      if (p.swap_a) cols_lane_body<S, OP, VF, false, true>(p);
-      else cols_lane_body<S, OP, VF, false, false>(p);
+      if (p.swap_a) cols_lane_body<S, OP, VF, true>(p);
+      else cols_lane_body<S, OP, VF, false>(p);
       return;
     }
   }
-  if (p.swap_a) cols_lane_body<S, OP, 1, false, true>(p);
-  else cols_lane_body<S, OP, 1, false, false>(p);
+  if (p.swap_a) cols_lane_body<S, OP, 1, true>(p);
+  else cols_lane_body<S, OP, 1, false>(p);
 }
 
 // (a kernel of its own: beside the other forms it cost those registers, 2 % of some sums)
@@ -1207,17 +1207,15 @@ template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) voi
   KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
   if (p.warm) warm_arguments<RedArgs>();
   using A = typename Reducer<S, OP>::A;
-  constexpr int VF = 16 / (int)sizeof(storage_t<S>) > 0 ? 16 / (int)sizeof(storage_t<S>) : 1;
+  constexpr int VF = 16 / (int)sizeof(storage_t<S>);
   extern __shared__ __align__(16) unsigned char red_cols_lds_raw[];
   A *lds = reinterpret_cast<A *>(red_cols_lds_raw);
-  if constexpr (VF > 1 && VF <= 8) {
-    if (p.swap_a) {
-      if (p.nt_load) cols_flat_body<S, OP, VF, true, true>(p, lds);
-      else cols_flat_body<S, OP, VF, false, true>(p, lds);
-    } else {
-      if (p.nt_load) cols_flat_body<S, OP, VF, true, false>(p, lds);
-      else cols_flat_body<S, OP, VF, false, false>(p, lds);
-    }
+  if (p.swap_a) {
+    if (p.nt_load) cols_flat_body<S, OP, VF, true, true>(p, lds);
+    else cols_flat_body<S, OP, VF, false, true>(p, lds);
+  } else {
+    if (p.nt_load) cols_flat_body<S, OP, VF, true, false>(p, lds);
+    else cols_flat_body<S, OP, VF, false, false>(p, lds);
   }
 }
 
