@@ -1691,9 +1691,13 @@ OCN_DEV void box_output(KBoxOutput &k, BoxOutput &x) {
                "s"(x.pos[0][2]), "s"(x.pos[1][0]), "s"(x.pos[1][1]), "s"(x.pos[1][2]), "s"(x.unit), "s"(x.lim_run));
 }
 
-// Vectors of a staged input, and passes of inputs read in place, that a lane has in flight.  Four of
-// either take 87 to 97 registers instead of 59, and fewer wavefronts lose more than the loads win (6000 x
-// 5000 plus a transpose 69 us with two and two, 76 with four passes, 72 with one).
+// Vectors of a staged input, and passes of inputs read in place, that a lane has in flight.  With two and
+// two, kernels of two inputs take 53 to 86 registers (5 to 7 wavefronts per SIMD; floats 65), 134 of one-byte
+// types (3); those of one input 38 to 68, unless an elementary function takes more.  Four of either take 87 to
+// 97 of floats, and fewer wavefronts lose more than the loads win (6000 x 5000 plus a transpose 69 us with
+// two and two, 76 with four passes, 72 with one).
+// The private segment of 68 or 132 bytes that kernels of two inputs reserve holds scalar registers that the
+// compiler then keeps in lanes of a vector register: no instruction accesses it.
 constexpr int kBoxLoads = 2, kBoxAhead = 2;
 // STA, STB: the input is staged in LDS (else read in place).
 template <class G, bool STA, bool STB>

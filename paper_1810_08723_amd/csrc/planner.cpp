@@ -323,7 +323,8 @@ void choose_tiles(EwPlan &p, TileRule rule, int fa, int fb) {
 //
 // A box has about this many elements (twice as many of one or two bytes): staged inputs take 8 to 32 KiB
 // of LDS, so that four or more workgroups share a CU (4096 complex elements in 64 KiB: 49 us where
-// 2048 take 44), and a lane moves two to four vectors of each operand.
+// 2048 take 44; three, of one-byte types with two inputs, for their registers), and a lane moves two to
+// four vectors of each operand.
 constexpr int64_t kBoxElems = 2048;
 constexpr int64_t kBoxLds = 32 * 1024;
 // The contiguous bytes each operand should have in a box: two lines, since runs start anywhere and
@@ -834,15 +835,17 @@ int plan_elementwise(int nin, int op, const ocn_tensor *a, const ocn_tensor *b,
       return OCN_OK;
     }
     if (rule == kTilesAny) {
-      // Boxes of any extents where the tiles above do not fit: over forty shapes of two to five dims,
-      // odd ones, and ten type combinations 0.97 to 5.3 times as fast as tiles of any alignment (6000 x
-      // 5000 plus a transpose 73.7 -> 69.3 us, float [200001, 17, 17] transposed 289 -> 105, complex
-      // products of [5, 25, 5, 38, 17] 15.3 -> 6.9), 0.88 in one (bytes [50001, 289] transposed).  Those
-      // keep what was not measured, 2^31 elements and more; inputs strided along their own fastest
-      // axis, which they gather (every other float of [200001, 17, 17] 174 us, 373 by elements in boxes);
-      // and of matrices: large ones of four bytes with one input, which gain 2 % (5000 x 3001 33.0 and
-      // 32.2), small ones that fill tiles of 64 x 64 to 70 %, and those with an output axis of a quarter
-      // vector, whose routes are part of what plan inspection has always reported.
+      // Boxes of any extents where the tiles above do not fit: over 34500 random calls of one to five dims, 2000
+      // to 60 million elements and ten types they take 0.72 of the time of tiles of any alignment (6000 x 5000
+      // plus a transpose 73.7 -> 69.3 us, float [200001, 17, 17] transposed 289 -> 105, complex products of
+      // [5, 25, 5, 38, 17] 15.3 -> 6.9); one call in 38 is slower by more than 5 %, one in 300 by 20 %.  Tiles
+      // keep what was not measured, 2^31 elements and more; inputs strided along their own fastest axis,
+      // which they gather (every other float of [200001, 17, 17] 174 us, 373 by elements in boxes); and of
+      // matrices: large ones of four bytes with one input (5000 x 3001 27.4 us in tiles and 32.7 in boxes,
+      // 1185 x 50123 83 and 119, 3490 x 1122 12.6 and 10.8), and two kinds whose layout plan inspection has
+      // always reported as tiles although boxes are faster: small ones that fill tiles of 64 x 64 to 70 %
+      // (float 500 x 701 6.5 us in tiles, 5.0 in boxes) and those with an output axis of a quarter vector
+      // (bytes 4194304 x 2 13.9 and 9.6).
       const int64_t n0 = p.size[0], n1 = p.size[n - 1];
       const bool matrix_in_tiles =
           n == 2 && ((nin == 1 && es_o == 4 && es_a == 4 && n0 >= 1024 && n1 >= 1024) ||
