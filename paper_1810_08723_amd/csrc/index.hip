@@ -20,6 +20,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <type_traits>
 
 #include "../../include/ocn.h"
 #include "dtypes.hpp"
@@ -167,7 +168,6 @@ struct MaskArgs {
   int32_t contig;                     // the mask is one contiguous, 16-byte aligned run
   uint32_t *block_counts;             // [nblocks]; after the scan: exclusive prefixes
   uint32_t nblocks;
-  int32_t before;                     // how a workgroup of the write kernel finds its place: kBefore*
   int64_t *offsets;
   int64_t capacity;
   int64_t *count;
@@ -371,7 +371,9 @@ constexpr uint32_t kMaskDirect = 98304, kMaskSumChunks = 2048, kMaskSumGroups = 
 // FLAT: a contiguous mask and offsets that advance by one stride.  Bound by instructions as much as by the
 // 120 MB of offsets of 30 million elements with half of them selected: two offsets per lane and store, whole
 // lines, no index decomposition (35.1 -> 30.4 us in a trace of threshold, count and this, 5 TB/s).
-template <bool FLAT> __global__ __launch_bounds__(kBlock) void mask_write_kernel(const MaskArgs p) {
+// (BEFORE: one of the above.  Told at run time, the ways that a launch does not take cost every small launch
+// 0.3 to 0.8 us, masks with gaps 5 %.)
+template <bool FLAT, int BEFORE> __global__ __launch_bounds__(kBlock) void mask_write_kernel(const MaskArgs p) {
   __shared__ uint32_t lds[kBlock / kWave], lds_before[kBlock / kWave];
   // the positions (inside this workgroup's chunk) of its selected elements, in order: 8 KiB,
   // where the offsets themselves would take 32 KiB and leave room for five workgroups per CU
@@ -379,9 +381,9 @@ template <bool FLAT> __global__ __launch_bounds__(kBlock) void mask_write_kernel
   static_assert(kMaskChunk <= 65536, "positions inside a chunk are staged as 16-bit values");
   const uint32_t chunk = blockIdx.x, chunk0 = chunk * (uint32_t)kMaskChunk;
   const uint32_t flags = mask_flags(p, chunk0 + threadIdx.x * kMaskPerLane);
-  if (p.before != kBeforeScan) {
+  if constexpr (BEFORE != kBeforeScan) {
     uint32_t c = 0;
-    if (p.before == kBeforeCount) {
+    if constexpr (BEFORE == kBeforeCount) {
       // eight loads in flight, past the end the first one again
       constexpr uint32_t kAhead = 8;
       for (uint32_t j = 0; j < chunk; j += kAhead) {
@@ -392,7 +394,7 @@ template <bool FLAT> __global__ __launch_bounds__(kBlock) void mask_write_kernel
 #pragma unroll
         for (uint32_t k = 0; k < kAhead; ++k) c += j + k < chunk ? nonzero_bytes(v[k]) : 0u;
       }
-    } else if (p.before == kBeforeGroups) {
+    } else if constexpr (BEFORE == kBeforeGroups) {
       const uint32_t g = chunk / kMaskGroup;
       if (threadIdx.x < chunk % kMaskGroup) c = p.block_counts[g * kMaskGroup + threadIdx.x];
 #pragma unroll 4
@@ -415,7 +417,7 @@ template <bool FLAT> __global__ __launch_bounds__(kBlock) void mask_write_kernel
   }
   __syncthreads();
   int64_t base = 0;
-  if (p.before == kBeforeScan) {
+  if constexpr (BEFORE == kBeforeScan) {
     base = p.block_counts[chunk];
   } else {
 #pragma unroll
@@ -829,17 +831,26 @@ int ocn_mask_offsets(const ocn_tensor *mask, const int64_t *target_strides, void
   m.count = (int64_t *)count;
   m.nt_store = std::min<int64_t>(capacity, m.n) * 8 >= ((int64_t)32 << 20);  // too large to stay cached
   const uint32_t groups = (m.nblocks + kMaskGroup - 1) / kMaskGroup;
-  m.before = m.contig && m.n <= kMaskDirect ? kBeforeCount : m.nblocks <= kMaskSumChunks ? kBeforeSum
-             : m.contig && groups <= kMaskSumGroups ? kBeforeGroups : kBeforeScan;
-  if (m.before != kBeforeCount) {
-    if (m.before == kBeforeGroups) hipLaunchKernelGGL(mask_count_contig_kernel<true>, dim3(groups), dim3(kMaskGroup * kWave), 0, s, m);
+  const int before = m.contig && m.n <= kMaskDirect ? kBeforeCount : m.nblocks <= kMaskSumChunks ? kBeforeSum
+                     : m.contig && groups <= kMaskSumGroups ? kBeforeGroups : kBeforeScan;
+  if (before != kBeforeCount) {
+    if (before == kBeforeGroups) hipLaunchKernelGGL(mask_count_contig_kernel<true>, dim3(groups), dim3(kMaskGroup * kWave), 0, s, m);
     else if (m.contig)
       hipLaunchKernelGGL(mask_count_contig_kernel<false>, dim3((m.nblocks + kBlock / kWave - 1) / (kBlock / kWave)), dim3(kBlock), 0, s, m);
     else hipLaunchKernelGGL(mask_count_kernel, dim3(m.nblocks), dim3(kBlock), 0, s, m);
   }
-  if (m.before == kBeforeScan) hipLaunchKernelGGL(mask_scan_kernel, dim3(1), dim3(kScanBlock), 0, s, m);
-  if (m.contig && m.ndim <= 1) hipLaunchKernelGGL(mask_write_kernel<true>, dim3(m.nblocks), dim3(kBlock), 0, s, m);
-  else hipLaunchKernelGGL(mask_write_kernel<false>, dim3(m.nblocks), dim3(kBlock), 0, s, m);
+  if (before == kBeforeScan) hipLaunchKernelGGL(mask_scan_kernel, dim3(1), dim3(kScanBlock), 0, s, m);
+  auto write = [&](auto before) {
+    constexpr int BEFORE = decltype(before)::value;
+    if (m.contig && m.ndim <= 1) hipLaunchKernelGGL((mask_write_kernel<true, BEFORE>), dim3(m.nblocks), dim3(kBlock), 0, s, m);
+    else hipLaunchKernelGGL((mask_write_kernel<false, BEFORE>), dim3(m.nblocks), dim3(kBlock), 0, s, m);
+  };
+  switch (before) {
+    case kBeforeCount: write(std::integral_constant<int, kBeforeCount>{}); break;
+    case kBeforeGroups: write(std::integral_constant<int, kBeforeGroups>{}); break;
+    case kBeforeSum: write(std::integral_constant<int, kBeforeSum>{}); break;
+    default: write(std::integral_constant<int, kBeforeScan>{}); break;
+  }
   return done(hipGetLastError());
 }
 
