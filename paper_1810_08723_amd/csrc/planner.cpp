@@ -482,6 +482,9 @@ bool plan_boxes(EwPlan &p, bool tiles_stage) {
   // (four short axes, and a long one that no box may cover too: less than a wavefront's work per workgroup;
   // float [2, 5, 866805, 2, 3] in boxes of 60 elements 1694 us, 329 in tiles)
   if (elems < kWave * V && p.total_tiles > 2 * kNumCUs) return false;
+  // (the same of more boxes, but for less than an element per lane: doubles [176656, 4, 2, 8, 2] compared in
+  // boxes of 128 elements 354 us, 77 in tiles)
+  if (elems < kBlock && p.total_tiles > 16 * kNumCUs) return false;
   // the orders inside the box, and how far runs go
   for (int x = 0; x <= nin; ++x) {
     int m = 0;

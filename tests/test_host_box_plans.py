@@ -43,6 +43,11 @@ def test_no_boxes_of_a_few_elements():
     sizes = (2, 5, 8668, 2, 3)
     p = _binary("float", 4, sizes, (1040160, 208032, 24, 12, 4), (4, 16, 240, 8, 80))
     assert 2 * 5 * 8668 * 2 * 3 >= p["grid"] * 64 * p["vec"]
+    # thousands of boxes, each less than an element per lane
+    p = ocn.plan_binary("gt", _tensor("double", 8, (16656, 4, 2, 8, 2), (1024, 256, 128, 16, 8), 1),
+                        _tensor("double", 8, (16656, 4, 2, 8, 2), (256, 4263936, 8, 16, 128), 2),
+                        _tensor("bool", 1, (16656, 4, 2, 8, 2), None, 0))
+    assert 16656 * 128 >= p["grid"] * 256
 
 
 def test_lanes_do_not_read_from_the_same_banks():
