@@ -1188,11 +1188,16 @@ ColsShape choose_cols_shape(int64_t col_lanes, int64_t others, int64_t rows, int
 // if it fills three quarters of the chip evenly by itself, which saves the second launch (not in blocks
 // below 24 lanes where its rows are whole lines: [20, 4000, 800] floats 45.1 us split, 49.6 in 17 lanes).
 // Floats [64, 2000, 516] 73 -> 47 us, [128, 512, 132] 15.6 -> 9.4, [200, 1000, 280] 47 -> 37; halves [48, 1000,
-// 777] 27.7 -> 19.8.
+// 777] 27.7 -> 19.8; few rows gain as well, eight trips of the workgroup at least (int32 [3, 109, 24665] 12.4
+// -> 7.0, cfloat [230, 89, 192] 9.3 -> 6.5; none of 539 calls of 32 to 127 rows loses).
 constexpr int kFlatLanes = 1024;
 int choose_flat_columns(int64_t col_lanes, int64_t others, int64_t rows, int cpw, int64_t split, bool aligned) {
   const int64_t blocks = (col_lanes + cpw - 1) / cpw;
-  if (blocks < 2 || blocks * others > 4 * kNumCUs || col_lanes > 4096 || rows < 128) return 0;
+  if (blocks < 2 || blocks * others > 4 * kNumCUs) return 0;
+  // (wide columns of rows on vector boundaries, a thousand and more, fill the chip as they are: doubles [2588, 13648]
+  // 46.4 us split and 54.1 so, eight of 96 such calls slower and the mean 1.10 times as fast; 3 of 637 wide ones with
+  // fewer rows or rows off those boundaries, mean 1.17)
+  if (col_lanes > 4096 && aligned && rows >= 1024) return 0;
   // (at least 15 % fewer lanes than the fullest CU has; at most a quarter more than an even share)
   int64_t best = split > 1 ? col_lanes * others * 5 / (4 * kNumCUs) + 1 : (blocks * others + kNumCUs - 1) / kNumCUs * cpw * 85 / 100;
   int lanes = 0;

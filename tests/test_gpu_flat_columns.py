@@ -9,11 +9,13 @@ from workloads.views import View
 
 pytestmark = pytest.mark.gpu
 
-# (the last five take the form for the types in FLAT; the others for some types, and the forms beside it)
+# (the last nine take the form for the types in FLAT; the others for some types, and the forms beside it)
 SHAPES = [(100, 500, 260), (3, 40, 300, 260), (64, 129, 516), (100, 131, 400), (30, 128, 1001),
-          (48, 1000, 777), (3, 257, 777), (2, 200, 1300), (5, 200, 1040), (3, 515, 1040)]
+          (48, 1000, 777), (3, 257, 777), (2, 200, 1300), (5, 200, 1040), (3, 515, 1040),
+          (19, 49, 3546), (179, 55, 601), (69, 76, 1699), (1, 300, 33003)]
 VECTOR = {"int32": 4, "int64": 2, "int16": 8, "float": 4, "double": 2, "half": 8, "cfloat": 2}
-FLAT = {(48, 1000, 777): (2, 4, 8), (3, 257, 777): (2, 4, 8), (2, 200, 1300): (2, 4, 8), (5, 200, 1040): (2, 4), (3, 515, 1040): (8,)}
+FLAT = {(48, 1000, 777): (2, 4, 8), (3, 257, 777): (2, 4, 8), (2, 200, 1300): (2, 4, 8), (5, 200, 1040): (2, 4), (3, 515, 1040): (8,),
+        (19, 49, 3546): (2,), (179, 55, 601): (4,), (69, 76, 1699): (8,), (1, 300, 33003): (2, 4, 8)}
 
 
 def _in_equal_blocks(op, a, axis, out, vec):

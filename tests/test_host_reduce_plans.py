@@ -53,3 +53,14 @@ def test_few_rows_of_wide_columns(dtype, es, rows, cols, lane):
     lanes = -(-cols // (16 // es))
     p = _plan("max", dtype, es, (rows, cols), 0)
     assert p["vec"] == 16 // es and (p["grid"] == -(-lanes // 256)) == lane, p
+
+
+@pytest.mark.parametrize("dtype,es,sizes,equal", [("int32", 4, (3, 109, 24665), True), ("cfloat", 8, (230, 89, 192), True), ("double", 8, (19, 49, 3546), True),
+                                                  ("float", 4, (1, 300, 33003), True), ("float", 4, (1, 1100, 40001), True), ("double", 8, (1, 2588, 13648), False),
+                                                  ("double", 8, (2, 1559, 13504), False), ("float", 4, (20, 4000, 800), False)])
+def test_columns_in_equal_blocks(dtype, es, sizes, equal):
+    """Equal blocks of columns do not depend on how many columns and rows there are, but for long wide rows on vector boundaries."""
+    p = _plan("sum" if dtype == "cfloat" else "max", dtype, es, sizes, 1)
+    lanes = -(-sizes[2] * es // 16)
+    assert p["kernel"] == "red_cols" and p["vec"] == 16 // es
+    assert (p["split"] == 1 and all(p["grid"] != -(-lanes // c) * sizes[0] for c in (1, 2, 4, 8, 16, 32, 64))) == equal, p
