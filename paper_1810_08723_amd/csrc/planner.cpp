@@ -1124,10 +1124,15 @@ constexpr int64_t kTargetWaves = OCN_RED_TARGET_WAVES;  // enough wavefronts to 
 constexpr int64_t kLeanSplitWaves = 256 * 8;
 // Outputs of at most this many bytes of input that would be split (a chip hardly filled) are taken whole
 // by sixteen wavefronts each: one reads 256 KiB in about 2 us, and the second launch of a split
-// reduction costs 2 to 5 (float sums of 128 to 250 KiB 5.5 -> 4.1 .. 4.8 us; maxima of bytes, the slowest,
-// 6.3 and 6.4 at 224 KiB).  Not where vectors may start inside four bytes, which one CU reads at a third of
-// that rate (128 KiB 6.4 us both ways, 250 KiB 6.9 and 9.7).
-constexpr int64_t kOneWorkgroupBytes = 256 * 1024, kOneWorkgroupOfBytes = 224 * 1024;
+// reduction costs 2 to 5 (float sums of 128 to 250 KiB 5.5 -> 4.1 .. 4.8 us; int8 of 254 KiB 6.4 -> 5.3).  Fewer
+// where a CU is slower than that: vectors that start inside four bytes, which it reads at a third of the
+// rate (halves of 150 KiB 7.2 us both ways, of 250 KiB 7.5 split and 9.8 whole), and products of signed
+// bytes (160 KiB 11.1 and 11.7, 250 KiB 11.4 and 16.4).  But such outputs too where there are half as many as
+// CUs, which a split does not make faster by much (128 of 200 KiB 10.1 and 9.3, 200 of them 12.0 and 9.8).
+constexpr int64_t kOneWorkgroupBytes = 256 * 1024, kOneWorkgroupSlowBytes = 160 * 1024;
+bool one_workgroup_each(int64_t bytes, int64_t nout, bool slow) {
+  return bytes <= (slow && nout < kNumCUs / 2 ? kOneWorkgroupSlowBytes : kOneWorkgroupBytes);
+}
 constexpr int kLeanMaxLanes = 1024;
 
 // Launch shape of the column kernels (plain and fused): lanes per row of columns, wavefronts per
@@ -1292,7 +1297,8 @@ void choose_reduce_launch(RedPlan &p) {
       const int64_t per_lane = p.vec > 1 && p.nred > 1 && nvec >= (int64_t)p.group * 16 ? 4 : 16;
       const int64_t most = std::max<int64_t>(1, nvec / ((int64_t)p.group * per_lane));
       p.split = std::max<int64_t>(1, std::min(want, most));
-      if (p.split > 1 && lean_shape && nvec * 16 <= (es == 1 ? kOneWorkgroupOfBytes : kOneWorkgroupBytes) && all_aligned(4, -1, p.nred - 1)) {
+      const bool slow = (p.op == R_PROD && p.a_dtype == OCN_INT8) || !all_aligned(4, -1, p.nred - 1);
+      if (p.split > 1 && lean_shape && one_workgroup_each(nvec * 16, p.nout, slow)) {
         p.split = 1;
         p.group = p.block = kLeanMaxLanes;
       }
@@ -1549,7 +1555,7 @@ void choose_fused_launch(RedPlan &p) {
       }
       const bool dwords = (intptr_t)p.a_ptr % 4 == 0 && (intptr_t)p.b_ptr % 4 == 0 &&
                           (p.nkept == 0 || (p.kstride_a[0] % 4 == 0 && p.kstride_b[0] % 4 == 0));
-      if (split > 1 && nv * 32 <= kOneWorkgroupBytes && dwords) {
+      if (split > 1 && one_workgroup_each(nv * 32, p.nout, !dwords)) {
         split = 1;
         group = kLeanMaxLanes;
       }

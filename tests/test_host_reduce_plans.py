@@ -22,13 +22,17 @@ def _plan(op, dtype, es, sizes, axis, strides=None, offset=0):
                            ocn.Tensor(BASE_OUT, dtype, tuple(kept), tuple(out), 0, 0))
 
 
-@pytest.mark.parametrize("dtype,es,offset,whole", [("half", 2, 0, 256), ("half", 2, 4, 256), ("half", 2, 2, 0), ("uint8", 1, 0, 224),
-                                                   ("uint8", 1, 1, 0), ("int8", 1, 2, 0), ("float", 4, 4, 256), ("double", 8, 8, 256)])
-def test_one_workgroup_reads_whole_words(dtype, es, offset, whole):
-    """Vectors that start inside four bytes are left to several workgroups."""
-    for kib in (160, 220, 250, 300):
-        p = _plan("max", dtype, es, (kib * 1024 // es,), 0, offset=offset)
+@pytest.mark.parametrize("op,dtype,es,offset,whole", [("max", "half", 2, 0, 256), ("max", "half", 2, 4, 256), ("max", "half", 2, 2, 160), ("sum", "uint8", 1, 0, 256),
+                                                      ("max", "uint8", 1, 1, 160), ("max", "int8", 1, 2, 160), ("max", "float", 4, 4, 256),
+                                                      ("max", "double", 8, 8, 256), ("prod", "int8", 1, 0, 160), ("prod", "uint8", 1, 0, 256)])
+def test_one_workgroup_reads_whole_words(op, dtype, es, offset, whole):
+    """Vectors that start inside four bytes, and products of signed bytes, are left to several workgroups beyond
+    160 KiB; not where the outputs are half as many as CUs."""
+    for kib in (160, 180, 220, 250, 300):
+        p = _plan(op, dtype, es, (kib * 1024 // es,), 0, offset=offset)
         assert (p["passes"], p["block"]) == ((1, 1024) if kib <= whole else (2, 256)), (kib, p)
+        many = _plan(op, dtype, es, (128, kib * 1024 // es), 1, offset=offset)
+        assert (many["passes"], many["block"]) == ((1, 1024) if kib <= 256 else (2, 256)), (kib, many)
 
 
 def test_one_workgroup_reads_whole_words_of_every_row():
@@ -43,6 +47,9 @@ def test_one_workgroup_of_a_fused_product(offset, passes):
     a, b = (ocn.Tensor(base, "half", (n,), (2,), offset, 0) for base in (BASE_A, BASE_B))
     p = ocn.plan_binary_reduce("mul", "sum", a, b, [0], ocn.Tensor(BASE_OUT, "half", (), (), 0, 0), "half")
     assert p["passes"] == passes and p["fused"]
+    a, b = (ocn.Tensor(base, "half", (128, n), (2 * n, 2), offset, 0) for base in (BASE_A, BASE_B))
+    p = ocn.plan_binary_reduce("mul", "sum", a, b, [1], ocn.Tensor(BASE_OUT, "half", (128,), (2,), 0, 0), "half")
+    assert p["passes"] == 1 and p["fused"]
 
 
 @pytest.mark.parametrize("dtype,es,rows,cols,lane", [("int16", 2, 2, 335298, False), ("half", 2, 7, 600800, False), ("half", 2, 7, 900000, True),
