@@ -1220,8 +1220,9 @@ int choose_flat_columns(int64_t col_lanes, int64_t others, int64_t rows, int cpw
 // a wavefront's lanes would cover several rows of columns (complex sums of [244044, 5, 15] 471 -> 38 us,
 // int32 [60000, 32, 20] 152 -> 42), at most eight where columns are wide ([8, 1000, 5000] halves 32 -> 25; with
 // 16 rows of 4096 floats 21.5 and 25.6, wavefronts that stream whole lines are faster); and enough lanes:
-// three times as many for wide columns of 16 bits, whose vectors of eight are few (int16 [2, 335298] 5.4 us
-// in blocks, 5.9 so; half [7, 600800] 6.3 and 7.3).
+// twice as many for wide columns of 16 bits, whose vectors of eight are few (int16 [2, 335298] 5.4 us
+// in blocks, 5.9 so; over 2 to 8 rows of 33000 vectors blocks take 0.9 of the time, of 60000 the same, of
+// 90000 1.05 to 1.4).
 // Bytes in vectors of sixteen keep the forms above: sixteen wide sums are too many registers (bool
 // any of [5000, 20, 64] 43 us, where 27 columns, one to a lane, gain eight times).
 constexpr int64_t kLaneRows = 32, kLaneWide = 48, kLaneColumns = 32768;
@@ -1334,7 +1335,7 @@ void choose_reduce_launch(RedPlan &p) {
     p.split = (p.nredtot + p.chunk - 1) / p.chunk;
     p.grid = blocks0 * p.split;
     const int64_t lane_vec = nc < p.vec ? 1 : p.vec, lanes = (nc + lane_vec - 1) / lane_vec * others;
-    const int64_t enough = lane_vec == 8 && col_lanes >= kLaneWide ? 3 * kLaneColumns : kLaneColumns;
+    const int64_t enough = lane_vec == 8 && col_lanes >= kLaneWide ? 2 * kLaneColumns : kLaneColumns;
     if (p.nred == 1 && p.vec <= 8 && (p.nredtot <= 8 || (p.nredtot <= kLaneRows && col_lanes < kLaneWide)) && lanes >= enough &&
         lanes < ((int64_t)1 << 31) - kBlock) {
       p.flat_cols = false;

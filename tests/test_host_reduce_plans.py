@@ -52,7 +52,7 @@ def test_one_workgroup_of_a_fused_product(offset, passes):
     assert p["passes"] == 1 and p["fused"]
 
 
-@pytest.mark.parametrize("dtype,es,rows,cols,lane", [("int16", 2, 2, 335298, False), ("half", 2, 7, 600800, False), ("half", 2, 7, 900000, True),
+@pytest.mark.parametrize("dtype,es,rows,cols,lane", [("int16", 2, 2, 335298, False), ("half", 2, 7, 480000, False), ("half", 2, 7, 600800, True), ("half", 2, 4, 724206, True),
                                                      ("float", 4, 2, 335298, True), ("int32", 4, 8, 131072, True), ("int32", 4, 9, 131072, False),
                                                      ("double", 8, 8, 65536, True), ("double", 8, 8, 65534, False)])
 def test_few_rows_of_wide_columns(dtype, es, rows, cols, lane):
