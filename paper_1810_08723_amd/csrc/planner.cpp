@@ -1124,12 +1124,13 @@ constexpr int64_t kTargetWaves = OCN_RED_TARGET_WAVES;  // enough wavefronts to 
 constexpr int64_t kLeanSplitWaves = 256 * 8;
 // Outputs of at most this many bytes of input that would be split (a chip hardly filled) are taken whole
 // by sixteen wavefronts each: one reads 256 KiB in about 2 us, and the second launch of a split
-// reduction costs 2 to 5 (float sums of 128 to 250 KiB 5.5 -> 4.1 .. 4.8 us; int8 of 254 KiB 6.4 -> 5.3).  Fewer
-// where a CU is slower than that: vectors that start inside four bytes, which it reads at a third of the
-// rate (halves of 150 KiB 7.2 us both ways, of 250 KiB 7.5 split and 9.8 whole), and products of signed
-// bytes (160 KiB 11.1 and 11.7, 250 KiB 11.4 and 16.4).  But such outputs too where there are half as many as
-// CUs, which a split does not make faster by much (128 of 200 KiB 10.1 and 9.3, 200 of them 12.0 and 9.8).
-constexpr int64_t kOneWorkgroupBytes = 256 * 1024, kOneWorkgroupSlowBytes = 160 * 1024;
+// reduction costs 2 to 5 (float sums of 128 to 250 KiB 5.5 -> 4.1 .. 4.8 us; int8 of 254 KiB 6.4 -> 5.3).  Where a
+// CU is slower than that, below the size that is split in three: vectors that start inside four bytes, which
+// it reads at a third of the rate (maxima of 130 KiB of halves 7.1 us in two parts and 6.6, of 180 KiB 7.7 and
+// 7.9; int16 sums of 175 KiB 8.6 and 7.9; of 200 KiB in three 7.1 and 8.5, of 250 KiB 7.4 and 9.8), and products
+// of signed bytes (160 KiB 11.1 and 11.7, 250 KiB 11.4 and 16.4).  But such outputs too where there are half as
+// many as CUs, which a split does not make faster by much (128 of 200 KiB 10.1 and 9.3, 200 of them 12.0 and 9.8).
+constexpr int64_t kOneWorkgroupBytes = 256 * 1024, kOneWorkgroupSlowBytes = 192 * 1024 - 1;
 bool one_workgroup_each(int64_t bytes, int64_t nout, bool slow) {
   return bytes <= (slow && nout < kNumCUs / 2 ? kOneWorkgroupSlowBytes : kOneWorkgroupBytes);
 }

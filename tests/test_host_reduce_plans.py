@@ -22,13 +22,13 @@ def _plan(op, dtype, es, sizes, axis, strides=None, offset=0):
                            ocn.Tensor(BASE_OUT, dtype, tuple(kept), tuple(out), 0, 0))
 
 
-@pytest.mark.parametrize("op,dtype,es,offset,whole", [("max", "half", 2, 0, 256), ("max", "half", 2, 4, 256), ("max", "half", 2, 2, 160), ("sum", "uint8", 1, 0, 256),
-                                                      ("max", "uint8", 1, 1, 160), ("max", "int8", 1, 2, 160), ("max", "float", 4, 4, 256),
-                                                      ("max", "double", 8, 8, 256), ("prod", "int8", 1, 0, 160), ("prod", "uint8", 1, 0, 256)])
+@pytest.mark.parametrize("op,dtype,es,offset,whole", [("max", "half", 2, 0, 256), ("max", "half", 2, 4, 256), ("max", "half", 2, 2, 191), ("sum", "uint8", 1, 0, 256),
+                                                      ("max", "uint8", 1, 1, 191), ("max", "int8", 1, 2, 191), ("max", "float", 4, 4, 256),
+                                                      ("max", "double", 8, 8, 256), ("prod", "int8", 1, 0, 191), ("prod", "uint8", 1, 0, 256)])
 def test_one_workgroup_reads_whole_words(op, dtype, es, offset, whole):
     """Vectors that start inside four bytes, and products of signed bytes, are left to several workgroups beyond
-    160 KiB; not where the outputs are half as many as CUs."""
-    for kib in (160, 180, 220, 250, 300):
+    192 KiB; not where the outputs are half as many as CUs."""
+    for kib in (160, 190, 192, 220, 250, 300):
         p = _plan(op, dtype, es, (kib * 1024 // es,), 0, offset=offset)
         assert (p["passes"], p["block"]) == ((1, 1024) if kib <= whole else (2, 256)), (kib, p)
         many = _plan(op, dtype, es, (128, kib * 1024 // es), 1, offset=offset)
