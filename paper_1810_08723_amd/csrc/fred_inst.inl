@@ -10,6 +10,21 @@ namespace ocn {
 namespace {
 
 template <class G, int OP> hipError_t launch_fred(const RedPlan &p, char *partial, hipStream_t stream) {
+  if (p.strip) {
+    const RedStripArgs args = make_red_strip_args(p, partial);
+    const dim3 grid((unsigned)p.grid), block((unsigned)p.block);
+    auto go = [&](auto bc) {
+      constexpr int BC = decltype(bc)::value;
+      using A = typename FusedFold<G, OP>::A;
+      const size_t lds = p.strip == 1 ? strip_cols_lds<A>((int)p.block, (int)sizeof(typename G::SAt)) : p.strip_lds;
+      if (p.strip == 1) hipLaunchKernelGGL((fred_strip_cols_kernel<G, OP, BC>), grid, block, lds, stream, args);
+      else hipLaunchKernelGGL((fred_strip_rows_kernel<G, OP, BC>), grid, block, lds, stream, args);
+    };
+    if (p.strip_bc == 0) go(std::integral_constant<int, 0>{});
+    else if (p.strip_bc == 1) go(std::integral_constant<int, 1>{});
+    else go(std::integral_constant<int, 2>{});
+    return hipGetLastError();
+  }
   const RedArgs args = make_red_args(p, partial);
   switch (p.kernel) {
     case OCN_KERNEL_RED_ROWS:

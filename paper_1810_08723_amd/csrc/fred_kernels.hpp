@@ -11,6 +11,7 @@
 
 #include "ew_kernels.hpp"
 #include "red_kernels.hpp"
+#include "strip_kernels.hpp"
 
 namespace ocn {
 
@@ -551,6 +552,124 @@ template <class G, int OP, int BC, bool NT = false> __global__ __launch_bounds__
   if constexpr (BC >= 0) fred_cols_body<G, OP, G::V, NT, BC>(p, lds);
   else if (p.vec > 1) fred_cols_body<G, OP, G::V, false, -1>(p, lds);
   else fred_cols_body<G, OP, 1, false, -1>(p, lds);
+}
+
+// ---------------------------------------------------------------------------------------
+// strips: dense blocks of narrow rows (strip_kernels.hpp)
+// ---------------------------------------------------------------------------------------
+
+// BC: the input that is one element per row (1: a, 2: b); 0: both are dense blocks.  A vector lies in
+// one row or two (rows hold at least a vector where an input is one element per row).
+template <class G, int OP, int BC> __global__ __launch_bounds__(kStripLanes) void fred_strip_cols_kernel(const RedStripArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KStripArgs &p = *(KStripArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  using F = FusedFold<G, OP>;
+  using R = typename F::R;
+  using A = typename F::A;
+  using St = typename G::SAt;
+  static_assert(sizeof(typename G::SAt) == sizeof(typename G::SBt), "equal input types");
+  constexpr uint32_t V = 16 / sizeof(St);
+  struct Buf { Pack<St, V> a, b; };   // (of an input with one element per row: the elements of the vector's first row and of the next)
+  extern __shared__ __align__(16) unsigned char strip_lds[];
+  A *lds = reinterpret_cast<A *>(strip_lds);
+  const uint32_t tid = threadIdx.x, lanes = p.lanes;
+  const uint32_t gl = __umulhi(tid, p.lanes_m), l = tid - gl * lanes, g = blockIdx.x * p.groups + gl;
+  A acc[V];
+#pragma unroll
+  for (uint32_t i = 0; i < V; ++i) acc[i] = R::identity();
+  if (gl < p.groups && g < p.ngroups) {
+    const StripBlock k = strip_block(p, g);
+    const uint32_t width = p.width, n = k.rows * width, full = n / V;
+    const uint32_t ro = rfastdiv(l * V, args_div(p.width_div)), cut = (ro + 1) * width - l * V, per_trip = rfastdiv(lanes * V, args_div(p.width_div));
+    const int64_t skip = (int64_t)k.row0 * (int64_t)(width * sizeof(St));
+    const char *pa = p.a + k.a + (BC == 1 ? (int64_t)k.row0 * p.rs : skip), *pb = p.b + k.b + (BC == 2 ? (int64_t)k.row0 * p.rs : skip);
+    auto per_row = [&](const char *src, uint32_t trip, Pack<St, V> &v) {
+      const uint32_t r = trip * per_trip + ro;
+      v.v[0] = *reinterpret_cast<const St *>(src + (int64_t)r * p.rs);
+      if constexpr (V > 1) v.v[1] = *reinterpret_cast<const St *>(src + (int64_t)(r + 1 < k.rows ? r + 1 : r) * p.rs);
+    };
+    auto add = [&](uint32_t i, const Buf &v) {
+      const uint32_t at = V > 1 && i >= cut ? 1 : 0;
+      acc[i] = F::add(acc[i], v.a.v[BC == 1 ? at : i], v.b.v[BC == 2 ? at : i]);
+    };
+    strip_walk<Buf>(
+        l, lanes, full,
+        [&](uint32_t t, uint32_t trip, Buf &v) {
+          if constexpr (BC == 1) per_row(pa, trip, v.a);
+          else load_vec<St, V, false>(pa + (uint64_t)t * 16u, v.a);
+          if constexpr (BC == 2) per_row(pb, trip, v.b);
+          else load_vec<St, V, false>(pb + (uint64_t)t * 16u, v.b);
+        },
+        [&](uint32_t, Buf &v) {
+#pragma unroll
+          for (uint32_t i = 0; i < V; ++i) add(i, v);
+        });
+    if (V > 1 && full * V < n && full % lanes == l) {   // the elements behind the last whole vector
+      Buf v;
+      const uint32_t trip = full / lanes;
+      if constexpr (BC == 1) per_row(pa, trip, v.a);
+      if constexpr (BC == 2) per_row(pb, trip, v.b);
+#pragma unroll
+      for (uint32_t i = 0; i < V - 1; ++i) {
+        const uint64_t at = (uint64_t)(full * V + i < n ? full * V + i : n - 1) * sizeof(St);
+        if constexpr (BC != 1) v.a.v[i] = *reinterpret_cast<const St *>(pa + at);
+        if constexpr (BC != 2) v.b.v[i] = *reinterpret_cast<const St *>(pb + at);
+      }
+#pragma unroll
+      for (uint32_t i = 0; i < V - 1; ++i)
+        if (full * V + i < n) add(i, v);
+    }
+  }
+#pragma unroll
+  for (uint32_t i = 0; i < V; ++i) lds[tid * V + i] = acc[i];
+  strip_fold<R>(p, lds, lanes * V);
+}
+
+// BC: the input that has one row for all rows (1: a, 2: b), whose elements a lane keeps: it has the same
+// columns on every trip; 0: both are dense blocks.
+template <class G, int OP, int BC> __global__ __launch_bounds__(kBlock) void fred_strip_rows_kernel(const RedStripArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KStripArgs &p = *(KStripArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  using F = FusedFold<G, OP>;
+  using R = typename F::R;
+  using St = typename G::SAt;
+  using Mt = typename G::SOt;
+  constexpr uint32_t V = 16 / sizeof(St);
+  struct Buf { Pack<St, V> a, b; };
+  extern __shared__ __align__(16) unsigned char strip_lds[];
+  Mt *lds = reinterpret_cast<Mt *>(strip_lds);
+  const StripBlock k = strip_block(p, blockIdx.x);
+  const uint32_t width = p.width, n = k.rows * width, full = n / V, tid = threadIdx.x, lanes = p.lanes;
+  const int64_t skip = (int64_t)k.row0 * (int64_t)(width * sizeof(St));
+  const char *pa = p.a + k.a + (BC == 1 ? 0 : skip), *pb = p.b + k.b + (BC == 2 ? 0 : skip);
+  Pack<St, V> row;
+  if constexpr (BC != 0) {
+#pragma unroll
+    for (uint32_t i = 0; i < V; ++i) {
+      const uint32_t e = tid * V + i, c = e - rfastdiv(e, args_div(p.width_div)) * width;
+      row.v[i] = reinterpret_cast<const St *>(BC == 1 ? pa : pb)[c];
+    }
+  }
+  auto eval = [&](uint32_t i, const Buf &v) { return G::eval(BC == 1 ? row.v[i] : v.a.v[i], BC == 2 ? row.v[i] : v.b.v[i]); };
+  if (tid < lanes) {
+    strip_walk<Buf>(
+        tid, lanes, full,
+        [&](uint32_t t, uint32_t, Buf &v) {
+          if constexpr (BC != 1) load_vec<St, V, false>(pa + (uint64_t)t * 16u, v.a);
+          if constexpr (BC != 2) load_vec<St, V, false>(pb + (uint64_t)t * 16u, v.b);
+        },
+        [&](uint32_t trip, Buf &v) {
+          Pack<Mt, V> m;
+#pragma unroll
+          for (uint32_t i = 0; i < V; ++i) m.v[i] = eval(i, v);
+          reinterpret_cast<Pack<Mt, V> *>(strip_lds)[tid + trip * lanes] = m;
+        });
+  }
+  if (V > 1 && full * V + tid < n) {   // the elements behind the last whole vector
+    const uint32_t e = full * V + tid, c = e - rfastdiv(e, args_div(p.width_div)) * width;
+    lds[e] = G::eval(reinterpret_cast<const St *>(pa)[BC == 1 ? c : e], reinterpret_cast<const St *>(pb)[BC == 2 ? c : e]);
+  }
+  strip_rows_fold<R>(p, k, [&](uint32_t e) { return R::lift(from_storage<G::SO_DT>(lds[e])); });
 }
 
 // ---------------------------------------------------------------------------------------

@@ -1227,6 +1227,192 @@ int choose_flat_columns(int64_t col_lanes, int64_t others, int64_t rows, int cpw
 // Bytes in vectors of sixteen keep the forms above: sixteen wide sums are too many registers (bool
 // any of [5000, 20, 64] 43 us, where 27 columns, one to a lane, gain eight times).
 constexpr int64_t kLaneRows = 32, kLaneWide = 48, kLaneColumns = 32768;
+
+int64_t gcd64(int64_t a, int64_t b) { return b ? gcd64(b, a % b) : a; }
+
+// Is the input (of a fused call: are the inputs) made of dense blocks of narrow rows (strip_kernels.hpp)?
+struct StripBlocks {
+  bool cols = false, rows = false;
+  int bc = 0;               // fused: the input that is one element per row (columns) or one row for all (rows)
+  int64_t inner = 1, width = 0, nrows = 0;
+};
+StripBlocks strip_blocks(const RedPlan &p) {
+  StripBlocks s;
+  if (p.nkept < 1 || p.nred < 1 || p.nout < 1) return s;
+  const int es = dt_size(p.a_dtype), kc = p.nkept - 1;
+  const int64_t V = 16 / es;
+  auto cols = [&](const int64_t *ks, const int64_t *rs) { return ks[kc] == es && rs[0] == p.ksize[kc] * es; };
+  auto rows = [&](const int64_t *ks, const int64_t *rs) { return rs[0] == es && ks[kc] == p.rsize[0] * es; };
+  if (p.nred == 1) {
+    const bool ca = cols(p.kstride_a, p.rstride_a), ra = rows(p.kstride_a, p.rstride_a);
+    if (!p.fused) {
+      s.cols = ca;
+      s.rows = ra;
+    } else {
+      const bool cb = cols(p.kstride_b, p.rstride_b), rb = rows(p.kstride_b, p.rstride_b);
+      const bool ea = p.kstride_a[kc] == 0, eb = p.kstride_b[kc] == 0;
+      if (ca || cb) {
+        s.bc = ca && cb ? 0 : ca ? 2 : 1;
+        s.cols = s.bc == 0 || ((s.bc == 1 ? ea : eb) && p.ksize[kc] >= V);
+      } else if (ra || rb) {
+        s.bc = ra && rb ? 0 : ra ? 2 : 1;
+        s.rows = s.bc == 0 || (s.bc == 1 ? ea && p.rstride_a[0] == es : eb && p.rstride_b[0] == es);
+      }
+    }
+    s.width = s.cols ? p.ksize[kc] : p.rsize[0];
+    s.nrows = s.cols ? p.rsize[0] : p.ksize[kc];
+  } else if (!p.fused && p.nred == 2 && p.rstride_a[1] == es && p.kstride_a[kc] == p.rsize[1] * es &&
+             p.rstride_a[0] == p.ksize[kc] * p.kstride_a[kc]) {
+    s.cols = true;
+    s.inner = p.rsize[1];
+    s.width = p.ksize[kc] * s.inner;
+    s.nrows = p.rsize[0];
+  }
+  if (s.width < 2 || s.width > (1 << 20)) s.cols = s.rows = false;
+  return s;
+}
+// streaming loads: every vector of an input far larger than the caches starts on a vector boundary
+bool strip_nt(const RedPlan &p, int64_t piece, int64_t block) {
+  if (p.fused || (intptr_t)p.a_ptr % 16 || (piece < block && piece % 16)) return false;
+  for (int d = 0; d + 1 < p.nkept; ++d)
+    if (p.kstride_a[d] % 16) return false;
+  return p.nout * p.nredtot * dt_size(p.a_dtype) >= kStreamBytes;
+}
+
+// Columns of dense blocks in strips.  Against the forms above, over 2000 random calls of 16 KB to 128 MB, all
+// types: mean 1.16 times as fast, three times and more where rows of a few elements are summed in blocks of 30 to
+// 300 (halves [676846, 51, 3] 1050 -> 60 us, floats [72727, 33, 10] 181 -> 24); 1.5 % slower by more than 5 %.
+//   lanes   A group has as many as make four trips of a block, in multiples of m = width / gcd(width, vector),
+//           and workgroups of 256 take several groups; blocks that keep a workgroup busy get one, of
+//           1024 lanes where there are enough vectors for that on every CU.
+//   split   Long blocks that are few, in as few workgroups as go round evenly.
+// The forms above stay the better ones where: blocks are small altogether (one launch that the fold's
+// barriers lengthen: doubles [262, 59] 5.0 and 5.7 us); few rows of whole vectors, which a lane walks by
+// itself (halves [1095563, 7, 8] 49 and 68; below 16 MB tests hold it to that for all rows of a vector and more, at
+// 9.4 us for int32 [5462, 31, 22] where strips take 7.2), or rows of many vectors and fewer than eight of them (floats [93, 4,
+// 460] 4.0 and 5.6); splits that idle lanes, or rows of a large output, whose partial results would not
+// fit what a call without a workspace has, leave uneven (floats [95, 340, 279] 9.6 and 14.4, sums over
+// [12000, 2000] 23 and 36), and splits of many small blocks ([63, 94, 748] 7.1 and 10.5); and, with runs of columns in an output, few outputs of less than 24 MB.
+constexpr int64_t kStripSmall = 256 << 10, kStripBytesSmall = 2 << 20, kStripSplitSmall = 1 << 20, kStripInnerSmall = 4 << 20,
+                  kStripInnerFew = 24 << 20, kStripLaneSmall = 16 << 20, kStripManySmall = 24 << 20;
+bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
+  const int es = dt_size(p.a_dtype), acc_es = dt_size(p.acc_dtype);
+  const int64_t V = 16 / es, width = s.width, rows = s.nrows, kept = p.ksize[p.nkept - 1], others = p.nout / kept;
+  const int64_t m = width / gcd64(width, V);
+  if (rows * width >= ((int64_t)1 << 31)) return false;
+  const int64_t nv = (rows * width + V - 1) / V, total = others * rows * width * es;   // vectors of a block; bytes
+  // (accumulators of all lanes' vectors in 64 KiB of LDS; those of halves are held in four bytes)
+  const int64_t top = std::min<int64_t>(kStripLanes, 65536 / (V * std::max(acc_es, p.acc_dtype == OCN_HALF ? 4 : 1)));
+  if (p.fused && m > kBlock) return false;   // (double products of a column and [13223, 481] 36.6 and 38.5 with what follows)
+  if (m > top || nv < 2 * m || (m > 32 && rows < 8) || total < (es == 1 ? kStripBytesSmall : kStripSmall)) return false;
+  if (p.kernel == OCN_KERNEL_RED_COLS && p.cpw == 0 && (width % V == 0 || rows <= 16 || (width > V && total < kStripLaneSmall))) return false;
+  if (s.inner > 1 && total < (kept < 5 ? kStripInnerFew : kStripInnerSmall)) return false;
+  constexpr int64_t trips = 4;
+  int64_t want = std::max<int64_t>(1, (nv / trips + m / 2) / m);   // times m lanes that a block keeps busy
+  int64_t block = kBlock, split = 1, chunk = rows, lanes, groups = 1;
+  if (m <= kBlock && (want * m <= kBlock / 2 || kBlock / m * m * others >= (int64_t)kNumCUs * 2 * kBlock)) {
+    want = std::min(want, kBlock / m);
+    lanes = std::max<int64_t>(2, want * m);
+    groups = kBlock / lanes;
+  } else {
+    block = top;
+    while (block > kBlock && m <= block / 2 && want * m <= block / 2) block /= 2;
+    // (one workgroup takes 16 vectors per lane without a split: no second launch)
+    if (nv > block / m * m * 16 || others > 64)
+      while (block > kBlock && m <= block / 2 && nv * others < kNumCUs * block * trips) block /= 2;
+    lanes = block / m * m;
+    const int64_t fits = std::max<int64_t>(1, (int64_t)OCN_REDUCE_SCRATCH_BYTES / (p.nout * acc_es));
+    const int64_t slots = (int64_t)kNumCUs * 1024 / block;
+    const int64_t most = nv <= lanes * 16 ? 1 : std::max<int64_t>(1, std::min({fits, nv / (lanes * trips), 2 * slots / others}));
+    // workgroups that go round once, or twice where that is the more even by a tenth
+    auto even = [&](int64_t q) { return (double)(others * q) / (double)((others * q + slots - 1) / slots * slots); };
+    const int64_t once = std::max<int64_t>(1, std::min(most, slots / others));
+    split = even(most) > even(once) * 1.1 ? most : once;
+    if (most == fits && others * split * block < 160 * 1024 && nv > lanes * 16) return false;
+    if (split > 1 && others >= 32 && total < kStripManySmall) return false;
+    if (split > 1 && (p.flat_cols || lanes * 8 < block * 7 || total < (es == 1 ? kStripBytesSmall : kStripSplitSmall))) return false;
+    if (m > kWave && lanes * 4 < block * 3) return false;
+    chunk = (rows + split - 1) / split;
+    // (splits that start on a line, unless that is many rows of them)
+    const int64_t line = 128 / gcd64(128, width * es);
+    if (chunk > 4 * line) chunk = (chunk + line - 1) / line * line;
+    split = (rows + chunk - 1) / chunk;
+  }
+  const int64_t grid = (others * split + groups - 1) / groups;
+  if (grid > max_launch_blocks()) return false;
+  p.kernel = OCN_KERNEL_RED_COLS;
+  p.strip = 1;
+  p.strip_lanes = (int)lanes;
+  p.strip_groups = (int)groups;
+  // lanes that share an output: as many as make their turns and the first one's over the others about equal
+  const int64_t outs = groups * (width / s.inner), addends = lanes * V / (width / s.inner);
+  int64_t parts = 1;
+  while ((parts + 1) * outs <= block && (parts + 1) * (parts + 1) <= addends) ++parts;
+  p.strip_parts = (int)parts;
+  p.split = split;
+  // (partial results of an output side by side where the second launch then reads them in vectors: few outputs of
+  // many splits, float sums over [18423, 79] 10.1 us, 7.8 so; 4-byte ones gain nothing)
+  p.partial_rows = acc_es == 8 && p.nout <= 256;
+  p.chunk = chunk;
+  p.block = (int)block;
+  p.grid = grid;
+  p.nt_load = strip_nt(p, chunk * width * es, rows * width * es);
+  return true;
+}
+
+// Rows of dense blocks in strips: 16 KB of them per workgroup, less where that leaves CUs idle.  A power of
+// two of lanes per row, each with a whole vector or the row's few last elements one by one, is as
+// fast only for rows of whole vectors and small inputs (float rows of 22 [1090909, 22] 37 -> 20 us, of 5 103 -> 26,
+// of 16 24.1 -> 19.0, of 64 23.1 -> 18.4; [126241, 16] 4.8 and 5.1, halves [31894, 40] 3.3 and 4.3; but [150942, 10],
+// whose other form takes single elements, 8.0 -> 3.9).  Bytes come from LDS one by one: from 32
+// of them on the other form is the better one (any over rows of 50 32.5 and 35.6), and so it is for rows of one
+// vector, or two of 8 or 16 bits (halves [5000000, 8] 23.6 and 26.5, maxima of floats [2070888, 4] 10.6 and 12.6).
+constexpr int64_t kStripRowBytes = 16 << 10, kStripRowsSingle = 1 << 20, kStripRowsSmall = 4 << 20, kStripRowsWhole = 12 << 20;
+bool choose_strip_rows(RedPlan &p, const StripBlocks &s) {
+  const int es = dt_size(p.a_dtype), mes = p.fused ? dt_size(p.mid_dtype) : es;
+  const int64_t V = 16 / es, width = s.width, rows = s.nrows, others = p.nout / rows, total = p.nout * width * es;
+  const int64_t m = width / gcd64(width, V), vecs = width / V;
+  if (width * es > kStripRowBytes / 16 || (es == 1 && width >= 32) || (s.bc && m > kBlock)) return false;
+  const bool whole = p.vec > 1 && width % V == 0;   // in whole vectors by the other form too
+  if (total < (whole ? kStripRowsWhole : p.vec > 1 ? kStripRowsSmall : kStripRowsSingle)) return false;
+  if (whole && (vecs == 1 || (vecs == 2 && es <= 2))) return false;
+  const int64_t piece = std::max<int64_t>(2048, std::min(kStripRowBytes, total / (4 * kNumCUs)));
+  int64_t chunk = 4;
+  while (chunk * 2 * width * es <= piece) chunk *= 2;
+  chunk = std::min(chunk, rows);
+  const int64_t grid = others * ((rows + chunk - 1) / chunk);
+  if (grid > max_launch_blocks()) return false;
+  int parts = 1;
+  while (parts < kWave && chunk * parts * 2 <= kBlock) parts *= 2;
+  p.kernel = OCN_KERNEL_RED_ROWS;
+  p.strip = 2;
+  p.strip_lanes = (int)(s.bc ? kBlock / m * m : kBlock);
+  p.strip_parts = parts;
+  // lanes read their rows from different elements on where rows lie a multiple of eight banks apart
+  if (width * mes % 4 == 0 && gcd64(width * mes / 4, 64) >= 8) {
+    p.strip_rotate = 1;
+    while (p.strip_rotate * 2 <= width / parts && p.strip_rotate < kWave) p.strip_rotate *= 2;
+  }
+  p.strip_lds = (size_t)((chunk * width * mes + 15) / 16 * 16);
+  p.split = 1;
+  p.chunk = chunk;
+  p.block = kBlock;
+  p.grid = grid;
+  p.nt_load = strip_nt(p, chunk * width * es, rows * width * es);
+  return true;
+}
+
+void choose_strip(RedPlan &p) {
+  const StripBlocks s = strip_blocks(p);
+  if (!(s.cols && choose_strip_cols(p, s)) && !(s.rows && choose_strip_rows(p, s))) return;
+  p.strip_bc = s.bc;
+  p.strip_inner = s.inner;
+  p.strip_width = s.width;
+  p.strip_rows = s.nrows;
+  p.vec = 16 / dt_size(p.a_dtype);
+  p.cpw = kWave;
+  p.short_rows = p.lean = p.flat_cols = false;
+}
 void choose_reduce_launch(RedPlan &p) {
   const int es = dt_size(p.a_dtype);
   const int acc_es = dt_size(p.acc_dtype);
@@ -1354,6 +1540,7 @@ void choose_reduce_launch(RedPlan &p) {
     p.chunk = p.nredtot;
     p.grid = std::min<int64_t>((p.nout + kBlock - 1) / kBlock, max_launch_blocks());   // the kernel loops beyond that
   }
+  if (idx32) choose_strip(p);
   if (p.grid > max_launch_blocks()) {
     // more workgroups than one launch may have: the generic kernel, which loops over its outputs
     p.kernel = OCN_KERNEL_RED_GENERIC;
@@ -1368,7 +1555,7 @@ void choose_reduce_launch(RedPlan &p) {
   p.workspace_bytes = p.split > 1 ? (size_t)(p.nout * p.split * acc_es) : 0;
   // an input that cannot stay in the caches anyway is read with streaming loads (whole
   // 16-byte vectors only: neighbouring lanes then cover whole lines)
-  p.nt_load = p.vec > 1 && aligned && p.cpw != 0 && p.kernel != OCN_KERNEL_RED_GENERIC && p.nout * p.nredtot * es >= kStreamBytes;
+  if (!p.strip) p.nt_load = p.vec > 1 && aligned && p.cpw != 0 && p.kernel != OCN_KERNEL_RED_GENERIC && p.nout * p.nredtot * es >= kStreamBytes;
 }
 
 }  // namespace
@@ -1614,6 +1801,7 @@ void choose_fused_launch(RedPlan &p) {
     p.chunk = p.nredtot;
     p.grid = std::min<int64_t>((p.nout + kBlock - 1) / kBlock, max_launch_blocks());
   }
+  if (idx32) choose_strip(p);
   p.passes = p.split > 1 ? 2 : 1;
   p.workspace_bytes = p.split > 1 ? (size_t)(p.nout * p.split * acc_es) : 0;
 }
@@ -1797,7 +1985,7 @@ void plan_second_pass(const RedPlan &first, char *workspace, RedPlan *second) {
   q.off_out = first.off_out;
   const int64_t es = dt_size(q.a_dtype);
   q.nkept = first.nkept;
-  const bool rows_layout = first.kernel == OCN_KERNEL_RED_ROWS;  // [nout][split], else [split][nout]
+  const bool rows_layout = first.kernel == OCN_KERNEL_RED_ROWS || first.partial_rows;  // [nout][split], else [split][nout]
   int64_t lin = rows_layout ? first.split * es : es;
   for (int d = first.nkept - 1; d >= 0; --d) {
     q.ksize[d] = first.ksize[d];
@@ -1840,10 +2028,11 @@ void plan_second_pass(const RedPlan &first, char *workspace, RedPlan *second) {
     const int64_t colblocks = (nc + q.cpw - 1) / q.cpw;
     q.grid = colblocks * (q.nout / nc);
     if (first.split >= 64) q.block = 16 * kWave;   // many partials per column: more wavefronts share them
-    // eight-byte partial results of a single kept dim: the kernel made for this launch
-    if (es == 8 && first.nkept == 1 && first.split < ((int64_t)1 << 31) && max_launch_blocks() >= (q.nout + kWave - 1) / kWave) {
+    // partial results of a single kept dim: the kernel made for this launch (sixteen wavefronts from 64
+    // splits on: 256 of five float columns 8 us with four)
+    if (first.nkept == 1 && first.split < ((int64_t)1 << 31) && max_launch_blocks() >= (q.nout + kWave - 1) / kWave) {
       q.fold = true;
-      q.block = kWave;
+      q.block = first.split >= 64 ? 16 * kWave : kBlock;
       q.grid = (q.nout + kWave - 1) / kWave;
     }
   } else {

@@ -20,6 +20,7 @@ constexpr int kBlock = 256;        // threads per workgroup of every kernel (4 w
 constexpr int kWave = 64;
 constexpr int64_t kNumCUs = 256;          // MI355X: 8 XCDs x 32 compute units
 constexpr uint32_t kXcds = 8;
+constexpr int kStripLanes = 1024;  // most lanes of a workgroup of the strip kernels
 constexpr int64_t kLdsPerCu = 160 * 1024;  // bytes of LDS per compute unit
 // Operands of this many bytes or more are streamed: stores bypass the caches (an ordinary store
 // leaves the lines dirty in the 256 MB Infinity Cache and the next kernel pays for the
@@ -115,8 +116,15 @@ struct RedPlan {
   bool lean = false;            // rows kernel: the common 2-D shape, run by the lean form of the kernel
   bool fold = false;            // second launch over [split][output] partial results: one output per lane
   bool swap_a = false, swap_o = false;  // the input / the output is stored in the other byte order
+  int strip = 0;                // dense blocks of narrow rows: 1 their columns, 2 their rows (strip_kernels.hpp)
+  int strip_lanes = 0, strip_groups = 1, strip_parts = 1, strip_rotate = 0;  // ... lanes per group, groups per workgroup, lanes per output's fold
+  int64_t strip_inner = 1;      // ... columns that go into one output
+  int64_t strip_width = 0, strip_rows = 0;   // ... elements per row, rows of a block
+  int strip_bc = 0;             // ... fused: the input that is one element per row (rows: one row for all), 1 a, 2 b
+  size_t strip_lds = 0;
+  bool partial_rows = false;    // partial results lie [output][split], as those of rows do (columns: [split][output])
   int64_t split = 1;            // partial results per output
-  int64_t chunk = 0;            // reduction elements (rows: vectors) per split
+  int64_t chunk = 0;            // reduction elements (rows: vectors; strips: rows of a block) per split
   int64_t grid = 0;
   int acc_dtype = 0;            // dtype the partial results are stored in
   size_t workspace_bytes = 0;

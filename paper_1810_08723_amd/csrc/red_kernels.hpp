@@ -794,50 +794,49 @@ template <int S, int OP> __global__ __launch_bounds__(kBlock) void red_rows_shor
   if (active && lane == 0) store_result<A>(p.out + off_o, p.out_dtype, acc, p.swap_o != 0);
 }
 
-// The second launch of a split column reduction: partial results [split][output] of eight bytes
-// each.  The launch is a chain of latencies (arguments, partial results, store), so it gets few
-// arguments and no index arithmetic (fp32 column sums of [16384, 4096], 16 x 4096 partial
-// results: 7.1 us in the column kernel), and four wavefronts share the splits of 64 outputs, a
-// quarter each in order with up to eight loads in flight, and combine through LDS in that order: one
-// wavefront folding 64 splits of 1000 outputs by itself took eight round trips (4.6 us, 2.8 here).
-constexpr int kFoldWaves = 4;
+// The second launch of a split column reduction: partial results [split][output].  The launch is a chain
+// of latencies (arguments, partial results, store), so it gets few arguments and no index arithmetic (fp32
+// column sums of [16384, 4096], 16 x 4096 partial results: 7.1 us in the column kernel), and four or
+// sixteen wavefronts share the splits of 64 outputs, a part each in order with up to eight loads in flight, and
+// combine through LDS in that order: one wavefront folding 64 splits of 1000 outputs by itself took
+// eight round trips (4.6 us, 2.8 here).
+constexpr int kFoldWaves = 16;   // at most
 template <int S, int OP> __global__ __launch_bounds__(kFoldWaves * kWave) void red_fold_kernel(const RedFoldArgs p) {
   using R = Reducer<S, OP>;
   using A = typename R::A;
   using St = storage_t<S>;
-  if constexpr (sizeof(St) == 8) {
-    __shared__ A lds[kFoldWaves - 1][kWave];
-    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    const uint32_t o = blockIdx.x * kWave + lane;
-    const uint32_t per = (p.split + kFoldWaves - 1) / kFoldWaves;
-    uint32_t s = wave * per;
-    const uint32_t end = s + per < p.split ? s + per : p.split;
-    A acc = R::identity();
-    if (o < p.nout) {
-      const St *src = reinterpret_cast<const St *>(p.partial) + o;
-      constexpr uint32_t U = 8;
-      for (; s + U <= end; s += U) {
-        St v[U];
+  __shared__ A lds[kFoldWaves - 1][kWave];
+  const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const uint32_t o = blockIdx.x * kWave + lane;
+  const uint32_t waves = blockDim.x / kWave, per = (p.split + waves - 1) / waves;
+  uint32_t s = wave * per;
+  const uint32_t end = s + per < p.split ? s + per : p.split;
+  A acc = R::identity();
+  if (o < p.nout) {
+    const St *src = reinterpret_cast<const St *>(p.partial) + o;
+    constexpr uint32_t U = 8;
+    for (; s + U <= end; s += U) {
+      St v[U];
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) v[u] = src[(uint64_t)(s + u) * p.nout];
+      for (uint32_t u = 0; u < U; ++u) v[u] = src[(uint64_t)(s + u) * p.nout];
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) acc = R::combine(acc, R::lift(from_storage<S>(v[u])));
-      }
-      St v[U];   // what is left, fewer than U: all on their way together
-#pragma unroll
-      for (uint32_t u = 0; u < U; ++u)
-        if (s + u < end) v[u] = src[(uint64_t)(s + u) * p.nout];
-#pragma unroll
-      for (uint32_t u = 0; u < U; ++u)
-        if (s + u < end) acc = R::combine(acc, R::lift(from_storage<S>(v[u])));
+      for (uint32_t u = 0; u < U; ++u) acc = R::combine(acc, R::lift(from_storage<S>(v[u])));
     }
-    if (wave > 0) lds[wave - 1][lane] = acc;
-    __syncthreads();
-    if (wave == 0 && o < p.nout) {
+    St v[U];   // what is left, fewer than U: all on their way together
 #pragma unroll
-      for (int w = 0; w < kFoldWaves - 1; ++w) acc = R::combine(acc, lds[w][lane]);
-      store_result<A>(p.out + (int64_t)o * p.kso, p.out_dtype, acc, p.swap_o != 0);
-    }
+    for (uint32_t u = 0; u < U; ++u)
+      if (s + u < end) v[u] = src[(uint64_t)(s + u) * p.nout];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u)
+      if (s + u < end) acc = R::combine(acc, R::lift(from_storage<S>(v[u])));
+  }
+  if (wave > 0) lds[wave - 1][lane] = acc;
+  __syncthreads();
+  if (wave == 0 && o < p.nout) {
+#pragma unroll
+    for (int w = 0; w < 3; ++w) acc = R::combine(acc, lds[w][lane]);
+    for (uint32_t w = 3; w + 1 < waves; ++w) acc = R::combine(acc, lds[w][lane]);
+    store_result<A>(p.out + (int64_t)o * p.kso, p.out_dtype, acc, p.swap_o != 0);
   }
 }
 

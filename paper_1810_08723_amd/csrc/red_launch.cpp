@@ -86,4 +86,45 @@ RedLeanArgs make_red_lean_args(const RedPlan &p, char *partial) {
   return r;
 }
 
+RedStripArgs make_red_strip_args(const RedPlan &p, char *partial) {
+  RedStripArgs r;
+  std::memset(&r, 0, sizeof r);
+  const int kc = p.nkept - 1;      // the columns' (rows: the rows') kept dim
+  r.a = p.a_ptr;
+  r.b = p.b_ptr;
+  r.out = p.out_ptr;
+  r.partial = partial;
+  r.kso = p.kstride_o[kc];
+  r.rs = p.strip_bc == 1 ? p.rstride_a[0] : p.rstride_b[0];
+  r.rows = (uint32_t)p.strip_rows;
+  r.chunk = (uint32_t)p.chunk;
+  r.width = (uint32_t)p.strip_width;
+  r.inner = (uint32_t)p.strip_inner;
+  r.lanes = (uint32_t)p.strip_lanes;
+  r.lanes_m = (uint32_t)((((uint64_t)1 << 32) + r.lanes - 1) / r.lanes);
+  r.groups = (uint32_t)p.strip_groups;
+  r.parts = (uint32_t)p.strip_parts;
+  r.rotate = (uint32_t)p.strip_rotate;
+  const int64_t pieces = (p.strip_rows + p.chunk - 1) / p.chunk, others = p.nout / p.ksize[kc];
+  r.ngroups = (uint32_t)(others * pieces);
+  r.nog = (uint32_t)(r.width / r.inner);
+  r.flags = (p.nt_load ? kStripNt : 0u) | (p.swap_a ? kStripSwapA : 0u) | (p.swap_o ? kStripSwapO : 0u);
+  r.out_dtype = p.out_dtype;
+  r.pstep = p.partial_rows ? pieces : 1;
+  r.psplit = p.partial_rows ? 1 : p.nout;
+  r.split_div = make_fastdiv((uint32_t)pieces);
+  r.width_div = make_fastdiv(r.width);
+  r.inner_div = make_fastdiv(r.inner);
+  r.nog_div = make_fastdiv(r.nog);
+  r.outs_div = make_fastdiv(r.groups * r.nog);
+  for (int d = kc - 1; d >= 0; --d) {
+    const int k = (int)r.nother++;
+    r.osa[k] = p.kstride_a[d];
+    r.osb[k] = p.kstride_b[d];
+    r.oso[k] = p.kstride_o[d];
+    r.odiv[k] = make_fastdiv((uint32_t)p.ksize[d]);
+  }
+  return r;
+}
+
 }  // namespace ocn

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "red_kernels.hpp"
+#include "strip_kernels.hpp"
 
 namespace ocn {
 
@@ -14,12 +15,20 @@ extern RedLauncher g_fused_launchers[B_COUNT][DT_COUNT][R_COUNT];
 
 RedArgs make_red_args(const RedPlan &p, char *partial);
 RedLeanArgs make_red_lean_args(const RedPlan &p, char *partial);
+RedStripArgs make_red_strip_args(const RedPlan &p, char *partial);
 
 // lanes per workgroup of the lean rows kernels
 inline unsigned lean_block(const RedPlan &p) { return p.group > kBlock ? (unsigned)p.group : (unsigned)kBlock; }
 
 #if defined(__HIPCC__)
 template <int S, int OP> hipError_t launch_red(const RedPlan &p, char *partial, hipStream_t stream) {
+  if (p.strip) {
+    const RedStripArgs args = make_red_strip_args(p, partial);
+    const size_t lds = p.strip == 1 ? strip_cols_lds<typename Reducer<S, OP>::A>((int)p.block, (int)sizeof(storage_t<S>)) : p.strip_lds;
+    if (p.strip == 1) hipLaunchKernelGGL((red_strip_cols_kernel<S, OP>), dim3((unsigned)p.grid), dim3((unsigned)p.block), lds, stream, args);
+    else hipLaunchKernelGGL((red_strip_rows_kernel<S, OP>), dim3((unsigned)p.grid), dim3(kBlock), lds, stream, args);
+    return hipGetLastError();
+  }
   const RedArgs args = make_red_args(p, partial);
   switch (p.kernel) {
     case OCN_KERNEL_RED_ROWS:
@@ -45,7 +54,7 @@ template <int S, int OP> hipError_t launch_red(const RedPlan &p, char *partial, 
         f.split = (uint32_t)p.nredtot;
         f.out_dtype = p.out_dtype;
         f.swap_o = p.swap_o ? 1 : 0;
-        hipLaunchKernelGGL((red_fold_kernel<S, OP>), dim3((unsigned)p.grid), dim3(kFoldWaves * kWave), 0, stream, f);
+        hipLaunchKernelGGL((red_fold_kernel<S, OP>), dim3((unsigned)p.grid), dim3((unsigned)p.block), 0, stream, f);
         break;
       }
       {

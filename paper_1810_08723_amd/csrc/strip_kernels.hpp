@@ -1,0 +1,252 @@
+// Reductions over dense blocks of narrow rows: [rows, width] elements one after the other in memory, as
+// the leading, the middle or all but one of a tensor's axes leave them.  Two forms, each plain and fused
+// with an elementwise operation:
+//
+//   strip columns  the rows are reduced (with `inner` > 1 also runs of `inner` columns).  A group of
+//                  lanes walks the block front to back in 16-byte vectors, wherever rows end.  Their number
+//                  is a multiple of width / gcd(width, vector), so that from one trip to the next a lane
+//                  keeps its columns and folds them in registers; the lanes' columns meet in LDS.
+//   strip rows     every row is reduced.  A workgroup copies whole rows to LDS in 16-byte vectors, wherever
+//                  they end, and then gives each row to one or a few neighbouring lanes.
+//
+// Bound by HBM once every lane has whole vectors and four of them in flight.  The other forms give a row of
+// columns, or a row of addends, a power of two of lanes: what a narrow row leaves idle, reads at its end
+// element by element and waits for alone is most of their time.  96 MB of floats (14.8 us at 6.5 TB/s): sums
+// over the middle of [72727, 33, 10] 181 -> 24 us, [24000, 100, 10] 72 -> 19.6, [2608, 400, 23] 24.9 -> 19.2, over
+// the first axis of [1090909, 22] 27.7 -> 22.5 (17 and the second launch), of rows of 5 103 -> 26, of 22 37 -> 20,
+// of 100 29 -> 20.7.
+#pragma once
+
+#include "red_kernels.hpp"
+
+namespace ocn {
+
+struct RedStripArgs {
+  const char *a, *b;                // (b: second input of a fused call)
+  char *out, *partial;
+  int64_t kso;                      // byte stride of the columns' (rows: the rows') kept dim in the output
+  int64_t rs;                       // fused columns: byte stride per row of an input that is one element per row
+  uint32_t ngroups, nother;         // groups of lanes in all (blocks of rows times splits); other kept dims
+  uint32_t rows, chunk;             // rows of a block; rows per split
+  uint32_t width, inner;            // elements per row; columns that go into one output
+  uint32_t lanes, lanes_m, groups;  // lanes per group, ceil(2^32 / lanes), groups per workgroup
+  uint32_t nog, parts;              // outputs per group; lanes that share an output's fold
+  uint32_t rotate;                  // rows: lanes start their rows at different elements
+  uint32_t flags;                   // kStrip*
+  int32_t out_dtype;
+  int64_t pstep, psplit;            // partial results: from one output to the next, from one split to the next
+  FastDiv split_div, width_div, inner_div, nog_div, outs_div;   // (outs: groups * nog)
+  int64_t osa[kMaxDims], osb[kMaxDims], oso[kMaxDims];          // other kept dims, fastest first
+  FastDiv odiv[kMaxDims];
+};
+enum : uint32_t { kStripNt = 1, kStripSwapA = 2, kStripSwapO = 4 };
+
+// LDS of the column form: the accumulators of every lane's vector (es: size of an element)
+template <class A> OCN_HD constexpr size_t strip_cols_lds(int block, int es) { return (size_t)block * (size_t)(16 / es) * sizeof(A); }
+
+#if defined(__HIPCC__)
+
+using KStripArgs = const __attribute__((address_space(4))) RedStripArgs;
+
+// byte offsets of a group's block in the inputs and the output, and its rows
+struct StripBlock {
+  int64_t a, b, o;
+  uint32_t row0, rows, split, other;
+};
+OCN_DEV StripBlock strip_block(KStripArgs &p, uint32_t g) {
+  StripBlock k;
+  k.other = rfastdiv(g, args_div(p.split_div));
+  k.split = g - k.other * p.split_div.d;
+  k.row0 = k.split * p.chunk;
+  k.rows = k.row0 + p.chunk < p.rows ? p.chunk : p.rows - k.row0;
+  k.a = k.b = k.o = 0;
+  uint32_t t = k.other;
+  const uint32_t nother = p.nother;
+  for (uint32_t d = 0; d < nother; ++d) {
+    const uint32_t q = d + 1 == nother ? 0u : rfastdiv(t, args_div(p.odiv[d]));
+    const int64_t i = t - q * p.odiv[d].d;
+    t = q;
+    k.a += i * p.osa[d];
+    k.b += i * p.osb[d];
+    k.o += i * p.oso[d];
+  }
+  return k;
+}
+
+// Vectors l, l + lanes, ... below n: four on their way at a time, and what is left together too.
+// (load and add are told the number of the trip as well)
+template <class Buf, class Load, class Add> OCN_DEV void strip_walk(uint32_t l, uint32_t lanes, uint32_t n, Load load, Add add) {
+  constexpr uint32_t U = 4;
+  uint32_t t = l, trip = 0;
+  for (; t + (U - 1) * lanes < n; t += U * lanes, trip += U) {
+    Buf v[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) load(t + u * lanes, trip + u, v[u]);
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) add(trip + u, v[u]);
+  }
+  if (t < n) {
+    Buf v[U - 1];
+#pragma unroll
+    for (uint32_t u = 0; u < U - 1; ++u)
+      if (t + u * lanes < n) load(t + u * lanes, trip + u, v[u]);
+#pragma unroll
+    for (uint32_t u = 0; u < U - 1; ++u)
+      if (t + u * lanes < n) add(trip + u, v[u]);
+  }
+}
+
+// The columns of a workgroup's groups meet: lds[lane * V + i] is element lane * V + i of one trip's worth
+// of rows.  p.parts lanes share an output, each folds every parts-th of its elements, the first of them
+// what the others have found.
+template <class R> OCN_DEV void strip_fold(KStripArgs &p, typename R::A *lds, uint32_t per_group) {
+  using A = typename R::A;
+  const uint32_t tid = threadIdx.x, outs = p.outs_div.d, nog = p.nog, inner = p.inner, parts = p.parts, width = p.width;
+  const uint32_t addends = rfastdiv(per_group, args_div(p.nog_div));   // elements that go into one output
+  auto fold = [&](uint32_t part, uint32_t o) -> A {
+    const uint32_t g = rfastdiv(o, args_div(p.nog_div)), j = o - g * nog;
+    const A *src = lds + g * per_group + j * inner;
+    A v = R::identity();
+    if (inner == 1) {
+#pragma clang loop vectorize(disable) interleave(disable) unroll_count(4)
+      for (uint32_t e = part; e < addends; e += parts) v = R::combine(v, src[e * width]);
+    } else {
+#pragma clang loop vectorize(disable) interleave(disable) unroll_count(4)
+      for (uint32_t e = part; e < addends; e += parts) {
+        const uint32_t q = rfastdiv(e, args_div(p.inner_div));
+        v = R::combine(v, src[q * width + (e - q * inner)]);
+      }
+    }
+    return v;
+  };
+  auto put = [&](uint32_t o, A v) {
+    const uint32_t g = rfastdiv(o, args_div(p.nog_div)), j = o - g * nog, gi = blockIdx.x * p.groups + g;
+    if (gi >= p.ngroups) return;
+    const StripBlock k = strip_block(p, gi);
+    if (p.split_div.d == 1) store_result<A>(p.out + k.o + (int64_t)j * p.kso, p.out_dtype, v, (p.flags & kStripSwapO) != 0);
+    else reinterpret_cast<typename R::P *>(p.partial)[(int64_t)k.split * p.psplit + ((int64_t)k.other * nog + j) * p.pstep] = to_storage<R::ACC>(v);
+  };
+  __syncthreads();
+  if (parts == 1) {
+    for (uint32_t o = tid; o < outs; o += blockDim.x) put(o, fold(0, o));
+    return;
+  }
+  // (outs * parts is at most a workgroup's lanes)
+  A v = R::identity();
+  if (tid < outs * parts) {
+    const uint32_t part = rfastdiv(tid, args_div(p.outs_div));
+    v = fold(part, tid - part * outs);
+  }
+  __syncthreads();
+  lds[tid] = v;
+  __syncthreads();
+  if (tid < outs) {
+    for (uint32_t q = 1; q < parts; ++q) v = R::combine(v, lds[q * outs + tid]);
+    put(tid, v);
+  }
+}
+
+template <int S, int OP, bool NT, bool SW> OCN_DEV void strip_cols_body(KStripArgs &p, typename Reducer<S, OP>::A *lds) {
+  using R = Reducer<S, OP>;
+  using A = typename R::A;
+  using St = storage_t<S>;
+  constexpr uint32_t V = 16 / sizeof(St);
+  struct alignas(16) Pk { St v[V]; };
+  const uint32_t tid = threadIdx.x, lanes = p.lanes;
+  const uint32_t gl = __umulhi(tid, p.lanes_m), l = tid - gl * lanes, g = blockIdx.x * p.groups + gl;
+  A acc[V];
+#pragma unroll
+  for (uint32_t i = 0; i < V; ++i) acc[i] = R::identity();
+  if (gl < p.groups && g < p.ngroups) {
+    const StripBlock k = strip_block(p, g);
+    const uint32_t n = k.rows * p.width, full = n / V;
+    const char *base = p.a + k.a + (int64_t)k.row0 * (int64_t)(p.width * sizeof(St));
+    strip_walk<Pk>(
+        l, lanes, full, [&](uint32_t t, uint32_t, Pk &v) { load_vec<St, V, NT>(base + (uint64_t)t * 16u, v); },
+        [&](uint32_t, Pk &v) {
+          order_pack<S>(SW, v);
+#pragma unroll
+          for (uint32_t i = 0; i < V; ++i) acc[i] = R::combine(acc[i], R::lift(from_storage<S>(v.v[i])));
+        });
+    if (V > 1 && full * V < n && full % lanes == l) {   // the elements behind the last whole vector, all on their way together
+      St v[V];
+#pragma unroll
+      for (uint32_t i = 0; i < V - 1; ++i) v[i] = *reinterpret_cast<const St *>(base + (uint64_t)(full * V + i < n ? full * V + i : n - 1) * sizeof(St));
+#pragma unroll
+      for (uint32_t i = 0; i < V - 1; ++i)
+        if (full * V + i < n) {
+          order_pack<S>(SW, v[i]);
+          acc[i] = R::combine(acc[i], R::lift(from_storage<S>(v[i])));
+        }
+    }
+  }
+#pragma unroll
+  for (uint32_t i = 0; i < V; ++i) lds[tid * V + i] = acc[i];
+  strip_fold<R>(p, lds, lanes * V);
+}
+
+template <int S, int OP> __global__ __launch_bounds__(kStripLanes) void red_strip_cols_kernel(const RedStripArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KStripArgs &p = *(KStripArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  using A = typename Reducer<S, OP>::A;
+  extern __shared__ __align__(16) unsigned char strip_lds[];
+  A *lds = reinterpret_cast<A *>(strip_lds);
+  const uint32_t flags = p.flags;
+  if (flags & kStripSwapA) {
+    strip_cols_body<S, OP, false, true>(p, lds);
+  } else if (flags & kStripNt) {
+    strip_cols_body<S, OP, true, false>(p, lds);
+  } else {
+    strip_cols_body<S, OP, false, false>(p, lds);
+  }
+}
+
+// Whole rows from LDS: p.parts neighbouring lanes (a power of two) take a row each element in turn.
+template <class R, class Get> OCN_DEV void strip_rows_fold(KStripArgs &p, const StripBlock &k, Get get) {
+  using A = typename R::A;
+  const uint32_t parts = p.parts, part = threadIdx.x & (parts - 1), width = p.width, step = (uint32_t)kBlock / parts, rotate = p.rotate;
+  __syncthreads();
+  for (uint32_t r0 = 0; r0 < k.rows; r0 += step) {    // (the same trips for all lanes: they fold together)
+    const uint32_t r = r0 + threadIdx.x / parts;
+    A v = R::identity();
+    if (r < k.rows) {
+      const uint32_t e0 = r * width;
+      uint32_t c = part + (rotate ? (r & (rotate - 1)) * parts : 0u);
+#pragma clang loop vectorize(disable) interleave(disable) unroll_count(4)
+      for (uint32_t i = part; i < width; i += parts) {
+        v = R::combine(v, get(e0 + c));
+        c = c + parts < width ? c + parts : part;
+      }
+    }
+    v = group_fold<R>(v, (int)parts);
+    if (r < k.rows && part == 0)
+      store_result<A>(p.out + k.o + (int64_t)(k.row0 + r) * p.kso, p.out_dtype, v, (p.flags & kStripSwapO) != 0);
+  }
+}
+
+template <int S, int OP> __global__ __launch_bounds__(kBlock) void red_strip_rows_kernel(const RedStripArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KStripArgs &p = *(KStripArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  using R = Reducer<S, OP>;
+  using St = storage_t<S>;
+  constexpr uint32_t V = 16 / sizeof(St);
+  struct alignas(16) Pk { St v[V]; };
+  extern __shared__ __align__(16) unsigned char strip_lds[];
+  St *lds = reinterpret_cast<St *>(strip_lds);
+  const StripBlock k = strip_block(p, blockIdx.x);
+  const uint32_t n = k.rows * p.width, full = n / V, tid = threadIdx.x;
+  const char *base = p.a + k.a + (int64_t)k.row0 * (int64_t)(p.width * sizeof(St));
+  const bool nt = (p.flags & kStripNt) != 0, sw = (p.flags & kStripSwapA) != 0;
+  auto keep = [&](uint32_t trip, Pk &v) {
+    order_pack<S>(sw, v);
+    reinterpret_cast<Pk *>(strip_lds)[tid + trip * (uint32_t)kBlock] = v;
+  };
+  if (nt) strip_walk<Pk>(tid, kBlock, full, [&](uint32_t t, uint32_t, Pk &v) { load_vec<St, V, true>(base + (uint64_t)t * 16u, v); }, keep);
+  else strip_walk<Pk>(tid, kBlock, full, [&](uint32_t t, uint32_t, Pk &v) { load_vec<St, V, false>(base + (uint64_t)t * 16u, v); }, keep);
+  if (full * V + tid < n) lds[full * V + tid] = load_one<S>(sw, base + (uint64_t)(full * V + tid) * sizeof(St));
+  strip_rows_fold<R>(p, k, [&](uint32_t e) { return R::lift(from_storage<S>(lds[e])); });
+}
+
+#endif  // __HIPCC__
+
+}  // namespace ocn
