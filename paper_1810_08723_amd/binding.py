@@ -77,6 +77,14 @@ class OcnError(RuntimeError):
 
 _lib: Optional[C.CDLL] = None
 
+# The calls without the interpreter's share of their time (csrc/pycall.cpp); the functions below serve
+# by themselves where that module has not been built for this interpreter.
+try:
+    from . import _call
+except ImportError:
+    _call = None
+_direct: dict = {}      # callables of that module by the name of the function each stands for
+
 
 def lib() -> C.CDLL:
     """The loaded library.  Raises if it has not been built (python -m paper_1810_08723_amd.build)."""
@@ -128,6 +136,8 @@ def lib() -> C.CDLL:
                                        C.c_size_t, C.c_void_p]
         L.ocn_gather.argtypes = [T, C.c_void_p, C.c_int64, C.c_int64, C.c_int64, T, C.c_void_p]
         L.ocn_scatter.argtypes = [T, C.c_void_p, C.c_int64, C.c_int64, C.c_int64, T, C.c_void_p]
+        for name, direct in _direct.items():
+            direct.address = C.cast(getattr(L, "ocn_" + name), C.c_void_p).value
         _lib = L
     return _lib
 
@@ -147,6 +157,7 @@ class Tensor:
     # The C struct is built at the first call that takes the tensor and dropped when a field is
     # assigned (the library never writes to it).  _ref: the struct by reference, as the calls take it.
     _ref = None
+    _desc = None     # ... the same struct for the calls of csrc/pycall.cpp
 
     def __init__(self, base, dtype, sizes, strides, offset=0, device=0, keepalive=None, byteswapped=False):
         self.__dict__.update(base=base, dtype=dtype, sizes=sizes, strides=strides, offset=offset, device=device,
@@ -155,6 +166,7 @@ class Tensor:
     def __setattr__(self, name, value):
         self.__dict__[name] = value
         self.__dict__.pop("_ref", None)
+        self.__dict__.pop("_desc", None)
 
     @staticmethod
     def on_storage(storage, dtype: str, sizes: Sequence[int], strides: Sequence[int],
@@ -178,6 +190,8 @@ class Tensor:
         # kept only where the sizes and strides cannot change behind the tensor's back
         if type(self.sizes) is tuple and type(self.strides) is tuple:
             self.__dict__["_ref"] = ref
+            if _call is not None:
+                self.__dict__["_desc"] = _call.Desc(bytes(t))
         return ref
 
     def desc(self) -> OcnTensor:
@@ -378,6 +392,11 @@ def scatter(src: Tensor, offsets, lo: int, hi: int, out_inner: Tensor, stream=No
                       out_inner._ref or out_inner._make_ref(), _stream(stream))
     if rc:
         _check(rc)
+
+
+if _call is not None:
+    for _name in ("unary", "binary", "cast_copy", "reduce", "binary_reduce", "index_offsets", "mask_offsets", "gather", "scatter"):
+        globals()[_name] = _direct[_name] = _call.Call(_name, globals()[_name], globals(), Tensor)
 
 
 def domain_check(op: str, a: Tensor, flag=None, workspace=None, stream=None):

@@ -15,6 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 _TAG = os.environ.get("OCN_BUILD_TAG", "")
 OBJ = os.path.join(HERE, "_build" + ("_" + _TAG if _TAG else ""))
 LIB = os.path.join(HERE, "libocn" + ("_" + _TAG if _TAG else "") + ".so")
+CALL = os.path.join(HERE, "_call.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Floating-point contraction stays off: a*b+c must round twice, as in the definition of each
@@ -63,6 +64,16 @@ def _compile(src: str, force: bool = True) -> str:
     return obj
 
 
+def build_call() -> None:
+    """The binding's call module (host code only, for the interpreter that builds it)."""
+    import sysconfig
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        sys.stderr.write("no Python headers: the binding goes through ctypes\n")
+        return
+    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + include, os.path.join(CSRC, "pycall.cpp"), "-o", CALL], check=True)
+
+
 def build(jobs: int | None = None, force: bool = True) -> str:
     """Compiles every source and links the library.  force=False recompiles only the objects
     whose source, headers or flags changed since they were last built."""
@@ -72,6 +83,7 @@ def build(jobs: int | None = None, force: bool = True) -> str:
         objs = list(ex.map(lambda src: _compile(src, force), SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
+    build_call()
     return LIB
 
 

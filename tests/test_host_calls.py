@@ -1,0 +1,142 @@
+"""The binding's direct calls hand the C ABI what its own functions hand it, and leave every call in another
+form, and every error, to them (no GPU needed: a callback stands in for the library)."""
+import ctypes as C
+import inspect
+
+import pytest
+
+import paper_1810_08723_amd as ocn
+from paper_1810_08723_amd import binding
+
+pytestmark = pytest.mark.skipif(binding._call is None, reason="the call module is not built for this interpreter")
+
+P, T, I32, I64, SZ = C.c_void_p, C.POINTER(binding.OcnTensor), C.c_int32, C.c_int64, C.c_size_t
+AX, ST = C.POINTER(I32), C.POINTER(I64)
+C_ARGS = {"unary": (C.c_int, T, T, C.c_uint32, P), "binary": (C.c_int, T, T, T, C.c_uint32, P), "cast_copy": (T, T, P),
+          "reduce": (C.c_int, T, AX, I32, T, P, SZ, P), "binary_reduce": (C.c_int, C.c_int, T, T, AX, I32, T, I32, P, SZ, P),
+          "index_offsets": (T, I64, I64, T, P, P), "mask_offsets": (T, ST, P, I64, P, P, SZ, P),
+          "gather": (T, P, I64, I64, I64, T, P), "scatter": (T, P, I64, I64, I64, T, P)}
+
+
+class Memory:
+    """Stands in for a torch tensor."""
+    def __init__(self, address, n):
+        self.address, self.n = address, n
+
+    def data_ptr(self):
+        return self.address
+
+    def numel(self):
+        return self.n
+
+
+def _tensors():
+    made = [ocn.Tensor(1 << 40 + i, "float", (4 + i, 8), (32, 4), 16 * i, 0) for i in range(3)]
+    for t in made:
+        t.desc()
+    return made
+
+
+def _usual():
+    a, b, o = _tensors()
+    ws = Memory(1 << 50, 4096)
+    return {"unary": ("sin", a, o), "binary": ("add", a, b, o), "cast_copy": (a, o), "reduce": ("max", a, [1], o, ws),
+            "binary_reduce": ("mul", "sum", a, b, (0, 1), o, "double", ws), "index_offsets": (a, 7, -12, o, Memory(1 << 51, 1)),
+            "mask_offsets": (a, [8, 4], Memory(1 << 52, 0), Memory(1 << 53, 1), ws), "gather": (a, Memory(1 << 52, 9), -3, 1 << 40, o),
+            "scatter": (a, Memory(1 << 52, 0), 0, 5, o)}
+
+
+def _seen(args):
+    """What reached the C function: structs by their bytes, arrays by their first two elements, addresses as numbers."""
+    out = []
+    for x in args:
+        if isinstance(x, T):
+            out.append(bytes(x.contents))
+        elif isinstance(x, (AX, ST)):
+            out.append(("list", x[0]))
+        else:
+            out.append(0 if x is None else x)
+    return out
+
+
+def _direct(name, rc=0):
+    record, fallback = [], []
+    proto = C.CFUNCTYPE(C.c_int, *C_ARGS[name])
+
+    @proto
+    def stand_in(*args):
+        record.append(_seen(args))
+        return rc
+
+    names = dict(vars(binding), _raw_stream=(lambda device: 0x5000 + device, lambda: 3))
+    call = binding._call.Call(name, lambda *a, **k: fallback.append((a, k)), names, ocn.Tensor)
+    call.address = C.cast(stand_in, P).value
+    return call, record, fallback, stand_in
+
+
+@pytest.mark.parametrize("name", sorted(C_ARGS))
+def test_the_same_reaches_the_library(name, monkeypatch):
+    args = _usual()[name]
+    call, record, fallback, _keep = _direct(name)
+    call(*args)
+    call(*args, stream=77)
+    params = list(inspect.signature(getattr(ocn, name)).parameters)
+    call(**dict(zip(params, args)), stream=77)
+    assert not fallback and len(record) == 3 and record[1] == record[2] and record[0][:-1] == record[1][:-1]
+    assert record[0][-1] == 0x5003 and record[1][-1] == 77
+    # what the binding's own function passes, through the same stand-in
+    own = []
+    proto = C.CFUNCTYPE(C.c_int, *C_ARGS[name])
+    through = proto(lambda *a: own.append(_seen(a)) or 0)
+    monkeypatch.setattr(binding, "_ocn_" + name, through)
+    getattr(ocn, name).__wrapped__(*args, stream=77)
+    assert own == [record[1]]
+
+
+@pytest.mark.parametrize("name", sorted(C_ARGS))
+def test_other_forms_go_to_the_function(name):
+    call, record, fallback, _keep = _direct(name)
+    args = list(_usual()[name])
+
+    class Other(ocn.Tensor):
+        pass
+
+    def with_first_tensor(x):
+        at = next(i for i, v in enumerate(args) if isinstance(v, ocn.Tensor))
+        return args[:at] + [x] + args[at + 1:]
+
+    fresh = ocn.Tensor(1 << 40, "float", (4, 8), (32, 4))                     # no descriptor yet
+    listed = ocn.Tensor(1 << 40, "float", [4, 8], [32, 4])
+    listed.desc()                                                              # ... never one that is kept
+    assigned = _tensors()[0]
+    assigned.offset = 64                                                       # ... dropped
+    forms = [with_first_tensor(x) for x in (fresh, listed, assigned, Other(1 << 40, "float", (4, 8), (32, 4)), None)]
+    forms += [args[:-1], args + [None] * 9]
+    if isinstance(args[0], str):
+        forms += [["no such"] + args[1:], [3] + args[1:]]
+    if name in ("unary", "binary"):
+        forms += [args + [True], args + [-1]]
+    if name in ("reduce", "binary_reduce"):
+        axes = 2 if name == "reduce" else 4
+        forms += [args[:axes] + [x] + args[axes + 1:] for x in ([1.0], [True], iter([1]), [0] * 9, [1 << 40])]
+        forms += [args[:-1] + [None]]
+    for f in forms:
+        call(*f)
+    call(*args, stream="0")
+    call(*args, no_such=1)
+    call.address = 0
+    call(*args)
+    assert not record and len(fallback) == len(forms) + 3
+
+
+def test_errors_are_the_bindings():
+    call, record, fallback, _keep = _direct("binary", rc=binding.ERR["SHAPE"])
+    with pytest.raises(ocn.OcnError) as e:
+        call(*_usual()["binary"])
+    assert e.value.code == binding.ERR["SHAPE"] and record and not fallback
+
+
+def test_names_and_signatures_stay():
+    for name in C_ARGS:
+        f = getattr(ocn, name)
+        assert f.__name__ == name and inspect.signature(f) == inspect.signature(f.__wrapped__) and f.__doc__ == f.__wrapped__.__doc__
