@@ -670,6 +670,45 @@ template <class P> OCN_HDF void rows_next(const P &p, RowsPlace &r) {
   }
 }
 
+// V elements from element s on (0 <= s < V) of the 2 V that lie in a and b one after the other
+template <class S, int V> OCN_DEV Pack<S, V> two_pieces(const Pack<S, V> &a, const Pack<S, V> &b, uint32_t s) {
+  Pack<S, V> r;
+  constexpr int B = (int)sizeof(S) * V;
+  if constexpr (V == 1) {
+    r = a;
+  } else if constexpr (B % 4 != 0) {
+    S c[2 * V];
+#pragma unroll
+    for (int i = 0; i < V; ++i) c[i] = a.v[i], c[V + i] = b.v[i];
+#pragma unroll
+    for (int step = 1; step < V; step *= 2)
+#pragma unroll
+      for (int i = 0; i + step < 2 * V; ++i) c[i] = s & step ? c[i + step] : c[i];
+#pragma unroll
+    for (int i = 0; i < V; ++i) r.v[i] = c[i];
+  } else {
+    constexpr int W = B / 4;
+    uint32_t w[2 * W + 1];
+    __builtin_memcpy(w, &a, B);
+    __builtin_memcpy(w + W, &b, B);
+    w[2 * W] = 0;
+    const uint32_t bytes = s * (uint32_t)sizeof(S), words = bytes / 4;
+#pragma unroll
+    for (int step = W / 2 > 0 ? W / 2 : 1; step >= 1; step /= 2) {
+      if (step < W) {
+#pragma unroll
+        for (int i = 0; i + step < 2 * W; ++i) w[i] = words & step ? w[i + step] : w[i];
+      }
+    }
+    if constexpr (sizeof(S) < 4) {
+#pragma unroll
+      for (int i = 0; i < W; ++i) w[i] = __builtin_amdgcn_alignbyte(w[i + 1], w[i], bytes & 3);
+    }
+    __builtin_memcpy(&r, w, B);
+  }
+  return r;
+}
+
 template <class G> __global__ __launch_bounds__(kBlock) void ew_rows_kernel(const RowsArgs by_value) {
   constexpr int V = G::VR, U = G::UR;
   using SAt = typename G::SAt;
@@ -719,16 +758,69 @@ template <class G> __global__ __launch_bounds__(kBlock) void ew_rows_kernel(cons
           else load_pack_any<SBt, V, ALB>(pb, vb[u], (flags & kRowsNtB) != 0);
         }
       }
-      // element by element: a vector that is not whole, or an input whose rows it crosses
       if (!va_ok || !vb_ok) {
-#pragma unroll
-        for (int i = 0; i < V; ++i) {
-          if (i >= r.lo && i < r.hi) {
-            if (!va_ok) va[u].v[i] = *reinterpret_cast<const SAt *>(p.a + rows_offset(r, 1, i, ESA, alin, abc));
-            if constexpr (BIN) {
-              if (!vb_ok) vb[u].v[i] = *reinterpret_cast<const SBt *>(p.b + rows_offset(r, 2, i, ESB, blin, bbc));
+        if (U == 1 && whole && p.inner >= (uint32_t)V) {
+          // An input whose vector goes on into the next row: the last V elements of the one row and the first
+          // V of the other, whole vectors both.  (Element by element, in a lane or two of every wavefront, products
+          // of halves [78078, 666] with a row took 58 us, 36 so, [1268292, 41] 81, 45; of doubles [292682, 41] 39, 34.
+          // Not with several vectors per lane, where each would be waited for before the next is asked for: halves
+          // times floats [548387, 62] 48 us, 72 so.)
+          const uint32_t from = r.col - (p.inner - (uint32_t)V);
+          const int here = V - (int)from;
+          RowsPlace next = r;
+          next.col = 0;
+          rows_outer(p, r.row + 1, next.off);
+          r.col = p.inner - (uint32_t)V;
+          Pack<SAt, V> na;
+          Pack<SBt, V> nb;
+          if (!va_ok) {
+            if (abc) {
+              va[u].v[0] = *reinterpret_cast<const SAt *>(p.a + r.off[1]);
+              na.v[0] = *reinterpret_cast<const SAt *>(p.a + next.off[1]);
+            } else {
+              load_pack_any<SAt, V, ALA>(p.a + rows_offset(r, 1, 0, ESA, false, false), va[u]);
+              load_pack_any<SAt, V, ALA>(p.a + next.off[1], na);
             }
-            rows_next(p, r);
+          }
+          if constexpr (BIN) {
+            if (!vb_ok) {
+              if (bbc) {
+                vb[u].v[0] = *reinterpret_cast<const SBt *>(p.b + r.off[2]);
+                nb.v[0] = *reinterpret_cast<const SBt *>(p.b + next.off[2]);
+              } else {
+                load_pack_any<SBt, V, ALB>(p.b + rows_offset(r, 2, 0, ESB, false, false), vb[u]);
+                load_pack_any<SBt, V, ALB>(p.b + next.off[2], nb);
+              }
+            }
+          }
+          if (!va_ok) {
+            if (abc) {
+#pragma unroll
+              for (int i = V - 1; i >= 0; --i) va[u].v[i] = i < here ? va[u].v[0] : na.v[0];
+            } else {
+              va[u] = two_pieces(va[u], na, from);
+            }
+          }
+          if constexpr (BIN) {
+            if (!vb_ok) {
+              if (bbc) {
+#pragma unroll
+                for (int i = V - 1; i >= 0; --i) vb[u].v[i] = i < here ? vb[u].v[0] : nb.v[0];
+              } else {
+                vb[u] = two_pieces(vb[u], nb, from);
+              }
+            }
+          }
+        } else {   // element by element: a vector that is not whole, or rows shorter than one
+#pragma unroll
+          for (int i = 0; i < V; ++i) {
+            if (i >= r.lo && i < r.hi) {
+              if (!va_ok) va[u].v[i] = *reinterpret_cast<const SAt *>(p.a + rows_offset(r, 1, i, ESA, alin, abc));
+              if constexpr (BIN) {
+                if (!vb_ok) vb[u].v[i] = *reinterpret_cast<const SBt *>(p.b + rows_offset(r, 2, i, ESB, blin, bbc));
+              }
+              rows_next(p, r);
+            }
           }
         }
       }
