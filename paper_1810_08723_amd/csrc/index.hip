@@ -11,7 +11,7 @@
 //                      its selected elements behind its prefix (smaller masks: behind the sum of the counts,
 //                      or of the mask itself, before it) (staged in LDS so that the
 //                      stores are coalesced).  Lanes own 16 consecutive mask bytes (one 128-bit
-//                      load when the mask is contiguous).
+//                      load when the mask is contiguous), four in smaller masks.
 //   ocn_gather/scatter one lane per copied item (an element, or 16 bytes where the rows' fastest
 //                      dimension is contiguous and aligned), rows of `inner` elements per offset
 //                      (gapless rows in 16-byte pieces of any alignment: row_pieces_kernel);
@@ -400,12 +400,11 @@ __global__ __launch_bounds__(kScanBlock) void mask_scan_kernel(const MaskArgs p)
   if (t == 0) *p.count = carry;
 }
 
-// A workgroup of the write kernel takes a chunk and needs the number of elements that are selected
-// before it:
+// A workgroup of a write kernel needs the number of elements that are selected before its chunk:
 //   kBeforeCount  adds up the mask itself up to there: no other launch at all (contiguous masks of at
 //                 most kMaskDirect elements: the last workgroup reads 96 KiB in three trips of eight
-//                 loads, against the 2.5 us and more that each further launch costs; at 100 000 elements
-//                 the kernel takes 7.3 us, 3.4 and 5.0 in two launches, at 260 000 13.6);
+//                 loads, against the 2.5 us and more that each further launch costs; with the chunk counts
+//                 of another launch 40000 elements take 8.3 us instead of 7.3, 98304 8.6 instead of 9.0);
 //   kBeforeGroups adds up the totals of the groups of chunks before its own and the counts inside it
 //                 (contiguous masks of up to kMaskSumGroups groups, 67 million elements: 4 KiB read
 //                 per workgroup at most, which hide behind the others' stores);
@@ -413,7 +412,7 @@ __global__ __launch_bounds__(kScanBlock) void mask_scan_kernel(const MaskArgs p)
 //   kBeforeScan   reads its prefix, for which a launch of one workgroup scans the counts (6.0 us for the
 //                 7325 chunks of 30 million elements).
 enum { kBeforeCount = 0, kBeforeSum = 1, kBeforeScan = 2, kBeforeGroups = 3 };
-constexpr uint32_t kMaskDirect = 98304, kMaskSumChunks = 2048, kMaskSumGroups = 1024;
+constexpr uint32_t kMaskDirect = 98304, kMaskQuarters = 1 << 20, kMaskSumChunks = 2048, kMaskSumGroups = 1024;
 
 // FLAT: a contiguous mask and offsets that advance by one stride.  Bound by instructions as much as by the
 // 120 MB of offsets of 30 million elements with half of them selected: two offsets per lane and store, whole
@@ -430,18 +429,7 @@ template <bool FLAT, int BEFORE> __global__ __launch_bounds__(kBlock) void mask_
   const uint32_t flags = mask_flags(p, chunk0 + threadIdx.x * kMaskPerLane);
   if constexpr (BEFORE != kBeforeScan) {
     uint32_t c = 0;
-    if constexpr (BEFORE == kBeforeCount) {
-      // eight loads in flight, past the end the first one again
-      constexpr uint32_t kAhead = 8;
-      for (uint32_t j = 0; j < chunk; j += kAhead) {
-        uint4 v[kAhead];
-#pragma unroll
-        for (uint32_t k = 0; k < kAhead; ++k)
-          v[k] = *reinterpret_cast<const uint4 *>(p.mask + (j + k < chunk ? j + k : 0u) * (uint32_t)kMaskChunk + threadIdx.x * 16u);
-#pragma unroll
-        for (uint32_t k = 0; k < kAhead; ++k) c += j + k < chunk ? nonzero_bytes(v[k]) : 0u;
-      }
-    } else if constexpr (BEFORE == kBeforeGroups) {
+    if constexpr (BEFORE == kBeforeGroups) {
       const uint32_t g = chunk / kMaskGroup;
       if (threadIdx.x < chunk % kMaskGroup) c = p.block_counts[g * kMaskGroup + threadIdx.x];
 #pragma unroll 4
@@ -507,6 +495,59 @@ template <bool FLAT, int BEFORE> __global__ __launch_bounds__(kBlock) void mask_
         }
       }
   }
+}
+
+// Contiguous masks of at most kMaskQuarters elements: a workgroup per quarter of a chunk, a lane per four elements
+// instead of sixteen, the quarters before its own counted from the mask.  Bound by the latency of one workgroup,
+// most of it the sixteen turns of the loop that stages a lane's positions and the stores behind it; four times the
+// workgroups of a quarter of that work, which still run all at once: with the threshold and the count before it 1000
+// elements 7.2 -> 5.1 us, 98304 10.2 -> 9.0, 10^6 12.6 -> 11.7; 2 * 10^6 the same, 4 * 10^6 19.7 -> 21.1.
+template <int BEFORE> __global__ __launch_bounds__(kBlock) void mask_write_quarters_kernel(const MaskArgs p) {
+  constexpr uint32_t kQuarter = kMaskChunk / 4;
+  static_assert(kQuarter == kBlock * 4, "four mask bytes per lane");
+  __shared__ uint32_t lds[kBlock / kWave], lds_before[kBlock / kWave];
+  __shared__ uint16_t staged[kQuarter];
+  const uint32_t tid = threadIdx.x, chunk = blockIdx.x / 4, chunk0 = chunk * (uint32_t)kMaskChunk, q0 = blockIdx.x * kQuarter;
+  const uint32_t e0 = q0 + tid * 4u;
+  uint32_t own = 0;
+  if (e0 + 4u <= p.n) own = *reinterpret_cast<const uint32_t *>(p.mask + e0);
+  else
+    for (uint32_t i = 0; e0 + i < p.n; ++i) own |= (uint32_t) * reinterpret_cast<const uint8_t *>(p.mask + e0 + i) << (8 * i);
+  uint32_t c = 0;                       // (the quarters before a workgroup's own are whole)
+  if (chunk0 + tid * 16u < q0) c = nonzero_bytes(*reinterpret_cast<const uint4 *>(p.mask + chunk0 + tid * 16u));
+  if constexpr (BEFORE == kBeforeCount) {
+    // eight loads in flight, past the end the first one again
+    constexpr uint32_t kAhead = 8;
+    for (uint32_t j = 0; j < chunk; j += kAhead) {
+      uint4 v[kAhead];
+#pragma unroll
+      for (uint32_t k = 0; k < kAhead; ++k)
+        v[k] = *reinterpret_cast<const uint4 *>(p.mask + (j + k < chunk ? j + k : 0u) * (uint32_t)kMaskChunk + tid * 16u);
+#pragma unroll
+      for (uint32_t k = 0; k < kAhead; ++k) c += j + k < chunk ? nonzero_bytes(v[k]) : 0u;
+    }
+  } else {
+#pragma unroll 4
+    for (uint32_t i = tid; i < chunk; i += kBlock) c += p.block_counts[i];
+  }
+#pragma unroll
+  for (int d = kWave / 2; d >= 1; d >>= 1) c += (uint32_t)__shfl_xor((int)c, d, kWave);
+  if ((tid & (kWave - 1)) == 0) lds_before[tid / kWave] = c;   // read behind the next barrier
+  const uint32_t set = (((own & 0x7f7f7f7fu) + 0x7f7f7f7fu) | own) & 0x80808080u;
+  uint32_t sum;
+  uint32_t slot = block_exclusive_scan((uint32_t)__popc(set), lds, sum);
+#pragma unroll
+  for (uint32_t k = 0; k < 4; ++k)
+    if ((set >> (8 * k + 7)) & 1u) staged[slot++] = (uint16_t)(tid * 4u + k);
+  __syncthreads();
+  int64_t base = 0;
+#pragma unroll
+  for (int w = 0; w < kBlock / kWave; ++w) base += lds_before[w];
+  if (blockIdx.x + 1 == gridDim.x && tid == 0) *p.count = base + sum;
+  const int64_t stride = p.ndim > 0 ? p.st[0] : 0, origin = (int64_t)q0 * stride;
+  const int64_t room = p.capacity - base;          // offsets that may be stored
+  const uint32_t end = room < 0 ? 0u : room < (int64_t)sum ? (uint32_t)room : sum;
+  for (uint32_t i = tid; i < end; i += kBlock) p.offsets[base + i] = origin + (int64_t)staged[i] * stride;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -893,10 +934,20 @@ int ocn_mask_offsets(const ocn_tensor *mask, const int64_t *target_strides, void
     else hipLaunchKernelGGL(mask_count_kernel, dim3(m.nblocks), dim3(kBlock), 0, s, m);
   }
   if (before == kBeforeScan) hipLaunchKernelGGL(mask_scan_kernel, dim3(1), dim3(kScanBlock), 0, s, m);
+  const bool quarters = m.contig && m.n <= kMaskQuarters;
   auto write = [&](auto before) {
     constexpr int BEFORE = decltype(before)::value;
-    if (m.contig && m.ndim <= 1) hipLaunchKernelGGL((mask_write_kernel<true, BEFORE>), dim3(m.nblocks), dim3(kBlock), 0, s, m);
-    else hipLaunchKernelGGL((mask_write_kernel<false, BEFORE>), dim3(m.nblocks), dim3(kBlock), 0, s, m);
+    if constexpr (BEFORE == kBeforeCount || BEFORE == kBeforeSum) {
+      if (BEFORE == kBeforeCount || quarters) {
+        const dim3 grid((m.n + kMaskChunk / 4 - 1) / (kMaskChunk / 4));
+        hipLaunchKernelGGL(mask_write_quarters_kernel<BEFORE>, grid, dim3(kBlock), 0, s, m);
+        return;
+      }
+    }
+    if constexpr (BEFORE != kBeforeCount) {
+      if (m.contig && m.ndim <= 1) hipLaunchKernelGGL((mask_write_kernel<true, BEFORE>), dim3(m.nblocks), dim3(kBlock), 0, s, m);
+      else hipLaunchKernelGGL((mask_write_kernel<false, BEFORE>), dim3(m.nblocks), dim3(kBlock), 0, s, m);
+    }
   };
   switch (before) {
     case kBeforeCount: write(std::integral_constant<int, kBeforeCount>{}); break;
