@@ -1238,8 +1238,16 @@ struct StripBlocks {
 };
 StripBlocks strip_blocks(const RedPlan &p) {
   StripBlocks s;
-  if (p.nkept < 1 || p.nred < 1 || p.nout < 1) return s;
+  if (p.nkept < 1 || p.nout < 1 || p.nredtot < 1) return s;
   const int es = dt_size(p.a_dtype), kc = p.nkept - 1;
+  // Reduced axes of one element: rows of one (17 million floats 62 -> 43 us, halves 57 -> 43, doubles 68 -> 55;
+  // bytes, stored one by one, 47 and 53)
+  if (p.nred < 1) {
+    s.rows = !p.fused && es > 1 && p.kstride_a[kc] == es;
+    s.width = 1;
+    s.nrows = p.ksize[kc];
+    return s;
+  }
   const int64_t V = 16 / es;
   auto cols = [&](const int64_t *ks, const int64_t *rs) { return ks[kc] == es && rs[0] == p.ksize[kc] * es; };
   auto rows = [&](const int64_t *ks, const int64_t *rs) { return rs[0] == es && ks[kc] == p.rsize[0] * es; };
@@ -1364,17 +1372,20 @@ bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
 // two of lanes per row, each with a whole vector or the row's few last elements one by one, is as
 // fast only for rows of whole vectors and small inputs (float rows of 22 [1090909, 22] 37 -> 20 us, of 5 103 -> 26,
 // of 16 24.1 -> 19.0, of 64 23.1 -> 18.4; [126241, 16] 4.8 and 5.1, halves [31894, 40] 3.3 and 4.3; but [150942, 10],
-// whose other form takes single elements, 8.0 -> 3.9).  Bytes come from LDS one by one: from 32
-// of them on the other form is the better one (any over rows of 50 32.5 and 35.6), and so it is for rows of one
-// vector, or two of 8 or 16 bits (halves [5000000, 8] 23.6 and 26.5, maxima of floats [2070888, 4] 10.6 and 12.6).
-constexpr int64_t kStripRowBytes = 16 << 10, kStripRowsSingle = 1 << 20, kStripRowsSmall = 4 << 20, kStripRowsWhole = 12 << 20;
+// whose other form takes single elements, 8.0 -> 3.9).  Bytes come from LDS in words, those of a fused
+// call one by one: from 32 of them on the other form is the better one there (any over rows of 50 32.5 and 35.6), and
+// so it is for rows of one vector, or two of 8 or 16 bits (halves [5000000, 8] 23.6 and 26.5, maxima of floats
+// [2070888, 4] 10.6 and 12.6) and for bytes in whole vectors below 48 MB (int8 sums in rows of 64: 16 MB 6.2 and
+// 6.7 us, 30 MB 10.4 either way, 50 MB 15.3 -> 12.9; rows of 33 gain at all sizes, 6 MB 6.3 -> 4.5).
+constexpr int64_t kStripRowBytes = 16 << 10, kStripRowsSingle = 1 << 20, kStripRowsSmall = 4 << 20, kStripRowsWhole = 12 << 20, kStripByteRowsWhole = 48 << 20;
 bool choose_strip_rows(RedPlan &p, const StripBlocks &s) {
   const int es = dt_size(p.a_dtype), mes = p.fused ? dt_size(p.mid_dtype) : es;
   const int64_t V = 16 / es, width = s.width, rows = s.nrows, others = p.nout / rows, total = p.nout * width * es;
   const int64_t m = width / gcd64(width, V), vecs = width / V;
-  if (width * es > kStripRowBytes / 16 || (es == 1 && width >= 32) || (s.bc && m > kBlock)) return false;
+  const bool words = es == 1 && !p.fused;   // read from LDS in words
+  if (width * es > kStripRowBytes / 16 || (es == 1 && p.fused && width >= 32) || (s.bc && m > kBlock)) return false;
   const bool whole = p.vec > 1 && width % V == 0;   // in whole vectors by the other form too
-  if (total < (whole ? kStripRowsWhole : p.vec > 1 ? kStripRowsSmall : kStripRowsSingle)) return false;
+  if (total < (whole ? (words ? kStripByteRowsWhole : kStripRowsWhole) : p.vec > 1 ? kStripRowsSmall : kStripRowsSingle)) return false;
   if (whole && (vecs == 1 || (vecs == 2 && es <= 2))) return false;
   const int64_t piece = std::max<int64_t>(2048, std::min(kStripRowBytes, total / (4 * kNumCUs)));
   int64_t chunk = 4;
@@ -1391,7 +1402,7 @@ bool choose_strip_rows(RedPlan &p, const StripBlocks &s) {
   // lanes read their rows from different elements on where rows lie a multiple of eight banks apart
   if (width * mes % 4 == 0 && gcd64(width * mes / 4, 64) >= 8) {
     p.strip_rotate = 1;
-    while (p.strip_rotate * 2 <= width / parts && p.strip_rotate < kWave) p.strip_rotate *= 2;
+    while (p.strip_rotate * 2 <= (words ? width / 4 : width) / parts && p.strip_rotate < kWave) p.strip_rotate *= 2;
   }
   p.strip_lds = (size_t)((chunk * width * mes + 15) / 16 * 16);
   p.split = 1;
@@ -1509,6 +1520,12 @@ void choose_reduce_launch(RedPlan &p) {
     p.cpw = shape.cpw;
     p.split = shape.split;
     int nw = shape.nw;
+    // bytes whose lanes and wavefronts meet in packed words, and whose blocks of 64 lanes are 1024 columns: narrower
+    // ones, down to a line, while most CUs have none (bool any over the rows of [222, 2382] 8.2 -> 6.0 us, sums 7.5 -> 6.5;
+    // with sixteen accumulators, which meet one by one, int8 maxima of [33, 5000] took 7.7 instead of 6.0)
+    const bool packed = es == 1 && (p.acc_dtype == OCN_BOOL || (p.op == R_SUM && (p.a_dtype == OCN_INT8 || p.a_dtype == OCN_UINT8) && p.nredtot <= 256 * nw));
+    if (packed && p.vec > 1 && p.split == 1)
+      while (p.cpw > 8 && (col_lanes + p.cpw - 1) / p.cpw * others * 4 <= kNumCUs && p.nredtot >= nw * (kWave / p.cpw) * 4) p.cpw /= 2;
     const int flat = p.nred == 1 && p.vec > 1 && p.vec <= 8 ? choose_flat_columns(col_lanes, others, p.nredtot, p.cpw, p.split, aligned) : 0;
     if (flat) {
       p.flat_cols = true;

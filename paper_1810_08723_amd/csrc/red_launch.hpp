@@ -60,7 +60,7 @@ template <int S, int OP> hipError_t launch_red(const RedPlan &p, char *partial, 
       {
         using A = typename Reducer<S, OP>::A;
         constexpr int VF = 16 / (int)sizeof(storage_t<S>) > 0 ? 16 / (int)sizeof(storage_t<S>) : 1;
-        const size_t lds = cols_lds_bytes<A>((int)p.block, p.vec > 1 ? VF : 1);
+        const size_t lds = cols_bits<S, OP>() && p.vec > 1 ? (size_t)p.block * 16 : cols_lds_bytes<A>((int)p.block, p.vec > 1 ? VF : 1);
         if constexpr (VF > 1 && VF <= 8) {
           if (p.flat_cols) {
             hipLaunchKernelGGL((red_cols_flat_kernel<S, OP>), dim3((unsigned)p.grid), dim3((unsigned)p.block), lds, stream, args);

@@ -154,6 +154,35 @@ template <int S, int OP, bool NT, bool SW> OCN_DEV void strip_cols_body(KStripAr
   struct alignas(16) Pk { St v[V]; };
   const uint32_t tid = threadIdx.x, lanes = p.lanes;
   const uint32_t gl = __umulhi(tid, p.lanes_m), l = tid - gl * lanes, g = blockIdx.x * p.groups + gl;
+  if constexpr (cols_bits<S, OP>()) {   // sixteen columns in four registers
+    using Bits = BitFold<S, OP>;
+    uint32_t bits[4] = {Bits::kStart, Bits::kStart, Bits::kStart, Bits::kStart};
+    if (gl < p.groups && g < p.ngroups) {
+      const StripBlock k = strip_block(p, g);
+      const uint32_t n = k.rows * p.width, full = n / V;
+      const char *base = p.a + k.a + (int64_t)k.row0 * (int64_t)p.width;
+      auto add = [&](uint32_t, Pk &v) {
+        uint32_t w[4];
+        __builtin_memcpy(w, &v, 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bits[i] = Bits::add(bits[i], w[i]);
+      };
+      strip_walk<Pk>(l, lanes, full, [&](uint32_t t, uint32_t, Pk &v) { load_vec<St, V, NT>(base + (uint64_t)t * 16u, v); }, add);
+      if (full * V < n && full % lanes == l) {   // the elements behind the last whole vector
+        Pk v;
+#pragma unroll
+        for (uint32_t i = 0; i < V; ++i) {
+          const St x = *reinterpret_cast<const St *>(base + (full * V + i < n ? full * V + i : n - 1));
+          v.v[i] = full * V + i < n ? x : (St)(Bits::kNeutral & 0xffu);
+        }
+        add(0, v);
+      }
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < V; ++i) lds[tid * V + i] = Bits::result(bits[i / 4], (int)(i % 4));
+    strip_fold<R>(p, lds, lanes * V);
+    return;
+  }
   A acc[V];
 #pragma unroll
   for (uint32_t i = 0; i < V; ++i) acc[i] = R::identity();
@@ -224,6 +253,88 @@ template <class R, class Get> OCN_DEV void strip_rows_fold(KStripArgs &p, const 
   }
 }
 
+// A lane's fold over one-byte elements, four at a time; kNeutral changes nothing.
+template <int S, int OP> struct WordFold {
+  using R = Reducer<S, OP>;
+  using A = typename R::A;
+  static constexpr bool kBits = cols_bits<S, OP>(), kDot = OP == R_SUM && (S == DT_I8 || S == DT_U8);
+  static constexpr uint32_t kNeutral = kBits         ? BitFold<S, OP>::kNeutral
+                                       : OP == R_SUM ? 0u
+                                       : OP == R_MIN ? (S == DT_I8 ? 0x7f7f7f7fu : ~0u)
+                                       : OP == R_MAX ? (S == DT_I8 ? 0x80808080u : 0u)
+                                                     : 0x01010101u;
+  // extremes compare two bytes at a time, each the high one of 16 bits (what lies below only breaks ties)
+  static constexpr bool kPairs = !kBits && (OP == R_MIN || OP == R_MAX);
+  using Half = std::conditional_t<S == DT_I8, int16_t, uint16_t>;
+  using Pair = Half __attribute__((ext_vector_type(2)));
+  static constexpr int kKind = kPairs ? 0 : kBits || kDot ? 1 : 2;
+  struct Pairs { Pair even, odd; };
+  std::conditional_t<kKind == 0, Pairs, std::conditional_t<kKind == 1, uint32_t, A>> acc;
+  OCN_DEV static Pair extreme(Pair x, uint32_t w) {
+    const Pair y = __builtin_bit_cast(Pair, w);
+    return OP == R_MAX ? __builtin_elementwise_max(x, y) : __builtin_elementwise_min(x, y);
+  }
+  OCN_DEV void init() {
+    if constexpr (kPairs) acc.even = acc.odd = __builtin_bit_cast(Pair, kNeutral);
+    else if constexpr (kBits) acc = BitFold<S, OP>::kStart;
+    else if constexpr (kDot) acc = 0u;
+    else acc = R::identity();
+  }
+  OCN_DEV void add(uint32_t w) {
+    if constexpr (kPairs) {
+      acc.even = extreme(acc.even, w << 8);
+      acc.odd = extreme(acc.odd, w);
+    } else if constexpr (kBits) acc = BitFold<S, OP>::add(acc, w);
+    else if constexpr (kDot && S == DT_I8) acc = (uint32_t)__builtin_amdgcn_sdot4((int)w, 0x01010101, (int)acc, false);
+    else if constexpr (kDot) acc = __builtin_amdgcn_udot4(w, 0x01010101u, acc, false);
+    else {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc = R::combine(acc, R::lift(from_storage<S>((storage_t<S>)(uint8_t)(w >> (8 * b)))));
+    }
+  }
+  OCN_DEV A result() {
+    if constexpr (kPairs) {
+      const Pair v = extreme(acc.even, __builtin_bit_cast(uint32_t, acc.odd));
+      const Half x = OP == R_MAX ? (v.x > v.y ? v.x : v.y) : (v.x < v.y ? v.x : v.y);
+      return (A)(x >> 8);
+    } else if constexpr (kBits) return BitFold<S, OP>::whole(acc);
+    else if constexpr (kDot && S == DT_I8) return (A)(int32_t)acc;   // (rows of 1024 bytes at most)
+    else if constexpr (kDot) return (A)acc;
+    else return acc;
+  }
+};
+
+// Rows of bytes come from LDS in the aligned words that cover them, with the neighbours' bytes in the first
+// and the last word replaced.  Byte by byte the reads and their addresses were the time of rows of 32 and more,
+// which therefore stayed with lanes that load their row's vectors themselves and take its last bytes one by one:
+// 100 MB of int8 sums in rows of 33 63 -> 25.5 us, of 156 62.5 -> 22.9, of 1000 40 -> 21.7 (15.4 at 6.5 TB/s), of 17 (byte by byte before) 37 -> 32.
+template <int S, int OP> OCN_DEV void strip_byte_rows_fold(KStripArgs &p, const StripBlock &k, const uint32_t *lds) {
+  using F = WordFold<S, OP>;
+  using R = typename F::R;
+  using A = typename R::A;
+  const uint32_t parts = p.parts, part = threadIdx.x & (parts - 1), width = p.width, step = (uint32_t)kBlock / parts, rotate = p.rotate;
+  __syncthreads();
+  for (uint32_t r0 = 0; r0 < k.rows; r0 += step) {    // (the same trips for all lanes: they fold together)
+    const uint32_t r = r0 + threadIdx.x / parts;
+    F f;
+    f.init();
+    if (r < k.rows) {
+      const uint32_t e0 = r * width, e1 = e0 + width, w0 = e0 / 4, nw = (e1 + 3) / 4 - w0;
+      const uint32_t head = ~0u << (8 * (e0 & 3)), tail = ~0u >> (8 * ((0u - e1) & 3));
+      uint32_t c = part + (rotate ? (r & (rotate - 1)) * parts : 0u);
+#pragma clang loop vectorize(disable) interleave(disable) unroll_count(4)
+      for (uint32_t i = part; i < nw; i += parts) {
+        const uint32_t m = (c == 0 ? head : ~0u) & (c + 1 == nw ? tail : ~0u);
+        f.add((lds[w0 + c] & m) | (F::kNeutral & ~m));
+        c = c + parts < nw ? c + parts : part;
+      }
+    }
+    const A v = group_fold<R>(f.result(), (int)parts);
+    if (r < k.rows && part == 0)
+      store_result<A>(p.out + k.o + (int64_t)(k.row0 + r) * p.kso, p.out_dtype, v, (p.flags & kStripSwapO) != 0);
+  }
+}
+
 template <int S, int OP> __global__ __launch_bounds__(kBlock) void red_strip_rows_kernel(const RedStripArgs by_value) {
   (void)by_value;  // read through the kernarg segment, which can be indexed at run time
   KStripArgs &p = *(KStripArgs *)__builtin_amdgcn_kernarg_segment_ptr();
@@ -244,7 +355,8 @@ template <int S, int OP> __global__ __launch_bounds__(kBlock) void red_strip_row
   if (nt) strip_walk<Pk>(tid, kBlock, full, [&](uint32_t t, uint32_t, Pk &v) { load_vec<St, V, true>(base + (uint64_t)t * 16u, v); }, keep);
   else strip_walk<Pk>(tid, kBlock, full, [&](uint32_t t, uint32_t, Pk &v) { load_vec<St, V, false>(base + (uint64_t)t * 16u, v); }, keep);
   if (full * V + tid < n) lds[full * V + tid] = load_one<S>(sw, base + (uint64_t)(full * V + tid) * sizeof(St));
-  strip_rows_fold<R>(p, k, [&](uint32_t e) { return R::lift(from_storage<S>(lds[e])); });
+  if constexpr (sizeof(St) == 1) strip_byte_rows_fold<S, OP>(p, k, reinterpret_cast<const uint32_t *>(strip_lds));
+  else strip_rows_fold<R>(p, k, [&](uint32_t e) { return R::lift(from_storage<S>(lds[e])); });
 }
 
 #endif  // __HIPCC__
