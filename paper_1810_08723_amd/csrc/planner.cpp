@@ -1413,9 +1413,77 @@ bool choose_strip_rows(RedPlan &p, const StripBlocks &s) {
   return true;
 }
 
+// Runs of columns in an output, rows too long for a strip.  A workgroup gets the outputs whose columns fill 32 to 256
+// lanes best, with what a run's ends share of a line counted against short ones; rows are split while workgroups are
+// fewer than two per CU and eight trips are left to each.
+// The forms above, where lanes share an output and read its run of every row in lines of its own, stay the better
+// ones for long runs (half sums over the outer axes of [980, 193, 96] 14.7 and 16.3 us, bytes in runs of 500 to 5000
+// 1.2 to 2.4 times as long so) and for few rows unless there is much of them (maxima of floats [148, 453, 28] 6.2 and
+// 9.4; [227, 5192, 13] 21.3 -> 18.7).  170 random calls that may take this form, before these limits: mean 1.71 times as
+// fast, 8.4 ms together -> 3.1 (floats [1049, 7872, 8] 168 -> 44, halves [957, 7281, 7] 113 -> 27, int8 [87453,
+// 159, 8] 175 -> 29); 256 splits at most, whose fold is one workgroup's for few outputs.
+constexpr int64_t kRunsSmall = 2 << 20, kRunsBytesSmall = 4 << 20, kRunsRows = 300, kRunsFewRows = 128, kRunsMuch = 32 << 20, kRunsLong = 64,
+                  kRunsBytes = 256, kRunsSplits = 256;
+bool choose_strip_runs(RedPlan &p) {
+  if (p.fused || p.nkept != 1 || p.nred != 2) return false;
+  const int es = dt_size(p.a_dtype), acc_es = dt_size(p.acc_dtype);
+  const int64_t V = 16 / es, inner = p.rsize[1], rows = p.rsize[0], width = p.nout * inner;
+  if (inner < 2 || p.rstride_a[1] != es || p.kstride_a[0] != inner * es) return false;
+  if (width < 32 * V || width >= ((int64_t)1 << 31) || rows < kRunsFewRows) return false;
+  const int64_t total = rows * width * es;
+  if (total < (es == 1 ? kRunsBytesSmall : kRunsSmall) || (rows < kRunsRows && total < kRunsMuch)) return false;
+  if (inner * es > kRunsBytes || inner > (es == 1 ? kRunsLong / 2 : kRunsLong)) return false;
+  // (512 lanes for bytes, whose sixteen columns a lane leave few workgroups)
+  const int64_t top = std::min<int64_t>(es == 1 ? kStripLanes / 2 : kStripLanes, 65536 / (V * std::max(acc_es, p.acc_dtype == OCN_HALF ? 4 : 1)));
+  const int64_t least = std::max<int64_t>(1, 32 * V / inner), most = std::max<int64_t>(1, 256 * V / inner), by = std::max<int64_t>(1, (most - least) / 64);
+  const int64_t slots = (int64_t)kNumCUs * 2 * kStripLanes / top, fits = (int64_t)OCN_REDUCE_SCRATCH_BYTES / (p.nout * acc_es);
+  int64_t outs = 0, lanes = 0, blocks = 0, split = 1;
+  double best = 0;
+  for (int64_t q = least; q <= most; q += by) {
+    const int64_t n = std::min(q, p.nout), l = (n * inner + V - 1) / V, nb = (p.nout + n - 1) / n;
+    if (l > top) break;
+    const double bytes = (double)(n * inner * es);
+    const int64_t splits = std::max<int64_t>(1, std::min({slots / nb, rows / (top / std::max<int64_t>(2, l) * 8), fits, kRunsSplits}));
+    const double share = (double)(top / l * n * inner) / (double)(top * V) * (double)p.nout / (double)(nb * n) * bytes / (bytes + 96) *
+                         std::min(1.0, (double)(nb * splits) / (double)kNumCUs);
+    if (share > best) {
+      best = share;
+      outs = n;
+      lanes = std::max<int64_t>(2, l);
+      blocks = nb;
+      split = splits;
+    }
+  }
+  if (!outs || blocks * split > max_launch_blocks() || blocks * split < kNumCUs / 4) return false;
+  const int64_t groups = top / lanes;
+  int64_t parts = 1;
+  while (parts < kWave && parts * 2 <= inner && parts * 2 * outs <= top) parts *= 2;
+  p.kernel = OCN_KERNEL_RED_COLS;
+  p.strip = 3;
+  p.strip_lanes = (int)lanes;
+  p.strip_groups = (int)groups;
+  p.strip_parts = (int)parts;
+  p.strip_inner = inner;
+  p.strip_width = outs * inner;
+  p.strip_rows = rows;
+  p.chunk = (rows + split - 1) / split;
+  p.split = (rows + p.chunk - 1) / p.chunk;
+  p.block = (int)top;
+  p.grid = blocks * p.split;
+  p.vec = (int)V;
+  p.cpw = kWave;
+  p.nt_load = (intptr_t)p.a_ptr % 16 == 0 && p.rstride_a[0] % 16 == 0 && outs * inner * es % 16 == 0 && width * es % 16 == 0 &&
+              rows * width * es >= kStreamBytes;
+  p.short_rows = p.lean = p.flat_cols = false;
+  return true;
+}
+
 void choose_strip(RedPlan &p) {
   const StripBlocks s = strip_blocks(p);
-  if (!(s.cols && choose_strip_cols(p, s)) && !(s.rows && choose_strip_rows(p, s))) return;
+  if (!(s.cols && choose_strip_cols(p, s)) && !(s.rows && choose_strip_rows(p, s))) {
+    choose_strip_runs(p);
+    return;
+  }
   p.strip_bc = s.bc;
   p.strip_inner = s.inner;
   p.strip_width = s.width;

@@ -116,7 +116,7 @@ struct RedPlan {
   bool lean = false;            // rows kernel: the common 2-D shape, run by the lean form of the kernel
   bool fold = false;            // second launch over [split][output] partial results: one output per lane
   bool swap_a = false, swap_o = false;  // the input / the output is stored in the other byte order
-  int strip = 0;                // dense blocks of narrow rows: 1 their columns, 2 their rows (strip_kernels.hpp)
+  int strip = 0;                // dense blocks of narrow rows: 1 their columns, 2 their rows, 3 runs of columns of long rows (strip_kernels.hpp)
   int strip_lanes = 0, strip_groups = 1, strip_parts = 1, strip_rotate = 0;  // ... lanes per group, groups per workgroup, lanes per output's fold
   int64_t strip_inner = 1;      // ... columns that go into one output
   int64_t strip_width = 0, strip_rows = 0;   // ... elements per row, rows of a block

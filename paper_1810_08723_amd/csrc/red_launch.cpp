@@ -95,7 +95,7 @@ RedStripArgs make_red_strip_args(const RedPlan &p, char *partial) {
   r.out = p.out_ptr;
   r.partial = partial;
   r.kso = p.kstride_o[kc];
-  r.rs = p.strip_bc == 1 ? p.rstride_a[0] : p.rstride_b[0];
+  r.rs = p.strip_bc == 1 || p.strip == 3 ? p.rstride_a[0] : p.rstride_b[0];
   r.rows = (uint32_t)p.strip_rows;
   r.chunk = (uint32_t)p.chunk;
   r.width = (uint32_t)p.strip_width;
@@ -106,7 +106,7 @@ RedStripArgs make_red_strip_args(const RedPlan &p, char *partial) {
   r.parts = (uint32_t)p.strip_parts;
   r.rotate = (uint32_t)p.strip_rotate;
   const int64_t pieces = (p.strip_rows + p.chunk - 1) / p.chunk, others = p.nout / p.ksize[kc];
-  r.ngroups = (uint32_t)(others * pieces);
+  r.ngroups = (uint32_t)(p.strip == 3 ? p.nout : others * pieces);
   r.nog = (uint32_t)(r.width / r.inner);
   r.flags = (p.nt_load ? kStripNt : 0u) | (p.swap_a ? kStripSwapA : 0u) | (p.swap_o ? kStripSwapO : 0u);
   r.out_dtype = p.out_dtype;

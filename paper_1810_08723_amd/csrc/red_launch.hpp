@@ -24,8 +24,9 @@ inline unsigned lean_block(const RedPlan &p) { return p.group > kBlock ? (unsign
 template <int S, int OP> hipError_t launch_red(const RedPlan &p, char *partial, hipStream_t stream) {
   if (p.strip) {
     const RedStripArgs args = make_red_strip_args(p, partial);
-    const size_t lds = p.strip == 1 ? strip_cols_lds<typename Reducer<S, OP>::A>((int)p.block, (int)sizeof(storage_t<S>)) : p.strip_lds;
+    const size_t lds = p.strip != 2 ? strip_cols_lds<typename Reducer<S, OP>::A>((int)p.block, (int)sizeof(storage_t<S>)) : p.strip_lds;
     if (p.strip == 1) hipLaunchKernelGGL((red_strip_cols_kernel<S, OP>), dim3((unsigned)p.grid), dim3((unsigned)p.block), lds, stream, args);
+    else if (p.strip == 3) hipLaunchKernelGGL((red_strip_runs_kernel<S, OP>), dim3((unsigned)p.grid), dim3((unsigned)p.block), lds, stream, args);
     else hipLaunchKernelGGL((red_strip_rows_kernel<S, OP>), dim3((unsigned)p.grid), dim3(kBlock), lds, stream, args);
     return hipGetLastError();
   }

@@ -25,8 +25,8 @@ struct RedStripArgs {
   const char *a, *b;                // (b: second input of a fused call)
   char *out, *partial;
   int64_t kso;                      // byte stride of the columns' (rows: the rows') kept dim in the output
-  int64_t rs;                       // fused columns: byte stride per row of an input that is one element per row
-  uint32_t ngroups, nother;         // groups of lanes in all (blocks of rows times splits); other kept dims
+  int64_t rs;                       // fused columns: byte stride per row of an input that is one element per row; runs: of the rows
+  uint32_t ngroups, nother;         // groups of lanes in all (blocks of rows times splits; runs: outputs); other kept dims
   uint32_t rows, chunk;             // rows of a block; rows per split
   uint32_t width, inner;            // elements per row; columns that go into one output
   uint32_t lanes, lanes_m, groups;  // lanes per group, ceil(2^32 / lanes), groups per workgroup
@@ -251,6 +251,82 @@ template <class R, class Get> OCN_DEV void strip_rows_fold(KStripArgs &p, const 
     if (r < k.rows && part == 0)
       store_result<A>(p.out + k.o + (int64_t)(k.row0 + r) * p.kso, p.out_dtype, v, (p.flags & kStripSwapO) != 0);
   }
+}
+
+// Runs of columns in an output where rows are too long for the forms above ([rows, outputs, run], rows any distance
+// apart): a workgroup owns p.nog whole outputs, p.lanes lanes take their columns of a row in 16-byte vectors,
+// p.groups rows go at a time; the runs meet in LDS.  Lanes that share an output read its run, a piece of every
+// row, by themselves otherwise, each in lines of its own.
+template <int S, int OP, bool NT, bool SW> OCN_DEV void strip_runs_body(KStripArgs &p, typename Reducer<S, OP>::A *lds) {
+  using R = Reducer<S, OP>;
+  using A = typename R::A;
+  using St = storage_t<S>;
+  constexpr uint32_t V = 16 / sizeof(St);
+  struct alignas(16) Pk { St v[V]; };
+  const uint32_t tid = threadIdx.x, lanes = p.lanes, inner = p.inner, groups = p.groups;
+  const uint32_t g = __umulhi(tid, p.lanes_m), l = tid - g * lanes;
+  const uint32_t cb = rfastdiv(blockIdx.x, args_div(p.split_div)), split = blockIdx.x - cb * p.split_div.d;
+  const uint32_t row0 = split * p.chunk, rows = row0 + p.chunk < p.rows ? p.chunk : p.rows - row0;
+  const uint32_t o0 = cb * p.nog, outs = o0 + p.nog < p.ngroups ? p.nog : p.ngroups - o0, cw = outs * inner;
+  if (g < groups && l * V < cw) {
+    // (the last vector ends with the last column; its first elements, a neighbour's, are dropped)
+    const int skip = l * V + V > cw ? (int)(l * V + V - cw) : 0;
+    const int64_t rs = p.rs, col = (int64_t)o0 * inner + (int64_t)(l * V) - skip;
+    const char *base = p.a + col * (int64_t)sizeof(St) + (int64_t)row0 * rs;
+    A acc[V];
+    auto load = [&](uint32_t t, uint32_t, Pk &v) { load_vec<St, V, NT>(base + (int64_t)t * rs, v); };
+    if constexpr (cols_bits<S, OP>()) {
+      using Bits = BitFold<S, OP>;
+      uint32_t bits[4] = {Bits::kStart, Bits::kStart, Bits::kStart, Bits::kStart};
+      strip_walk<Pk>(g, groups, rows, load, [&](uint32_t, Pk &v) {
+        uint32_t w[4];
+        __builtin_memcpy(w, &v, 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) bits[i] = Bits::add(bits[i], w[i]);
+      });
+#pragma unroll
+      for (uint32_t i = 0; i < V; ++i) acc[i] = Bits::result(bits[i / 4], (int)(i % 4));
+    } else {
+#pragma unroll
+      for (uint32_t i = 0; i < V; ++i) acc[i] = R::identity();
+      strip_walk<Pk>(g, groups, rows, load, [&](uint32_t, Pk &v) {
+        order_pack<S>(SW, v);
+#pragma unroll
+        for (uint32_t i = 0; i < V; ++i) acc[i] = R::combine(acc[i], R::lift(from_storage<S>(v.v[i])));
+      });
+    }
+    A *dst = lds + g * cw + l * V;
+#pragma unroll
+    for (int i = 0; i < (int)V; ++i)
+      if (i >= skip) dst[i - skip] = acc[i];
+  }
+  __syncthreads();
+  const uint32_t parts = p.parts, part = tid & (parts - 1), step = blockDim.x / parts;
+  for (uint32_t first = 0; first < outs; first += step) {   // (the same trips for all lanes: they fold together)
+    const uint32_t o = first + tid / parts;
+    A v = R::identity();
+    if (o < outs)
+      for (uint32_t q = 0; q < groups; ++q) {
+        const A *src = lds + q * cw + o * inner;
+#pragma clang loop vectorize(disable) interleave(disable) unroll_count(4)
+        for (uint32_t j = part; j < inner; j += parts) v = R::combine(v, src[j]);
+      }
+    v = group_fold<R>(v, (int)parts);
+    if (o < outs && part == 0) {
+      if (p.split_div.d == 1) store_result<A>(p.out + (int64_t)(o0 + o) * p.kso, p.out_dtype, v, (p.flags & kStripSwapO) != 0);
+      else reinterpret_cast<typename R::P *>(p.partial)[(int64_t)split * p.psplit + (int64_t)(o0 + o) * p.pstep] = to_storage<R::ACC>(v);
+    }
+  }
+}
+template <int S, int OP> __global__ __launch_bounds__(kStripLanes) void red_strip_runs_kernel(const RedStripArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KStripArgs &p = *(KStripArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  extern __shared__ __align__(16) unsigned char strip_lds[];
+  auto *lds = reinterpret_cast<typename Reducer<S, OP>::A *>(strip_lds);
+  const uint32_t flags = p.flags;
+  if (flags & kStripSwapA) strip_runs_body<S, OP, false, true>(p, lds);
+  else if (flags & kStripNt) strip_runs_body<S, OP, true, false>(p, lds);
+  else strip_runs_body<S, OP, false, false>(p, lds);
 }
 
 // A lane's fold over one-byte elements, four at a time; kNeutral changes nothing.

@@ -68,6 +68,12 @@ def test_columns_of_many_blocks(dtype, rows, width):
     _reduce(_bytes(rng, dtype, (many * rows // 7, 7, width)), (0,), ("any", "all"))
 
 
+@pytest.mark.parametrize("dtype", ("bool", "int8"))
+@pytest.mark.parametrize("sizes", [(1700, 301, 9), (2100, 67, 31)])
+def test_runs_of_columns(dtype, sizes):
+    _reduce(_bytes(rng_for(31500), dtype, sizes, first=3), (0, 2), ("any", "all", "min", "max"))
+
+
 @pytest.mark.parametrize("dtype", ("bool", "uint8", "half", "float", "double", "cfloat", "cdouble"))
 def test_axes_of_one_element(dtype):
     rng = rng_for(31600)

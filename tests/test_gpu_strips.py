@@ -129,3 +129,14 @@ def test_nan_and_infinity(dtype, sizes, axes):
         print("strips", op, dtype, sizes, flush=True)
         got, want = H.run_reduce(op, a, axes, out)
         assert H.storages_equal(out.dtype, got, want), (op, dtype, H.first_mismatch(out.dtype, got, want))
+
+
+@pytest.mark.parametrize("dtype", ("int8", "half", "int32", "double", "cfloat"))
+@pytest.mark.parametrize("rows,kept,inner", [(300, 1501, 20), (620, 1300, 9), (701, 601, 13), (1000, 67, 31), (300, 9001, 2)])
+def test_runs_of_columns_of_long_rows(dtype, rows, kept, inner):
+    """Runs whose workgroups end inside a vector, the last one with fewer outputs, split and whole, rows apart."""
+    rng = rng_for(28000 + kept + inner)
+    rows = max(rows, (4300 << 10) // (kept * inner * SIZE[dtype]) + 1)
+    for a in _variants(rng, dtype, (rows, kept, inner), 0)[:: 1 if rows * kept < 1 << 20 else 3]:
+        _reduce(a, (0, 2))
+    _reduce(random_view(rng, dtype, (2 * rows, kept, inner), specials=False).slice(0, 0, 2 * rows, 2), (0, 2))
