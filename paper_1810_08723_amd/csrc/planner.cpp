@@ -1419,9 +1419,10 @@ bool choose_strip_rows(RedPlan &p, const StripBlocks &s) {
 // The forms above, where lanes share an output and read its run of every row in lines of its own, stay the better
 // ones for long runs (half sums over the outer axes of [980, 193, 96] 14.7 and 16.3 us, bytes in runs of 500 to 5000
 // 1.2 to 2.4 times as long so) and for few rows unless there is much of them (maxima of floats [148, 453, 28] 6.2 and
-// 9.4; [227, 5192, 13] 21.3 -> 18.7).  170 random calls that may take this form, before these limits: mean 1.71 times as
-// fast, 8.4 ms together -> 3.1 (floats [1049, 7872, 8] 168 -> 44, halves [957, 7281, 7] 113 -> 27, int8 [87453,
-// 159, 8] 175 -> 29); 256 splits at most, whose fold is one workgroup's for few outputs.
+// 9.4; [227, 5192, 13] 21.3 -> 18.7).  Floats [1049, 7872, 8] 168 -> 44, halves [957, 7281, 7] 113 -> 27,
+// bool any over [1356, 3062, 5] 31 -> 13.  With strips, which take the shorter rows, 170 random calls with runs of 2 to 256
+// bytes are 1.72 times as fast in the mean as without either, 8.4 ms together -> 3.1.  256 splits at most, whose fold is
+// one workgroup's for few outputs.
 constexpr int64_t kRunsSmall = 2 << 20, kRunsBytesSmall = 4 << 20, kRunsRows = 300, kRunsFewRows = 128, kRunsMuch = 32 << 20, kRunsLong = 64,
                   kRunsBytes = 256, kRunsSplits = 256;
 bool choose_strip_runs(RedPlan &p) {
