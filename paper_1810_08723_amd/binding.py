@@ -9,6 +9,7 @@ from __future__ import annotations
 import ctypes as C
 import functools
 import os
+import types
 from dataclasses import dataclass, field
 from typing import Any, Optional, Sequence, Tuple
 
@@ -78,12 +79,14 @@ class OcnError(RuntimeError):
 _lib: Optional[C.CDLL] = None
 
 # The calls without the interpreter's share of their time (csrc/pycall.cpp); the functions below serve
-# by themselves where that module has not been built for this interpreter.
+# by themselves where that module has not been built for this interpreter, or from other sources.
 try:
     from . import _call
+    if getattr(_call, "INTERFACE", 0) != 1:
+        _call = None
 except ImportError:
     _call = None
-_direct: dict = {}      # callables of that module by the name of the function each stands for
+_direct: dict = {}      # callables of that module by the name of the function each serves
 
 
 def lib() -> C.CDLL:
@@ -394,9 +397,18 @@ def scatter(src: Tensor, offsets, lo: int, hi: int, out_inner: Tensor, stream=No
         _check(rc)
 
 
+def _serve(f) -> None:
+    """Calls of `f` in their usual form go to the library directly, the others through `f` as it is written;
+    f.__wrapped__ is `f` as it is written for all calls."""
+    f.__wrapped__ = types.FunctionType(f.__code__, f.__globals__, f.__name__, f.__defaults__, f.__closure__)
+    f.__wrapped__.__annotations__, f.__wrapped__.__doc__ = f.__annotations__, f.__doc__
+    _direct[f.__name__] = _call.Call(f.__name__, f.__wrapped__, globals(), Tensor)
+    _direct[f.__name__].serve(f)
+
+
 if _call is not None:
-    for _name in ("unary", "binary", "cast_copy", "reduce", "binary_reduce", "index_offsets", "mask_offsets", "gather", "scatter"):
-        globals()[_name] = _direct[_name] = _call.Call(_name, globals()[_name], globals(), Tensor)
+    for _f in (unary, binary, cast_copy, reduce, binary_reduce, index_offsets, mask_offsets, gather, scatter):
+        _serve(_f)
 
 
 def domain_check(op: str, a: Tensor, flag=None, workspace=None, stream=None):

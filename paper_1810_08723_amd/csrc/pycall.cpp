@@ -1,7 +1,9 @@
 // The calls of the Python binding without its interpreter work: callables that take the arguments of
 // the binding's own functions in their usual form (a Tensor whose descriptor is built, an operation by its
 // name, axes as plain ints, the current stream) straight to the C ABI, and hand every other call, and
-// every error, to the function they stand for.
+// every error, to the function they stand for.  The public names stay the Python functions that they
+// are, for whatever a program does with a function besides calling it: what serve() changes is where
+// the interpreter enters them.
 //
 // A small call is bound by the host: sines of 3000 floats took 4.0 us a call, of which HIP's launch takes 2.4 to 3.5
 // (with the machine; 1.3 for a kernel without arguments) and the plan 0.1; the rest was the interpreter and
@@ -9,13 +11,15 @@
 // kernels by themselves take 18.5.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
-#include <structmember.h>
 
 #include <cstring>
 
 #include "../../include/ocn.h"
 
 namespace {
+
+// what the binding expects of this module, counted up with every change to it (binding.py has the same number)
+constexpr int kInterface = 1;
 
 enum Kind { UNARY, BINARY, CAST_COPY, REDUCE, BINARY_REDUCE, INDEX_OFFSETS, MASK_OFFSETS, GATHER, SCATTER, KINDS };
 // the parameters of each, in order; the last one is the stream, and those from `needed` on may be left out
@@ -32,7 +36,7 @@ const Shape kShapes[KINDS] = {
     {"scatter", 5, 6, {"src", "offsets", "lo", "hi", "out_inner", "stream"}},
 };
 PyObject *g_params[KINDS][9];   // the same, interned
-PyObject *s_desc, *s_raw_stream, *s_data_ptr, *s_numel, *s_check, *s_unary, *s_binary, *s_reduce, *s_dtype;
+PyObject *s_direct, *s_desc, *s_raw_stream, *s_data_ptr, *s_numel, *s_check, *s_unary, *s_binary, *s_reduce, *s_dtype;
 
 // ---- a descriptor that belongs to a Tensor ------------------------------------------------
 struct Desc {
@@ -64,7 +68,10 @@ struct Call {
   PyObject *function;     // what this stands for
   PyObject *globals;      // the binding's
   PyTypeObject *tensor;   // its Tensor
+  PyObject *body, *defaults;   // of the function it serves, as they were
 };
+
+PyTypeObject CallType = {PyVarObject_HEAD_INIT(nullptr, 0) "_call.Call"};
 
 // the descriptor of an argument, or null (no error set): not a plain Tensor, or not built yet
 const ocn_tensor *descriptor(const Call *c, PyObject *o) {
@@ -224,12 +231,12 @@ bool direct(const Call *c, PyObject *const *v, int *rc) {
   return false;
 }
 
-PyObject *call(PyObject *self, PyObject *const *args, size_t nargsf, PyObject *kwnames) {
-  Call *c = (Call *)self;
+// The call if it is in the usual form (its result, or null with the error set), else `usual` is false and nothing is done.
+PyObject *call_direct(const Call *c, PyObject *const *args, size_t nargsf, PyObject *kwnames, bool &usual) {
   const Shape &shape = kShapes[c->kind];
   const Py_ssize_t n = PyVectorcall_NARGS(nargsf), nkw = kwnames ? PyTuple_GET_SIZE(kwnames) : 0;
   PyObject *v[9] = {nullptr};
-  bool usual = c->address && n <= shape.total;
+  usual = c->address && n <= shape.total;
   for (Py_ssize_t i = 0; usual && i < n; ++i) v[i] = args[i];
   for (Py_ssize_t k = 0; usual && k < nkw; ++k) {
     int at = 0;
@@ -238,19 +245,63 @@ PyObject *call(PyObject *self, PyObject *const *args, size_t nargsf, PyObject *k
     else v[at] = args[n + k];
   }
   int rc = 0;
-  if (usual && direct(c, v, &rc)) {
-    if (rc == 0) Py_RETURN_NONE;
-    PyObject *check = PyDict_GetItemWithError(c->globals, s_check), *code_ = check ? PyLong_FromLong(rc) : nullptr;
-    if (!code_) {
-      if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, "the binding's _check is gone");
-      return nullptr;
-    }
-    PyObject *none = PyObject_CallOneArg(check, code_);   // raises
-    Py_DECREF(code_);
-    return none;
+  usual = usual && direct(c, v, &rc);
+  if (!usual) {
+    PyErr_Clear();   // (what the function finds wrong itself it says itself)
+    return nullptr;
   }
-  PyErr_Clear();   // (what the function finds wrong itself it says itself)
-  return PyObject_Vectorcall(c->function, args, nargsf & ~PY_VECTORCALL_ARGUMENTS_OFFSET, kwnames);
+  if (rc == 0) Py_RETURN_NONE;
+  PyObject *check = PyDict_GetItemWithError(c->globals, s_check), *code_ = check ? PyLong_FromLong(rc) : nullptr;
+  if (!code_) {
+    if (!PyErr_Occurred()) PyErr_SetString(PyExc_RuntimeError, "the binding's _check is gone");
+    return nullptr;
+  }
+  PyObject *none = PyObject_CallOneArg(check, code_);   // raises
+  Py_DECREF(code_);
+  return none;
+}
+
+PyObject *call(PyObject *self, PyObject *const *args, size_t nargsf, PyObject *kwnames) {
+  bool usual;
+  PyObject *result = call_direct((Call *)self, args, nargsf, kwnames, usual);
+  return usual ? result : PyObject_Vectorcall(((Call *)self)->function, args, nargsf & ~PY_VECTORCALL_ARGUMENTS_OFFSET, kwnames);
+}
+
+// Where the interpreter enters a function that is served; its Call is an attribute of the function.
+vectorcallfunc g_interpret;   // where it enters any other
+PyObject *function_call(PyObject *self, PyObject *const *args, size_t nargsf, PyObject *kwnames) {
+  const PyFunctionObject *f = (PyFunctionObject *)self;
+  Call *c = f->func_dict ? (Call *)PyDict_GetItemWithError(f->func_dict, s_direct) : nullptr;
+  if (c && Py_TYPE(c) == &CallType && f->func_code == c->body && f->func_defaults == c->defaults) {   // (no other body given)
+    bool usual;
+    Py_INCREF(c);
+    PyObject *result = call_direct(c, args, nargsf, kwnames, usual);
+    Py_DECREF(c);
+    if (usual) return result;
+  }
+  return g_interpret(self, args, nargsf, kwnames);
+}
+PyObject *call_serve(PyObject *self, PyObject *function) {
+  if (!PyFunction_Check(function)) {
+    PyErr_SetString(PyExc_TypeError, "not a Python function");
+    return nullptr;
+  }
+  PyFunctionObject *f = (PyFunctionObject *)function;
+  Call *c = (Call *)self;
+  if (PyObject_SetAttr(function, s_direct, self) < 0) return nullptr;
+  Py_XINCREF(f->func_code);
+  Py_XSETREF(c->body, f->func_code);
+  Py_XINCREF(f->func_defaults);
+  Py_XSETREF(c->defaults, f->func_defaults);
+  if (f->vectorcall != function_call) {
+    g_interpret = f->vectorcall;
+#if PY_VERSION_HEX >= 0x030c0000
+    PyFunction_SetVectorcall(f, function_call);
+#else
+    f->vectorcall = function_call;
+#endif
+  }
+  Py_RETURN_NONE;
 }
 
 int call_init(PyObject *self, PyObject *args, PyObject *) {
@@ -279,6 +330,8 @@ int call_traverse(PyObject *self, visitproc visit, void *arg) {
   Py_VISIT(c->function);
   Py_VISIT(c->globals);
   Py_VISIT(c->tensor);
+  Py_VISIT(c->body);
+  Py_VISIT(c->defaults);
   return 0;
 }
 int call_clear(PyObject *self) {
@@ -287,6 +340,8 @@ int call_clear(PyObject *self) {
   Py_CLEAR(c->function);
   Py_CLEAR(c->globals);
   Py_CLEAR(c->tensor);
+  Py_CLEAR(c->body);
+  Py_CLEAR(c->defaults);
   return 0;
 }
 void call_dealloc(PyObject *self) {
@@ -294,14 +349,6 @@ void call_dealloc(PyObject *self) {
   call_clear(self);
   Py_TYPE(self)->tp_free(self);
 }
-// name, documentation and signature are those of the function
-PyObject *call_getattr(PyObject *self, PyObject *name) {
-  PyObject *own = PyObject_GenericGetAttr(self, name);
-  if (own || !PyErr_ExceptionMatches(PyExc_AttributeError) || !((Call *)self)->function) return own;
-  PyErr_Clear();
-  return PyObject_GetAttr(((Call *)self)->function, name);
-}
-PyObject *call_doc(PyObject *self, void *) { return PyObject_GetAttrString(((Call *)self)->function, "__doc__"); }
 PyObject *call_get_address(PyObject *self, void *) { return PyLong_FromVoidPtr(((Call *)self)->address); }
 int call_set_address(PyObject *self, PyObject *value, void *) {
   void *p = value ? PyLong_AsVoidPtr(value) : nullptr;
@@ -309,9 +356,8 @@ int call_set_address(PyObject *self, PyObject *value, void *) {
   ((Call *)self)->address = p;
   return 0;
 }
-PyGetSetDef call_getset[] = {{"__doc__", call_doc, nullptr, nullptr, nullptr}, {"address", call_get_address, call_set_address, nullptr, nullptr}, {nullptr}};
-PyMemberDef call_members[] = {{"__wrapped__", T_OBJECT_EX, offsetof(Call, function), READONLY, nullptr}, {nullptr}};
-PyTypeObject CallType = {PyVarObject_HEAD_INIT(nullptr, 0) "_call.Call"};
+PyGetSetDef call_getset[] = {{"address", call_get_address, call_set_address, nullptr, nullptr}, {nullptr}};
+PyMethodDef call_methods[] = {{"serve", call_serve, METH_O, "Calls of a function go this way first."}, {nullptr}};
 
 PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_call", nullptr, -1, nullptr};
 
@@ -330,20 +376,20 @@ PyMODINIT_FUNC PyInit__call() {
   CallType.tp_traverse = call_traverse;
   CallType.tp_clear = call_clear;
   CallType.tp_dealloc = call_dealloc;
-  CallType.tp_getattro = call_getattr;
   CallType.tp_getset = call_getset;
-  CallType.tp_members = call_members;
+  CallType.tp_methods = call_methods;
   if (PyType_Ready(&DescType) < 0 || PyType_Ready(&CallType) < 0) return nullptr;
   for (int k = 0; k < KINDS; ++k)
     for (int i = 0; i < kShapes[k].total; ++i)
       if (!g_params[k][i] && !(g_params[k][i] = PyUnicode_InternFromString(kShapes[k].params[i]))) return nullptr;
-  struct { PyObject **s; const char *text; } names[] = {{&s_desc, "_desc"}, {&s_raw_stream, "_raw_stream"}, {&s_data_ptr, "data_ptr"}, {&s_numel, "numel"},
+  struct { PyObject **s; const char *text; } names[] = {{&s_direct, "_direct"}, {&s_desc, "_desc"}, {&s_raw_stream, "_raw_stream"}, {&s_data_ptr, "data_ptr"}, {&s_numel, "numel"},
                                                         {&s_check, "_check"}, {&s_unary, "UNARY_CODE"}, {&s_binary, "BINARY_CODE"}, {&s_reduce, "REDUCE_CODE"},
                                                         {&s_dtype, "DTYPE_CODE"}};
   for (auto &e : names)
     if (!*e.s && !(*e.s = PyUnicode_InternFromString(e.text))) return nullptr;
   PyObject *m = PyModule_Create(&module_def);
   if (!m) return nullptr;
+  if (PyModule_AddIntConstant(m, "INTERFACE", kInterface) < 0) return nullptr;
   Py_INCREF(&DescType);
   Py_INCREF(&CallType);
   if (PyModule_AddObject(m, "Desc", (PyObject *)&DescType) < 0 || PyModule_AddObject(m, "Call", (PyObject *)&CallType) < 0) return nullptr;

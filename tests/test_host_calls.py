@@ -1,7 +1,13 @@
 """The binding's direct calls hand the C ABI what its own functions hand it, and leave every call in another
 form, and every error, to them (no GPU needed: a callback stands in for the library)."""
+import copy
 import ctypes as C
 import inspect
+import os
+import pickle
+import subprocess
+import sys
+import weakref
 
 import pytest
 
@@ -140,3 +146,54 @@ def test_names_and_signatures_stay():
     for name in C_ARGS:
         f = getattr(ocn, name)
         assert f.__name__ == name and inspect.signature(f) == inspect.signature(f.__wrapped__) and f.__doc__ == f.__wrapped__.__doc__
+
+
+def test_the_public_names_stay_functions():
+    """What a program may do with a function, it may do with these: copy and pickle them by name, refer to them weakly,
+    keep attributes on them, make methods of them and give them another body."""
+    for name in C_ARGS:
+        f = getattr(ocn, name)
+        assert inspect.isfunction(f) and pickle.loads(pickle.dumps(f)) is f and copy.deepcopy(f) is f and weakref.ref(f)() is f
+        f.note = 1
+        assert f.note == 1
+        del f.note
+
+    class Holder:
+        method = ocn.unary
+
+    assert Holder().method.__self__ is not None
+
+
+def test_public_functions_go_to_the_library_directly(monkeypatch):
+    """... and without the interpreter's share, unless they have been given another body."""
+    record = []
+    stand_in = C.CFUNCTYPE(C.c_int, *C_ARGS["unary"])(lambda *a: record.append(_seen(a)) or 0)
+    monkeypatch.setattr(binding, "_raw_stream", (lambda device: 0x5000 + device, lambda: 3))
+    monkeypatch.setattr(binding._direct["unary"], "address", C.cast(stand_in, P).value)
+    monkeypatch.setattr(binding, "_ocn_unary", lambda *a: record.append("interpreter") or 0)
+    args = _usual()["unary"]
+    ocn.unary(*args)
+    ocn.unary(args[0], a=args[1], out=args[2], stream=5)
+    assert [r[-1] for r in record] == [0x5003, 5]
+    with pytest.raises(TypeError):
+        ocn.unary(*args, no_such=1)
+    own = ocn.unary.__code__
+    try:
+        ocn.unary.__code__ = _another.__code__
+        assert ocn.unary(*args) == ("another", "sin")
+    finally:
+        ocn.unary.__code__ = own
+    assert len(record) == 2
+
+
+def _another(op, a, out, flags=0, stream=None):
+    return "another", op
+
+
+def test_a_module_from_other_sources_is_left_alone():
+    code = ("import sys, types, inspect; sys.modules['paper_1810_08723_amd._call'] = types.ModuleType('_call')\n"
+            "import paper_1810_08723_amd as ocn\n"
+            "from paper_1810_08723_amd import binding\n"
+            "assert binding._call is None and not binding._direct and not hasattr(ocn.unary, '__wrapped__')\n"
+            "ocn.Tensor(4096, 'float', (2,), (4,)).desc()")
+    subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), check=True, timeout=300)
