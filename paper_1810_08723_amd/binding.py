@@ -82,7 +82,7 @@ _lib: Optional[C.CDLL] = None
 # by themselves where that module has not been built for this interpreter, or from other sources.
 try:
     from . import _call
-    if getattr(_call, "INTERFACE", 0) != 1:
+    if getattr(_call, "INTERFACE", 0) != 2:
         _call = None
 except ImportError:
     _call = None
@@ -160,7 +160,7 @@ class Tensor:
     # The C struct is built at the first call that takes the tensor and dropped when a field is
     # assigned (the library never writes to it).  _ref: the struct by reference, as the calls take it.
     _ref = None
-    _desc = None     # ... the same struct for the calls of csrc/pycall.cpp
+    _desc = None     # the memory it lies on, where the calls of csrc/pycall.cpp read it
 
     def __init__(self, base, dtype, sizes, strides, offset=0, device=0, keepalive=None, byteswapped=False):
         self.__dict__.update(base=base, dtype=dtype, sizes=sizes, strides=strides, offset=offset, device=device,
@@ -179,7 +179,10 @@ class Tensor:
         return Tensor(storage.data_ptr(), dtype, tuple(sizes), tuple(strides), offset, dev, storage, byteswapped)
 
     def _make_ref(self):
-        t = OcnTensor()
+        # kept only where the sizes and strides cannot change behind the tensor's back
+        keep = type(self.sizes) is tuple and type(self.strides) is tuple
+        memory = _call.Desc() if keep and _call is not None else None
+        t = OcnTensor() if memory is None else OcnTensor.from_buffer(memory)
         t.base = self.base
         t.offset = self.offset
         t.dtype = DTYPE_CODE[self.dtype] if isinstance(self.dtype, str) else int(self.dtype)
@@ -190,11 +193,10 @@ class Tensor:
         t.device = self.device
         t.byteswapped = 1 if self.byteswapped else 0
         ref = C.byref(t)
-        # kept only where the sizes and strides cannot change behind the tensor's back
-        if type(self.sizes) is tuple and type(self.strides) is tuple:
+        if keep:
             self.__dict__["_ref"] = ref
-            if _call is not None:
-                self.__dict__["_desc"] = _call.Desc(bytes(t))
+            if memory is not None:
+                self.__dict__["_desc"] = memory
         return ref
 
     def desc(self) -> OcnTensor:

@@ -19,7 +19,7 @@
 namespace {
 
 // what the binding expects of this module, counted up with every change to it (binding.py has the same number)
-constexpr int kInterface = 1;
+constexpr int kInterface = 2;
 
 enum Kind { UNARY, BINARY, CAST_COPY, REDUCE, BINARY_REDUCE, INDEX_OFFSETS, MASK_OFFSETS, GATHER, SCATTER, KINDS };
 // the parameters of each, in order; the last one is the stream, and those from `needed` on may be left out
@@ -38,26 +38,17 @@ const Shape kShapes[KINDS] = {
 PyObject *g_params[KINDS][9];   // the same, interned
 PyObject *s_direct, *s_desc, *s_raw_stream, *s_data_ptr, *s_numel, *s_check, *s_unary, *s_binary, *s_reduce, *s_dtype;
 
-// ---- a descriptor that belongs to a Tensor ------------------------------------------------
+// ---- a descriptor that belongs to a Tensor: memory that its ctypes structure lies on -------
 struct Desc {
   PyObject_HEAD
   ocn_tensor t;
 };
 PyTypeObject DescType = {PyVarObject_HEAD_INIT(nullptr, 0) "_call.Desc"};
 
-PyObject *desc_new(PyTypeObject *type, PyObject *args, PyObject *) {
-  Py_buffer view;
-  if (!PyArg_ParseTuple(args, "y*", &view)) return nullptr;
-  if (view.len != (Py_ssize_t)sizeof(ocn_tensor)) {
-    PyBuffer_Release(&view);
-    PyErr_SetString(PyExc_ValueError, "not a descriptor");
-    return nullptr;
-  }
-  Desc *d = (Desc *)type->tp_alloc(type, 0);
-  if (d) std::memcpy(&d->t, view.buf, sizeof(ocn_tensor));
-  PyBuffer_Release(&view);
-  return (PyObject *)d;
+int desc_buffer(PyObject *self, Py_buffer *view, int flags) {
+  return PyBuffer_FillInfo(view, self, &((Desc *)self)->t, (Py_ssize_t)sizeof(ocn_tensor), 0, flags);
 }
+PyBufferProcs desc_as_buffer = {desc_buffer, nullptr};
 
 // ---- a call -------------------------------------------------------------------------------
 struct Call {
@@ -366,7 +357,8 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_call", nullptr, -1, nullptr};
 PyMODINIT_FUNC PyInit__call() {
   DescType.tp_basicsize = sizeof(Desc);
   DescType.tp_flags = Py_TPFLAGS_DEFAULT;
-  DescType.tp_new = desc_new;
+  DescType.tp_new = PyType_GenericNew;
+  DescType.tp_as_buffer = &desc_as_buffer;
   CallType.tp_basicsize = sizeof(Call);
   CallType.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_GC | Py_TPFLAGS_HAVE_VECTORCALL;
   CallType.tp_vectorcall_offset = offsetof(Call, vectorcall);

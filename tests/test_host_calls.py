@@ -197,3 +197,19 @@ def test_a_module_from_other_sources_is_left_alone():
             "assert binding._call is None and not binding._direct and not hasattr(ocn.unary, '__wrapped__')\n"
             "ocn.Tensor(4096, 'float', (2,), (4,)).desc()")
     subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), check=True, timeout=300)
+
+
+@pytest.mark.parametrize("name", sorted(C_ARGS))
+def test_what_desc_returns_is_what_calls_read(name):
+    """An edit of the struct reaches the next call, whether it goes to the library directly or through the function."""
+    args = _usual()[name]
+    call, record, fallback, _keep = _direct(name)
+    call(*args)
+    for t in (x for x in args if isinstance(x, ocn.Tensor)):
+        t.desc().offset += 1 << 20
+        t.desc().size[0] = 3
+        assert (t.desc().offset, t._ref._obj.size[0]) == (t.offset + (1 << 20), 3)
+    call(*args)
+    structs = [[binding.OcnTensor.from_buffer_copy(x) for x in r if isinstance(x, bytes)] for r in record]
+    assert not fallback and [t.offset for t in structs[1]] == [t.offset + (1 << 20) for t in structs[0]]
+    assert all(t.size[0] == 3 for t in structs[1])
