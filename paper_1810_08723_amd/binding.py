@@ -82,7 +82,7 @@ _lib: Optional[C.CDLL] = None
 # by themselves where that module has not been built for this interpreter, or from other sources.
 try:
     from . import _call
-    if getattr(_call, "INTERFACE", 0) != 2:
+    if getattr(_call, "INTERFACE", 0) != 3:
         _call = None
 except ImportError:
     _call = None
@@ -181,7 +181,14 @@ class Tensor:
     def _make_ref(self):
         # kept only where the sizes and strides cannot change behind the tensor's back
         keep = type(self.sizes) is tuple and type(self.strides) is tuple
-        memory = _call.Desc() if keep and _call is not None else None
+        memory = None
+        if keep and _call is not None and type(self) is Tensor:
+            memory = self._desc or _call.describe(self.__dict__, DTYPE_CODE)
+            if memory is not None:
+                ref = C.byref(OcnTensor.from_buffer(memory))
+                self.__dict__.update(_ref=ref, _desc=memory)
+                return ref
+            memory = _call.Desc()    # (fields in another form)
         t = OcnTensor() if memory is None else OcnTensor.from_buffer(memory)
         t.base = self.base
         t.offset = self.offset

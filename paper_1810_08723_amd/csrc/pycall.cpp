@@ -1,5 +1,5 @@
 // The calls of the Python binding without its interpreter work: callables that take the arguments of
-// the binding's own functions in their usual form (a Tensor whose descriptor is built, an operation by its
+// the binding's own functions in their usual form (a Tensor of plain fields, an operation by its
 // name, axes as plain ints, the current stream) straight to the C ABI, and hand every other call, and
 // every error, to the function they stand for.  The public names stay the Python functions that they
 // are, for whatever a program does with a function besides calling it: what serve() changes is where
@@ -19,7 +19,7 @@
 namespace {
 
 // what the binding expects of this module, counted up with every change to it (binding.py has the same number)
-constexpr int kInterface = 2;
+constexpr int kInterface = 3;
 
 enum Kind { UNARY, BINARY, CAST_COPY, REDUCE, BINARY_REDUCE, INDEX_OFFSETS, MASK_OFFSETS, GATHER, SCATTER, KINDS };
 // the parameters of each, in order; the last one is the stream, and those from `needed` on may be left out
@@ -37,6 +37,7 @@ const Shape kShapes[KINDS] = {
 };
 PyObject *g_params[KINDS][9];   // the same, interned
 PyObject *s_direct, *s_desc, *s_raw_stream, *s_data_ptr, *s_numel, *s_check, *s_unary, *s_binary, *s_reduce, *s_dtype;
+PyObject *s_ref, *s_base, *s_dtype_field, *s_sizes, *s_strides, *s_offset, *s_device, *s_byteswapped;   // of a Tensor
 
 // ---- a descriptor that belongs to a Tensor: memory that its ctypes structure lies on -------
 struct Desc {
@@ -49,6 +50,69 @@ int desc_buffer(PyObject *self, Py_buffer *view, int flags) {
   return PyBuffer_FillInfo(view, self, &((Desc *)self)->t, (Py_ssize_t)sizeof(ocn_tensor), 0, flags);
 }
 PyBufferProcs desc_as_buffer = {desc_buffer, nullptr};
+
+bool plain_int(PyObject *o, long long *out) {
+  if (!PyLong_CheckExact(o)) return false;
+  int over = 0;
+  *out = PyLong_AsLongLongAndOverflow(o, &over);
+  return over == 0;
+}
+
+// The descriptor of a Tensor out of its fields (its dictionary), as the binding builds it; null, with no error set,
+// where they are not plain values within the struct's ranges and the binding has its own say.  (Building it there,
+// field by field through ctypes, took three quarters of a call with new tensors: a binary call with three of them
+// 8.3 us without this module, 10 with one that only served built ones, 2.5 so; with a library that does nothing.)
+Desc *describe(PyObject *fields, PyObject *dtypes) {
+  PyObject *sizes = PyDict_GetItemWithError(fields, s_sizes), *strides = PyDict_GetItemWithError(fields, s_strides);
+  if (!sizes || !strides || !PyTuple_CheckExact(sizes) || !PyTuple_CheckExact(strides)) return nullptr;   // (a list may change: never kept)
+  const Py_ssize_t ndim = PyTuple_GET_SIZE(sizes);
+  if (ndim > OCN_MAX_DIMS || PyTuple_GET_SIZE(strides) < ndim) return nullptr;
+  ocn_tensor t;
+  std::memset(&t, 0, sizeof t);
+  long long x;
+  auto field = [&](PyObject *name) {
+    PyObject *o = PyDict_GetItemWithError(fields, name);
+    return o && plain_int(o, &x);
+  };
+  PyObject *base = PyDict_GetItemWithError(fields, s_base);
+  if (!base || !PyLong_CheckExact(base)) return nullptr;
+  t.base = (void *)PyLong_AsUnsignedLongLong(base);
+  if (PyErr_Occurred()) {   // (negative, or more than an address)
+    PyErr_Clear();
+    return nullptr;
+  }
+  if (!field(s_offset)) return nullptr;
+  t.offset = x;
+  PyObject *dtype = PyDict_GetItemWithError(fields, s_dtype_field);
+  PyObject *code = dtype && PyUnicode_CheckExact(dtype) ? PyDict_GetItemWithError(dtypes, dtype) : nullptr;
+  if (!code || !plain_int(code, &x)) return nullptr;
+  t.dtype = (int32_t)x;
+  t.ndim = (int32_t)ndim;
+  for (Py_ssize_t d = 0; d < ndim; ++d) {
+    if (!plain_int(PyTuple_GET_ITEM(sizes, d), &x)) return nullptr;
+    t.size[d] = x;
+    if (!plain_int(PyTuple_GET_ITEM(strides, d), &x)) return nullptr;
+    t.stride[d] = x;
+  }
+  if (!field(s_device) || x != (int32_t)x) return nullptr;
+  t.device = (int32_t)x;
+  PyObject *swapped = PyDict_GetItemWithError(fields, s_byteswapped);
+  if (swapped != Py_True && swapped != Py_False) return nullptr;
+  t.byteswapped = swapped == Py_True;
+  Desc *d = PyObject_New(Desc, &DescType);
+  if (!d) PyErr_Clear();
+  else d->t = t;
+  return d;
+}
+PyObject *module_describe(PyObject *, PyObject *const *args, Py_ssize_t n) {
+  if (n != 2 || !PyDict_CheckExact(args[0]) || !PyDict_CheckExact(args[1])) {
+    PyErr_SetString(PyExc_TypeError, "describe(fields, dtypes)");
+    return nullptr;
+  }
+  Desc *d = describe(args[0], args[1]);
+  if (!d) Py_RETURN_NONE;
+  return (PyObject *)d;
+}
 
 // ---- a call -------------------------------------------------------------------------------
 struct Call {
@@ -64,14 +128,22 @@ struct Call {
 
 PyTypeObject CallType = {PyVarObject_HEAD_INIT(nullptr, 0) "_call.Call"};
 
-// the descriptor of an argument, or null (no error set): not a plain Tensor, or not built yet
+// the descriptor of an argument, built and kept by the first call that takes the tensor, or null (no error set): not a
+// plain Tensor, or one with fields in another form
 const ocn_tensor *descriptor(const Call *c, PyObject *o) {
   if (Py_TYPE(o) != c->tensor) return nullptr;
   PyObject **dict = _PyObject_GetDictPtr(o);
   if (!dict || !*dict) return nullptr;
   PyObject *d = PyDict_GetItemWithError(*dict, s_desc);
-  if (!d || Py_TYPE(d) != &DescType) return nullptr;
-  return &((Desc *)d)->t;
+  if (d) return Py_TYPE(d) == &DescType ? &((Desc *)d)->t : nullptr;
+  PyObject *dtypes = PyDict_GetItemWithError(c->globals, s_dtype);
+  if (!dtypes || !PyDict_CheckExact(dtypes) || PyDict_GetItemWithError(*dict, s_ref)) return nullptr;
+  Desc *made = describe(*dict, dtypes);
+  if (!made) return nullptr;
+  const bool kept = PyDict_SetItem(*dict, s_desc, (PyObject *)made) == 0;
+  Py_DECREF(made);
+  if (!kept) PyErr_Clear();
+  return kept ? &made->t : nullptr;
 }
 // a code out of one of the binding's dictionaries (by the name of a global)
 bool code(const Call *c, PyObject *table, PyObject *name, int *out) {
@@ -81,12 +153,6 @@ bool code(const Call *c, PyObject *table, PyObject *name, int *out) {
   if (!v || !PyLong_CheckExact(v)) return false;
   *out = (int)PyLong_AsLong(v);
   return true;
-}
-bool plain_int(PyObject *o, long long *out) {
-  if (!PyLong_CheckExact(o)) return false;
-  int over = 0;
-  *out = PyLong_AsLongLongAndOverflow(o, &over);
-  return over == 0;
 }
 bool plain_ints(PyObject *o, int most, long long *out, int *n) {
   if (!PyList_CheckExact(o) && !PyTuple_CheckExact(o)) return false;
@@ -129,6 +195,9 @@ bool direct(const Call *c, PyObject *const *v, int *rc) {
   const Shape &shape = kShapes[c->kind];
   for (int i = 0; i < shape.needed; ++i)
     if (!v[i]) return false;
+  // (a workspace that the function is to find: nothing else is looked at)
+  const int memory = c->kind == REDUCE || c->kind == MASK_OFFSETS ? 4 : c->kind == BINARY_REDUCE ? 7 : -1;
+  if (memory >= 0 && (!v[memory] || v[memory] == Py_None)) return false;
   // (copied while the interpreter is ours: another thread may replace a Tensor's descriptor meanwhile)
   ocn_tensor t[3];
   auto take = [&](int slot, int arg) {
@@ -157,7 +226,7 @@ bool direct(const Call *c, PyObject *const *v, int *rc) {
     return true;
   };
   auto find_flags = [&](PyObject *o) { return !o || (plain_int(o, &flags) && flags >= 0 && flags <= 0xffffffffll); };
-  auto find_memory = [&](PyObject *o) { return o && o != Py_None && method_int(o, s_data_ptr, &p) && method_int(o, s_numel, &n); };
+  auto find_memory = [&](PyObject *o) { return method_int(o, s_data_ptr, &p) && method_int(o, s_numel, &n); };
   switch (c->kind) {
     case UNARY: {
       if (!code(c, s_unary, v[0], &op) || !take(0, 1) || !take(1, 2) || !find_flags(v[3]) || !find_stream()) return false;
@@ -350,7 +419,8 @@ int call_set_address(PyObject *self, PyObject *value, void *) {
 PyGetSetDef call_getset[] = {{"address", call_get_address, call_set_address, nullptr, nullptr}, {nullptr}};
 PyMethodDef call_methods[] = {{"serve", call_serve, METH_O, "Calls of a function go this way first."}, {nullptr}};
 
-PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_call", nullptr, -1, nullptr};
+PyMethodDef module_methods[] = {{"describe", (PyCFunction)(void (*)())module_describe, METH_FASTCALL, "The descriptor of a Tensor's fields, or None."}, {nullptr}};
+PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_call", nullptr, -1, module_methods};
 
 }  // namespace
 
@@ -376,7 +446,8 @@ PyMODINIT_FUNC PyInit__call() {
       if (!g_params[k][i] && !(g_params[k][i] = PyUnicode_InternFromString(kShapes[k].params[i]))) return nullptr;
   struct { PyObject **s; const char *text; } names[] = {{&s_direct, "_direct"}, {&s_desc, "_desc"}, {&s_raw_stream, "_raw_stream"}, {&s_data_ptr, "data_ptr"}, {&s_numel, "numel"},
                                                         {&s_check, "_check"}, {&s_unary, "UNARY_CODE"}, {&s_binary, "BINARY_CODE"}, {&s_reduce, "REDUCE_CODE"},
-                                                        {&s_dtype, "DTYPE_CODE"}};
+                                                        {&s_dtype, "DTYPE_CODE"}, {&s_ref, "_ref"}, {&s_base, "base"}, {&s_dtype_field, "dtype"}, {&s_sizes, "sizes"},
+                                                        {&s_strides, "strides"}, {&s_offset, "offset"}, {&s_device, "device"}, {&s_byteswapped, "byteswapped"}};
   for (auto &e : names)
     if (!*e.s && !(*e.s = PyUnicode_InternFromString(e.text))) return nullptr;
   PyObject *m = PyModule_Create(&module_def);

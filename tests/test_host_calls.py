@@ -111,12 +111,14 @@ def test_other_forms_go_to_the_function(name):
         at = next(i for i, v in enumerate(args) if isinstance(v, ocn.Tensor))
         return args[:at] + [x] + args[at + 1:]
 
-    fresh = ocn.Tensor(1 << 40, "float", (4, 8), (32, 4))                     # no descriptor yet
     listed = ocn.Tensor(1 << 40, "float", [4, 8], [32, 4])
-    listed.desc()                                                              # ... never one that is kept
-    assigned = _tensors()[0]
-    assigned.offset = 64                                                       # ... dropped
-    forms = [with_first_tensor(x) for x in (fresh, listed, assigned, Other(1 << 40, "float", (4, 8), (32, 4)), None)]
+    listed.desc()                                                              # (never one that is kept)
+    plain = dict(base=1 << 40, dtype="float", sizes=(4, 8), strides=(32, 4))
+    odd = [dict(base=None), dict(base=-1), dict(base=1 << 64), dict(base=1.0), dict(dtype=10), dict(dtype="no such"), dict(sizes=(4, 8.0)), dict(sizes=(4, True)),
+           dict(sizes=(1,) * 9, strides=(4,) * 9), dict(strides=(32,)), dict(strides=(1 << 63, 4)), dict(offset=None), dict(offset=1 << 63), dict(device=1 << 31),
+           dict(device="0"), dict(byteswapped=1), dict(byteswapped=None)]
+    forms = [with_first_tensor(x) for x in (listed, Other(1 << 40, "float", (4, 8), (32, 4)), None)]
+    forms += [with_first_tensor(ocn.Tensor(**dict(plain, **x))) for x in odd]
     forms += [args[:-1], args + [None] * 9]
     if isinstance(args[0], str):
         forms += [["no such"] + args[1:], [3] + args[1:]]
@@ -213,3 +215,28 @@ def test_what_desc_returns_is_what_calls_read(name):
     structs = [[binding.OcnTensor.from_buffer_copy(x) for x in r if isinstance(x, bytes)] for r in record]
     assert not fallback and [t.offset for t in structs[1]] == [t.offset + (1 << 20) for t in structs[0]]
     assert all(t.size[0] == 3 for t in structs[1])
+
+
+@pytest.mark.parametrize("name", sorted(C_ARGS))
+def test_new_and_changed_tensors_go_directly_too(name, monkeypatch):
+    """Their descriptor is the one that the binding builds, and is kept as that one is."""
+    args = list(_usual()[name])
+    call, record, fallback, _keep = _direct(name)
+    for form in (dict(base=(1 << 64) - 16, dtype="cdouble", sizes=(5, 0, 7), strides=(-112, 1 << 62, 16), offset=-48, device=3, byteswapped=True),
+                 dict(base=1 << 40, dtype="bool", sizes=(), strides=()), dict(base=0, dtype="half", sizes=(2,) * 8, strides=(2,) * 9, offset=6)):
+        new = [ocn.Tensor(**form) for x in args if isinstance(x, ocn.Tensor)]
+        if name == "mask_offsets":
+            args[1] = [8] * 8
+        put = iter(new)
+        call(*[next(put) if isinstance(x, ocn.Tensor) else x for x in args])
+        seen = [x for x in record[-1] if isinstance(x, bytes)]
+        with monkeypatch.context() as without:
+            without.setattr(binding, "_call", None)
+            plain = bytes(ocn.Tensor(**form).desc())
+        assert not fallback and seen == [plain] * len(new)
+        assert all(bytes(t.desc()) == seen[0] and t.desc() is t.desc() for t in new)
+        new[0].offset = 64
+        put = iter(new)
+        call(*[next(put) if isinstance(x, ocn.Tensor) else x for x in args])
+        seen = [binding.OcnTensor.from_buffer_copy(x) for x in record[-1] if isinstance(x, bytes)]
+        assert not fallback and [t.offset for t in seen] == [64] + [form.get("offset", 0)] * (len(new) - 1)
