@@ -7,6 +7,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -15,7 +16,8 @@ CSRC = os.path.join(HERE, "csrc")
 _TAG = os.environ.get("OCN_BUILD_TAG", "")
 OBJ = os.path.join(HERE, "_build" + ("_" + _TAG if _TAG else ""))
 LIB = os.path.join(HERE, "libocn" + ("_" + _TAG if _TAG else "") + ".so")
-CALL = os.path.join(HERE, "_call.so")
+# the binding's call module, under a name that only the interpreter it is built for looks for
+CALL = os.path.join(HERE, "_call" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Floating-point contraction stays off: a*b+c must round twice, as in the definition of each
@@ -65,13 +67,22 @@ def _compile(src: str, force: bool = True) -> str:
 
 
 def build_call() -> None:
-    """The binding's call module (host code only, for the interpreter that builds it)."""
-    import sysconfig
+    """The binding's call module (host code only, for the interpreter that builds it).  Without it the binding goes
+    through ctypes, so that the build goes on where it cannot be built; an older one does not stay behind."""
+    if _TAG:    # (an experimental library; the binding and its module stay as they are)
+        return
+    for old in (CALL, os.path.join(HERE, "_call.so")):    # (any interpreter would load the untagged name)
+        if os.path.exists(old):
+            os.remove(old)
     include = sysconfig.get_paths()["include"]
     if not os.path.exists(os.path.join(include, "Python.h")):
         sys.stderr.write("no Python headers: the binding goes through ctypes\n")
         return
-    subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + include, os.path.join(CSRC, "pycall.cpp"), "-o", CALL], check=True)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I" + include, os.path.join(CSRC, "pycall.cpp"), "-o", CALL]
+    try:
+        subprocess.run(cmd, check=True)
+    except (OSError, subprocess.CalledProcessError) as e:
+        sys.stderr.write(f"the call module was not built ({e}): the binding goes through ctypes\n")
 
 
 def build(jobs: int | None = None, force: bool = True) -> str:
