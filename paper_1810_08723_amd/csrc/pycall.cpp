@@ -327,11 +327,13 @@ PyObject *call(PyObject *self, PyObject *const *args, size_t nargsf, PyObject *k
   return usual ? result : PyObject_Vectorcall(((Call *)self)->function, args, nargsf & ~PY_VECTORCALL_ARGUMENTS_OFFSET, kwnames);
 }
 
-// Where the interpreter enters a function that is served; its Call is an attribute of the function.
+// Where the interpreter enters a function that is served; its Call is an attribute of the function.  A thread
+// that is profiled or traced sees the function's own frame.
 vectorcallfunc g_interpret;   // where it enters any other
 PyObject *function_call(PyObject *self, PyObject *const *args, size_t nargsf, PyObject *kwnames) {
   const PyFunctionObject *f = (PyFunctionObject *)self;
-  Call *c = f->func_dict ? (Call *)PyDict_GetItemWithError(f->func_dict, s_direct) : nullptr;
+  const PyThreadState *thread = PyThreadState_Get();
+  Call *c = f->func_dict && !thread->c_profilefunc && !thread->c_tracefunc ? (Call *)PyDict_GetItemWithError(f->func_dict, s_direct) : nullptr;
   if (c && Py_TYPE(c) == &CallType && f->func_code == c->body && f->func_defaults == c->defaults) {   // (no other body given)
     bool usual;
     Py_INCREF(c);

@@ -188,6 +188,23 @@ def test_public_functions_go_to_the_library_directly(monkeypatch):
     assert len(record) == 2
 
 
+@pytest.mark.parametrize("name", sorted(C_ARGS))
+@pytest.mark.parametrize("watch", (sys.setprofile, sys.settrace))
+def test_profilers_and_tracers_see_the_function(name, watch, monkeypatch):
+    """A program that is profiled or traced finds the call under the function's own name."""
+    stand_in = C.CFUNCTYPE(C.c_int, *C_ARGS[name])(lambda *a: 0)
+    monkeypatch.setattr(binding._direct[name], "address", C.cast(stand_in, P).value)
+    monkeypatch.setattr(binding, "_ocn_" + name, stand_in)
+    args, entered = _usual()[name], []
+    before = sys.getprofile() if watch is sys.setprofile else sys.gettrace()
+    watch(lambda frame, event, arg: entered.append(frame.f_code.co_name) if event == "call" else None)
+    try:
+        getattr(ocn, name)(*args, stream=5)
+    finally:
+        watch(before)
+    assert entered.count(name) == 1
+
+
 def _another(op, a, out, flags=0, stream=None):
     return "another", op
 
