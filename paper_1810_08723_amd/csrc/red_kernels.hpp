@@ -13,6 +13,7 @@
 //                       (with few columns a wavefront covers several rows at a time), the
 //                       wavefronts of a workgroup take interleaved rows and are combined
 //                       through LDS; row ranges can be split the same way.
+//   red_cols_bits_kernel  the same for any and all of bytes, sixteen columns of a lane in four registers
 //   red_generic_kernel  any layout and 64-bit extents: one output per lane, sequential fold.
 // No floating-point atomics anywhere: the grouping of addends is fixed by the launch
 // geometry, so results are reproducible bit for bit.
@@ -871,128 +872,97 @@ template <int S, int OP> OCN_HD constexpr bool cols_bits() {
   return dt_size(S) == 1 && (OP == R_ANY || OP == R_ALL || (S == DT_BOOL && (OP == R_MIN || OP == R_MAX)));
 }
 
+// What a lane of the column kernels takes: V columns (of elements of ES bytes) and rows r, r + rpw, ... below r1.
+struct ColsPlace {
+  int lane, wave, waves;            // waves: of the workgroup
+  uint32_t split, other;            // which split of the rows, which of the other kept dims' outputs
+  int lr, rpw;                      // its row among those that a wavefront takes at a time, and their number
+  int ncol, skip;                   // its columns; how many of the first are its neighbour's
+  int64_t col0, off_a, off_o;       // the first one, and the byte offsets of it in the input and the output
+  int64_t r, r1, per_wave;          // per_wave: rows of a wavefront
+};
+template <int ES, int V> OCN_DEV ColsPlace cols_place(KRedArgs &p) {
+  ColsPlace k;
+  const int tid = threadIdx.x;
+  k.lane = tid & (kWave - 1);
+  k.wave = tid / kWave;
+  k.waves = (int)blockDim.x / kWave;
+
+  // block -> (split, other kept dims, column block)
+  uint32_t b = blockIdx.x;
+  const uint32_t per_split = (uint32_t)(p.colblocks_div.d * (uint32_t)(p.nout / p.nc));
+  k.split = b / per_split;
+  b -= k.split * per_split;
+  k.other = rfastdiv(b, args_div(p.colblocks_div));
+  const uint32_t cb = b - k.other * p.colblocks_div.d;
+  // p.cpw lanes (a power of two) cover one row of columns; with fewer than 64 of them a
+  // wavefront takes 64 / cpw rows at a time
+  const int cpw_log2 = __ffs(p.cpw) - 1;
+  const int lc = k.lane & (p.cpw - 1);
+  k.lr = k.lane >> cpw_log2;
+  k.rpw = kWave >> cpw_log2;
+  k.col0 = ((int64_t)cb * p.cpw + lc) * V;
+  const int64_t left = p.nc - k.col0;
+  k.ncol = left >= V ? V : (left > 0 ? (int)left : 0);
+  // The lane with the last few columns takes a whole vector that ends with the last column: the
+  // first `skip` of its columns are its neighbour's and are dropped at the end.
+  k.skip = 0;
+  if (k.ncol > 0 && k.ncol < V && p.nc >= V) {
+    k.skip = V - k.ncol;
+    k.col0 -= k.skip;
+    k.ncol = V;
+  }
+
+  // offsets of the other kept dims (kept dim 0 is the column dim)
+  k.off_a = k.col0 * (int64_t)ES;
+  k.off_o = k.col0 * p.kso[0];
+  {
+    uint32_t o = k.other;
+    const int nkept = p.nkept;
+    for (int d = 1; d < nkept; ++d) {
+      const uint32_t q = (d == nkept - 1) ? 0u : rfastdiv(o, args_div(p.kdiv[d]));
+      const uint32_t i = o - q * p.kdiv[d].d;
+      o = q;
+      k.off_a += (int64_t)i * p.ksa[d];
+      k.off_o += (int64_t)i * p.kso[d];
+    }
+  }
+
+  const int64_t r0 = (int64_t)k.split * p.chunk;
+  k.r1 = r0 + p.chunk;
+  if (k.r1 > p.nredtot) k.r1 = p.nredtot;
+  // Each wavefront takes one contiguous run of the workgroup's rows (rpw rows at a time).
+  // Dealing the rows out in turn instead - wavefront w taking rows w, w + waves, ... - measured
+  // 10 % slower (fp32 column sums of [16384, 4096]: 46.2 against 41.5 us).
+  k.per_wave = (((k.r1 - r0) + k.waves - 1) / k.waves + k.rpw - 1) / k.rpw * k.rpw;
+  const int64_t w0 = r0 + (int64_t)k.wave * k.per_wave;   // this wavefront's rows: w0 .. r1 - 1
+  if (w0 + k.per_wave < k.r1) k.r1 = w0 + k.per_wave;
+  k.r = w0 + k.lr;
+  return k;
+}
 // SINGLE: one reduced dim, so that row r lies r strides further on (no index decomposition)
+template <bool SINGLE> OCN_DEV int64_t cols_row_offset(KRedArgs &p, int64_t r) {
+  if constexpr (SINGLE) return r * p.rsa[0];
+  else return reduced_offset(p, (uint32_t)r, 0);
+}
+
 template <int S, int OP, int V, bool NT, bool SINGLE>
 OCN_DEV void cols_body(KRedArgs &p, typename Reducer<S, OP>::A *lds) {
   using R = Reducer<S, OP>;
   using A = typename R::A;
   using St = storage_t<S>;
-  auto row_offset = [&](int64_t r) -> int64_t {
-    if constexpr (SINGLE) return r * p.rsa[0];
-    else return reduced_offset(p, (uint32_t)r, 0);
-  };
-  const int tid = threadIdx.x;
-  const int lane = tid & (kWave - 1);
-  const int wave = tid / kWave;
-  const int NW = (int)blockDim.x / kWave;
-
-  // block -> (split, other kept dims, column block)
-  uint32_t b = blockIdx.x;
-  const uint32_t per_split = (uint32_t)(p.colblocks_div.d * (uint32_t)(p.nout / p.nc));
-  const uint32_t s = b / per_split;
-  b -= s * per_split;
-  const uint32_t other = rfastdiv(b, args_div(p.colblocks_div));
-  const uint32_t cb = b - other * p.colblocks_div.d;
-  // p.cpw lanes (a power of two) cover one row of columns; with fewer than 64 of them a
-  // wavefront takes 64 / cpw rows at a time
-  const int cpw_log2 = __ffs(p.cpw) - 1;
-  const int lc = lane & (p.cpw - 1), lr = lane >> cpw_log2;
-  const int RPW = kWave >> cpw_log2;
-  int64_t col0 = ((int64_t)cb * p.cpw + lc) * V;
-  const int64_t left = p.nc - col0;
-  int ncol = left >= V ? V : (left > 0 ? (int)left : 0);
-  // The lane with the last few columns takes a whole vector that ends with the last column: the
-  // first `skip` of its columns are its neighbour's and are dropped at the end.
-  int skip = 0;
-  if (ncol > 0 && ncol < V && p.nc >= V) {
-    skip = V - ncol;
-    col0 -= skip;
-    ncol = V;
-  }
-
-  // offsets of the other kept dims (kept dim 0 is the column dim)
-  int64_t off_a = col0 * (int64_t)sizeof(St), off_o = col0 * p.kso[0];
-  {
-    uint32_t o = other;
-    const int nkept = p.nkept;
-    for (int k = 1; k < nkept; ++k) {
-      const uint32_t q = (k == nkept - 1) ? 0u : rfastdiv(o, args_div(p.kdiv[k]));
-      const uint32_t i = o - q * p.kdiv[k].d;
-      o = q;
-      off_a += (int64_t)i * p.ksa[k];
-      off_o += (int64_t)i * p.kso[k];
-    }
-  }
-
+  auto row_offset = [&](int64_t r) { return cols_row_offset<SINGLE>(p, r); };
+  const ColsPlace k0 = cols_place<(int)sizeof(St), V>(p);
+  const int lane = k0.lane, wave = k0.wave, NW = k0.waves, lr = k0.lr, RPW = k0.rpw, ncol = k0.ncol, skip = k0.skip;
+  const uint32_t s = k0.split, other = k0.other;
+  const int64_t col0 = k0.col0, off_a = k0.off_a, off_o = k0.off_o, r1 = k0.r1, per_wave = k0.per_wave;
+  int64_t r = k0.r;
   A acc[V];
 #pragma unroll
   for (int i = 0; i < V; ++i) acc[i] = R::identity();
-  const int64_t r0 = (int64_t)s * p.chunk;
-  int64_t r1 = r0 + p.chunk;
-  if (r1 > p.nredtot) r1 = p.nredtot;
-  using Bits = BitFold<S, OP>;
-  constexpr bool BITS = cols_bits<S, OP>() && V == 16;
-  constexpr int U = BITS ? 8 : 4;  // rows in flight per wavefront
+  constexpr int U = 4;  // rows in flight per wavefront
   struct alignas(sizeof(St) * V >= 16 ? 16 : sizeof(St) * V) Pk { St v[V]; };
-  // Each wavefront takes one contiguous run of the workgroup's rows (RPW rows at a time).
-  // Dealing the rows out in turn instead - wavefront w taking rows w, w + NW, ... - measured
-  // 10 % slower (fp32 column sums of [16384, 4096]: 46.2 against 41.5 us).
   const int RS = RPW;                // rows between two rows of the same lane
-  const int64_t per_wave = (((r1 - r0) + NW - 1) / NW + RPW - 1) / RPW * RPW;
-  const int64_t w0 = r0 + (int64_t)wave * per_wave;   // this wavefront's rows: w0 .. r1 - 1
-  if (w0 + per_wave < r1) r1 = w0 + per_wave;
-  int64_t r = w0 + lr;
-  // Any and all of bytes: a lane's sixteen columns in four registers, which also meet as such (sixteen
-  // accumulators of a byte each took a shuffle and a round through LDS apiece: bool any over the rows of
-  // [3840, 72] 19.2 -> 8.3 us, of [222, 2382] 10.7 -> 8.2).
-  if constexpr (BITS) {
-    if (p.nc >= V) {   // (whole vectors of columns, for all lanes alike)
-      uint32_t bits[4] = {Bits::kStart, Bits::kStart, Bits::kStart, Bits::kStart};
-      auto add_row = [&](const Pk &pk) {
-        uint32_t w[4];
-        __builtin_memcpy(w, &pk, 16);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) bits[k] = Bits::add(bits[k], w[k]);
-      };
-      if (ncol == V) {
-        for (; r + (int64_t)(U - 1) * RS < r1; r += RS * U) {
-          Pk pk[U];
-#pragma unroll
-          for (int u = 0; u < U; ++u) load_vec<St, V, NT>(p.a + off_a + row_offset(r + (int64_t)u * RS), pk[u]);
-#pragma unroll
-          for (int u = 0; u < U; ++u) add_row(pk[u]);
-        }
-        if (r < r1) {   // the last rows, all on their way together (the last one again where there are fewer)
-          Pk pk[U - 1];
-#pragma unroll
-          for (int u = 0; u < U - 1; ++u) load_vec<St, V, NT>(p.a + off_a + row_offset(r + (int64_t)u * RS < r1 ? r + (int64_t)u * RS : r), pk[u]);
-#pragma unroll
-          for (int u = 0; u < U - 1; ++u) add_row(pk[u]);
-        }
-      }
-      uint32_t *words = reinterpret_cast<uint32_t *>(lds);   // [word of the vector][wavefront][lane]
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        for (int d = kWave / 2; d >= p.cpw; d >>= 1) bits[k] = Bits::combine(bits[k], (uint32_t)__shfl_down((int)bits[k], d));
-        words[(k * NW + wave) * kWave + lane] = bits[k];
-      }
-      __syncthreads();
-      for (int k = wave; k < 4; k += NW) {
-        if (lr != 0 || ncol != V) continue;
-        uint32_t v = words[k * NW * kWave + lane];
-        for (int w = 1; w < NW; ++w) v = Bits::combine(v, words[(k * NW + w) * kWave + lane]);
-#pragma unroll
-        for (int b8 = 0; b8 < 4; ++b8) {
-          const int i = 4 * k + b8;
-          if (i < skip) continue;
-          const A x = Bits::result(v, b8);
-          if (p.split == 1) store_result<A>(p.out + off_o + (int64_t)i * p.kso[0], p.out_dtype, x, p.swap_o != 0);
-          else reinterpret_cast<typename R::P *>(p.partial)[(int64_t)s * p.nout + (int64_t)other * p.nc + col0 + i] = to_storage<R::ACC>(x);
-        }
-      }
-      return;
-    }
-  }
   // Sums of 8-bit integers: the sixteen columns of a vector are added two at a time, as 16-bit
   // halves of 32-bit words (signed bytes biased by 128 to make them unsigned), and spilled into
   // the 64-bit accumulators every 256 rows, before a half can overflow (256 * 255 < 2^16).
@@ -1101,9 +1071,11 @@ OCN_DEV void cols_body(KRedArgs &p, typename Reducer<S, OP>::A *lds) {
       spill();
     }
   }
+  // (any and all of bytes come here with fewer columns than a vector holds only)
+  constexpr bool WHOLE = !(cols_bits<S, OP>() && V == 16);
   if (packed_done) {
     // (nothing left to add)
-  } else if (ncol == V) {  // whole vectors of columns: no per-element conditions
+  } else if (WHOLE && ncol == V) {  // whole vectors of columns: no per-element conditions
     // (one loop per byte order: decided per row inside the loop, the reversal is computed for
     // every vector and selected away)
     auto rows = [&](auto swapped) {
@@ -1365,6 +1337,76 @@ template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) voi
   } else {
     cols_body<S, OP, 1, false, false>(p, lds);
   }
+}
+
+// Any and all over whole vectors of byte columns: a lane's sixteen columns in four registers, which also meet as
+// such, with eight rows in flight (sixteen accumulators of a byte each took a shuffle and a round through LDS
+// apiece: bool any over the rows of [3840, 72] 19.2 -> 8.3 us, of [222, 2382] 10.7 -> 8.2).  In a kernel of their own:
+// beside the other body they took its registers from 69 to 128 and spilled.
+template <int S, int OP, bool NT, bool SINGLE> OCN_DEV void cols_bits_body(KRedArgs &p, uint32_t *words) {
+  using R = Reducer<S, OP>;
+  using A = typename R::A;
+  using St = storage_t<S>;
+  using Bits = BitFold<S, OP>;
+  constexpr int V = 16, U = 8;
+  struct alignas(16) Pk { St v[V]; };
+  const ColsPlace k = cols_place<1, V>(p);
+  uint32_t bits[4] = {Bits::kStart, Bits::kStart, Bits::kStart, Bits::kStart};
+  if (k.ncol == V) {
+    const char *base = p.a + k.off_a;
+    auto add_row = [&](const Pk &pk) {
+      uint32_t w[4];
+      __builtin_memcpy(w, &pk, 16);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bits[i] = Bits::add(bits[i], w[i]);
+    };
+    int64_t r = k.r;
+    for (; r + (int64_t)(U - 1) * k.rpw < k.r1; r += (int64_t)k.rpw * U) {
+      Pk pk[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) load_vec<St, V, NT>(base + cols_row_offset<SINGLE>(p, r + (int64_t)u * k.rpw), pk[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) add_row(pk[u]);
+    }
+    if (r < k.r1) {   // the last rows, all on their way together (the first of them again where there are fewer)
+      Pk pk[U - 1];
+#pragma unroll
+      for (int u = 0; u < U - 1; ++u)
+        load_vec<St, V, NT>(base + cols_row_offset<SINGLE>(p, r + (int64_t)u * k.rpw < k.r1 ? r + (int64_t)u * k.rpw : r), pk[u]);
+#pragma unroll
+      for (int u = 0; u < U - 1; ++u) add_row(pk[u]);
+    }
+  }
+  // words[word of the vector][wavefront][lane]
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    for (int d = kWave / 2; d >= p.cpw; d >>= 1) bits[i] = Bits::combine(bits[i], (uint32_t)__shfl_down((int)bits[i], d));
+    words[(i * k.waves + k.wave) * kWave + k.lane] = bits[i];
+  }
+  __syncthreads();
+  if (k.lr != 0 || k.ncol != V) return;
+  for (int i = k.wave; i < 4; i += k.waves) {
+    uint32_t v = words[i * k.waves * kWave + k.lane];
+    for (int w = 1; w < k.waves; ++w) v = Bits::combine(v, words[(i * k.waves + w) * kWave + k.lane]);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const int c = 4 * i + b;
+      if (c < k.skip) continue;
+      const A x = Bits::result(v, b);
+      if (p.split == 1) store_result<A>(p.out + k.off_o + (int64_t)c * p.kso[0], p.out_dtype, x, p.swap_o != 0);
+      else reinterpret_cast<typename R::P *>(p.partial)[(int64_t)k.split * p.nout + (int64_t)k.other * p.nc + k.col0 + c] = to_storage<R::ACC>(x);
+    }
+  }
+}
+template <int S, int OP> __global__ __launch_bounds__(kColsMaxWaves * kWave) void red_cols_bits_kernel(const RedArgs by_value) {
+  (void)by_value;  // read through the kernarg segment, which can be indexed at run time
+  KRedArgs &p = *(KRedArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if (p.warm) warm_arguments<RedArgs>();
+  extern __shared__ __align__(16) unsigned char red_cols_lds_raw[];
+  uint32_t *words = reinterpret_cast<uint32_t *>(red_cols_lds_raw);
+  if (p.nred != 1) cols_bits_body<S, OP, false, false>(p, words);
+  else if (p.nt_load) cols_bits_body<S, OP, true, true>(p, words);
+  else cols_bits_body<S, OP, false, true>(p, words);
 }
 
 // ---------------------------------------------------------------------------------------

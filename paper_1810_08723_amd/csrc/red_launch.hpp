@@ -61,7 +61,13 @@ template <int S, int OP> hipError_t launch_red(const RedPlan &p, char *partial, 
       {
         using A = typename Reducer<S, OP>::A;
         constexpr int VF = 16 / (int)sizeof(storage_t<S>) > 0 ? 16 / (int)sizeof(storage_t<S>) : 1;
-        const size_t lds = cols_bits<S, OP>() && p.vec > 1 ? (size_t)p.block * 16 : cols_lds_bytes<A>((int)p.block, p.vec > 1 ? VF : 1);
+        if constexpr (cols_bits<S, OP>()) {   // (a lane's last vector ends with the last column: sixteen of them at least)
+          if (p.vec > 1 && p.ksize[p.nkept - 1] >= VF) {
+            hipLaunchKernelGGL((red_cols_bits_kernel<S, OP>), dim3((unsigned)p.grid), dim3((unsigned)p.block), (size_t)p.block * 16, stream, args);
+            break;
+          }
+        }
+        const size_t lds = cols_lds_bytes<A>((int)p.block, p.vec > 1 ? VF : 1);
         if constexpr (VF > 1 && VF <= 8) {
           if (p.flat_cols) {
             hipLaunchKernelGGL((red_cols_flat_kernel<S, OP>), dim3((unsigned)p.grid), dim3((unsigned)p.block), lds, stream, args);
