@@ -362,7 +362,8 @@ typedef struct {
   int64_t red_stride_a[OCN_MAX_DIMS];
   int32_t vec;                        /* elements per lane access along the fastest dim     */
   int32_t tile_log2[OCN_MAX_DIMS];    /* tiled kernel: log2 of the tile extent per dim, rounded up (tiles of any extents have no more elements than these say) */
-  int32_t stage_a, stage_b;           /* tiled kernel: operand goes through LDS             */
+  int32_t stage_a, stage_b;           /* tiled kernel: operand goes through LDS; reductions: stage_a is the form of
+                                         strips (1 columns, 2 rows, 3 runs of columns of long rows), 0 for others */
   int32_t specialised;                /* 1: dtype-specialised kernel; 0: generic-dtype path */
   int32_t passes;                     /* kernel launches the call would make                */
   int64_t grid, block;                /* first launch                                       */

@@ -486,6 +486,7 @@ def _info_dict(info: OcnPlanInfo) -> dict:
         "stage_b": bool(info.stage_b), "specialised": bool(info.specialised), "passes": info.passes,
         "grid": info.grid, "block": info.block, "split": info.split, "lds_bytes": info.lds_bytes, "unclipped": bool(info.unclipped),
         "fused": bool(info.fused), "tile_group": info.tile_group,
+        "strip": info.stage_a if KERNELS[info.kernel].startswith("red") else 0,
     }
 
 

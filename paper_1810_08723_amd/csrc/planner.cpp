@@ -2184,6 +2184,7 @@ void fill_info(const RedPlan &p, ocn_plan_info *info) {
   info->grid = p.grid;
   info->block = p.block;
   info->split = p.split;
+  info->stage_a = p.strip;
 }
 
 }  // namespace ocn
