@@ -1370,14 +1370,30 @@ bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
 
 // Rows of dense blocks in strips: 16 KB of them per workgroup, less where that leaves CUs idle.  A power of
 // two of lanes per row, each with a whole vector or the row's few last elements one by one, is as
-// fast only for rows of whole vectors and small inputs (float rows of 22 [1090909, 22] 37 -> 20 us, of 5 103 -> 26,
-// of 16 24.1 -> 19.0, of 64 23.1 -> 18.4; [126241, 16] 4.8 and 5.1, halves [31894, 40] 3.3 and 4.3; but [150942, 10],
-// whose other form takes single elements, 8.0 -> 3.9).  Bytes come from LDS in words, those of a fused
-// call one by one: from 32 of them on the other form is the better one there (any over rows of 50 32.5 and 35.6), and
-// so it is for rows of one vector, or two of 8 or 16 bits (halves [5000000, 8] 23.6 and 26.5, maxima of floats
-// [2070888, 4] 10.6 and 12.6) and for bytes in whole vectors below 48 MB (int8 sums in rows of 64: 16 MB 6.2 and
-// 6.7 us, 30 MB 10.4 either way, 50 MB 15.3 -> 12.9; rows of 33 gain at all sizes, 6 MB 6.3 -> 4.5).
-constexpr int64_t kStripRowBytes = 16 << 10, kStripRowsSingle = 1 << 20, kStripRowsSmall = 4 << 20, kStripRowsWhole = 12 << 20, kStripByteRowsWhole = 48 << 20;
+// fast only for small inputs and rows of whole vectors (float rows of 22 [1090909, 22] 37 -> 20 us, of 5 103 -> 26,
+// of 16 24.1 -> 19.0, of 64 23.1 -> 18.4), and for blocks that end long before a workgroup's share.  Where the lines lie, by what
+// the other form does and by element size, over 5500 random calls (ratio of the times, other form to this):
+//   single elements   (rows shorter than two vectors that start anywhere) from 1 MB on, of 4 bytes 2 MB (0.96 below, 1.2 above),
+//                     of 8 bytes 4 MB (0.84 below, 1.06 above), of 16 bytes 8 MB (0.93 below, 1.1 above)
+//   vectors, rests    from 4 MB on, of 8 bytes 6 MB (1.05 below, 1.1 above); of a fused call with one row for all from 12 MB on
+//                     (2 bytes 0.93 below, with halves [22935, 242] 5.3 and 7.0 us; 4 bytes 1.0 below; 1.15 above), of 8 bytes 8 MB
+//                     (1.0 below, 1.2 above)
+//   whole vectors     from 12 MB on, of 4 bytes 16 MB (1.0 below, 1.25 above), of 2 bytes 32 MB (0.98 below, 1.1 above); not rows
+//                     of one vector, or two of 8 or 16 bits (halves [5000000, 8] 23.6 and 26.5, maxima of floats
+//                     [2070888, 4] 10.6 and 12.6); bytes from 48 MB on (int8 sums in rows of 64: 16 MB 6.2 and
+//                     6.7 us, 30 MB 10.4 either way, 50 MB 15.3 -> 12.9; rows of 33 gain at all sizes, 6 MB 6.3 -> 4.5)
+//   blocks of few     a workgroup takes rows of one block: from 5 KB of them on, single elements 512 bytes times their size
+//   rows              (cfloat [48969, 18, 2] minus a row 6.7 and 56 us, doubles [100131, 5, 3] 7.0 and 108)
+// Bytes come from LDS in words, those of a fused
+// call one by one: from 32 of them on the other form is the better one there (any over rows of 50 32.5 and 35.6).
+constexpr int64_t kStripRowBytes = 16 << 10, kStripByteRowsWhole = 48 << 20, kStripRowsBlock = 5 << 10, kStripRowsBlockSingle = 512;
+int64_t strip_rows_from(int es, bool vectors, bool whole, bool words, bool one_row) {
+  const int64_t mb = 1 << 20;
+  if (!vectors) return es <= 2 ? mb : es / 2 * mb;
+  if (whole) return words ? kStripByteRowsWhole : es == 2 ? 32 * mb : es == 4 ? 16 * mb : 12 * mb;
+  if (one_row) return es <= 4 ? 12 * mb : 8 * mb;
+  return es >= 8 ? 6 * mb : 4 * mb;
+}
 bool choose_strip_rows(RedPlan &p, const StripBlocks &s) {
   const int es = dt_size(p.a_dtype), mes = p.fused ? dt_size(p.mid_dtype) : es;
   const int64_t V = 16 / es, width = s.width, rows = s.nrows, others = p.nout / rows, total = p.nout * width * es;
@@ -1385,11 +1401,12 @@ bool choose_strip_rows(RedPlan &p, const StripBlocks &s) {
   const bool words = es == 1 && !p.fused;   // read from LDS in words
   if (width * es > kStripRowBytes / 16 || (es == 1 && p.fused && width >= 32) || (s.bc && m > kBlock)) return false;
   const bool whole = p.vec > 1 && width % V == 0;   // in whole vectors by the other form too
-  if (total < (whole ? (words ? kStripByteRowsWhole : kStripRowsWhole) : p.vec > 1 ? kStripRowsSmall : kStripRowsSingle)) return false;
+  if (total < strip_rows_from(es, p.vec > 1, whole, words, s.bc != 0)) return false;
   if (whole && (vecs == 1 || (vecs == 2 && es <= 2))) return false;
   const int64_t piece = std::max<int64_t>(2048, std::min(kStripRowBytes, total / (4 * kNumCUs)));
   int64_t chunk = 4;
   while (chunk * 2 * width * es <= piece) chunk *= 2;
+  if (rows < chunk && rows * width * es < (p.vec > 1 ? kStripRowsBlock : kStripRowsBlockSingle * es)) return false;
   chunk = std::min(chunk, rows);
   const int64_t grid = others * ((rows + chunk - 1) / chunk);
   if (grid > max_launch_blocks()) return false;
