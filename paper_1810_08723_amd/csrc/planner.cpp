@@ -1297,12 +1297,20 @@ bool strip_nt(const RedPlan &p, int64_t piece, int64_t block) {
 // The forms above stay the better ones where: blocks are small altogether (one launch that the fold's
 // barriers lengthen: doubles [262, 59] 5.0 and 5.7 us); few rows of whole vectors, which a lane walks by
 // itself (halves [1095563, 7, 8] 49 and 68; below 16 MB tests hold it to that for all rows of a vector and more, at
-// 9.4 us for int32 [5462, 31, 22] where strips take 7.2), or rows of many vectors and fewer than eight of them (floats [93, 4,
+// 9.4 us for int32 [5462, 31, 22] where strips take 7.2), or of bytes that a lane sums one by one, where a strip's lane
+// sums sixteen in 64 bits each (int8 [249498, 17, 2] 7.8 and 17.6, uint8 [25146, 24, 12] 4.8 and 9.4); rows of many
+// vectors and fewer than eight of them (floats [93, 4,
 // 460] 4.0 and 5.6); splits that idle lanes, or rows of a large output, whose partial results would not
 // fit what a call without a workspace has, leave uneven (floats [95, 340, 279] 9.6 and 14.4, sums over
-// [12000, 2000] 23 and 36), and splits of many small blocks ([63, 94, 748] 7.1 and 10.5); and, with runs of columns in an output, few outputs of less than 24 MB.
-constexpr int64_t kStripSmall = 256 << 10, kStripBytesSmall = 2 << 20, kStripSplitSmall = 1 << 20, kStripInnerSmall = 4 << 20,
-                  kStripInnerFew = 24 << 20, kStripLaneSmall = 16 << 20, kStripManySmall = 24 << 20;
+// [12000, 2000] 23 and 36), splits of many small blocks ([63, 94, 748] 7.1 and 10.5), and splits of several blocks of fewer than
+// 1024 rows of 4 bytes and more that take one launch otherwise (doubles [16, 85, 459] 4.0 and 7.0; 59 calls 0.86 times as fast
+// so, longer ones 1.1; comparisons gain 2.3 times and stay); a workgroup per block where a fused call computes elements of 4
+// bytes and more, and one input is an element per row (floats [65, 959, 118] 9.3 and 12.4; 310 calls 0.91) or blocks are short (4
+// bytes: fewer than 64 rows 0.92, 8: than 256 0.92, beyond it 1.1 and 1.04); a few short blocks of 16-bit elements that a lane
+// takes one by one otherwise (halves [616, 5, 48] 3.6 and 7.2; 13 calls 0.8).  With runs of columns in an output: few outputs of
+// less than 24 MB.
+constexpr int64_t kStripSmall = 256 << 10, kStripBytesSmall = 2 << 20, kStripSplitSmall = 1 << 20, kStripInnerSmall = 4 << 20, kStripInnerFew = 24 << 20,
+                  kStripLaneSmall = 16 << 20, kStripManySmall = 24 << 20, kStripSplitRows = 1024, kStripFewGroups = 40;
 bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
   const int es = dt_size(p.a_dtype), acc_es = dt_size(p.acc_dtype);
   const int64_t V = 16 / es, width = s.width, rows = s.nrows, kept = p.ksize[p.nkept - 1], others = p.nout / kept;
@@ -1313,7 +1321,10 @@ bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
   const int64_t top = std::min<int64_t>(kStripLanes, 65536 / (V * std::max(acc_es, p.acc_dtype == OCN_HALF ? 4 : 1)));
   if (p.fused && m > kBlock) return false;   // (double products of a column and [13223, 481] 36.6 and 38.5 with what follows)
   if (m > top || nv < 2 * m || (m > 32 && rows < 8) || total < (es == 1 ? kStripBytesSmall : kStripSmall)) return false;
-  if (p.kernel == OCN_KERNEL_RED_COLS && p.cpw == 0 && (width % V == 0 || rows <= 16 || (width > V && total < kStripLaneSmall))) return false;
+  const bool wide = es == 1 && acc_es == 8;   // (a lane's sixteen accumulators take 32 registers)
+  if (p.kernel == OCN_KERNEL_RED_COLS && p.cpw == 0 &&
+      (width % V == 0 || rows <= 16 || (width > V && total < kStripLaneSmall) || (wide && width < 3 * V)))
+    return false;
   if (s.inner > 1 && total < (kept < 5 ? kStripInnerFew : kStripInnerSmall)) return false;
   constexpr int64_t trips = 4;
   int64_t want = std::max<int64_t>(1, (nv / trips + m / 2) / m);   // times m lanes that a block keeps busy
@@ -1338,6 +1349,12 @@ bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
     split = even(most) > even(once) * 1.1 ? most : once;
     if (most == fits && others * split * block < 160 * 1024 && nv > lanes * 16) return false;
     if (split > 1 && others >= 32 && total < kStripManySmall) return false;
+    const bool compares = p.fused && p.mid_dtype == OCN_BOOL;
+    if (split > 1 && others > 1 && p.split == 1 && rows < kStripSplitRows && es >= 4 && !compares) return false;
+    if (split == 1 && others > 1 && block > kBlock) {
+      if (p.fused && !compares && es >= 4 && (p.vec > 1 || es == 16) && (s.bc || rows < (es == 4 ? 64 : es == 8 ? 256 : 0))) return false;
+      if (wide && rows < kLaneRows) return false;   // (sums of bool [3126, 20, 914] 33.6 and 46.8)
+    }
     if (split > 1 && (p.flat_cols || lanes * 8 < block * 7 || total < (es == 1 ? kStripBytesSmall : kStripSplitSmall))) return false;
     if (m > kWave && lanes * 4 < block * 3) return false;
     chunk = (rows + split - 1) / split;
@@ -1348,6 +1365,7 @@ bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
   }
   const int64_t grid = (others * split + groups - 1) / groups;
   if (grid > max_launch_blocks()) return false;
+  if (es == 2 && p.kernel == OCN_KERNEL_RED_COLS && p.vec == 1 && rows < 32 && grid < kStripFewGroups) return false;
   p.kernel = OCN_KERNEL_RED_COLS;
   p.strip = 1;
   p.strip_lanes = (int)lanes;

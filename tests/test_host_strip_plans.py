@@ -63,3 +63,22 @@ def test_rows_by_size(dtype, sizes, form):
                                                    ("double", (13924, 55), "row", 0), ("double", (20000, 55), "row", ROWS)])
 def test_fused_rows_by_size(dtype, sizes, lone, form):
     assert _fused("mul", dtype, sizes, 1, lone) == form
+
+
+@pytest.mark.parametrize("op,dtype,sizes,form", [("sum", "int8", (249498, 17, 2), 0), ("sum", "uint8", (25146, 24, 12), 0), ("sum", "bool", (75176, 26, 8), 0), ("sum", "int8", (90000, 40, 2), COLUMNS),
+                                                 ("sum", "bool", (3126, 20, 914), 0), ("sum", "double", (16, 85, 459), 0), ("sum", "float", (3, 94, 962), 0),                                                  ("sum", "half", (9000, 24, 49), COLUMNS), ("sum", "double", (16, 8500, 59), COLUMNS), ("sum", "half", (67684, 51, 3), COLUMNS)])
+def test_columns(op, dtype, sizes, form):
+    assert _strip(op, dtype, sizes, (1,)) == form
+
+
+def test_columns_of_few_short_blocks_read_one_by_one():
+    assert _strip("sum", "half", (616, 5, 48), (1,), first=1) == 0
+    assert _strip("sum", "half", (700, 20, 42), (1,), first=1) == COLUMNS
+
+
+@pytest.mark.parametrize("op,dtype,sizes,lone,form", [("mul", "float", (65, 959, 118), "column", 0), ("mul", "cdouble", (48, 196, 67), "column", 0), ("mul", "double", (71, 177, 292), "column", 0),
+                                                      ("sub", "cfloat", (2, 124, 212), "column", 0), ("mul", "int32", (9, 51, 960), "block", 0), ("mul", "double", (54, 144, 199), "block", 0),
+                                                      ("lt", "float", (60, 959, 118), "column", COLUMNS), ("mul", "float", (3000, 51, 10), "column", COLUMNS),
+                                                      ("mul", "half", (398, 25, 18), "column", 0), ("mul", "float", (904802, 22), "column", COLUMNS)])
+def test_fused_columns(op, dtype, sizes, lone, form):
+    assert _fused(op, dtype, sizes, len(sizes) - 2, lone, "bool" if op == "lt" else None) == form
