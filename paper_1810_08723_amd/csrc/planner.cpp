@@ -1308,9 +1308,13 @@ bool strip_nt(const RedPlan &p, int64_t piece, int64_t block) {
 // bytes and more, and one input is an element per row (floats [65, 959, 118] 9.3 and 12.4; 310 calls 0.91) or blocks are short (4
 // bytes: fewer than 64 rows 0.92, 8: than 256 0.92, beyond it 1.1 and 1.04); a few short blocks of 16-bit elements that a lane
 // takes one by one otherwise (halves [616, 5, 48] 3.6 and 7.2; 13 calls 0.8).  With runs of columns in an output: few outputs of
-// less than 24 MB.
+// less than 24 MB, and runs that are read in vectors anyhow (strip_runs_from).
 constexpr int64_t kStripSmall = 256 << 10, kStripBytesSmall = 2 << 20, kStripSplitSmall = 1 << 20, kStripInnerSmall = 4 << 20, kStripInnerFew = 24 << 20,
                   kStripLaneSmall = 16 << 20, kStripManySmall = 24 << 20, kStripSplitRows = 1024, kStripFewGroups = 40;
+// Runs that the forms above read in vectors: bytes from which strips, and runs of long rows, are faster.  By the bytes of
+// a run and whether they are whole vectors, over 1500 random calls (ratio of the times): below 64 bytes from 8 MB on (1.0 below, 1.4
+// above), whole vectors 10 (0.75, 1.5); longer ones from 12 (0.93, 1.4; sums of halves [1474, 42, 64] 6.2 and 9.8 us), whole 16 (0.85, 1.25).
+constexpr int64_t strip_runs_from(int64_t run, bool whole) { return (run < 64 ? (whole ? 10 : 8) : (whole ? 16 : 12)) * ((int64_t)1 << 20); }
 bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
   const int es = dt_size(p.a_dtype), acc_es = dt_size(p.acc_dtype);
   const int64_t V = 16 / es, width = s.width, rows = s.nrows, kept = p.ksize[p.nkept - 1], others = p.nout / kept;
@@ -1325,7 +1329,7 @@ bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
   if (p.kernel == OCN_KERNEL_RED_COLS && p.cpw == 0 &&
       (width % V == 0 || rows <= 16 || (width > V && total < kStripLaneSmall) || (wide && width < 3 * V)))
     return false;
-  if (s.inner > 1 && total < (kept < 5 ? kStripInnerFew : kStripInnerSmall)) return false;
+  if (s.inner > 1 && total < std::max(kept < 5 ? kStripInnerFew : 0, p.vec > 1 ? strip_runs_from(s.inner * es, s.inner % V == 0) : kStripInnerSmall)) return false;
   constexpr int64_t trips = 4;
   int64_t want = std::max<int64_t>(1, (nv / trips + m / 2) / m);   // times m lanes that a block keeps busy
   int64_t block = kBlock, split = 1, chunk = rows, lanes, groups = 1;
@@ -1454,7 +1458,8 @@ bool choose_strip_rows(RedPlan &p, const StripBlocks &s) {
 // The forms above, where lanes share an output and read its run of every row in lines of its own, stay the better
 // ones for long runs (half sums over the outer axes of [980, 193, 96] 14.7 and 16.3 us, bytes in runs of 500 to 5000
 // 1.2 to 2.4 times as long so) and for few rows unless there is much of them (maxima of floats [148, 453, 28] 6.2 and
-// 9.4; [227, 5192, 13] 21.3 -> 18.7).  Floats [1049, 7872, 8] 168 -> 44, halves [957, 7281, 7] 113 -> 27,
+// 9.4; [227, 5192, 13] 21.3 -> 18.7), and where lanes read the runs in vectors, as far as strip_runs_from says (sums of int8
+// [555, 597, 16] 3.9 and 10.8).  Floats [1049, 7872, 8] 168 -> 44, halves [957, 7281, 7] 113 -> 27,
 // bool any over [1356, 3062, 5] 31 -> 13.  With strips, which take the shorter rows, 170 random calls with runs of 2 to 256
 // bytes are 1.72 times as fast in the mean as without either, 8.4 ms together -> 3.1.  256 splits at most, whose fold is
 // one workgroup's for few outputs.
@@ -1467,7 +1472,7 @@ bool choose_strip_runs(RedPlan &p) {
   if (inner < 2 || p.rstride_a[1] != es || p.kstride_a[0] != inner * es) return false;
   if (width < 32 * V || width >= ((int64_t)1 << 31) || rows < kRunsFewRows) return false;
   const int64_t total = rows * width * es;
-  if (total < (es == 1 ? kRunsBytesSmall : kRunsSmall) || (rows < kRunsRows && total < kRunsMuch)) return false;
+  if (total < (p.vec > 1 ? strip_runs_from(inner * es, inner % V == 0) : es == 1 ? kRunsBytesSmall : kRunsSmall) || (rows < kRunsRows && total < kRunsMuch)) return false;
   if (inner * es > kRunsBytes || inner > (es == 1 ? kRunsLong / 2 : kRunsLong)) return false;
   // (512 lanes for bytes, whose sixteen columns a lane leave few workgroups)
   const int64_t top = std::min<int64_t>(es == 1 ? kStripLanes / 2 : kStripLanes, 65536 / (V * std::max(acc_es, p.acc_dtype == OCN_HALF ? 4 : 1)));

@@ -82,3 +82,10 @@ def test_columns_of_few_short_blocks_read_one_by_one():
                                                       ("mul", "half", (398, 25, 18), "column", 0), ("mul", "float", (904802, 22), "column", COLUMNS)])
 def test_fused_columns(op, dtype, sizes, lone, form):
     assert _fused(op, dtype, sizes, len(sizes) - 2, lone, "bool" if op == "lt" else None) == form
+
+
+@pytest.mark.parametrize("op,dtype,sizes,form", [("sum", "int8", (555, 597, 16), 0), ("sum", "half", (1474, 42, 64), 0), ("max", "half", (3833, 13, 52), 0), ("sum", "int32", (17878, 4, 44), 0),
+                                                 ("sum", "int32", (19330, 16, 9), COLUMNS), ("sum", "half", (10000, 42, 62), RUNS),
+                                                 ("sum", "float", (1049, 7872, 8), RUNS), ("sum", "half", (957, 7281, 7), RUNS), ("sum", "double", (298, 335, 6), 0)])
+def test_runs_of_columns(op, dtype, sizes, form):
+    assert _strip(op, dtype, sizes, (0, 2)) == form
