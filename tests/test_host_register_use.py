@@ -32,3 +32,10 @@ def test_any_and_all_of_byte_columns(tmp_path):
     kinds = [(s, op) for s in ("DT_BOOL", "DT_I8", "DT_U8") for op in ("R_ANY", "R_ALL")] + [("DT_BOOL", "R_MIN"), ("DT_BOOL", "R_MAX")]
     use = _usage(tmp_path, [f"{k}<{s}, {op}>(const RedArgs)" for s, op in kinds for k in ("red_cols_kernel", "red_cols_bits_kernel")])
     assert all(used <= 72 and spilled == 0 for _, used, spilled in use), use     # (seven wavefronts of a SIMD)
+
+
+def test_bytes_in_strips(tmp_path):
+    """Sixteen 64-bit sums of a lane and the words that become them: four vectors of unsigned bytes ahead spill."""
+    use = _usage(tmp_path, [f"red_strip_{k}_kernel<{s}, {op}>(const RedStripArgs)" for k in ("cols", "runs") for s in ("DT_BOOL", "DT_I8", "DT_U8")
+                            for op in ("R_SUM", "R_PROD", "R_MAX", "R_ANY")])
+    assert all(spilled == 0 for _, _, spilled in use), use
