@@ -720,7 +720,11 @@ template <class S, int V> OCN_DEV Pack<S, V> two_pieces(const Pack<S, V> &a, con
   return r;
 }
 
-template <class G> __global__ __launch_bounds__(kBlock) void ew_rows_kernel(const RowsArgs by_value) {
+// PIECES: vectors that go on into the next row in two whole pieces, not element by element.  The code for them costs every
+// other vector registers and time (two inputs of bytes 85 registers, 49 without, and three wavefronts of eight from every SIMD;
+// flat calls of any length 1 to 4 %, negated halves 4, sines of floats 2), so that it is a kernel of its own, chosen by
+// rows_in_pieces.
+template <class G, bool PIECES> __global__ __launch_bounds__(kBlock) void ew_rows_kernel(const RowsArgs by_value) {
   constexpr int V = G::VR, U = G::UR;
   using SAt = typename G::SAt;
   using SBt = typename G::SBt;
@@ -770,7 +774,7 @@ template <class G> __global__ __launch_bounds__(kBlock) void ew_rows_kernel(cons
         }
       }
       if (!va_ok || !vb_ok) {
-        if (U == 1 && whole && p.inner >= (uint32_t)V) {
+        if (PIECES && whole && p.inner >= (uint32_t)V) {
           // An input whose vector goes on into the next row: the last V elements of the one row and the first
           // V of the other, whole vectors both.  (Element by element, in a lane or two of every wavefront, products
           // of halves [78078, 666] with a row took 58 us, 36 so, [1268292, 41] 81, 45; of doubles [292682, 41] 39, 34.

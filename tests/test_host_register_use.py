@@ -39,3 +39,10 @@ def test_bytes_in_strips(tmp_path):
     use = _usage(tmp_path, [f"red_strip_{k}_kernel<{s}, {op}>(const RedStripArgs)" for k in ("cols", "runs") for s in ("DT_BOOL", "DT_I8", "DT_U8")
                             for op in ("R_SUM", "R_PROD", "R_MAX", "R_ANY")])
     assert all(spilled == 0 for _, _, spilled in use), use
+
+
+def test_rows_of_bytes_without_pieces(tmp_path):
+    """What flat calls, and rows shorter than a vector of bytes, run: as many wavefronts as a SIMD has."""
+    sigs = [f"Sig<{op}, {t}, {t}, {t}, 2>" for op in ("B_ADD", "B_MUL") for t in ("DT_I8", "DT_U8")] + ["Sig<B_LAND, DT_BOOL, DT_BOOL, DT_BOOL, 2>"]
+    use = _usage(tmp_path, [f"ew_rows_kernel<{s}, false>(const RowsArgs)" for s in sigs], header="ew_kernels.hpp")
+    assert all(used <= 64 and spilled == 0 for _, used, spilled in use), use
