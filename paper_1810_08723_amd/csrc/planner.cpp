@@ -1312,9 +1312,13 @@ bool strip_nt(const RedPlan &p, int64_t piece, int64_t block) {
 constexpr int64_t kStripSmall = 256 << 10, kStripBytesSmall = 2 << 20, kStripSplitSmall = 1 << 20, kStripInnerSmall = 4 << 20, kStripInnerFew = 24 << 20,
                   kStripLaneSmall = 16 << 20, kStripManySmall = 24 << 20, kStripSplitRows = 1024, kStripFewGroups = 40;
 // Runs that the forms above read in vectors: bytes from which strips, and runs of long rows, are faster.  By the bytes of
-// a run and whether they are whole vectors, over 1500 random calls (ratio of the times): below 64 bytes from 8 MB on (1.0 below, 1.4
-// above), whole vectors 10 (0.75, 1.5); longer ones from 12 (0.93, 1.4; sums of halves [1474, 42, 64] 6.2 and 9.8 us), whole 16 (0.85, 1.25).
-constexpr int64_t strip_runs_from(int64_t run, bool whole) { return (run < 64 ? (whole ? 10 : 8) : (whole ? 16 : 12)) * ((int64_t)1 << 20); }
+// a run and whether they are whole vectors, over 2100 random calls (ratio of the times, other form to this): runs below 64 bytes
+// from 8 MB on (0.9 below 6, 1.2 from 8 to 12, 1.9 above), longer ones from 12 (0.95, 1.4; sums of halves [1474, 42, 64] 6.2 and 9.8
+// us), whole vectors 16 (0.85, 1.35).  Two outputs stay with the other form (50 calls 0.92; maxima of bool [295229, 2, 48]
+// 8.8 and 18.3), three and four come from 24 MB on (three 0.78 below, 1.4 above).
+constexpr int64_t strip_runs_from(int64_t run, bool whole, int64_t outputs) {
+  return outputs < 3 ? INT64_MAX : outputs < 5 ? (int64_t)24 << 20 : (run < 64 ? 8 : whole ? 16 : 12) * ((int64_t)1 << 20);
+}
 bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
   const int es = dt_size(p.a_dtype), acc_es = dt_size(p.acc_dtype);
   const int64_t V = 16 / es, width = s.width, rows = s.nrows, kept = p.ksize[p.nkept - 1], others = p.nout / kept;
@@ -1329,7 +1333,7 @@ bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
   if (p.kernel == OCN_KERNEL_RED_COLS && p.cpw == 0 &&
       (width % V == 0 || rows <= 16 || (width > V && total < kStripLaneSmall) || (wide && width < 3 * V)))
     return false;
-  if (s.inner > 1 && total < std::max(kept < 5 ? kStripInnerFew : 0, p.vec > 1 ? strip_runs_from(s.inner * es, s.inner % V == 0) : kStripInnerSmall)) return false;
+  if (s.inner > 1 && total < (p.vec > 1 ? strip_runs_from(s.inner * es, s.inner % V == 0, kept) : kept < 5 ? kStripInnerFew : kStripInnerSmall)) return false;
   constexpr int64_t trips = 4;
   int64_t want = std::max<int64_t>(1, (nv / trips + m / 2) / m);   // times m lanes that a block keeps busy
   int64_t block = kBlock, split = 1, chunk = rows, lanes, groups = 1;
@@ -1472,7 +1476,7 @@ bool choose_strip_runs(RedPlan &p) {
   if (inner < 2 || p.rstride_a[1] != es || p.kstride_a[0] != inner * es) return false;
   if (width < 32 * V || width >= ((int64_t)1 << 31) || rows < kRunsFewRows) return false;
   const int64_t total = rows * width * es;
-  if (total < (p.vec > 1 ? strip_runs_from(inner * es, inner % V == 0) : es == 1 ? kRunsBytesSmall : kRunsSmall) || (rows < kRunsRows && total < kRunsMuch)) return false;
+  if (total < (p.vec > 1 ? strip_runs_from(inner * es, inner % V == 0, p.nout) : es == 1 ? kRunsBytesSmall : kRunsSmall) || (rows < kRunsRows && total < kRunsMuch)) return false;
   if (inner * es > kRunsBytes || inner > (es == 1 ? kRunsLong / 2 : kRunsLong)) return false;
   // (512 lanes for bytes, whose sixteen columns a lane leave few workgroups)
   const int64_t top = std::min<int64_t>(es == 1 ? kStripLanes / 2 : kStripLanes, 65536 / (V * std::max(acc_es, p.acc_dtype == OCN_HALF ? 4 : 1)));

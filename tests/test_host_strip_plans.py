@@ -86,6 +86,7 @@ def test_fused_columns(op, dtype, sizes, lone, form):
 
 @pytest.mark.parametrize("op,dtype,sizes,form", [("sum", "int8", (555, 597, 16), 0), ("sum", "half", (1474, 42, 64), 0), ("max", "half", (3833, 13, 52), 0), ("sum", "int32", (17878, 4, 44), 0),
                                                  ("sum", "int32", (19330, 16, 9), COLUMNS), ("sum", "half", (10000, 42, 62), RUNS),
-                                                 ("sum", "float", (1049, 7872, 8), RUNS), ("sum", "half", (957, 7281, 7), RUNS), ("sum", "double", (298, 335, 6), 0)])
+                                                 ("sum", "float", (1049, 7872, 8), RUNS), ("sum", "half", (957, 7281, 7), RUNS), ("sum", "double", (298, 335, 6), 0),
+                                                 ("max", "bool", (295229, 2, 48), 0), ("sum", "float", (61253, 2, 70), 0), ("sum", "int32", (18000, 3, 49), 0), ("sum", "float", (234811, 3, 29), COLUMNS)])
 def test_runs_of_columns(op, dtype, sizes, form):
     assert _strip(op, dtype, sizes, (0, 2)) == form
