@@ -1363,6 +1363,12 @@ bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
       if (p.fused && !compares && es >= 4 && (p.vec > 1 || es == 16) && (s.bc || rows < (es == 4 ? 64 : es == 8 ? 256 : 0))) return false;
       if (wide && rows < kLaneRows) return false;   // (sums of bool [3126, 20, 914] 33.6 and 46.8)
     }
+    // few blocks of long rows, whose columns the other form deals out to two workgroups and more, from four of a strip's vectors
+    // per lane on, 16-bit elements from ten (600 random calls: 0.9; those of 64 blocks and more or fewer vectors 1.0, complex doubles in
+    // two and three workgroups 1.04; maxima of halves [28, 119, 871] 5.9 and 8.8, doubles [27, 62, 484] 3.7 and 5.0)
+    if (split == 1 && p.split == 1 && others < kNumCUs / 4 && width * es >= 1024 && nv >= (es == 2 ? 10 : 4) * lanes &&
+        p.grid >= (es == 16 ? 4 : 2) * others)
+      return false;
     if (split > 1 && (p.flat_cols || lanes * 8 < block * 7 || total < (es == 1 ? kStripBytesSmall : kStripSplitSmall))) return false;
     if (m > kWave && lanes * 4 < block * 3) return false;
     chunk = (rows + split - 1) / split;

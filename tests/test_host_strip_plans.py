@@ -66,8 +66,15 @@ def test_fused_rows_by_size(dtype, sizes, lone, form):
 
 
 @pytest.mark.parametrize("op,dtype,sizes,form", [("sum", "int8", (249498, 17, 2), 0), ("sum", "uint8", (25146, 24, 12), 0), ("sum", "bool", (75176, 26, 8), 0), ("sum", "int8", (90000, 40, 2), COLUMNS),
-                                                 ("sum", "bool", (3126, 20, 914), 0), ("sum", "double", (16, 85, 459), 0), ("sum", "float", (3, 94, 962), 0),                                                  ("sum", "half", (9000, 24, 49), COLUMNS), ("sum", "double", (16, 8500, 59), COLUMNS), ("sum", "half", (67684, 51, 3), COLUMNS)])
+                                                 ("sum", "bool", (3126, 20, 914), 0), ("sum", "double", (16, 85, 459), 0), ("sum", "float", (3, 94, 962), 0),
+                                                 ("sum", "half", (9000, 24, 49), COLUMNS), ("sum", "double", (16, 8500, 59), COLUMNS), ("sum", "half", (67684, 51, 3), COLUMNS)])
 def test_columns(op, dtype, sizes, form):
+    assert _strip(op, dtype, sizes, (1,)) == form
+
+
+@pytest.mark.parametrize("op,dtype,sizes,form", [("max", "half", (28, 119, 871), 0), ("sum", "double", (27, 62, 484), 0), ("sum", "double", (27, 62, 121), COLUMNS), ("sum", "double", (270, 62, 484), COLUMNS),
+                                                 ("sum", "cdouble", (16, 31, 410), 0), ("sum", "cdouble", (20, 64, 121), COLUMNS), ("sum", "half", (10, 59, 524), COLUMNS)])
+def test_columns_of_few_blocks_of_long_rows(op, dtype, sizes, form):
     assert _strip(op, dtype, sizes, (1,)) == form
 
 
