@@ -1363,6 +1363,10 @@ bool choose_strip_cols(RedPlan &p, const StripBlocks &s) {
       if (p.fused && !compares && es >= 4 && (p.vec > 1 || es == 16) && (s.bc || rows < (es == 4 ? 64 : es == 8 ? 256 : 0))) return false;
       if (wide && rows < kLaneRows) return false;   // (sums of bool [3126, 20, 914] 33.6 and 46.8)
     }
+    // a workgroup of 1024 lanes for each of more blocks than CUs, of bytes that are compared one by one and rows of which it takes two
+    // at most (maxima of int8 and uint8: 57 random calls 0.78, none faster, more rows 1.25, smaller workgroups 1.08, fewer blocks
+    // 1.17; uint8 [672, 47, 847] 9.6 and 15.3)
+    if (split == 1 && block > 512 && es == 1 && acc_es == 1 && p.acc_dtype != OCN_BOOL && !p.fused && m >= 384 && others >= kNumCUs) return false;
     // few blocks of long rows, whose columns the other form deals out to two workgroups and more, from four of a strip's vectors
     // per lane on, 16-bit elements from ten (600 random calls: 0.9; those of 64 blocks and more or fewer vectors 1.0, complex doubles in
     // two and three workgroups 1.04; maxima of halves [28, 119, 871] 5.9 and 8.8, doubles [27, 62, 484] 3.7 and 5.0)

@@ -78,6 +78,12 @@ def test_columns_of_few_blocks_of_long_rows(op, dtype, sizes, form):
     assert _strip(op, dtype, sizes, (1,)) == form
 
 
+@pytest.mark.parametrize("op,dtype,sizes,form", [("max", "int8", (1917, 63, 847), 0), ("max", "uint8", (672, 47, 847), 0), ("max", "bool", (672, 47, 847), COLUMNS), ("max", "uint8", (473, 461, 192), COLUMNS),
+                                                 ("max", "uint8", (172, 147, 847), COLUMNS)])
+def test_columns_of_many_blocks_of_compared_bytes(op, dtype, sizes, form):
+    assert _strip(op, dtype, sizes, (1,)) == form
+
+
 def test_columns_of_few_short_blocks_read_one_by_one():
     assert _strip("sum", "half", (616, 5, 48), (1,), first=1) == 0
     assert _strip("sum", "half", (700, 20, 42), (1,), first=1) == COLUMNS
